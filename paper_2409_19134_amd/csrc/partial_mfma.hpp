@@ -5,7 +5,7 @@
 // i.e. one owner's term of Theorem 1 restricted to a token range.  Chunks of one row are later
 // combined with the n-way form of the same theorem (combine.hpp).
 //
-// Mapping onto a 64-lane wave (r = lane % 16, grp = lane / 16), 32 tokens per step:
+// Mapping onto a 64-lane wave (r = lane % 16, grp = lane / 16), 32 tokens per step (16 for 512-byte rows):
 //   S^T = K . Q^T   two v_mfma_f32_16x16x32_{bf16,f16} chains (D/32 MFMAs each):
 //                   the A operand is K as loaded (lane reads 16 B = 8 channels of token row r),
 //                   the B operand is Q (head r, rows >= G are zero).  The result lands with
@@ -25,6 +25,18 @@
 // loads, the token each of its values belongs to and the layout of the results are the same as above, only the
 // number of MFMAs per step differs (D/4 for S^T, D/2 for O^T at fp32, against D/16 and D/8 at 16 bits); P needs no
 // split.
+// fp32 with D = 128 and at most four query heads per KV head (kF32Quad) takes v_mfma_f32_4x4x1_16b_f32 instead, sixteen independent
+// 4x4 products per instruction at the same rate: the 16x16 tile spends 32 cycles on sixteen head columns of which G
+// hold a head, 4096 cycles per 32 tokens at D = 128 (1.7 us in which no other wave of the SIMD has the pipe); the 4x4
+// blocks need 1024.  With r = 4 * rq + i, block (grp, rq) of S^T takes tokens tb + grp*8 + a*4 + i and the
+// 16-byte piece rq of every 64 channel bytes (the four pieces are then summed over rq inside the 16-lane row with DPP
+// adds), so a lane ends up with head i and tokens tb + grp*8 + e, exactly the P that block (grp, rq) of O^T needs for
+// channels (4*rq + i)*(D/16) + cc.  O^T stays split over grp (disjoint tokens) until the segment ends.
+// fp32 rows of 512 bytes (D = 128) are HBM-bound once three things are so (8B shape, 16 users of 512-4096 tokens, 338 MB,
+// us per fused step): the 4x4 blocks 73.9 -> 71.7; a lane's V loads cover 256 contiguous bytes per instruction instead
+// of every other 16 (whose lines were asked for twice) -> 64.6; a wave's step is 16 tokens, 16 KB as at 16 bits, so that
+// three waves per SIMD fit and the public owner's pieces start with the private ones -> 62.1 (5.5 TB/s).  Two 16-token
+// steps in flight with two waves per SIMD: 64.4; the same order on 13 GB (1667 against 1702, before 1915).
 // Every K/V byte is read once per KV head (all G heads share the tile).
 // The four waves of a workgroup take interleaved 32-token steps and are combined through LDS; the result rows of a
 // workgroup that crosses many rows wait in LDS too and are stored together (the result ring, below).
@@ -70,6 +82,49 @@ struct Elt<SPD_F32> {
     }
 };
 
+// fp32 with D = 128 and at most four query heads per KV head: the kernels' own dtype code for the 4x4 blocks (see above).
+constexpr int kF32Quad = 3;
+constexpr int kQuadHeads = 4;
+template <>
+struct Elt<kF32Quad> {
+    static constexpr int kBytes = 4;
+    static constexpr float kPShift = 0.f;
+    static __device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+    }
+};
+
+// Sum over the four lanes of a 16-lane row that differ in bits 2 and 3 (rq), in all of them: two rotations of the row.
+__device__ __forceinline__ float row_quad_sum(float v)
+{
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xf, 0xf, true));  // row_ror:4
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));  // row_ror:8
+    return v;
+}
+
+// Sums an accumulator that is split over the four lane groups, each group keeping a quarter of the channel phases: on
+// return acc[0 .. CP/4) of lane group grp holds the totals of phases (grp >> 1) * CP/2 + (grp & 1) * CP/4 + k.
+// (A swap of half the lanes between two phases' registers brings each phase's two halves into the same lanes.)
+template <int CP>
+__device__ __forceinline__ void reduce_scatter_groups(f32x4 (&acc)[CP])
+{
+#pragma unroll
+    for (int k = 0; k < CP / 2; ++k)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[k][v]), __float_as_uint(acc[k + CP / 2][v]), false, false);
+            acc[k][v] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        }
+#pragma unroll
+    for (int k = 0; k < CP / 4; ++k)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[k][v]), __float_as_uint(acc[k + CP / 4][v]), false, false);
+            acc[k][v] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        }
+}
+
 // One step's loads of a lane, for rows of RB bytes (D channels of 2 or 4 bytes): RB/64 16-byte pieces of each of its
 // two K rows, and RB/16 bytes (D/16 channels) of each of its eight V rows.
 // A lane's share of one V row (RB/16 bytes), kept in the registers its loads deliver it in.
@@ -89,23 +144,39 @@ struct VRow<256> {
 };
 template <>
 struct VRow<512> {
-    u32x4 w0, w1;
+    u32x4 w0, w1;  // 16 bytes of each half of the row, so that an instruction's sixteen lanes cover 256 contiguous bytes
     __device__ __forceinline__ void load(const char *p)
     {
         w0 = stream_load16(p);
-        w1 = stream_load16(p + 16);
+        w1 = stream_load16(p + 256);
     }
     __device__ __forceinline__ unsigned dword(int i) const { return i < 4 ? w0[i] : w1[i - 4]; }  // i is a constant
 };
 
+// Lane r's first byte of a V row is r * v_lane_bytes(RB).
+__host__ __device__ constexpr int v_lane_bytes(int RB) { return RB == 512 ? 16 : RB / 16; }
+
+// The channel that row `row` (0..15) of the O^T tile's phase cc (0..CP-1) holds: lane r = row loaded it as value cc of its
+// share of a V row.
+template <int RB, int CP>
+__device__ __forceinline__ constexpr int o_channel(int row, int cc)
+{
+    return RB == 512 ? (cc >> 2) * 64 + row * 4 + (cc & 3) : row * CP + cc;
+}
+
+// 16-token S tiles per step of a wave: two, or one where rows are 512 bytes (fp32 with D = 128), so that a step is 16 KB
+// at either row size.
+__host__ __device__ constexpr int step_tiles(int RB) { return RB == 512 ? 1 : 2; }
+
 template <int RB>
 struct TileRegs {
-    u32x4 k[2][RB / 64];  // [S tile a][piece kk]: token row r of tile a, bytes kk*64 + grp*16 .. +16
-    VRow<RB> v[8];        // [e]: token tb + grp*8 + e, bytes r*(RB/16) .. +RB/16
+    u32x4 k[step_tiles(RB)][RB / 64];  // [S tile a][piece kk]: token row kt of tile a, bytes kk*64 + kc*16 .. +16 (see LaneConst)
+    VRow<RB> v[4 * step_tiles(RB)];    // [e]: token tb + grp*NE + e, RB/16 bytes from r*v_lane_bytes on
 };
 
 struct LaneConst {
     int r, grp;
+    int kt, kc;  // the lane's K rows: tokens tb + kt*8 + a*4 + (r & 3), 16-byte piece kc (r / 4 and grp; kF32Quad: grp and r / 4)
     const char *k_base;  // contiguous: user's K + head offset; paged: pool + head offset
     const char *v_base;
     const int32_t *bt_row;
@@ -138,29 +209,30 @@ __device__ __forceinline__ PagePair load_pages(const LaneConst &L, int tb, int t
 template <int RB, bool PAGED, bool APPEND>
 __device__ __forceinline__ void load_tile(TileRegs<RB> &T, const LaneConst &L, int tb, int t_last, PagePair &P, int step)
 {
-    const int gk = tb + (L.r >> 2) * 8;  // first token of the 8-token group this lane's K rows fall in
-    const int gv = tb + L.grp * 8;       // first token of the group this lane's V rows fall in
+    constexpr int NE = 4 * step_tiles(RB);
+    const int gk = tb + L.kt * NE;       // first token of the NE-token group this lane's K rows fall in
+    const int gv = tb + L.grp * NE;      // first token of the group this lane's V rows fall in
     const char *kp = L.k_base, *vp = L.v_base;
     if (PAGED) {
         kp += (int64_t)((gk - tb) >= 16 ? P.p1 : P.p0) * L.block_stride;
         vp += (int64_t)((gv - tb) >= 16 ? P.p1 : P.p0) * L.block_stride;
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
+    for (int a = 0; a < step_tiles(RB); ++a) {
         const int t = min(gk + a * 4 + (L.r & 3), t_last);  // rows past the chunk re-read its last token (masked later)
-        const char *p = kp + (int64_t)(PAGED ? (t & L.page_mask) : t) * L.token_stride + L.grp * 16;
+        const char *p = kp + (int64_t)(PAGED ? (t & L.page_mask) : t) * L.token_stride + L.kc * 16;
         if (APPEND && L.k_new_row && t == t_last)  // the appended token is read from the caller's buffer, not the cache
-            p = L.k_new_row + L.grp * 16;
+            p = L.k_new_row + L.kc * 16;
 #pragma unroll
         for (int kk = 0; kk < RB / 64; ++kk)
             T.k[a][kk] = stream_load16(p + kk * 64);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < NE; ++e) {
         const int t = min(gv + e, t_last);
-        const char *p = vp + (int64_t)(PAGED ? (t & L.page_mask) : t) * L.token_stride + L.r * (RB / 16);
+        const char *p = vp + (int64_t)(PAGED ? (t & L.page_mask) : t) * L.token_stride + L.r * v_lane_bytes(RB);
         if (APPEND && L.v_new_row && t == t_last)
-            p = L.v_new_row + L.r * (RB / 16);
+            p = L.v_new_row + L.r * v_lane_bytes(RB);
         T.v[e].load(p);
     }
     if (PAGED)
@@ -170,47 +242,58 @@ __device__ __forceinline__ void load_tile(TileRegs<RB> &T, const LaneConst &L, i
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// qB: Q as the B operand, loaded like a K row (head r instead of token r): bytes kk*64 + grp*16 .. +16 of the row.
+// qB: Q as the B operand, loaded like a K row (head r instead of token r): bytes kk*64 + kc*16 .. +16 of the row.
 template <int DT, int D>
 __device__ __forceinline__ void compute_tile(const TileRegs<D * Elt<DT>::kBytes> &T,
                                              const u32x4 (&qB)[D * Elt<DT>::kBytes / 64], int tb, int grp, int t_end,
                                              float c, float &m, float &l, f32x4 (&acc)[D / 16])
 {
     constexpr int RB = D * Elt<DT>::kBytes;
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (DT == SPD_F32) {
+    constexpr int NA = step_tiles(RB), NE = 4 * NA;
+    f32x4 s[NA];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+        s[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (Elt<DT>::kBytes == 4) {
 #pragma unroll
         for (int kk = 0; kk < RB / 64; ++kk)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {  // four channels per piece, one MFMA (k = 4: the lane groups) each
-                s0 = Elt<DT>::mfma(__uint_as_float(T.k[0][kk][e]), __uint_as_float(qB[kk][e]), s0);
-                s1 = Elt<DT>::mfma(__uint_as_float(T.k[1][kk][e]), __uint_as_float(qB[kk][e]), s1);
-            }
+            for (int e = 0; e < 4; ++e)  // four channels per piece, one MFMA (k = 4: the lane groups; k = 1 in 4x4 blocks) each
+#pragma unroll
+                for (int a = 0; a < NA; ++a)
+                    s[a] = Elt<DT>::mfma(__uint_as_float(T.k[a][kk][e]), __uint_as_float(qB[kk][e]), s[a]);
     } else {
         typedef typename Elt<DT>::vec8 vec8;
 #pragma unroll
-        for (int kk = 0; kk < RB / 64; ++kk) {
-            s0 = Elt<DT>::mfma(__builtin_bit_cast(vec8, T.k[0][kk]), __builtin_bit_cast(vec8, qB[kk]), s0);
-            s1 = Elt<DT>::mfma(__builtin_bit_cast(vec8, T.k[1][kk]), __builtin_bit_cast(vec8, qB[kk]), s1);
-        }
+        for (int kk = 0; kk < RB / 64; ++kk)
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+                s[a] = Elt<DT>::mfma(__builtin_bit_cast(vec8, T.k[a][kk]), __builtin_bit_cast(vec8, qB[kk]), s[a]);
+    }
+    if constexpr (DT == kF32Quad) {  // the four 16-byte pieces of every 64 channel bytes
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                s[a][e] = row_quad_sum(s[a][e]);
     }
     // scores in log2 units; tokens past the chunk end get -inf
-    const int t0 = tb + grp * 8;
-    float x[8];
+    const int t0 = tb + grp * NE;
+    float x[NE];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        x[e] = (t0 + e < t_end) ? s0[e] * c : -INFINITY;
-        x[4 + e] = (t0 + 4 + e < t_end) ? s1[e] * c : -INFINITY;
-    }
-    float mt = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+    for (int e = 0; e < NE; ++e)
+        x[e] = (t0 + e < t_end) ? s[e / 4][e % 4] * c : -INFINITY;
+    float mt = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    if constexpr (NE == 8)
+        mt = fmaxf(mt, fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
     mt = wave_xor_max<16>(mt);
     mt = wave_xor_max<32>(mt);
     const float m_new = fmaxf(m, mt);  // finite: every step holds at least one token of the chunk
     const float alpha = fast_exp2(m - m_new);
     const float m_p = m_new - Elt<DT>::kPShift;  // p (and with it l and acc) carries the factor 2^kPShift
-    float p[8], ps = 0.f;
+    float p[NE], ps = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < NE; ++e) {
         p[e] = fast_exp2(x[e] - m_p);
         ps += p[e];
     }
@@ -221,13 +304,20 @@ __device__ __forceinline__ void compute_tile(const TileRegs<D * Elt<DT>::kBytes>
         for (int cc = 0; cc < D / 16; ++cc)
             acc[cc] *= alpha;
     }
-    if constexpr (DT == SPD_F32) {
-        // channel phase cc: the lane's dword cc of each of its eight tokens; the MFMA's four k-values are the four
-        // lane groups' tokens grp*8 + e, and the B operand is the lane's own probability of that token
+    if constexpr (DT == kF32Quad) {
+        // a block per lane-group token and four of the lane's channels; the phases are independent chains
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int cc = 0; cc < D / 16; ++cc)
+                acc[cc] = Elt<DT>::mfma(__uint_as_float(T.v[e].dword(cc)), p[e], acc[cc]);
+    } else if constexpr (DT == SPD_F32) {
+        // channel phase cc: the lane's dword cc of each of its tokens; the MFMA's four k-values are the four
+        // lane groups' tokens grp*NE + e, and the B operand is the lane's own probability of that token
 #pragma unroll
         for (int cc = 0; cc < D / 16; ++cc)
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < NE; ++e)
                 acc[cc] = Elt<DT>::mfma(__uint_as_float(T.v[e].dword(cc)), p[e], acc[cc]);
     } else {
         typedef typename Elt<DT>::vec8 vec8;
@@ -297,10 +387,11 @@ __host__ __device__ constexpr int hpw_ring_rows_that_fit(int D, int G, int waves
     return n < 2 ? 0 : n > (size_t)kRingMaxRows ? kRingMaxRows : (int)n;
 }
 
-// Waves per SIMD the kernel is compiled for: a step's loads take RB/4 registers per lane (twice that with PREFETCH).
+// Waves per SIMD the kernel is compiled for: a step's loads take 64 registers per lane (32 with rows of 128 bytes), twice
+// that with PREFETCH.
 __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, bool hpw)
 {
-    return RB == 512 ? 2 : RB == 256 ? (prefetch ? 2 : 3) : (hpw ? 2 : 3);
+    return RB >= 256 ? (prefetch ? 2 : 3) : (hpw ? 2 : 3);
 }
 
 // One workgroup per piece (see DevItem); q: [U][Hq][D] of the element type DT (SPD_BF16, SPD_F16 or SPD_F32).  A
@@ -308,7 +399,7 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 // part_lse[slot][G], which combine_chunks_kernel then reduces.
 //
 // (Register counts below are those of 256-byte rows: 16-bit elements with D = 128.  Rows of 128 bytes need about half
-// and always run with PREFETCH; fp32 rows of 512 bytes need ~245 with one step in flight and never run with it.)
+// and always run with PREFETCH; fp32 rows of 512 bytes need ~160 with one 16-token step in flight and never run with it.)
 // PREFETCH = true keeps two 32-token steps of loads in flight per wave (~245 VGPRs, two waves per SIMD): for launches
 // that run several rounds of workgroups, and for small ones that fit two per CU anyway (half as many dependent round
 // trips per wave).  PREFETCH = false holds one step (~160 VGPRs, three waves per SIMD): as fast when the private
@@ -353,13 +444,15 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
     constexpr int CP = D / 16;  // channel phases of the O^T tile: a lane holds CP consecutive channels per accumulator row
     constexpr int kRowBytes = D * Elt<DT>::kBytes;
     constexpr int RB = kRowBytes;
+    constexpr bool kQuad = DT == kF32Quad;
     const int o_wave_stride = G * kOStride;
     // head-per-wave results go through a wave-private tile if the launch gave the room
     const bool staged = HPW && staging_fits(D, (int)(blockDim.x >> 6), G);
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    constexpr int kStep = HPW ? 32 : 32 * kWaves;
+    constexpr int kTile = 16 * step_tiles(RB);  // tokens per step of a wave
+    constexpr int kStep = HPW ? kTile : kTile * kWaves;
 
     // Everything a segment needs before its first MFMA: addresses, the KV append copy, Q, and the loads of the wave's
     // first 32-token step.  Issued for the *next* segment before the current one's epilogue, so that the barriers
@@ -367,6 +460,8 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
     auto begin_segment = [&](const DevItem &it, LaneConst &L, u32x4 (&qB)[RB / 64], int &tb, TileRegs<RB> &T0, PagePair &P) {
         L.r = lane & 15;
         L.grp = lane >> 4;
+        L.kt = kQuad ? L.grp : L.r >> 2;
+        L.kc = kQuad ? L.r >> 2 : L.grp;
         L.token_stride = kv.token_stride;
         L.block_stride = kv.block_stride;
         L.page_shift = kv.page_shift;
@@ -395,16 +490,17 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
                     copy16(const_cast<char *>(L.v_base) + off, L.v_new_row + (lane - kRowLanes) * 16);
             }
         }
-        // Q as the B operand: head r (zero beyond G), read like a K row: bytes kk*64 + grp*16 .. +16
-        const char *qrow = q + ((int64_t)it.user * Hq + (int64_t)kv_head * G + L.r) * kRowBytes + L.grp * 16;
+        // Q as the B operand: head r (4x4 blocks: r & 3; zero beyond G), read like a K row: bytes kk*64 + kc*16 .. +16
+        const int head = kQuad ? L.r & (kQuadHeads - 1) : L.r;
+        const char *qrow = q + ((int64_t)it.user * Hq + (int64_t)kv_head * G + head) * kRowBytes + L.kc * 16;
 #pragma unroll
         for (int kk = 0; kk < RB / 64; ++kk) {
             qB[kk] = u32x4{0u, 0u, 0u, 0u};
-            if (L.r < G)
+            if (head < G)
                 qB[kk] = *reinterpret_cast<const u32x4 *>(qrow + kk * 64);
         }
         // head-major: the four waves take interleaved 32-token steps; token-major: every wave takes every step
-        tb = HPW ? it.t_begin : it.t_begin + ((uniform(wave) - (it.rot & 3)) & (kWaves - 1)) * 32;
+        tb = HPW ? it.t_begin : it.t_begin + ((uniform(wave) - (it.rot & 3)) & (kWaves - 1)) * kTile;
         if (PAGED)
             P = load_pages(L, tb, t_last);
         if (PREFETCH && tb < it.t_end)
@@ -572,23 +668,33 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
         }
 
         // ---- ... and the four waves (LDS) ----
-        if (grp == 0) {
+        // (512-byte rows have no register to spare: their epilogue addresses are computed here, not held across the
+        // streaming loop, which an opaque copy of the thread index sees to)
+        int tid = threadIdx.x;
+        if constexpr (RB == 512)
+            asm("" : "+v"(tid));
+        const int head = kQuad ? r & (kQuadHeads - 1) : r;  // the query head of the lane's results
+        if (grp == 0) {  // (4x4 blocks: entries past head 3 are copies, never read)
             sm_m[wave][r] = m;
             sm_l[wave][r] = l;
         }
         __syncthreads();
-        float M = sm_m[0][r];
+        float M = sm_m[0][head];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w)
-            M = fmaxf(M, sm_m[w][r]);
+            M = fmaxf(M, sm_m[w][head]);
         const float f = fast_exp2(m - M);  // some wave holds tokens, so M is finite; an idle wave has m = -inf, f = 0
-        if (r < G) {
-            float *dst = &sm_o[wave * o_wave_stride + r * kOStride + grp * 4 * CP];
+        if constexpr (kQuad)
+            reduce_scatter_groups<CP>(acc);
+        if (head < G) {
+            // rows 4*grp + v of the tile; 4x4 blocks: rows 4*rq + v, and of the phases the lane group's quarter
+            float *dst = &sm_o[wave * o_wave_stride + head * kOStride];
+            const int row0 = kQuad ? (r & ~3) : grp * 4, cc0 = kQuad ? (grp >> 1) * (CP / 2) + (grp & 1) * (CP / 4) : 0;
 #pragma unroll
-            for (int cc = 0; cc < CP; ++cc)
+            for (int cc = 0; cc < (kQuad ? CP / 4 : CP); ++cc)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    dst[v * CP + cc] = acc[cc][v] * f;  // channel (4*grp + v)*CP + cc
+                    dst[o_channel<RB, CP>(row0 + v, cc0 + cc)] = acc[cc][v] * f;
         }
         __syncthreads();
 
@@ -605,7 +711,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
         typedef __attribute__((address_space(1))) float *global_f32;
         typedef __attribute__((address_space(3))) float *lds_f32;
         auto reduce_waves = [&](auto row_o, auto row_l) {
-            for (int idx = threadIdx.x; idx < GD; idx += kThreads) {
+            for (int idx = tid; idx < GD; idx += kThreads) {
                 const int g = idx / D, ch = idx % D;
                 float Mg = sm_m[0][g];
 #pragma unroll
@@ -627,7 +733,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
         else
             reduce_waves((global_f32)dst_o, (global_f32)dst_l);
         if (to_ring) {
-            if (threadIdx.x == 0) {
+            if (tid == 0) {
                 ring_dst_o[n_ring] = dst_o;
                 ring_dst_l[n_ring] = dst_l;
             }
@@ -637,10 +743,10 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
                 for (int i = 0; i < n_ring; ++i) {
                     const lds_f32 src = (lds_f32)(ring + i * ring_stride);
                     const global_f32 o = (global_f32)ring_dst_o[i];
-                    for (int idx = threadIdx.x; idx < GD; idx += kThreads)
+                    for (int idx = tid; idx < GD; idx += kThreads)
                         o[idx] = src[idx];
-                    if ((int)threadIdx.x < G)
-                        ((global_f32)ring_dst_l[i])[threadIdx.x] = src[GD + threadIdx.x];
+                    if (tid < G)
+                        ((global_f32)ring_dst_l[i])[tid] = src[GD + tid];
                 }
                 n_ring = 0;
             }

@@ -451,13 +451,14 @@ struct MfmaLaunch {
     spd::PartialArgs args;
 };
 
-// The kernel instances that exist: the head-per-wave mapping always keeps two steps in flight, fp32 rows of 512 bytes
-// always one (and have no head-per-wave mapping), rows of 128 bytes always two.
+// The kernel instances that exist: the head-per-wave mapping always keeps two steps in flight, fp32 always one (and
+// has no head-per-wave mapping), rows of 128 bytes always two.
 template <int DT, int D, bool PREFETCH, bool HPW>
 constexpr bool mfma_instance_exists()
 {
-    constexpr int RB = D * (DT == SPD_F32 ? 4 : 2);
-    return !(HPW && !PREFETCH) && !(DT == SPD_F32 && (HPW || PREFETCH)) && !(RB == 128 && !PREFETCH);
+    constexpr bool f32 = DT == SPD_F32 || DT == spd::kF32Quad;
+    constexpr int RB = D * (f32 ? 4 : 2);
+    return !(HPW && !PREFETCH) && !(f32 && (HPW || PREFETCH)) && !(RB == 128 && !PREFETCH) && !(DT == spd::kF32Quad && D != 128);
 }
 
 template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
@@ -525,7 +526,7 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     // 128 users 225.7 / 222.0, with 8 query heads per KV head 452.0 / 446.2; 128 users of 64-512 tokens 50.8 / 50.0; 256
     // such users 88.9 / 89.7; the standalone public call of workload 2 -0.3 us).  Head-per-wave workgroups fit one per
     // CU either way; with 128-byte rows a step is half the bytes, always two in flight; fp32 keeps one (at 128
-    // channels a step is already 32 KB per wave and fills the registers).  SPD_OPT_STEPS_IN_FLIGHT overrides the size
+    // channels two in flight with two waves per SIMD measured 2 % slower than one with three, also on 13 GB).  SPD_OPT_STEPS_IN_FLIGHT overrides the size
     // rule (tests run both kernels on the same small inputs).
     const int64_t cus = std::max(1, ctx->n_cus);
     const int row_bytes = D * elt_size(s->dtype);
@@ -544,7 +545,13 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
         ring_rows = std::min(ctx->result_rows, hpw ? spd::hpw_ring_rows_that_fit(D, G, waves) : spd::ring_rows_that_fit(D, G, two_per_cu));
     L.lds += (uint32_t)(ring_rows * sizeof(float) * (hpw ? (size_t)spd::hpw_ring_row_floats(D, G) * waves : (size_t)spd::ring_row_floats(D, G)));
     L.args.ring_rows = ring_rows;
-    const bool ok = with_value<SPD_F32, SPD_BF16, SPD_F16>(s->dtype, [&](auto dt) {
+    // fp32 rows of 512 bytes with up to four query heads per KV head run on the 4x4 matrix blocks, a quarter of the 16x16
+    // tile's time per step (measured in partial_mfma.hpp).  Five heads would need a second set of blocks and of
+    // accumulators (32 registers more than the kernel has), and the 16x16 tile is fuller there.  With 64 channels the
+    // kernel is HBM-bound either way (16 users of 8192-32768 tokens 204.4 / 203.5 us), and on calls of one or two users,
+    // which the host's launches bound, the shorter kernel only drains the queue (7.5 / 8.1 us).
+    const int dt_code = f32 && D == 128 && G <= spd::kQuadHeads ? spd::kF32Quad : s->dtype;
+    const bool ok = with_value<SPD_F32, SPD_BF16, SPD_F16, spd::kF32Quad>(dt_code, [&](auto dt) {
         return with_value<64, 128>(D, [&](auto d) {
             return with_bool(v0->block_size != 0, [&](auto paged) {
                 return with_bool(prefetch, [&](auto pf) {
@@ -560,7 +567,7 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     });
     if (!ok)
         return SPD_ERR_SHAPE;  // no kernel instance for this combination: a bug in the rules above
-    const int32_t inst[6] = {s->dtype, D, v0->block_size != 0, prefetch, hpw, nt.k != nullptr};
+    const int32_t inst[6] = {dt_code, D, v0->block_size != 0, prefetch, hpw, nt.k != nullptr};
     std::memcpy(ctx->last_instance, inst, sizeof inst);
     SPD_HIP(ctx, hipGetLastError());
     if (timed)

@@ -465,6 +465,19 @@ def test_fp32_edge_lengths(ctx, lp, lo, d):
     check_against_oracle(ctx, wl)
 
 
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("paged", [False, True])
+def test_fp32_matrix_blocks_at_tile_edges(ctx, G, d, paged):
+    """fp32 rows of 512 bytes (d = 128) run on 4x4 matrix blocks with up to four query heads per KV head, everything else
+    on the 16x16 tile; those rows take 16 tokens per wave and step, shorter ones 32: lengths around those tiles and
+    around one step of all four waves, in one launch."""
+    lens = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 1000]
+    wl = workloads.random_case(142, torch.float32, len(lens), 2 * G, 2, d, lens, lens[::-1], device=DEV, layout="hnd",
+                               paged=paged)
+    check_against_oracle(ctx, wl)
+
+
 def test_fp32_large_launch(ctx):
     """64 users x 8 KV heads x 3000 tokens in fp32 (1.6 GB): several resident rounds of pieces; sampled rows."""
     wl = workloads.random_case(115, torch.float32, 64, 16, 8, 128, [3000] * 64, [100] * 64, device=DEV, layout="hnd")
