@@ -293,8 +293,8 @@ int spd_attention_mass_track(spd_ctx *ctx, int32_t n_rows, const float *w_in, fl
 int spd_set_kernel_timing(spd_ctx *ctx, int32_t max_launches);
 /* Which instance of the partial kernel the context launched last, as its template arguments
  * {dtype, head_dim, paged, two steps in flight, head per wave, append} (all -1 before the first launch; dtype 3: the
- * kernel's code for fp32 with head_dim 128 and at most four query heads per KV head): lets a measurement say which kernel it timed, e.g.
- * partial_mfma_kernel<1, 128, false, false, false, false>. */
+ * kernel's code for fp32 on 4x4 matrix blocks; head per wave 2: the whole-rows kernel, which takes calls of short rows):
+ * lets a measurement say which kernel it timed, e.g. partial_mfma_kernel<1, 128, false, false, false, false>. */
 int spd_get_last_kernel_instance(const spd_ctx *ctx, int32_t instance[6]);
 int spd_get_kernel_timing(spd_ctx *ctx, int32_t entry_point, int32_t *n_launches, double *mean_us, double *min_us);
 /* The same, handing out every recorded duration (microseconds, in launch order) instead of their mean and minimum:

@@ -238,6 +238,8 @@ class Context:
         a = (C.c_int32 * 6)()
         self._check(lib.spd_get_last_kernel_instance(self.handle, a), "spd_get_last_kernel_instance")
         b = lambda x: "true" if x else "false"
+        if a[4] == 2:     # short rows, one workgroup each
+            return f"whole_rows_kernel<{a[0]}, {a[1]}, {b(a[2])}, {b(a[5])}>"
         return f"partial_mfma_kernel<{a[0]}, {a[1]}, {b(a[2])}, {b(a[3])}, {b(a[4])}, {b(a[5])}>"
 
     def spd_set_option(self, option: int, value: int):

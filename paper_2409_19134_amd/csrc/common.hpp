@@ -14,6 +14,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWaves = 4;            // waves per workgroup in the partial-attention kernels
 constexpr int kThreads = kWaves * 64;
+constexpr int kRowsMaxWaves = 12;    // waves of a whole-rows workgroup: three per SIMD, what a tile's registers allow
 constexpr int kMaxGroup = 16;        // query heads per KV head the MFMA tile can hold
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -45,6 +46,14 @@ struct DevItem {
                        // evenly loaded; bit 8 (kEndsRow): the segment ends at the last token of its row
 };
 constexpr int kEndsRow = 0x100;
+
+// A (user, KV head) row of one owner as the whole-rows kernel reads it, indexed user * Hkv + KV head; addresses as in
+// DevItem.
+struct RowItem {
+    const char *k_base, *v_base;
+    int32_t t_end;  // tokens
+    int32_t pad[3];
+};
 
 // 16-byte load of K/V data that is read exactly once: the non-temporal hint keeps the stream from displacing
 // other lines in L2 (measured: plain streaming reads reach ~6.3 TB/s on this GPU, non-temporal ones ~7.1 TB/s).

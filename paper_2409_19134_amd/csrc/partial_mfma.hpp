@@ -167,6 +167,7 @@ __device__ __forceinline__ constexpr int o_channel(int row, int cc)
 // 16-token S tiles per step of a wave: two, or one where rows are 512 bytes (fp32 with D = 128), so that a step is 16 KB
 // at either row size.
 __host__ __device__ constexpr int step_tiles(int RB) { return RB == 512 ? 1 : 2; }
+__host__ __device__ constexpr int step_tokens(int RB) { return 16 * step_tiles(RB); }
 
 template <int RB>
 struct TileRegs {
@@ -451,7 +452,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    constexpr int kTile = 16 * step_tiles(RB);  // tokens per step of a wave
+    constexpr int kTile = step_tokens(RB);  // tokens per step of a wave
     constexpr int kStep = HPW ? kTile : kTile * kWaves;
 
     // Everything a segment needs before its first MFMA: addresses, the KV append copy, Q, and the loads of the wave's

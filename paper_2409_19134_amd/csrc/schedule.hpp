@@ -308,6 +308,86 @@ struct DeviceTables {
     int64_t n_segments = 0;                   // segments with tokens, all pieces together
 };
 
+// The address of row (user, KV head h) of a view - or, where the kernel adds the pool or the user's pointer itself, its
+// offset from that.  es: bytes per K/V element.
+inline const char *row_base(const spd_kv_view *v, int es, int u, int h, bool is_v)
+{
+    const uintptr_t base = (v->block_size || v->k_ptrs_dev) ? 0 : reinterpret_cast<uintptr_t>(is_v ? v->v_ptrs[u] : v->k_ptrs[u]);
+    const int64_t hs = (v->head_strides && v->block_size == 0) ? v->head_strides[u] : v->head_stride;
+    return reinterpret_cast<const char *>(base + (uintptr_t)((int64_t)h * hs * es));
+}
+
+// The tables of the whole-rows kernel: an item per row, indexed user * Hkv + KV head, and the users by length, longest
+// first (the launch order where the rows do not all fit the device at once).
+constexpr int kWholeRows = 64;  // in place of the head-per-wave mapping's KV heads per workgroup (0, 2..8)
+inline void build_whole_rows(int Hkv, int es, const spd_kv_view *v, std::vector<spd::RowItem> &items, std::vector<int32_t> &order)
+{
+    items.assign((size_t)v->n_users * Hkv, spd::RowItem{});
+    order.resize((size_t)v->n_users);
+    for (int u = 0; u < v->n_users; ++u) {
+        order[(size_t)u] = u;
+        for (int h = 0; h < Hkv && v->lens[u] > 0; ++h) {
+            spd::RowItem &d = items[(size_t)u * Hkv + h];
+            d.k_base = row_base(v, es, u, h, false);
+            d.v_base = row_base(v, es, u, h, true);
+            d.t_end = v->lens[u];
+        }
+    }
+    std::stable_sort(order.begin(), order.end(), [v](int32_t a, int32_t b) { return v->lens[a] > v->lens[b]; });
+}
+
+// Whether a call's rows are taken whole, one workgroup each, and by how many waves.  In units of 16 KB (a wave's step):
+// `longest` is the longest row, `share` what each of the workgroups resident at once gets if the rows spread evenly.  The
+// launch lasts (longest - share) units longer than its bytes take, ~0.27 us each, against the 4-5 us that the split
+// schedule's closing launch costs: whole rows up to a difference of 16.  Measured, us per fused step, 8B shape in bf16,
+// split / whole (difference): 1 user 256 + 64 tokens 8.6 / 6.6 (10), 4 users of <= 384 + 128 8.5 / 7.8 (12), of <= 512 + 256
+// 8.8 / 9.1 (16.1), 16 such users 13.0 / 11.9 (12), 16 users of <= 768 + 256 13.5 / 15.3 (16.7), 32 of them 20.2 / 18.7
+// (10), 64 34.5 / 30.2; 256 users of <= 192 + 64 51.2 / 31.5, <= 384 + 128 73.5 / 56.2, <= 768 + 256 112.1 / 106.1,
+// 250-2000 + 64 215 / 199; 100 users with lognormal prompts of median 128, up to 2048, 38.7 / 49.3 (60).  Rows of more than
+// 64 units (2048 tokens at 256 bytes) gain nothing on balanced launches (256 users of 500-4000 + 1000: 454 / 477) and stay
+// with the split schedule, fp32 rows of 512 bytes from 48 (256 users of 96-768 + 256 tokens, 64 units: 201 / 203).
+struct WholeRowsLoad {
+    int tile = 32, step_bytes = 16384;  // tokens and K/V bytes of a wave's step
+    int Hkv = 0, n_cus = 0, n_users = 0;
+    const int32_t *lens0 = nullptr, *lens1 = nullptr;  // lens1: the second owner's, or nullptr
+    bool limit_halved = false;
+};
+// One owner's call saves less (its combine launch is shorter, ~3 us) and keeps the split schedule from 12 on (three calls,
+// 8 users of <= 1536 + 512 tokens, the public call at 12.2: 22.5 / 24.3; 16 users of <= 768 + 256, the private call at 15:
+// 21.9 / 22.5) - except with few rows, where the host's launches are the bound (one user's private call over 500 tokens,
+// 15.5: 10.6-11.9 / 8.3).
+constexpr int kWholeRowsTail = 16, kWholeRowsTailOneOwner = 12, kWholeRowsLimit = 64, kWholeRowsLimit512 = 48;
+inline int whole_rows_choice(const WholeRowsLoad &c)
+{
+    int64_t longest = 0, total = 0;  // steps
+    for (int u = 0; u < c.n_users; ++u) {
+        int64_t steps = ((int64_t)c.lens0[u] + c.tile - 1) / c.tile;
+        if (c.lens1)
+            steps += ((int64_t)c.lens1[u] + c.tile - 1) / c.tile;
+        longest = std::max(longest, steps);
+        total += steps;
+    }
+    const int64_t rows = (int64_t)c.n_users * c.Hkv, cus = std::max(1, c.n_cus);
+    // Waves: twelve fit a compute unit, whatever the workgroups.  Rows that all have a unit of their own take as few waves
+    // as make the same number of rounds; up to two rows per unit, eight waves (one workgroup per unit and a second round)
+    // from 17 steps on and four below (64 users of <= 768 + 256 tokens 30.1 / 32.0 us, of <= 192 + 64 12.0 / 11.0); more
+    // rows, four waves (256 users of <= 512 + 256 tokens: 82 us, 94 with eight or twelve).
+    int64_t waves = 4, slots = 3 * cus;
+    if (rows <= cus) {
+        const int64_t rounds = std::max<int64_t>(1, (longest + spd::kRowsMaxWaves - 1) / spd::kRowsMaxWaves);
+        waves = std::max<int64_t>(1, (longest + rounds - 1) / rounds);
+        slots = cus;
+    } else if (rows <= 2 * cus && longest > 16) {
+        waves = 8;
+        slots = cus;
+    }
+    const int64_t limit = (c.step_bytes / c.tile == 1024 ? kWholeRowsLimit512 : kWholeRowsLimit) >> (c.limit_halved ? 1 : 0);
+    const int64_t unit = 16384, tail = c.lens1 || rows * 8 <= cus ? kWholeRowsTail : kWholeRowsTailOneOwner;
+    if (longest * c.step_bytes > limit * unit || longest * c.step_bytes - total * c.Hkv * c.step_bytes / slots > tail * unit)
+        return 0;
+    return (int)std::min(waves, std::max<int64_t>(1, longest));
+}
+
 // es: bytes per K/V element.  Row addresses come from the view's host pointer arrays (contiguous mode without device
 // pointer tables); in the other modes the items hold offsets and the kernel adds the pool or the user's pointer.
 inline void build_device_tables(const Schedule &S, int Hkv, int es, const spd_kv_view *v, int hpw, DeviceTables &T)
@@ -326,17 +406,11 @@ inline void build_device_tables(const Schedule &S, int Hkv, int es, const spd_kv
     std::vector<DevItem> &dev_items = T.items;
     dev_items.assign((size_t)n_groups, DevItem{});
     dev_items.reserve((size_t)n_groups + S.items.size());
-    // the row's address - or, where the kernel adds the pool or the user's pointer itself, its offset from that
-    auto row_base = [&](int u, int h, bool is_v) -> const char * {
-        const uintptr_t base = (v->block_size || v->k_ptrs_dev) ? 0 : reinterpret_cast<uintptr_t>(is_v ? v->v_ptrs[u] : v->k_ptrs[u]);
-        const int64_t hs = (v->head_strides && v->block_size == 0) ? v->head_strides[u] : v->head_stride;
-        // head per wave: every wave adds its own head's offset (from head 0)
-        return reinterpret_cast<const char *>(base + (uintptr_t)(hpw ? 0 : (int64_t)h * hs * es));
-    };
     auto to_dev = [&](const spd_work_item &w, int rot) {
         DevItem d;
-        d.k_base = row_base(w.user, w.kv_head, false);
-        d.v_base = row_base(w.user, w.kv_head, true);
+        const int h = hpw ? 0 : w.kv_head;  // head per wave: every wave adds its own head's offset (from head 0)
+        d.k_base = row_base(v, es, w.user, h, false);
+        d.v_base = row_base(v, es, w.user, h, true);
         d.user = w.user;
         d.kv_head = w.kv_head;
         d.t_begin = w.t_begin;

@@ -21,6 +21,7 @@
 #include "partial_mfma.hpp"
 #include "schedule.hpp"
 #include "schedule_key.hpp"
+#include "whole_rows.hpp"
 
 namespace {
 
@@ -45,8 +46,8 @@ struct CachedSchedule {
     int32_t grow = 0;            // set by every lookup: tokens each row has gained over the lengths in `key`
     std::vector<uint8_t> key;
     int64_t n_items = 0, n_slots = 0, n_segments = 0;
-    int hpw = 0;             // 0, or the KV heads per workgroup of the head-per-wave kernel the pieces are for
-    int n_split_rows = 0;    // rows with several chunks: CombineRow[n_split_rows] follows the items
+    int hpw = 0;             // 0, the KV heads per workgroup of the head-per-wave kernel the pieces are for, or kWholeRows
+    int n_split_rows = 0;    // rows with several chunks: CombineRow[n_split_rows] follows the items (whole rows: the launch order)
     size_t off_rows = 0, off_info = 0;
     char *dev = nullptr;     // DevItem[n_items] | CombineRow[n_split_rows] | RowInfo[n_users * Hkv]
     char *pinned = nullptr;  // host staging copy of the same blob
@@ -171,6 +172,17 @@ struct ScheduleBlob {
 
 void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, const Tuning &tune, ScheduleBlob &B)
 {
+    if (hpw == kWholeRows) {
+        std::vector<spd::RowItem> items;
+        std::vector<int32_t> order;
+        build_whole_rows(s->n_kv_heads, elt_size(s->dtype), v, items, order);
+        B.off_rows = B.off_info = (items.size() * sizeof(spd::RowItem) + 255) / 256 * 256;
+        B.bytes.assign(B.off_rows + (order.size() * sizeof(int32_t) + 255) / 256 * 256, 0);
+        std::memcpy(B.bytes.data(), items.data(), items.size() * sizeof(spd::RowItem));
+        std::memcpy(B.bytes.data() + B.off_rows, order.data(), order.size() * sizeof(int32_t));
+        B.n_items = B.n_segments = (int64_t)items.size();
+        return;
+    }
     Schedule S;
     build_schedule(s->n_kv_heads, v->n_users, v->lens, n_cus, hpw, tune, S);
     DeviceTables T;
@@ -366,6 +378,40 @@ Tuning standalone_tuning(const spd_ctx *ctx, const spd_shape *s, const spd_kv_vi
     return t;
 }
 
+// Options at their defaults: none of those that shape or pick the split kernels has been asked for.
+bool default_kernel_options(const spd_ctx *ctx)
+{
+    const Tuning dflt;
+    return ctx->head_per_wave < 0 && ctx->steps_in_flight < 0 && std::memcmp(&ctx->tuning, &dflt, sizeof dflt) == 0;
+}
+
+// Waves per workgroup of the whole-rows kernel for a call over v0 (and v1: both owners of a fused step), or 0 if the call
+// takes the split schedule.  A whole-rows call is one launch without a closing kernel (4-5 us of GPU time, 3 of the
+// host's), but the device waits for the longest row.
+int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *v0, const spd_kv_view *v1)
+{
+    const int n = v0->n_users;
+    if (!default_kernel_options(ctx) || n > 65535 || (v1 && (v0->block_size != 0) != (v1->block_size != 0)))
+        return 0;
+    WholeRowsLoad load;
+    load.tile = spd::step_tokens(s->head_dim * elt_size(s->dtype));
+    load.step_bytes = 2 * load.tile * s->head_dim * elt_size(s->dtype);
+    load.Hkv = s->n_kv_heads;
+    load.n_cus = ctx->n_cus;
+    load.n_users = n;
+    load.lens0 = v0->lens;
+    load.lens1 = v1 ? v1->lens : nullptr;
+    // token-major storage long enough for the head-per-wave mapping, which reads whole DRAM pages: up to half the limit
+    // (two parties appending, token-major, 256 users of 96-768 + 256 tokens 116.1 us against 130.4, 192-1536 + 512: 214.5
+    // against 208.6)
+    load.limit_halved = head_per_wave_layout(s, v0) && (!v1 || head_per_wave_layout(s, v1)) &&
+                        head_per_wave_choice(ctx, s, total_steps(v0) + (v1 ? total_steps(v1) : 0)) != 0;
+    const int waves = whole_rows_choice(load);
+    // the slots of a workgroup with many query heads per KV head: what 64 KB of LDS hold (never fewer than 6)
+    const int64_t slot = (int64_t)spd::staging_bytes(s->head_dim, 1, s->n_q_heads / s->n_kv_heads);
+    return (int)std::min<int64_t>(waves, 64 * 1024 / slot - 1);
+}
+
 // Validation, schedule lookup and scratch growth of one partial-attention call.
 int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const void *q, const spd_kv_view *v, float *out,
                     float *lse, int mapping, const Tuning *tune, hipStream_t stream, CachedSchedule **e)
@@ -377,10 +423,14 @@ int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const void *q, 
     if (v->n_users == 0)
         return SPD_OK;
     Owner &own = ctx->owner[which];
-    // mapping: KV heads per workgroup of the head-per-wave mapping, 0 = head-major, -1 = whatever suits this view on its own
-    const int hpw = mapping >= 0 ? mapping : head_per_wave_layout(s, v) ? head_per_wave_choice(ctx, s, total_steps(v)) : 0;
+    // mapping: KV heads per workgroup of the head-per-wave mapping, 0 = head-major, kWholeRows, -1 = whatever suits this view
+    // on its own
+    int hpw = mapping;
+    if (hpw < 0)
+        hpw = head_per_wave_layout(s, v) ? head_per_wave_choice(ctx, s, total_steps(v)) : 0;
     // tune: the fused step's; none for a call that serves one owner alone
-    const int rs = get_schedule(ctx, own, s, v, hpw, tune ? *tune : standalone_tuning(ctx, s, v, hpw), stream, e);
+    const int rs = get_schedule(ctx, own, s, v, hpw, tune ? *tune : hpw == kWholeRows ? ctx->tuning : standalone_tuning(ctx, s, v, hpw),
+                                stream, e);
     if (rs != SPD_OK)
         return rs;
     const int G = s->n_q_heads / s->n_kv_heads;
@@ -575,6 +625,95 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     return SPD_OK;
 }
 
+spd::RowsOwner rows_owner(const CachedSchedule *e, const spd_shape *s, const spd_kv_view *v, float *out, float *lse, NewToken nt)
+{
+    const OwnerArgs a = owner_args(ScratchPtrs(), e, s, v, out, lse, nt.k, nt.v);
+    spd::RowsOwner r;
+    r.items = reinterpret_cast<const spd::RowItem *>(e->dev);
+    r.k_pool = a.k_pool;
+    r.v_pool = a.v_pool;
+    r.k_ptrs = a.k_ptrs;
+    r.v_ptrs = a.v_ptrs;
+    r.block_table = a.kv.block_table;
+    r.max_blocks = a.kv.max_blocks;
+    r.page_shift = a.kv.page_shift;
+    r.token_stride = a.kv.token_stride;
+    r.block_stride = a.kv.block_stride;
+    r.k_new = a.k_new;
+    r.v_new = a.v_new;
+    r.out = out;
+    r.lse = lse;
+    r.grow = e->grow;
+    return r;
+}
+
+// What a whole-rows launch merges, or nullptrs: with both owners their own partials, with one the delivered a_in / lse_in.
+struct MergeArgs {
+    const float *a_in = nullptr, *lse_in = nullptr;
+    float *y = nullptr, *lse = nullptr, *w_in = nullptr;
+};
+
+template <int DT, int D, bool PAGED, bool APPEND>
+bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsArgs &args)
+{
+    hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0, args);
+    return true;
+}
+
+// The one launch of a call whose rows are taken whole: owner 0 is e0's, with e1 both owners of a fused step.
+int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *e0, const spd_kv_view *v0, float *out0, float *lse0,
+                      const CachedSchedule *e1, const spd_kv_view *v1, float *out1, float *lse1, const spd_shape *s, const void *q,
+                      NewToken nt, const MergeArgs &mg, hipStream_t stream)
+{
+    const int G = s->n_q_heads / s->n_kv_heads, D = s->head_dim;
+    spd::RowsArgs R;
+    R.a0 = rows_owner(e0, s, v0, out0, lse0, which == 1 ? nt : NewToken());
+    R.a1 = e1 ? rows_owner(e1, s, v1, out1, lse1, which == 0 ? nt : NewToken()) : R.a0;
+    R.waves = waves;
+    R.both = e1 != nullptr;
+    R.Hkv = s->n_kv_heads;
+    R.Hq = s->n_q_heads;
+    R.G = G;
+    R.wave_mul = (uint32_t)(((1ull << 32) + waves - 1) / waves);
+    R.scale_log2e = s->scale * spd::kLog2e;
+    const int64_t rows = (int64_t)v0->n_users * s->n_kv_heads, cus = std::max(1, ctx->n_cus);
+    R.order = rows * waves > cus * spd::kRowsMaxWaves ? reinterpret_cast<const int32_t *>(e0->dev + e0->off_rows) : nullptr;
+    R.q = static_cast<const char *>(q);
+    R.a_in = mg.a_in;
+    R.lse_in = mg.lse_in;
+    R.y = mg.y;
+    R.lse = mg.lse;
+    R.w_in = mg.w_in;
+    Owner &town = ctx->owner[e1 ? 0 : which];
+    const bool timed = ctx->timing && town.ev_used < (int)town.ev_start.size();
+    MfmaLaunch L;
+    L.grid = dim3((unsigned)s->n_kv_heads, (unsigned)v0->n_users);
+    L.block = dim3(64u * (unsigned)waves);
+    L.lds = (uint32_t)spd::staging_bytes(D, waves + 1, G);
+    L.stream = stream;
+    L.ev0 = timed ? town.ev_start[town.ev_used] : nullptr;
+    L.ev1 = timed ? town.ev_stop[town.ev_used] : nullptr;
+    const int dt_code = s->dtype == SPD_F32 && G <= spd::kQuadHeads ? spd::kF32Quad : s->dtype;
+    const bool ok = with_value<SPD_F32, SPD_BF16, SPD_F16, spd::kF32Quad>(dt_code, [&](auto dt) {
+        return with_value<64, 128>(D, [&](auto d) {
+            return with_bool(v0->block_size != 0, [&](auto paged) {
+                return with_bool(nt.k != nullptr, [&](auto app) {
+                    return launch_rows_instance<decltype(dt)::value, decltype(d)::value, decltype(paged)::value,
+                                                decltype(app)::value>(L, R);
+                });
+            });
+        });
+    });
+    if (!ok)
+        return SPD_ERR_SHAPE;
+    const int32_t inst[6] = {dt_code, D, v0->block_size != 0, D * elt_size(s->dtype) == 128, 2, nt.k != nullptr};
+    std::memcpy(ctx->last_instance, inst, sizeof inst);
+    SPD_HIP(ctx, hipGetLastError());
+    if (timed)
+        ++town.ev_used;
+    return SPD_OK;
+}
+
 // The n-way combine of the rows that were split (a separate launch, see combine.hpp).
 int launch_combine(spd_ctx *ctx, int which, const CachedSchedule *e, const spd_shape *s, float *out, float *lse,
                    hipStream_t stream)
@@ -623,9 +762,12 @@ int partial_attention(spd_ctx *ctx, int which, const spd_shape *s, const void *q
         rc = validate_new_token(v, nt);
     if (rc != SPD_OK)
         return rc;
-    rc = prepare_partial(ctx, which, s, q, v, out, lse, -1, nullptr, stream, &e);
+    const int waves = whole_rows_waves(ctx, s, v, nullptr);
+    rc = prepare_partial(ctx, which, s, q, v, out, lse, waves ? kWholeRows : -1, nullptr, stream, &e);
     if (rc != SPD_OK || !e)
         return rc;
+    if (waves)
+        return launch_whole_rows(ctx, which, waves, e, v, out, lse, nullptr, nullptr, nullptr, nullptr, s, q, nt, MergeArgs(), stream);
     rc = launch_partial(ctx, which, e, v, out, lse, scratch_of(ctx->owner[which]), nullptr, nullptr, nullptr, nullptr,
                         ScratchPtrs(), s, q, nt, stream);
     if (rc != SPD_OK)
@@ -687,11 +829,17 @@ int validate_decode_step(spd_ctx *ctx, const spd_shape *shape, const void *q, co
 
 // Both owners of a fused step share one launch, so they share the mapping: head per wave if both layouts allow it and
 // the two together are bandwidth-bound (the value is the KV heads per workgroup, 0 for the head-major mapping).
-int fused_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_view *priv, const spd_kv_view *pub)
+int split_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_view *priv, const spd_kv_view *pub)
 {
     if (!head_per_wave_layout(shape, priv) || !head_per_wave_layout(shape, pub))
         return 0;
     return head_per_wave_choice(ctx, shape, total_steps(priv) + total_steps(pub));
+}
+
+// The same, or kWholeRows where the step's rows are short.
+int fused_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_view *priv, const spd_kv_view *pub)
+{
+    return whole_rows_waves(ctx, shape, priv, pub) ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
 }
 
 // Both owners of a fused step also share the device: if each would cut its rows into a full resident round of equal
@@ -721,6 +869,14 @@ int launch_decode_step(spd_ctx *ctx, const spd_shape *shape, const void *q, cons
                        float *lse, float *w_in, hipStream_t stream)
 {
     int rc;
+    if (ep->hpw == kWholeRows) {
+        MergeArgs mg;
+        mg.y = y;
+        mg.lse = lse;
+        mg.w_in = w_in;
+        return launch_whole_rows(ctx, 0, whole_rows_waves(ctx, shape, priv, pub), ep, priv, a_in, lse_in, eo, pub, a_out, lse_out, shape,
+                                 q, nt, mg, stream);
+    }
     // one grid for both owners, the private owner's long streams first (measured faster than public first): the
     // public owner's short, latency-bound pieces then run beside them on the workgroup slots that remain
     if ((priv->block_size != 0) == (pub->block_size != 0)) {
@@ -1165,18 +1321,24 @@ try {
     if (!st.ptr)
         return SPD_ERR_WORKSPACE;
     const int hpw = fused_step_mapping(ctx, shape, priv, pub);
-    const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);
+    const int split = hpw == kWholeRows ? split_step_mapping(ctx, shape, priv, pub) : hpw;
+    const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, split);
     const int G = shape->n_q_heads / shape->n_kv_heads;
-    // both schedules are built and checked against the array's limits before anything is enqueued
+    // both schedules are built and checked against the array's limits before anything is enqueued; the limits are those of
+    // the split schedule, also for a step whose rows are taken whole (which needs less)
     ScheduleBlob B[2];
     const spd_kv_view *views[2] = {priv, pub};
     std::vector<uint8_t> key[2];
     for (int w = 0; w < 2; ++w) {
-        build_blob(shape, views[w], hpw, ctx->n_cus, tune, B[w]);
+        build_blob(shape, views[w], split, ctx->n_cus, tune, B[w]);
         make_key(shape, views[w], hpw, &tune.target_wg_per_cu, kTuningInts, key[w]);
         if (B[w].bytes.size() > kStaticSchedBytes || (size_t)B[w].n_slots * G + 4 > kStaticLseFloats ||
             (size_t)B[w].n_slots * G * shape->head_dim + 4 > kStaticPartOFloats)
             return SPD_ERR_WORKSPACE;
+    }
+    for (int w = 0; w < 2 && hpw == kWholeRows; ++w) {
+        B[w] = ScheduleBlob();
+        build_blob(shape, views[w], hpw, ctx->n_cus, tune, B[w]);
     }
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     SPD_HIP(ctx, hipStreamIsCapturing(stream, &capture));
@@ -1236,9 +1398,19 @@ try {
     if (!aligned16(a_in) || !aligned16(y))
         return SPD_ERR_ALIGN;
     CachedSchedule *eo = nullptr;
-    rc = prepare_partial(ctx, 1, shape, q, pub, a_out, lse_out, -1, nullptr, stream, &eo);
+    const int waves = whole_rows_waves(ctx, shape, pub, nullptr);
+    rc = prepare_partial(ctx, 1, shape, q, pub, a_out, lse_out, waves ? kWholeRows : -1, nullptr, stream, &eo);
     if (rc != SPD_OK)
         return rc;
+    if (waves) {
+        MergeArgs mg;
+        mg.a_in = a_in;
+        mg.lse_in = lse_in;
+        mg.y = y;
+        mg.lse = lse;
+        mg.w_in = w_in;
+        return launch_whole_rows(ctx, 1, waves, eo, pub, a_out, lse_out, nullptr, nullptr, nullptr, nullptr, shape, q, nt, mg, stream);
+    }
     rc = launch_partial(ctx, 1, eo, pub, a_out, lse_out, scratch_of(ctx->owner[1]), nullptr, nullptr, nullptr, nullptr,
                         ScratchPtrs(), shape, q, nt, stream);
     if (rc != SPD_OK)

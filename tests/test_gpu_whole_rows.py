@@ -1,0 +1,126 @@
+"""Calls of short rows run on the whole-rows kernel: one launch, one workgroup per (user, KV head), no closing kernel.
+Against the oracle and against the split kernels, which the options that shape or pick them still select."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from test_gpu_parity import TOL, _check_one, _oracle_outputs, run_step
+from oracle import spd_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+OUTPUTS = ("a_in", "lse_in", "a_out", "lse_out", "y", "lse", "w_in")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2409_19134_amd as spd
+    c = spd.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+@pytest.fixture(scope="module")
+def split_ctx():
+    """A context whose calls all take the split schedule (an option that picks its kernels is set)."""
+    import paper_2409_19134_amd as spd
+    c = spd.Context(0)
+    c.spd_set_option(spd.SPD_OPT_STEPS_IN_FLIGHT, 1)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def _both_ways(ctx, split_ctx, wl):
+    """Every call form on whole rows against the oracle, and the fused step against the split kernels."""
+    want = _oracle_outputs(orc.from_workload(wl), None)
+    for fused in (False, True, "two_parties"):
+        step, _ = _check_one(ctx, wl, want, None, None, fused)
+        assert ctx.spd_last_kernel_name().startswith("whole_rows_kernel<"), ctx.spd_last_kernel_name()
+    ref = run_step(split_ctx, wl, True)
+    assert not split_ctx.spd_last_kernel_name().startswith("whole_rows")
+    for name in OUTPUTS:
+        a, b = getattr(step, name), getattr(ref, name)
+        fin = torch.isfinite(b)
+        assert torch.equal(fin, torch.isfinite(a)), name
+        # both are within TOL of the same value
+        assert (a[fin] - b[fin]).abs().max().item() <= 2 * TOL[wl.dtype] if fin.any() else True, name
+
+
+# lengths around a step (32 tokens; 16 for 512-byte rows), and totals around twelve of them: 1, 11, 12, 13 and more steps,
+# with one owner empty, both, and the owners' border inside a wave's share
+PRIVATE = [0, 1, 31, 32, 33, 320, 352, 384, 385, 0, 100, 190, 17]
+PUBLIC = [0, 0, 1, 33, 31, 64, 32, 0, 1, 385, 97, 193, 400]
+
+
+@pytest.mark.parametrize("dtype,d,Hq,Hkv", [(torch.bfloat16, 128, 8, 2), (torch.bfloat16, 128, 32, 2), (torch.float16, 64, 3, 3),
+                                            (torch.float16, 128, 14, 2), (torch.float32, 64, 4, 1), (torch.float32, 64, 5, 1),
+                                            (torch.float32, 128, 4, 2), (torch.float32, 128, 16, 1)])
+@pytest.mark.parametrize("storage", ["hnd", "nhd", "hnd_exact", "paged", "paged_tm"])
+def test_step_and_wave_edges(ctx, split_ctx, dtype, d, Hq, Hkv, storage):
+    paged = {"paged": True, "paged_tm": "token_major"}.get(storage, False)
+    div = 2 if dtype == torch.float32 and d == 128 else 1           # the same number of steps
+    wl = workloads.random_case(501, dtype, len(PRIVATE), Hq, Hkv, d, [-(-x // div) for x in PRIVATE], [-(-x // div) for x in PUBLIC],
+                               device=DEV, layout="nhd" if paged else storage, paged=paged)
+    _both_ways(ctx, split_ctx, wl)
+
+
+# 256 compute units: a workgroup each (up to 12 waves), up to two rows per unit (8 waves, or 4 for rows of up to 16 steps),
+# more rows than are resident at once (4 waves, launched by length)
+@pytest.mark.parametrize("U,top", [(1, 500), (31, 700), (33, 400), (60, 700), (65, 300), (300, 200)])
+def test_workgroup_sizes_and_launch_order(ctx, split_ctx, U, top):
+    rng = np.random.default_rng(U)
+    lo = rng.integers(0, 90, U)
+    wl = workloads.random_case(502, torch.bfloat16, U, 16, 8, 64 if U == 300 else 128, rng.integers(top - 150, top, U).tolist(),
+                               lo.tolist(), device=DEV, layout="hnd")
+    _both_ways(ctx, split_ctx, wl)
+
+
+def test_one_owners_nan_stays_out_of_the_others_partial(ctx):
+    wl = workloads.random_case(503, torch.bfloat16, 3, 8, 2, 128, [250, 40, 90], [200, 70, 33], device=DEV, layout="hnd")
+    clean = run_step(ctx, wl, True)
+    keep = {name: getattr(clean, name).clone() for name in OUTPUTS}
+    wl.private.v[1][0, 5, :] = float("nan")              # user 1, KV head 0, token 5
+    step = run_step(ctx, wl, True)
+    assert ctx.spd_last_kernel_name().startswith("whole_rows_kernel<")
+    rows = slice(0, 4)                                    # the query heads of KV head 0
+    assert torch.isnan(step.a_in[1, rows]).all() and torch.isnan(step.y[1, rows]).all()
+    assert torch.equal(step.a_out, keep["a_out"]) and torch.equal(step.lse_out, keep["lse_out"])
+    for name in ("a_in", "y"):
+        a, b = getattr(step, name).clone(), keep[name].clone()
+        a[1, rows] = b[1, rows] = 0
+        assert torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("paged", [False, True])
+def test_decode_loop_appends_on_whole_rows(ctx, paged):
+    """Twenty steps of a growing public cache: the appended rows reach the cache, the schedule is found again, results
+    agree with the oracle on the cache as it then is."""
+    import paper_2409_19134_amd as spd
+    U, Hkv, d, steps = 4, 2, 128, 20
+    lo0 = np.array([1, 31, 60, 128])
+    wl = workloads.random_case(504, torch.bfloat16, U, 8, Hkv, d, [200, 33, 64, 1], (lo0 + steps).tolist(), device=DEV, layout="hnd",
+                               paged=paged)
+    full_lens = wl.public.lens
+    gen = torch.Generator(device=DEV).manual_seed(505)
+    own = spd.Context(0)
+    for i in range(steps):
+        wl.public.lens = (lo0 + i + 1).astype(np.int32)
+        new = [torch.randn((U, Hkv, d), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2)]
+        step = spd.DecodeStep.from_workload(own, wl)
+        step.run_fused(wl.q, None, *new)
+        torch.cuda.synchronize()
+        assert own.spd_last_kernel_name().startswith("whole_rows_kernel<")
+        Y, _ = orc.attention(orc.from_workload(wl))      # the oracle reads the cache the call has written
+        assert np.abs(step.y.cpu().double().numpy().reshape(Y.shape) - Y).max() <= TOL[wl.dtype]
+        for u in range(U):
+            t = int(wl.public.lens[u]) - 1
+            for side, row in zip((wl.public.k_pool if paged else wl.public.k[u], wl.public.v_pool if paged else wl.public.v[u]), new):
+                at = side[int(wl.public.block_table[u, t // 16]), :, t % 16] if paged else side[:, t]
+                assert torch.equal(at, row[u])
+    builds, hits = own.spd_get_schedule_stats()
+    assert builds == 2 and hits == 2 * (steps - 1)
+    wl.public.lens = full_lens
+    own.close()
