@@ -5,6 +5,8 @@
 //                          A separate launch, not a last-workgroup-reduces scheme inside the partial kernel: on this
 //                          multi-die GPU a device-scope release/acquire writes back and invalidates a whole L2, which
 //                          cost more than the extra launch when every workgroup had to issue one.
+//   close_kernel           the closing kernel of both - one owner's combine, or both owners' and their merge - for rows of
+//                          at most 32 chunks, which is nearly all of them; the two kernels around it take the others
 //   finalize_step_kernel   last kernel of the fused step: combines whichever rows were split, for both owners, and
 //                          merges the owners, in one launch
 //   lse_merge_kernel       the two-owner merge itself: Y = w0 A_in + w1 A_out with w_x = exp(lse_x - lse).
@@ -276,6 +278,163 @@ __global__ __launch_bounds__(D) void finalize_step_kernel(const RowInfo *__restr
     if (tid == 0) {
         lse[row] = ls;
         w_in[row] = w0;
+    }
+}
+
+// ---- the closing kernel of steps and calls whose rows hold at most kCloseMaxChunks chunks ----------------------------
+// A thread takes four consecutive channels of one (user, query head); the sixteen lanes of a DPP row share a head, and lane i
+// of them holds the log-sum-exps (and weights) of chunks i and i + 16.  Bound by latency: three dependent round trips
+// (arguments, RowInfo, partials) and ~2 ns per instruction of a wave, so every load of both owners leaves at once, a
+// chunk's weight is computed once per row instead of once per channel, and 64-thread workgroups spread over the device.
+// Measured against the kernels above, which take rows of more chunks (us per call, before / after): the headline batch, 16
+// users of 512-4096 + 1-512 tokens, fused 33.6 / 33.0, 16 users of 96-768 + 256 13.4 / 12.9, 4 of them 8.8 / 8.4, 48 users
+// in token-major pages 164.0 / 162.7, 256 skewed users 453.0 / 450.7.
+constexpr int kCloseMaxChunks = 32;
+
+// All-reduce over the sixteen lanes of a DPP row (rotations by 8, 4, 2, 1).
+template <int CTRL>
+__device__ __forceinline__ float row_dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_max(float v)
+{
+    v = fmaxf(v, row_dpp<0x128>(v));
+    v = fmaxf(v, row_dpp<0x124>(v));
+    v = fmaxf(v, row_dpp<0x122>(v));
+    return fmaxf(v, row_dpp<0x121>(v));
+}
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += row_dpp<0x128>(v);
+    v += row_dpp<0x124>(v);
+    v += row_dpp<0x122>(v);
+    return v + row_dpp<0x121>(v);
+}
+
+// One owner's side of a head: up to MAXC (lse, four channels) pairs, all asked for at once.  A row that was not split (or
+// holds no token) is one pair, read from the caller's own A / lse arrays.
+template <int D, int MAXC>
+struct CloseRow {
+    static constexpr int NL = (MAXC + 15) / 16;  // log-sum-exps per lane
+    float l[NL];
+    f32x4 x[MAXC];
+    int n;
+
+    __device__ __forceinline__ void load(RowInfo ri, int G, int g, int64_t head, int ch, const float *part_o, const float *part_lse,
+                                         const float *a, const float *lse)
+    {
+        const bool split = ri.n_chunks > 1;
+        n = split ? ri.n_chunks : 1;
+        const int64_t slot = (int64_t)ri.first_slot * G + g;
+        const float *pl = split ? part_lse + slot : lse + head;
+        const float *po = (split ? part_o + slot * D : a + head * D) + ch;
+        const int last = n - 1, lane = threadIdx.x & 15;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            l[i] = pl[min(lane + 16 * i, last) * G];  // (past the end: the last pair again, with weight 0)
+#pragma unroll
+        for (int c = 0; c < MAXC; ++c)
+            x[c] = *reinterpret_cast<const f32x4 *>(po + (int64_t)min(c, last) * G * D);
+    }
+
+    template <int C = 0>
+    __device__ __forceinline__ void weighted(const float (&w)[NL], f32x4 &o) const
+    {
+        if constexpr (C < MAXC) {
+            const float wc = row_dpp<0x150 + (C & 15)>(w[C / 16]);  // row_newbcast: lane C & 15's value
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                o[v] = fmaf(wc, x[C][v], o[v]);
+            weighted<C + 1>(w, o);
+        }
+    }
+
+    // n-way form of Theorem 1, chunks in order; a single pair passes through unchanged (it may be an empty row: 0, -inf)
+    __device__ __forceinline__ void reduce(f32x4 &a_out, float &lse_out) const
+    {
+        const int lane = threadIdx.x & 15;
+        float m = -INFINITY, w[NL], den = 0.f;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            m = fmaxf(m, l[i]);
+        const float M = row_max(m);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            w[i] = lane + 16 * i >= n ? 0.f : n == 1 ? 1.f : fast_exp(l[i] - M);
+            den += w[i];
+        }
+        den = row_sum(den);
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        weighted(w, o);
+        a_out = n == 1 ? x[0] : o * fast_rcp(den);
+        lse_out = n == 1 ? l[0] : M + fast_log(den);
+    }
+};
+
+struct CloseArgs {
+    const RowInfo *rows_in, *rows_out;  // rows_in: nullptr if the first owner's partials are the caller's, finished
+    const float *part_o_in, *part_lse_in, *part_o_out, *part_lse_out;
+    const float *a_in_r, *lse_in_r;
+    float *a_in, *lse_in, *a_out, *lse_out;
+    float *y, *lse, *w_in;
+    int32_t heads, G;  // heads: users * Hq
+    uint32_t g_mul;    // ceil(2^32 / G): x / G is the high word of x * g_mul
+};
+
+// MAXI, MAXO: at least the chunks of any row of the first and the second owner; both owners' rows and their merge (as
+// finalize_step_kernel), or with MAXI = 0 the second owner's rows alone (as combine_chunks_kernel).
+template <int D, int MAXI, int MAXO>
+__global__ __launch_bounds__(64) void close_kernel(CloseArgs A)
+{
+    const int idx = (blockIdx.x * 64 + threadIdx.x) * 4, ch = idx % D;
+    const int64_t head = idx / D;
+    if (head >= A.heads)
+        return;  // whole 16-lane rows
+    const int row = A.G == 1 ? (int)head : (int)__umulhi((unsigned)head, A.g_mul), g = (int)head - row * A.G;
+    const RowInfo ro = A.rows_out[row], ri = MAXI && A.rows_in ? A.rows_in[row] : RowInfo{0, 1};
+    CloseRow<D, MAXO> out;
+    f32x4 x1;
+    float l1;
+    if constexpr (MAXI == 0) {
+        if (ro.n_chunks <= 1)
+            return;  // written by the partial kernel
+        out.load(ro, A.G, g, head, ch, A.part_o_out, A.part_lse_out, A.a_out, A.lse_out);
+        __builtin_amdgcn_sched_barrier(0);  // no load sinks to its use: they all leave now
+        out.reduce(x1, l1);
+        *reinterpret_cast<f32x4 *>(A.a_out + head * D + ch) = x1;
+        if (ch == 0)
+            A.lse_out[head] = l1;
+    } else {
+        CloseRow<D, MAXI> in;
+        in.load(ri, A.G, g, head, ch, A.part_o_in, A.part_lse_in, A.a_in_r, A.lse_in_r);
+        out.load(ro, A.G, g, head, ch, A.part_o_out, A.part_lse_out, A.a_out, A.lse_out);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 x0;
+        float l0;
+        in.reduce(x0, l0);
+        out.reduce(x1, l1);
+        if (ri.n_chunks > 1) {
+            *reinterpret_cast<f32x4 *>(A.a_in + head * D + ch) = x0;
+            if (ch == 0)
+                A.lse_in[head] = l0;
+        }
+        if (ro.n_chunks > 1) {
+            *reinterpret_cast<f32x4 *>(A.a_out + head * D + ch) = x1;
+            if (ch == 0)
+                A.lse_out[head] = l1;
+        }
+        float w0, w1, ls;
+        merge_weights(l0, l1, w0, w1, ls);
+        f32x4 y;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            y[v] = (w0 == 0.f ? 0.f : w0 * x0[v]) + (w1 == 0.f ? 0.f : w1 * x1[v]);
+        *reinterpret_cast<f32x4 *>(A.y + head * D + ch) = y;
+        if (ch == 0) {
+            A.lse[head] = ls;
+            A.w_in[head] = w0;
+        }
     }
 }
 

@@ -46,6 +46,7 @@ struct CachedSchedule {
     int32_t grow = 0;            // set by every lookup: tokens each row has gained over the lengths in `key`
     std::vector<uint8_t> key;
     int64_t n_items = 0, n_slots = 0, n_segments = 0;
+    int max_chunks = 0;      // chunks of the row that has the most
     int hpw = 0;             // 0, the KV heads per workgroup of the head-per-wave kernel the pieces are for, or kWholeRows
     int n_split_rows = 0;    // rows with several chunks: CombineRow[n_split_rows] follows the items (whole rows: the launch order)
     size_t off_rows = 0, off_info = 0;
@@ -168,6 +169,7 @@ struct ScheduleBlob {
     int64_t n_slots = 0;      // chunk partials
     int64_t n_segments = 0;   // segments with tokens
     int n_split_rows = 0;
+    int max_chunks = 0;
 };
 
 void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, const Tuning &tune, ScheduleBlob &B)
@@ -203,6 +205,8 @@ void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, co
     B.n_slots = S.n_slots;
     B.n_segments = T.n_segments;
     B.n_split_rows = (int)T.split_rows.size();
+    for (const RowInfo &r : T.row_info)
+        B.max_chunks = std::max(B.max_chunks, (int)r.n_chunks);
 }
 
 // Find or build the device-resident schedule for this view (hpw: pieces for the head-per-wave kernel).  Uploads are
@@ -320,6 +324,7 @@ int get_schedule(spd_ctx *ctx, Owner &own, const spd_shape *s, const spd_kv_view
     e.n_slots = B.n_slots;
     e.n_segments = B.n_segments;
     e.n_split_rows = B.n_split_rows;
+    e.max_chunks = B.max_chunks;
     e.off_rows = B.off_rows;
     e.off_info = B.off_info;
     *out = &e;
@@ -714,14 +719,48 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
     return SPD_OK;
 }
 
+// The closing kernel for rows of at most kCloseMaxChunks chunks (max_in: of the first owner, 0 if it is not there); false if
+// a row has more, or the heads do not fit its indices, and the general kernels have to do it.
+bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd::CloseArgs &C, hipStream_t stream)
+{
+    const int D = s->head_dim;
+    const int64_t heads = (int64_t)n_users * s->n_q_heads;
+    if (std::max(max_in, max_out) > spd::kCloseMaxChunks || heads * D >= (1ll << 30))
+        return false;
+    C.heads = (int32_t)heads;
+    C.G = s->n_q_heads / s->n_kv_heads;
+    C.g_mul = (uint32_t)(((1ull << 32) + C.G - 1) / C.G);
+    const dim3 grid((unsigned)((heads * D / 4 + 63) / 64));
+    auto size = [](int n) { return n <= 4 ? 4 : n <= 8 ? 8 : n <= 16 ? 16 : 32; };
+    return with_value<64, 128>(D, [&](auto d) {
+        return with_value<0, 4, 8, 16, 32>(max_in ? size(max_in) : 0, [&](auto mi) {
+            return with_value<4, 8, 16, 32>(size(max_out), [&](auto mo) {
+                hipLaunchKernelGGL((spd::close_kernel<decltype(d)::value, decltype(mi)::value, decltype(mo)::value>), grid, dim3(64), 0,
+                                   stream, C);
+                return true;
+            });
+        });
+    });
+}
+
 // The n-way combine of the rows that were split (a separate launch, see combine.hpp).
-int launch_combine(spd_ctx *ctx, int which, const CachedSchedule *e, const spd_shape *s, float *out, float *lse,
+int launch_combine(spd_ctx *ctx, int which, const CachedSchedule *e, const spd_shape *s, int n_users, float *out, float *lse,
                    hipStream_t stream)
 {
     if (e->n_split_rows == 0)
         return SPD_OK;
     Owner &own = ctx->owner[which];
     const int G = s->n_q_heads / s->n_kv_heads;
+    spd::CloseArgs C = {};
+    C.rows_out = reinterpret_cast<const RowInfo *>(e->dev + e->off_info);
+    C.part_o_out = own.part_o;
+    C.part_lse_out = own.part_lse;
+    C.a_out = out;
+    C.lse_out = lse;
+    if (launch_close(s, n_users, 0, e->max_chunks, C, stream)) {
+        SPD_HIP(ctx, hipGetLastError());
+        return SPD_OK;
+    }
     const CombineRow *rows = reinterpret_cast<const CombineRow *>(e->dev + e->off_rows);
     const dim3 grid((unsigned)e->n_split_rows, (unsigned)G);
     if (s->head_dim == 64)
@@ -772,7 +811,7 @@ int partial_attention(spd_ctx *ctx, int which, const spd_shape *s, const void *q
                         ScratchPtrs(), s, q, nt, stream);
     if (rc != SPD_OK)
         return rc;
-    return launch_combine(ctx, which, e, s, out, lse, stream);
+    return launch_combine(ctx, which, e, s, v->n_users, out, lse, stream);
 }
 
 // The closing kernel of a step: combines whichever rows either owner had to split and merges the owners.
@@ -786,6 +825,26 @@ int launch_finalize(spd_ctx *ctx, const spd_shape *shape, int n_users, const Cac
     const int G = shape->n_q_heads / shape->n_kv_heads;
     const RowInfo *ri = ep ? reinterpret_cast<const RowInfo *>(ep->dev + ep->off_info) : nullptr;
     const RowInfo *ro = reinterpret_cast<const RowInfo *>(eo->dev + eo->off_info);
+    spd::CloseArgs C = {};
+    C.rows_in = ri;
+    C.rows_out = ro;
+    C.part_o_in = sp_in.part_o;
+    C.part_lse_in = sp_in.part_lse;
+    C.part_o_out = sp_out.part_o;
+    C.part_lse_out = sp_out.part_lse;
+    C.a_in_r = a_in_r;
+    C.lse_in_r = lse_in_r;
+    C.a_in = a_in_w;
+    C.lse_in = lse_in_w;
+    C.a_out = a_out;
+    C.lse_out = lse_out;
+    C.y = y;
+    C.lse = lse;
+    C.w_in = w_in;
+    if (launch_close(shape, n_users, ep ? std::max(1, ep->max_chunks) : 1, eo->max_chunks, C, stream)) {
+        SPD_HIP(ctx, hipGetLastError());
+        return SPD_OK;
+    }
     const dim3 grid((unsigned)n_users, (unsigned)shape->n_kv_heads, (unsigned)G);
     if (shape->head_dim == 64)
         hipLaunchKernelGGL((spd::finalize_step_kernel<64>), grid, dim3(64), 0, stream, ri, ro, shape->n_kv_heads,
@@ -1364,6 +1423,7 @@ try {
         e[w].n_segments = B[w].n_segments;
         e[w].hpw = hpw;
         e[w].n_split_rows = B[w].n_split_rows;
+        e[w].max_chunks = B[w].max_chunks;
         e[w].off_rows = B[w].off_rows;
         e[w].off_info = B[w].off_info;
         sp[w].part_lse = reinterpret_cast<float *>(st.ptr + kStaticOffLse) + (size_t)w * kStaticLseFloats;

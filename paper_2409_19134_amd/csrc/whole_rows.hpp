@@ -52,27 +52,6 @@ __device__ __forceinline__ RowItem scalar_load_row(const RowItem *items, int idx
     return it;
 }
 
-// All-reduce over the sixteen lanes of a row (rotations by 8, 4, 2, 1).
-template <int CTRL>
-__device__ __forceinline__ float row_dpp(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float row_max(float v)
-{
-    v = fmaxf(v, row_dpp<0x128>(v));
-    v = fmaxf(v, row_dpp<0x124>(v));
-    v = fmaxf(v, row_dpp<0x122>(v));
-    return fmaxf(v, row_dpp<0x121>(v));
-}
-__device__ __forceinline__ float row_sum(float v)
-{
-    v += row_dpp<0x128>(v);
-    v += row_dpp<0x124>(v);
-    v += row_dpp<0x122>(v);
-    return v + row_dpp<0x121>(v);
-}
-
 // sum[v] += weight of slot S * os[S][v] over the slots; owner 0's sums (slots [0, n0)) move to `first`.
 template <int MAXS, int VEC, int S = 0>
 __device__ __forceinline__ void weighted_slots(const float (&os)[MAXS][VEC], float w, int n0, float (&first)[VEC], float (&sum)[VEC])

@@ -546,6 +546,24 @@ def test_run_to_run_determinism_and_user_permutation(ctx):
     own.close()
 
 
+@pytest.mark.parametrize("most", [4, 8, 16, 32, 33])     # 33: more than the closing kernel's instances hold
+@pytest.mark.parametrize("dtype,d,Hq,Hkv", [(torch.bfloat16, 128, 8, 2), (torch.float32, 64, 3, 3), (torch.float16, 64, 10, 2)])
+def test_closing_kernel_chunk_counts(most, dtype, d, Hq, Hkv):
+    """Rows of 0, 1, 2, ... `most` chunks of 128 tokens, each owner's largest in turn: the closing kernel is picked by the
+    most chunks either owner's rows have."""
+    import paper_2409_19134_amd as spd
+    own = spd.Context(0)
+    own.spd_set_option(spd.SPD_OPT_NO_SPLIT_MAX, 1 << 20)          # every row is cut into chunks of 128 tokens
+    counts = [n for n in (0, 1, 2, 4, 5, 8, 9, 16, 17, 32, 33) if n <= most]
+    some = [0, 1, 3, 2]
+    lens = [128 * n - 5 if n else 0 for n in counts]
+    few = [128 * some[i % 4] for i in range(len(counts))]
+    for lp, lo in ((lens, few), (few, lens), (lens, lens[::-1])):
+        wl = workloads.random_case(143, dtype, len(counts), Hq, Hkv, d, lp, lo, device=DEV, layout="hnd")
+        check_against_oracle(own, wl)
+    own.close()
+
+
 def test_token_permutation_invariance(ctx):
     """A decode query attends to a set of tokens: shuffling a cache's tokens (K and V together) changes nothing
     beyond rounding."""
