@@ -129,6 +129,8 @@ int spd_last_hip_error(const spd_ctx *ctx);
  * SPD_CHUNK_MAX=4096), read once at that moment; spd_set_option changes it for later calls of this context.  The
  * schedule-shaping options are part of the key a cached schedule is found by, so a change never reuses a schedule
  * built under other options.  Out-of-range values are refused with SPD_ERR_LEN, unknown options with SPD_ERR_SHAPE.
+ * Calls over short rows take every row whole, one workgroup each, in a single launch and without a split schedule - as
+ * long as the mapping, the schedule-shaping options and SPD_OPT_STEPS_IN_FLIGHT all hold their defaults.
  */
 enum {
     SPD_OPT_HEAD_PER_WAVE = 0,    /* -1 (default): head-per-wave mapping for large token-major views; 0 never; 1 whenever
@@ -225,7 +227,7 @@ int spd_lse_merge_n(spd_ctx *ctx, int32_t n_parts, int32_t n_rows, int32_t head_
  * The paper's prototype overlaps the users' private computation with the service's public one; here both owners'
  * work is placed in one launch (the public owner's short pieces run beside the private owner's long streams on the
  * same compute units) and a single closing kernel combines whatever rows either owner had to split and merges the
- * two owners.  Results are those of the three calls above made in sequence, all of them still delivered:
+ * two owners.  (A step over short rows is one launch that does all of this.)  Results are those of the three calls above made in sequence, all of them still delivered:
  *   a_in, lse_in   = spd_partial_attn_private(q, priv)            [n_users][Hq][d], [n_users][Hq]
  *   a_out, lse_out = spd_partial_attn_public_batched(q, pub)
  *   y, lse, w_in   = spd_lse_merge(a_in, lse_in, a_out, lse_out)   (all three required here)
@@ -324,7 +326,7 @@ typedef struct spd_work_item {
 /*
  * Build the split schedule for `lens` (HOST, [n_users]) on a device with `n_compute_units` CUs, under the default
  * options (see spd_set_option) or what the SPD_* environment variables say at the time of the call, as an owner of a
- * fused step gets it (a call for one owner alone takes half as many pieces per compute unit again).  The 32-token steps
+ * fused step whose rows are split gets it (a call for one owner alone takes half as many pieces per compute unit again).  The 32-token steps
  * of all rows, laid end to end, are cut into pieces of equal length (+-1 step, apart from what SPD_OPT_SEG_COST and
  * SPD_OPT_HALF_SKEW take from or add to a piece).  Every token of every (user, KV head)
  * is covered by exactly one segment; segment boundaries inside a row are multiples of 32 tokens.

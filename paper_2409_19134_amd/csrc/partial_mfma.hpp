@@ -36,7 +36,7 @@
 // us per fused step): the 4x4 blocks 73.9 -> 71.7; a lane's V loads cover 256 contiguous bytes per instruction instead
 // of every other 16 (whose lines were asked for twice) -> 64.6; a wave's step is 16 tokens, 16 KB as at 16 bits, so that
 // three waves per SIMD fit and the public owner's pieces start with the private ones -> 62.1 (5.5 TB/s).  Two 16-token
-// steps in flight with two waves per SIMD: 64.4; the same order on 13 GB (1667 against 1702, before 1915).
+// steps in flight with two waves per SIMD: 64.4; the same order on 10.9 GB (1667 against 1702, before 1915).
 // Every K/V byte is read once per KV head (all G heads share the tile).
 // The four waves of a workgroup take interleaved 32-token steps and are combined through LDS; the result rows of a
 // workgroup that crosses many rows wait in LDS too and are stored together (the result ring, below).

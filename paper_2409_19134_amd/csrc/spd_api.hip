@@ -581,8 +581,8 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     // 128 users 225.7 / 222.0, with 8 query heads per KV head 452.0 / 446.2; 128 users of 64-512 tokens 50.8 / 50.0; 256
     // such users 88.9 / 89.7; the standalone public call of workload 2 -0.3 us).  Head-per-wave workgroups fit one per
     // CU either way; with 128-byte rows a step is half the bytes, always two in flight; fp32 keeps one (at 128
-    // channels two in flight with two waves per SIMD measured 2 % slower than one with three, also on 13 GB).  SPD_OPT_STEPS_IN_FLIGHT overrides the size
-    // rule (tests run both kernels on the same small inputs).
+    // channels two in flight with two waves per SIMD measured 2 % slower than one with three, also on 10.9 GB).
+    // SPD_OPT_STEPS_IN_FLIGHT overrides the size rule (tests run both kernels on the same small inputs).
     const int64_t cus = std::max(1, ctx->n_cus);
     const int row_bytes = D * elt_size(s->dtype);
     const bool by_size = ctx->steps_in_flight < 0 ? n0 + n1 > cus * 4 : ctx->steps_in_flight == 2;
