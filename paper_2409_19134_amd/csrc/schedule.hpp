@@ -351,6 +351,7 @@ struct WholeRowsLoad {
     int Hkv = 0, n_cus = 0, n_users = 0;
     const int32_t *lens0 = nullptr, *lens1 = nullptr;  // lens1: the second owner's, or nullptr
     bool limit_halved = false;
+    bool always = false;  // whole rows whatever the rule says: the wave count is all that is asked for
 };
 // One owner's call saves less (its combine launch is shorter, ~3 us) and keeps the split schedule from 12 on (three calls,
 // 8 users of <= 1536 + 512 tokens, the public call at 12.2: 22.5 / 24.3; 16 users of <= 768 + 256, the private call at 15:
@@ -383,7 +384,7 @@ inline int whole_rows_choice(const WholeRowsLoad &c)
     }
     const int64_t limit = (c.step_bytes / c.tile == 1024 ? kWholeRowsLimit512 : kWholeRowsLimit) >> (c.limit_halved ? 1 : 0);
     const int64_t unit = 16384, tail = c.lens1 || rows * 8 <= cus ? kWholeRowsTail : kWholeRowsTailOneOwner;
-    if (longest * c.step_bytes > limit * unit || longest * c.step_bytes - total * c.Hkv * c.step_bytes / slots > tail * unit)
+    if (!c.always && (longest * c.step_bytes > limit * unit || longest * c.step_bytes - total * c.Hkv * c.step_bytes / slots > tail * unit))
         return 0;
     return (int)std::min(waves, std::max<int64_t>(1, longest));
 }

@@ -209,10 +209,16 @@ void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, co
         B.max_chunks = std::max(B.max_chunks, (int)r.n_chunks);
 }
 
+// A view whose lengths have grown can cross the border between whole and split rows: the schedule that the rule now wants
+// is then a new one, where the old one would still have served the call.  While the stream is being captured nothing is
+// built as long as the other way of taking the rows is remembered: the calls try the rule's, the other, and then build.
+constexpr int kNotRemembered = 1;  // (not an error code: those are negative)
+constexpr int kTries = 3;
+
 // Find or build the device-resident schedule for this view (hpw: pieces for the head-per-wave kernel).  Uploads are
-// enqueued on `stream`.
+// enqueued on `stream`.  build: false leaves it at kNotRemembered if the stream is being captured.
 int get_schedule(spd_ctx *ctx, Owner &own, const spd_shape *s, const spd_kv_view *v, int hpw, const Tuning &tune,
-                 hipStream_t stream, CachedSchedule **out)
+                 hipStream_t stream, bool build, CachedSchedule **out)
 {
     std::vector<uint8_t> &key = ctx->key_scratch;  // reused from call to call: no allocation on the hit path
     make_key(s, v, hpw, &tune.target_wg_per_cu, kTuningInts, key);
@@ -255,6 +261,12 @@ int get_schedule(spd_ctx *ctx, Owner &own, const spd_shape *s, const spd_kv_view
         ++ctx->schedule_hits;
         *out = grown;
         return SPD_OK;
+    }
+    if (!build) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        SPD_HIP(ctx, hipStreamIsCapturing(stream, &capture));
+        if (capture != hipStreamCaptureStatusNone)
+            return kNotRemembered;
     }
     ScheduleBlob B;
     build_blob(s, v, hpw, ctx->n_cus, tune, B);
@@ -393,7 +405,8 @@ bool default_kernel_options(const spd_ctx *ctx)
 // Waves per workgroup of the whole-rows kernel for a call over v0 (and v1: both owners of a fused step), or 0 if the call
 // takes the split schedule.  A whole-rows call is one launch without a closing kernel (4-5 us of GPU time, 3 of the
 // host's), but the device waits for the longest row.
-int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *v0, const spd_kv_view *v1)
+// always: the rule is not asked (the call takes whole rows if its views and the options allow them at all).
+int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *v0, const spd_kv_view *v1, bool always = false)
 {
     const int n = v0->n_users;
     if (!default_kernel_options(ctx) || n > 65535 || (v1 && (v0->block_size != 0) != (v1->block_size != 0)))
@@ -406,6 +419,7 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
     load.n_users = n;
     load.lens0 = v0->lens;
     load.lens1 = v1 ? v1->lens : nullptr;
+    load.always = always;
     // token-major storage long enough for the head-per-wave mapping, which reads whole DRAM pages: up to half the limit
     // (two parties appending, token-major, 256 users of 96-768 + 256 tokens 116.1 us against 130.4, 192-1536 + 512: 214.5
     // against 208.6)
@@ -419,7 +433,7 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
 
 // Validation, schedule lookup and scratch growth of one partial-attention call.
 int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const void *q, const spd_kv_view *v, float *out,
-                    float *lse, int mapping, const Tuning *tune, hipStream_t stream, CachedSchedule **e)
+                    float *lse, int mapping, const Tuning *tune, hipStream_t stream, bool build, CachedSchedule **e)
 {
     const int rc = spd_validate_partial(s, q, v, out, lse);
     if (rc != SPD_OK)
@@ -435,11 +449,24 @@ int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const void *q, 
         hpw = head_per_wave_layout(s, v) ? head_per_wave_choice(ctx, s, total_steps(v)) : 0;
     // tune: the fused step's; none for a call that serves one owner alone
     const int rs = get_schedule(ctx, own, s, v, hpw, tune ? *tune : hpw == kWholeRows ? ctx->tuning : standalone_tuning(ctx, s, v, hpw),
-                                stream, e);
+                                stream, build, e);
     if (rs != SPD_OK)
         return rs;
     const int G = s->n_q_heads / s->n_kv_heads;
     return ensure_scratch(ctx, own, (size_t)(*e)->n_slots * G * s->head_dim + 4, (size_t)(*e)->n_slots * G + 4);
+}
+
+// The schedule of a call for one owner alone: whole rows (*waves > 0) or split, see kNotRemembered.
+int prepare_one_owner(spd_ctx *ctx, int which, const spd_shape *s, const void *q, const spd_kv_view *v, float *out, float *lse,
+                      hipStream_t stream, CachedSchedule **e, int *waves)
+{
+    const int rule = whole_rows_waves(ctx, s, v, nullptr);
+    int rc = kNotRemembered;
+    for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {
+        *waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, s, v, nullptr, true);
+        rc = prepare_partial(ctx, which, s, q, v, out, lse, *waves ? kWholeRows : -1, nullptr, stream, t == kTries - 1, e);
+    }
+    return rc;
 }
 
 // Where one owner's chunk partials go: the context's own scratch memory, or a part of the library's fixed array.
@@ -801,8 +828,8 @@ int partial_attention(spd_ctx *ctx, int which, const spd_shape *s, const void *q
         rc = validate_new_token(v, nt);
     if (rc != SPD_OK)
         return rc;
-    const int waves = whole_rows_waves(ctx, s, v, nullptr);
-    rc = prepare_partial(ctx, which, s, q, v, out, lse, waves ? kWholeRows : -1, nullptr, stream, &e);
+    int waves = 0;
+    rc = prepare_one_owner(ctx, which, s, q, v, out, lse, stream, &e, &waves);
     if (rc != SPD_OK || !e)
         return rc;
     if (waves)
@@ -933,7 +960,7 @@ int launch_decode_step(spd_ctx *ctx, const spd_shape *shape, const void *q, cons
         mg.y = y;
         mg.lse = lse;
         mg.w_in = w_in;
-        return launch_whole_rows(ctx, 0, whole_rows_waves(ctx, shape, priv, pub), ep, priv, a_in, lse_in, eo, pub, a_out, lse_out, shape,
+        return launch_whole_rows(ctx, 0, whole_rows_waves(ctx, shape, priv, pub, true), ep, priv, a_in, lse_in, eo, pub, a_out, lse_out, shape,
                                  q, nt, mg, stream);
     }
     // one grid for both owners, the private owner's long streams first (measured faster than public first): the
@@ -1346,12 +1373,17 @@ try {
     if (rc != SPD_OK || priv->n_users == 0)
         return rc;
     CachedSchedule *ep = nullptr, *eo = nullptr;
-    const int hpw = fused_step_mapping(ctx, shape, priv, pub);
-    const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);
-    rc = prepare_partial(ctx, 0, shape, q, priv, a_in, lse_in, hpw, &tune, stream, &ep);
-    if (rc != SPD_OK)
-        return rc;
-    rc = prepare_partial(ctx, 1, shape, q, pub, a_out, lse_out, hpw, &tune, stream, &eo);  // an upload, if any, stays on `stream`
+    const int rule = fused_step_mapping(ctx, shape, priv, pub);
+    rc = kNotRemembered;
+    for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {  // see kNotRemembered
+        int hpw = rule;
+        if (t == 1)
+            hpw = rule != kWholeRows && whole_rows_waves(ctx, shape, priv, pub, true) ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
+        const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);
+        rc = prepare_partial(ctx, 0, shape, q, priv, a_in, lse_in, hpw, &tune, stream, t == kTries - 1, &ep);
+        if (rc == SPD_OK)
+            rc = prepare_partial(ctx, 1, shape, q, pub, a_out, lse_out, hpw, &tune, stream, t == kTries - 1, &eo);  // an upload, if any, stays on `stream`
+    }
     if (rc != SPD_OK)
         return rc;
     return launch_decode_step(ctx, shape, q, priv, pub, nt, ep, eo, scratch_of(ctx->owner[0]), scratch_of(ctx->owner[1]), a_in,
@@ -1458,8 +1490,8 @@ try {
     if (!aligned16(a_in) || !aligned16(y))
         return SPD_ERR_ALIGN;
     CachedSchedule *eo = nullptr;
-    const int waves = whole_rows_waves(ctx, shape, pub, nullptr);
-    rc = prepare_partial(ctx, 1, shape, q, pub, a_out, lse_out, waves ? kWholeRows : -1, nullptr, stream, &eo);
+    int waves = 0;
+    rc = prepare_one_owner(ctx, 1, shape, q, pub, a_out, lse_out, stream, &eo, &waves);
     if (rc != SPD_OK)
         return rc;
     if (waves) {

@@ -124,3 +124,59 @@ def test_decode_loop_appends_on_whole_rows(ctx, paged):
     assert builds == 2 and hits == 2 * (steps - 1)
     wl.public.lens = full_lens
     own.close()
+
+
+@pytest.mark.parametrize("entry", ["fused", "public", "merge"])
+def test_capture_of_a_view_that_has_grown_across_the_rule(entry):
+    """A schedule serves a view whose lengths have grown by up to 64 tokens, also while the stream is captured: so it does
+    where the growth takes the rows from whole to split - the remembered way of taking them is kept and nothing is built."""
+    import paper_2409_19134_amd as spd
+    U = 4
+    lp, lo = ([480, 100, 97, 128], [64] * U) if entry == "fused" else ([64] * U, [560, 100, 97, 128])
+    wl = workloads.random_case(506, torch.bfloat16, U, 8, 2, 128, lp, lo, device=DEV, layout="hnd")
+    lens = wl.public.lens.copy()
+    own = spd.Context(0)
+    side = torch.cuda.Stream()
+
+    def call(step):
+        if entry == "fused":
+            step.run_fused(wl.q)
+        elif entry == "public":
+            own.spd_partial_attn_public_batched(step.shape, wl.q, step.public, step.a_out, step.lse_out)
+        else:
+            own.spd_public_attn_merge(step.shape, wl.q, step.public, step.a_in, step.lse_in, step.a_out, step.lse_out, step.y,
+                                      step.lse, step.w_in)
+
+    def step_at(grown):
+        wl.public.lens = (lens - 60 + grown).astype(np.int32)
+        return spd.DecodeStep.from_workload(own, wl)
+
+    seen = set()
+    with torch.cuda.stream(side):
+        first = step_at(0)
+        for t in (first.a_in, first.lse_in):
+            t.zero_()
+        call(first)
+        torch.cuda.synchronize()
+        builds = own.spd_get_schedule_stats()[0]
+        for grown in (5, 30, 60):
+            step = step_at(grown)
+            for t in (step.a_in, step.lse_in):
+                t.zero_()
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                call(step)
+            seen.add(own.spd_last_kernel_name().split("<")[0])
+            for _ in range(3):
+                step.a_out.fill_(float("nan"))
+                graph.replay()
+                torch.cuda.synchronize()
+                A, _, _ = orc.partial(orc.from_workload(wl), orc.from_workload(wl).public)
+                assert np.abs(step.a_out.cpu().double().numpy().reshape(A.shape) - A).max() <= TOL[wl.dtype]
+        assert own.spd_get_schedule_stats()[0] == builds
+        assert seen == {"whole_rows_kernel"}
+        call(step_at(60))                          # outside a capture the rule decides: these rows are split
+        torch.cuda.synchronize()
+        assert own.spd_last_kernel_name().startswith("partial_mfma_kernel")
+    own.close()
