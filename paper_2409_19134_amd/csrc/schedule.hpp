@@ -320,6 +320,15 @@ inline const char *row_base(const spd_kv_view *v, int es, int u, int h, bool is_
 // The tables of the whole-rows kernel: an item per row, indexed user * Hkv + KV head, and the users by length, longest
 // first (the launch order where the rows do not all fit the device at once).
 constexpr int kWholeRows = 64;  // in place of the head-per-wave mapping's KV heads per workgroup (0, 2..8)
+// As laid out for device memory: RowItem[n_users * Hkv] | int32[n_users], each part 256-byte aligned.
+inline size_t whole_rows_order_offset(int n_users, int Hkv)
+{
+    return ((size_t)n_users * Hkv * sizeof(spd::RowItem) + 255) / 256 * 256;
+}
+inline size_t whole_rows_bytes(int n_users, int Hkv)
+{
+    return whole_rows_order_offset(n_users, Hkv) + ((size_t)n_users * sizeof(int32_t) + 255) / 256 * 256;
+}
 inline void build_whole_rows(int Hkv, int es, const spd_kv_view *v, std::vector<spd::RowItem> &items, std::vector<int32_t> &order)
 {
     items.assign((size_t)v->n_users * Hkv, spd::RowItem{});

@@ -178,8 +178,8 @@ void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, co
         std::vector<spd::RowItem> items;
         std::vector<int32_t> order;
         build_whole_rows(s->n_kv_heads, elt_size(s->dtype), v, items, order);
-        B.off_rows = B.off_info = (items.size() * sizeof(spd::RowItem) + 255) / 256 * 256;
-        B.bytes.assign(B.off_rows + (order.size() * sizeof(int32_t) + 255) / 256 * 256, 0);
+        B.off_rows = B.off_info = whole_rows_order_offset(v->n_users, s->n_kv_heads);
+        B.bytes.assign(whole_rows_bytes(v->n_users, s->n_kv_heads), 0);
         std::memcpy(B.bytes.data(), items.data(), items.size() * sizeof(spd::RowItem));
         std::memcpy(B.bytes.data() + B.off_rows, order.data(), order.size() * sizeof(int32_t));
         B.n_items = B.n_segments = (int64_t)items.size();
@@ -1411,12 +1411,16 @@ try {
     StaticScratch &st = g_static[(size_t)ctx->device];
     if (!st.ptr)
         return SPD_ERR_WORKSPACE;
-    const int hpw = fused_step_mapping(ctx, shape, priv, pub);
+    int hpw = fused_step_mapping(ctx, shape, priv, pub);
     const int split = hpw == kWholeRows ? split_step_mapping(ctx, shape, priv, pub) : hpw;
+    // The tables of rows taken whole can be larger than the split schedule's - token-major storage has an item per group of
+    // four or eight heads there, one per head here: what the array has no room for stays split.
+    if (hpw == kWholeRows && whole_rows_bytes(priv->n_users, shape->n_kv_heads) > kStaticSchedBytes)
+        hpw = split;
     const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, split);
     const int G = shape->n_q_heads / shape->n_kv_heads;
-    // both schedules are built and checked against the array's limits before anything is enqueued; the limits are those of
-    // the split schedule, also for a step whose rows are taken whole (which needs less)
+    // both schedules are built and checked against the array's limits before anything is enqueued; the step is refused by
+    // the split schedule's needs also if its rows are taken whole, so that the limits do not depend on the mapping
     ScheduleBlob B[2];
     const spd_kv_view *views[2] = {priv, pub};
     std::vector<uint8_t> key[2];

@@ -1,0 +1,204 @@
+// The library's host side on a HIP runtime that is not there: this program defines the runtime's functions itself, so that
+// the built library (loaded with dlopen) allocates from the heap and every launch is recorded instead of run - only the two
+// kernels that carry schedules are carried out.  Run without a GPU by tests/test_host_calls.py.
+#include <dlfcn.h>
+
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../../include/spd.h"
+
+struct dim3 {
+    uint32_t x, y, z;
+};
+struct Launch {
+    std::string kernel;
+    dim3 grid, block;
+    size_t lds;
+};
+struct Upload {  // bytes a schedule's upload has written
+    char *dst;
+    size_t n;
+};
+static std::vector<Launch> launches;
+static std::vector<Upload> uploads;
+
+static std::map<const void *, std::string> &names()
+{
+    static std::map<const void *, std::string> m;
+    return m;
+}
+static char *static_array()
+{
+    static char *p = static_cast<char *>(std::aligned_alloc(256, SPD_STATIC_SCRATCH_BYTES));
+    return p;
+}
+
+static void launched(const void *fn, dim3 grid, dim3 block, void **args, size_t lds)
+{
+    const std::string &name = names()[fn];
+    launches.push_back(Launch{name, grid, block, lds});
+    const bool by_args = name.find("upload_args_kernel") != std::string::npos;
+    if (by_args || name.find("upload_kernel") != std::string::npos) {
+        const char *src = by_args ? static_cast<const char *>(args[0]) : *static_cast<const char **>(args[0]);
+        char *dst = *static_cast<char **>(args[1]);
+        const size_t n = (size_t)*static_cast<unsigned *>(args[2]) * 16;
+        uploads.push_back(Upload{dst, n});
+        if (!by_args || (dst >= static_array() && dst + n <= static_array() + SPD_STATIC_SCRATCH_BYTES))
+            std::memcpy(dst, src, n);
+    }
+}
+
+extern "C" {
+struct Config {
+    dim3 grid, block;
+    size_t lds;
+    void *stream;
+};
+static Config pushed;
+int hipGetDeviceCount(int *n) { return *n = 1, 0; }
+int hipSetDevice(int) { return 0; }
+int hipDeviceGetAttribute(int *v, int, int) { return *v = 256, 0; }  // compute units
+int hipDeviceSynchronize() { return 0; }
+int hipMalloc(void **p, size_t n) { return *p = std::malloc(n), 0; }
+int hipFree(void *p) { return std::free(p), 0; }
+int hipHostMalloc(void **p, size_t n, unsigned) { return *p = std::malloc(n), 0; }
+int hipHostFree(void *p) { return std::free(p), 0; }
+int hipGetSymbolAddress(void **p, const void *) { return *p = static_array(), 0; }
+int hipEventCreate(void **e) { return *e = e, 0; }
+int hipEventCreateWithFlags(void **e, unsigned) { return *e = e, 0; }
+int hipEventDestroy(void *) { return 0; }
+int hipEventRecord(void *, void *) { return 0; }
+int hipEventSynchronize(void *) { return 0; }
+int hipEventElapsedTime(float *ms, void *, void *) { return *ms = 0.f, 0; }
+int hipGetLastError() { return 0; }
+int hipStreamIsCapturing(void *, int *status) { return *status = 0, 0; }
+void **__hipRegisterFatBinary(const void *)
+{
+    static void *handle;
+    return &handle;
+}
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *fn, char *, const char *name, unsigned, void *, void *, void *, void *, int *)
+{
+    names()[fn] = name;
+}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, void *stream)
+{
+    pushed = Config{grid, block, lds, stream};
+    return 0;
+}
+int __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, void **stream)
+{
+    *grid = pushed.grid, *block = pushed.block, *lds = pushed.lds, *stream = pushed.stream;
+    return 0;
+}
+int hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, void *)
+{
+    launched(fn, grid, block, args, lds);
+    return 0;
+}
+int hipExtLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, void *, void *, void *, int)
+{
+    launched(fn, grid, block, args, lds);
+    return 0;
+}
+}
+
+#define FAIL(...)                 \
+    do {                          \
+        std::printf(__VA_ARGS__); \
+        std::printf("\n");        \
+        return 1;                 \
+    } while (0)
+
+template <class F>
+static F symbol(void *lib, F, const char *name)
+{
+    return reinterpret_cast<F>(dlsym(lib, name));
+}
+#define SYM(f) const auto f##_ = symbol(lib, &f, #f)
+
+// Both owners of a step over users of `lp` and `lo` tokens; addresses are passed on, never read.
+struct Step {
+    spd_shape s;
+    std::vector<int32_t> lens[2];
+    std::vector<const void *> ptrs;
+    spd_kv_view v[2] = {};
+    float *buf = reinterpret_cast<float *>(0x700000000000ull);
+
+    Step(int dtype, int Hq, int Hkv, int d, int users, int lp, int lo, bool token_major)
+        : s{dtype, Hq, Hkv, d, 0.1f}, lens{std::vector<int32_t>((size_t)users, lp), std::vector<int32_t>((size_t)users, lo)}
+    {
+        for (int u = 0; u < users; ++u)
+            ptrs.push_back(reinterpret_cast<const void *>(0x100000000ull * (uint64_t)(u + 1)));
+        for (int w = 0; w < 2; ++w) {
+            v[w].n_users = users;
+            v[w].lens = lens[w].data();
+            v[w].k_ptrs = v[w].v_ptrs = ptrs.data();
+            v[w].token_stride = token_major ? (int64_t)Hkv * d : d;
+            v[w].head_stride = token_major ? d : (int64_t)4096 * d;
+        }
+    }
+};
+
+int main(int, char **argv)
+{
+    void *lib = dlopen(argv[1], RTLD_NOW);
+    if (!lib)
+        FAIL("%s", dlerror());
+    SYM(spd_create);
+    SYM(spd_destroy);
+    SYM(spd_decode_step_static);
+    SYM(spd_get_last_kernel_instance);
+    spd_ctx *ctx = nullptr;
+    if (spd_create_(&ctx, 0) != SPD_OK)
+        FAIL("spd_create");
+
+    // the static step: each owner's schedule stays inside its own half MiB of the array.  (Its own limits say what fits; a step
+    // that fits when its rows are split fits.)
+    struct Case {
+        int Hq, Hkv, d, users, lp, lo;
+        bool token_major;
+        int rc;
+    };
+    const Case cases[] = {
+        {8, 8, 64, 2500, 64, 32, true, SPD_OK},    // an item per four heads when split, one per head when taken whole
+        {16, 16, 64, 1200, 64, 32, true, SPD_OK},
+        {8, 8, 64, 2000, 64, 32, true, SPD_OK},    // the largest whole-rows tables that fit: 32 bytes a row, 4 a user
+        {8, 8, 64, 2016, 64, 32, true, SPD_OK},
+        {8, 8, 64, 2017, 64, 32, true, SPD_OK},
+        {32, 8, 128, 16, 200, 60, false, SPD_OK},
+        {32, 8, 128, 2100, 40, 40, false, SPD_ERR_WORKSPACE},
+    };
+    constexpr size_t kHalf = 512u << 10;
+    for (const Case &c : cases) {
+        Step st(SPD_BF16, c.Hq, c.Hkv, c.d, c.users, c.lp, c.lo, c.token_major);
+        uploads.clear();
+        const int rc = spd_decode_step_static_(ctx, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf, st.buf,
+                                               st.buf, st.buf, st.buf, nullptr);
+        if (rc != c.rc || (rc != SPD_OK && !uploads.empty()))
+            FAIL("static step, %d users: %d, %zu uploads", c.users, rc, uploads.size());
+        std::vector<std::pair<size_t, size_t>> at;
+        for (const Upload &u : uploads) {
+            const size_t b = (size_t)(u.dst - static_array()), e = b + u.n;
+            if (e > 2 * kHalf || (b < kHalf && e > kHalf))
+                FAIL("static step, %d users: bytes %zu..%zu leave their owner's part", c.users, b, e);
+            at.push_back({b, e});
+        }
+        std::sort(at.begin(), at.end());
+        for (size_t i = 1; i < at.size(); ++i)
+            if (at[i].first < at[i - 1].second)
+                FAIL("static step, %d users: the owners' tables overlap at %zu", c.users, at[i].first);
+    }
+    spd_destroy_(ctx);
+    std::printf("ok\n");
+    std::fflush(stdout);
+    _Exit(0);
+}

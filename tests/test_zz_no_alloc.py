@@ -115,3 +115,26 @@ def test_static_step_in_a_hip_graph_without_warm_up():
         for name in OUTPUTS:
             assert torch.equal(getattr(step, name).view(torch.int32), getattr(ref_step, name).view(torch.int32)), (rep, name)
     ctx.close()
+
+
+def test_static_step_whose_whole_rows_tables_exceed_the_array():
+    """Token-major, 2500 users of short rows: the split schedule has an item per four heads and fits, the tables of rows
+    taken whole have one per head and do not - the step takes the split schedule."""
+    import paper_2409_19134_amd as spd
+    ctx = spd.Context(0)
+    wl = workloads.random_case(84, torch.bfloat16, 2500, 8, 8, 64, [64] * 2500, [32] * 2500, device=DEV, layout="nhd")
+    step = spd.DecodeStep.from_workload(ctx, wl)
+    step.run_fused(wl.q)
+    assert ctx.spd_last_kernel_name().startswith("whole_rows_kernel<")     # the allocating step has the room
+    ctx.spd_decode_step_static(step.shape, wl.q, step.private, step.public, step.a_in, step.lse_in, step.a_out,
+                               step.lse_out, step.y, step.lse, step.w_in)
+    assert ctx.spd_last_kernel_name().startswith("partial_mfma_kernel<")
+    torch.cuda.synchronize()
+    split = spd.Context(0)
+    split.spd_set_option(spd.SPD_OPT_STEPS_IN_FLIGHT, 2)                   # what the head-per-wave mapping takes anyway
+    ref = spd.DecodeStep.from_workload(split, wl)
+    ref.run_fused(wl.q)
+    torch.cuda.synchronize()
+    _same({n: getattr(ref, n) for n in OUTPUTS}, {n: getattr(step, n) for n in OUTPUTS})
+    split.close()
+    ctx.close()
