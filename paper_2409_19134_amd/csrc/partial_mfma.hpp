@@ -440,7 +440,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
     __shared__ float sm_m[kWaves][16];
     __shared__ float sm_l[kWaves][16];
     __shared__ float *ring_dst_o[kRingMaxRows], *ring_dst_l[kRingMaxRows];  // where the ring's rows go
-    extern __shared__ float sm_o[];  // [waves][G * kOStride], sized by the launch: only G heads are staged; then the ring
+    extern __shared__ __align__(16) float sm_o[];  // [waves][G * kOStride], sized by the launch: only G heads are staged; then the ring
     constexpr int kOStride = o_stride(D);
     constexpr int CP = D / 16;  // channel phases of the O^T tile: a lane holds CP consecutive channels per accumulator row
     constexpr int kRowBytes = D * Elt<DT>::kBytes;

@@ -16,6 +16,15 @@
 
 namespace spd {
 
+// The kernel's static part of the LDS.  The slots' results follow it and are read and written 16 bytes at a time, so its
+// size is a multiple of 16.
+struct alignas(16) RowsShared {
+    float2 ml[kRowsMaxWaves + 1][16];  // running max and sum of every slot
+    int n0;                            // slots [0, n0) are owner 0's
+    int extra;                         // whether the extra slot is used
+};
+static_assert(sizeof(RowsShared) % 16 == 0, "the dynamic part starts where this ends");
+
 // One owner's call as the kernel needs it.
 struct RowsOwner {
     const RowItem *items;
@@ -171,9 +180,8 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     constexpr bool kQuad = DT == kF32Quad;
     constexpr int CP = D / 16;
     constexpr int kOStride = o_stride(D);
-    __shared__ float2 sm_ml[kRowsMaxWaves + 1][16];  // running max and sum of every slot
-    __shared__ int sm_split[2];      // slots [0, sm_split[0]) are owner 0's; whether the extra slot is used
-    extern __shared__ float sm_o[];  // [waves + 1][G][kOStride]
+    __shared__ RowsShared sm;
+    extern __shared__ __align__(16) float sm_o[];  // [waves + 1][G][kOStride]
 
     const int kvh = blockIdx.x;
     const int user = A.order ? scalar_load_i32(A.order, blockIdx.y) : (int)blockIdx.y;
@@ -202,10 +210,10 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
 
     if (lane == 0) {
         if (lo < S0 && S0 <= hi) {  // the wave that holds owner 0's last step
-            sm_split[0] = wave + 1;
-            sm_split[1] = S0 < hi;
+            sm.n0 = wave + 1;
+            sm.extra = S0 < hi;
         } else if (S0 == 0 && wave == 0) {
-            sm_split[0] = sm_split[1] = 0;
+            sm.n0 = sm.extra = 0;
         }
     }
 
@@ -289,7 +297,7 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
         l = wave_xor_sum<16>(l);
         l = wave_xor_sum<32>(l);
         if (L.grp == 0) {  // (4x4 blocks: entries past head 3 are copies, never read)
-            sm_ml[slot][L.r] = make_float2(m, l);
+            sm.ml[slot][L.r] = make_float2(m, l);
         }
         if constexpr (kQuad)
             reduce_scatter_groups<CP>(acc);
@@ -316,10 +324,10 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     }
     __syncthreads();
 
-    const int n0 = uniform(sm_split[0]), n_slots = W + uniform(sm_split[1]);
+    const int n0 = uniform(sm.n0), n_slots = W + uniform(sm.extra);
     const bool thread_per_channel = G * D <= (int)blockDim.x;
     auto reduce = [&](auto max_slots, auto vec) {
-        reduce_slots<DT, D, decltype(max_slots)::value, decltype(vec)::value>(A, sm_ml, sm_o, n0, n_slots, S0 > 0, S1 > 0, head0);
+        reduce_slots<DT, D, decltype(max_slots)::value, decltype(vec)::value>(A, sm.ml, sm_o, n0, n_slots, S0 > 0, S1 > 0, head0);
     };
     constexpr std::integral_constant<int, 5> few;  // four waves
     constexpr std::integral_constant<int, kRowsMaxWaves + 1> most;

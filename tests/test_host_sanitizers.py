@@ -1,6 +1,7 @@
 """The host side of the library (schedule builder, argument checks) under AddressSanitizer and UBSan.
 Host code only: the GPU pass is compiled without sanitizers and no device call is made."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -67,20 +68,33 @@ def test_oracle_under_asan_ubsan(tmp_path):
     assert run.returncode == 0 and run.stdout.strip().endswith("ok 60"), run.stdout[-3000:]
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not found")
-def test_no_kernel_spills_registers(tmp_path):
-    """Every kernel instance fits its register budget: a spill in the streaming kernel (which has happened after an
-    innocent-looking refactoring) costs several percent of bandwidth without failing any parity test."""
+@pytest.fixture(scope="module")
+def resource_report(tmp_path_factory):
+    """The compiler's resource report of every kernel instance, built with the library's flags."""
     import importlib.util
-    import re
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not found")
     spec = importlib.util.spec_from_file_location("spd_build", os.path.join(ROOT, "paper_2409_19134_amd", "build.py"))
     build = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(build)
-    cmd = [HIPCC, *build.HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-o", str(tmp_path / "lib.so"),
+    cmd = [HIPCC, *build.HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-o", str(tmp_path_factory.mktemp("report") / "lib.so"),
            os.path.join(ROOT, "paper_2409_19134_amd", "csrc", "spd_api.hip")]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert res.returncode == 0, res.stdout[-3000:]
-    spills = [int(x) for x in re.findall(r"VGPRs Spill: (\d+)", res.stdout)]
-    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", res.stdout)]
+    return res.stdout
+
+
+def test_no_kernel_spills_registers(resource_report):
+    """Every kernel instance fits its register budget: a spill in the streaming kernel (which has happened after an
+    innocent-looking refactoring) costs several percent of bandwidth without failing any parity test."""
+    spills = [int(x) for x in re.findall(r"VGPRs Spill: (\d+)", resource_report)]
+    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", resource_report)]
     assert len(spills) >= 40 and len(scratch) == len(spills)          # every kernel instance reported
     assert max(spills) == 0 and max(scratch) == 0
+
+
+def test_dynamic_lds_is_16_byte_aligned(resource_report):
+    """The kernels read and write their dynamic LDS 16 bytes at a time; it starts where the static part ends."""
+    lds = [int(x) for x in re.findall(r"LDS Size \[bytes/block\]: (\d+)", resource_report)]
+    assert len(lds) >= 40 and max(lds) > 0
+    assert [x for x in lds if x % 16] == []
