@@ -425,10 +425,7 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
     // against 208.6)
     load.limit_halved = head_per_wave_layout(s, v0) && (!v1 || head_per_wave_layout(s, v1)) &&
                         head_per_wave_choice(ctx, s, total_steps(v0) + (v1 ? total_steps(v1) : 0)) != 0;
-    const int waves = whole_rows_choice(load);
-    // the slots of a workgroup with many query heads per KV head: what 64 KB of LDS hold (never fewer than 6)
-    const int64_t slot = (int64_t)spd::staging_bytes(s->head_dim, 1, s->n_q_heads / s->n_kv_heads);
-    return (int)std::min<int64_t>(waves, 64 * 1024 / slot - 1);
+    return std::min(whole_rows_choice(load), spd::rows_waves_that_fit(s->head_dim, s->n_q_heads / s->n_kv_heads));
 }
 
 // Validation, schedule lookup and scratch growth of one partial-attention call.

@@ -25,6 +25,14 @@ struct alignas(16) RowsShared {
 };
 static_assert(sizeof(RowsShared) % 16 == 0, "the dynamic part starts where this ends");
 
+// Waves per workgroup whose slots (one more than waves), with the static part, fit the 64 KB a launch may ask for: all twelve
+// but with many query heads per KV head (6 for 16 heads of 128 channels).
+__host__ __device__ constexpr int rows_waves_that_fit(int D, int G)
+{
+    const size_t n = (64 * 1024 - sizeof(RowsShared)) / staging_bytes(D, 1, G) - 1;
+    return n > (size_t)kRowsMaxWaves ? kRowsMaxWaves : (int)n;
+}
+
 // One owner's call as the kernel needs it.
 struct RowsOwner {
     const RowItem *items;

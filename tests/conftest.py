@@ -50,3 +50,20 @@ def in_flight(ctx):
     yield apply
     ctx.spd_set_option(spd.SPD_OPT_STEPS_IN_FLIGHT, -1)
 
+
+@pytest.fixture(scope="session")
+def resource_report(tmp_path_factory):
+    """The compiler's resource report of every kernel instance, built with the library's flags."""
+    import importlib.util
+    import subprocess
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    spec = importlib.util.spec_from_file_location("spd_build", os.path.join(ROOT, "paper_2409_19134_amd", "build.py"))
+    build = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(build)
+    cmd = [hipcc, *build.HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-o", str(tmp_path_factory.mktemp("report") / "lib.so"),
+           os.path.join(ROOT, "paper_2409_19134_amd", "csrc", "spd_api.hip")]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout[-3000:]
+    return res.stdout

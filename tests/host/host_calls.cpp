@@ -148,15 +148,15 @@ struct Step {
     }
 };
 
-int main(int, char **argv)
+int main(int argc, char **argv)
 {
-    void *lib = dlopen(argv[1], RTLD_NOW);
+    void *lib = argc == 3 ? dlopen(argv[1], RTLD_NOW) : nullptr;
     if (!lib)
-        FAIL("%s", dlerror());
+        FAIL("host_calls <library> <static LDS bytes of the whole-rows kernel>");
     SYM(spd_create);
     SYM(spd_destroy);
     SYM(spd_decode_step_static);
-    SYM(spd_get_last_kernel_instance);
+    SYM(spd_decode_step);
     spd_ctx *ctx = nullptr;
     if (spd_create_(&ctx, 0) != SPD_OK)
         FAIL("spd_create");
@@ -197,6 +197,28 @@ int main(int, char **argv)
             if (at[i].first < at[i - 1].second)
                 FAIL("static step, %d users: the owners' tables overlap at %zu", c.users, at[i].first);
     }
+
+    // whole rows: no launch asks for more than 64 KB of LDS, the kernel's static part (argv[2], from the compiler's report) and
+    // the slots together
+    const size_t static_lds = (size_t)std::atoi(argv[2]);
+    for (int G = 1; G <= 16; ++G)
+        for (int d = 64; d <= 128; d *= 2)
+            for (int dtype : {SPD_F32, SPD_BF16, SPD_F16}) {
+                const int tile = dtype == SPD_F32 && d == 128 ? 16 : 32;
+                for (int steps = 1; steps <= 14; ++steps) {
+                    Step st(dtype, 2 * G, 2, d, 1, steps * tile, 1, false);
+                    launches.clear();
+                    if (spd_decode_step_(ctx, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf, st.buf, st.buf,
+                                         st.buf, st.buf, nullptr) != SPD_OK)
+                        FAIL("step");
+                    const Launch &l = launches.back();
+                    if (l.kernel.find("whole_rows_kernel") == std::string::npos)
+                        FAIL("G = %d, %d steps: %s", G, steps, l.kernel.c_str());
+                    const size_t slots = l.lds / (l.block.x / 64 + 1), need = (size_t)G * d * sizeof(float);
+                    if (l.block.x > 768 || slots < need || l.lds + static_lds > 64 * 1024)
+                        FAIL("G = %d, d = %d, %u threads: %zu + %zu bytes of LDS", G, d, l.block.x, l.lds, static_lds);
+                }
+            }
     spd_destroy_(ctx);
     std::printf("ok\n");
     std::fflush(stdout);

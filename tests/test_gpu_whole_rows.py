@@ -57,7 +57,8 @@ PUBLIC = [0, 0, 1, 33, 31, 64, 32, 0, 1, 385, 97, 193, 400]
 
 @pytest.mark.parametrize("dtype,d,Hq,Hkv", [(torch.bfloat16, 128, 8, 2), (torch.bfloat16, 128, 32, 2), (torch.float16, 64, 3, 3),
                                             (torch.float16, 128, 14, 2), (torch.float32, 64, 4, 1), (torch.float32, 64, 5, 1),
-                                            (torch.float32, 128, 4, 2), (torch.float32, 128, 16, 1)])
+                                            (torch.float32, 128, 4, 2), (torch.float32, 128, 16, 1),
+                                            (torch.bfloat16, 128, 22, 2), (torch.float16, 128, 13, 1), (torch.float32, 128, 15, 1)])
 @pytest.mark.parametrize("storage", ["hnd", "nhd", "hnd_exact", "paged", "paged_tm"])
 def test_step_and_wave_edges(ctx, split_ctx, dtype, d, Hq, Hkv, storage):
     paged = {"paged": True, "paged_tm": "token_major"}.get(storage, False)

@@ -68,22 +68,6 @@ def test_oracle_under_asan_ubsan(tmp_path):
     assert run.returncode == 0 and run.stdout.strip().endswith("ok 60"), run.stdout[-3000:]
 
 
-@pytest.fixture(scope="module")
-def resource_report(tmp_path_factory):
-    """The compiler's resource report of every kernel instance, built with the library's flags."""
-    import importlib.util
-    if not os.path.exists(HIPCC):
-        pytest.skip("hipcc not found")
-    spec = importlib.util.spec_from_file_location("spd_build", os.path.join(ROOT, "paper_2409_19134_amd", "build.py"))
-    build = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(build)
-    cmd = [HIPCC, *build.HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-o", str(tmp_path_factory.mktemp("report") / "lib.so"),
-           os.path.join(ROOT, "paper_2409_19134_amd", "csrc", "spd_api.hip")]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert res.returncode == 0, res.stdout[-3000:]
-    return res.stdout
-
-
 def test_no_kernel_spills_registers(resource_report):
     """Every kernel instance fits its register budget: a spill in the streaming kernel (which has happened after an
     innocent-looking refactoring) costs several percent of bandwidth without failing any parity test."""
