@@ -263,9 +263,11 @@ int get_schedule(spd_ctx *ctx, Owner &own, const spd_shape *s, const spd_kv_view
         return SPD_OK;
     }
     if (!build) {
+        // (an error - the null stream is asked about while another stream is being captured - means that this one is not)
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        SPD_HIP(ctx, hipStreamIsCapturing(stream, &capture));
-        if (capture != hipStreamCaptureStatusNone)
+        if (hipStreamIsCapturing(stream, &capture) != hipSuccess)
+            (void)hipGetLastError();
+        else if (capture != hipStreamCaptureStatusNone)
             return kNotRemembered;
     }
     ScheduleBlob B;

@@ -54,6 +54,9 @@ static void launched(const void *fn, dim3 grid, dim3 block, void **args, size_t 
     }
 }
 
+static int last_error = 0;
+static bool other_capture = false;
+
 extern "C" {
 struct Config {
     dim3 grid, block;
@@ -76,8 +79,18 @@ int hipEventDestroy(void *) { return 0; }
 int hipEventRecord(void *, void *) { return 0; }
 int hipEventSynchronize(void *) { return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { return *ms = 0.f, 0; }
-int hipGetLastError() { return 0; }
-int hipStreamIsCapturing(void *, int *status) { return *status = 0, 0; }
+int hipGetLastError()
+{
+    const int e = last_error;
+    return last_error = 0, e;
+}
+// while another stream is being captured the runtime does not tell whether the null stream is: hipErrorStreamCaptureImplicit
+int hipStreamIsCapturing(void *stream, int *status)
+{
+    if (!stream && other_capture)
+        return last_error = 906;
+    return *status = 0, 0;
+}
 void **__hipRegisterFatBinary(const void *)
 {
     static void *handle;
@@ -157,6 +170,7 @@ int main(int argc, char **argv)
     SYM(spd_destroy);
     SYM(spd_decode_step_static);
     SYM(spd_decode_step);
+    SYM(spd_partial_attn_private);
     spd_ctx *ctx = nullptr;
     if (spd_create_(&ctx, 0) != SPD_OK)
         FAIL("spd_create");
@@ -197,6 +211,18 @@ int main(int argc, char **argv)
             if (at[i].first < at[i - 1].second)
                 FAIL("static step, %d users: the owners' tables overlap at %zu", c.users, at[i].first);
     }
+
+    // calls on the null stream while another stream is being captured: new schedules, split and whole rows, and remembered ones
+    other_capture = true;
+    for (int again = 0; again < 2; ++again)
+        for (int tokens : {5000, 90}) {
+            Step st(SPD_BF16, 8, 2, 128, 1, tokens, 1, false);
+            if (spd_partial_attn_private_(ctx, &st.s, st.buf, &st.v[0], st.buf, st.buf, nullptr) != SPD_OK ||
+                spd_decode_step_(ctx, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf, st.buf, st.buf, st.buf,
+                                 st.buf, nullptr) != SPD_OK || last_error != 0)
+                FAIL("%d tokens on the null stream while another stream is captured", tokens);
+        }
+    other_capture = false;
 
     // whole rows: no launch asks for more than 64 KB of LDS, the kernel's static part (argv[2], from the compiler's report) and
     // the slots together
