@@ -338,15 +338,16 @@ struct CloseRow {
             x[c] = *reinterpret_cast<const f32x4 *>(po + (int64_t)min(c, last) * G * D);
     }
 
-    template <int C = 0>
+    // GUARD: pairs past the end are left out instead of given a weight of 0
+    template <bool GUARD, int C = 0>
     __device__ __forceinline__ void weighted(const float (&w)[NL], f32x4 &o) const
     {
         if constexpr (C < MAXC) {
             const float wc = row_dpp<0x150 + (C & 15)>(w[C / 16]);  // row_newbcast: lane C & 15's value
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                o[v] = fmaf(wc, x[C][v], o[v]);
-            weighted<C + 1>(w, o);
+                o[v] = fmaf(wc, GUARD && C >= n ? 0.f : x[C][v], o[v]);
+            weighted<GUARD, C + 1>(w, o);
         }
     }
 
@@ -366,7 +367,13 @@ struct CloseRow {
         }
         den = row_sum(den);
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        weighted(w, o);
+        weighted<false>(w, o);
+        // an infinite value times a stand-in's weight of 0 is NaN: once more without the stand-ins
+        const float nan_if_any = (o[0] + o[1]) + (o[2] + o[3]);
+        if (__any(nan_if_any != nan_if_any)) {
+            o = f32x4{0.f, 0.f, 0.f, 0.f};
+            weighted<true>(w, o);
+        }
         a_out = n == 1 ? x[0] : o * fast_rcp(den);
         lse_out = n == 1 ? l[0] : M + fast_log(den);
     }

@@ -140,6 +140,30 @@ __device__ __forceinline__ void reduce_slots(const RowsArgs &A, const float2 (*s
         const float L0 = row_sum(mine0 ? wl : 0.f), L1 = row_sum(mine0 ? 0.f : wl);
         float o0[VEC] = {}, o1[VEC] = {};
         weighted_slots<MAXS, VEC>(os, w, n0, o0, o1);
+        // an infinite value times a stand-in's weight of 0 is NaN: once more, over the slots that there are
+        float nan_if_any = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v)
+            nan_if_any += o0[v] + o1[v];
+        if (__any(nan_if_any != nan_if_any)) {
+            float sums[2][VEC] = {};
+#pragma unroll 1
+            for (int s = 0; s < n_slots; ++s) {
+                float x[VEC];
+                load_vec<VEC>(x, sm_o + (s * G + g) * kOStride + ch);
+                const float ws = __shfl(w, s, 16);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    sums[0][v] = s < n0 ? fmaf(ws, x[v], sums[0][v]) : sums[0][v];
+                    sums[1][v] = s < n0 ? sums[1][v] : fmaf(ws, x[v], sums[1][v]);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                o0[v] = sums[0][v];
+                o1[v] = n0 >= MAXS ? sums[0][v] : sums[1][v];
+            }
+        }
         // an owner without tokens: A = 0, lse = -inf
         const float i0 = fast_rcp(L0), i1 = fast_rcp(L1);
 #pragma unroll

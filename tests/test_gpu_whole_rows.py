@@ -95,6 +95,30 @@ def test_one_owners_nan_stays_out_of_the_others_partial(ctx):
         assert torch.equal(a, b), name
 
 
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,d", [(4, 1, 64), (10, 2, 128), (32, 2, 64)])
+def test_an_infinite_value_stays_infinite(ctx, split_ctx, split, Hq, Hkv, d):
+    """fp32 caches whose V holds an infinity: the channel's partials are that infinity, all others are finite, also where the
+    infinity is in the last chunk (split) or the last wave's share (whole rows), which is read in place of absent ones."""
+    c = split_ctx if split else ctx
+    lp, lo = ([300, 520, 140, 33], [150, 277, 260, 140]) if split else ([120, 130, 140, 33], [100, 90, 77, 140])
+    for at in (0, 1, 2):                                    # in the first, a middle and the last token but one
+        wl = workloads.random_case(507, torch.float32, 4, Hq, Hkv, d, lp, lo, device=DEV, layout="hnd")
+        for u, (side, n) in enumerate(((wl.private, lp[0]), (wl.public, lo[1]), (wl.private, lp[2]), (wl.public, lo[3]))):
+            side.v[u][Hkv - 1, (0, n // 2, n - 2)[at], 5 + u] = float("inf") if u % 2 else -float("inf")
+        step = run_step(c, wl, True)
+        assert c.spd_last_kernel_name().startswith("whole_rows") != split
+        G = Hq // Hkv
+        for u in range(4):
+            inf = torch.zeros((Hq, d), dtype=torch.bool, device=DEV)
+            inf[Hq - G:, 5 + u] = True
+            mine, other = (step.a_out, step.a_in) if u % 2 else (step.a_in, step.a_out)
+            for t in (mine[u], step.y[u]):
+                assert torch.equal(t == (float("inf") if u % 2 else -float("inf")), inf), (at, u)
+                assert torch.isfinite(t[~inf]).all(), (at, u)
+            assert torch.isfinite(other[u]).all()
+
+
 @pytest.mark.parametrize("paged", [False, True])
 def test_decode_loop_appends_on_whole_rows(ctx, paged):
     """Twenty steps of a growing public cache: the appended rows reach the cache, the schedule is found again, results
