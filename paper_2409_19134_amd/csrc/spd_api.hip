@@ -419,6 +419,7 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
     load.Hkv = s->n_kv_heads;
     load.n_cus = ctx->n_cus;
     load.n_users = n;
+    load.head_channels = s->n_q_heads / s->n_kv_heads * s->head_dim;
     load.lens0 = v0->lens;
     load.lens1 = v1 ? v1->lens : nullptr;
     load.always = always;

@@ -105,6 +105,12 @@ int main()
             FAIL("whole rows of %lld steps", (long long)longest);
         if (longest * c.step_bytes <= (c.lens1 ? kWholeRowsTail : kWholeRowsTailOneOwner) * 16384 && waves == 0)
             FAIL("rows of %lld steps are short whatever their number", (long long)longest);
+        // result channels ask for up to four waves, whatever the steps
+        WholeRowsLoad h = c;
+        h.head_channels = 64 * (1 + (int)(rnd() % 32));
+        const int least = std::min(4, (h.head_channels + 255) / 256);
+        if (whole_rows_choice(h) != (waves ? std::max(waves, least) : 0))
+            FAIL("%d waves for %d result channels", whole_rows_choice(h), h.head_channels);
         // the kernel's division by the wave count: x * ceil(2^32 / waves) >> 32, for every product it forms
         for (int w = 1; w <= spd::kRowsMaxWaves; ++w) {
             const uint32_t mul = (uint32_t)(((1ull << 32) + w - 1) / w);
