@@ -345,6 +345,13 @@ inline void build_whole_rows(int Hkv, int es, const spd_kv_view *v, std::vector<
     std::stable_sort(order.begin(), order.end(), [v](int32_t a, int32_t b) { return v->lens[a] > v->lens[b]; });
 }
 
+// Whether the rows of a whole-rows launch are started by length, longest first: there are more of them than workgroups of that
+// many waves (of the twelve that fit a compute unit) are resident at once.
+inline bool whole_rows_by_length(int64_t rows, int waves, int n_cus)
+{
+    return rows > (int64_t)std::max(1, n_cus) * (spd::kRowsMaxWaves / waves);
+}
+
 // Whether a call's rows are taken whole, one workgroup each, and by how many waves.  In units of 16 KB (a wave's step):
 // `longest` is the longest row, `share` what each of the workgroups resident at once gets if the rows spread evenly.  The
 // launch lasts (longest - share) units longer than its bytes take, ~0.27 us each, against the 4-5 us that the split

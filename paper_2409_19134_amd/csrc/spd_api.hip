@@ -708,8 +708,8 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
     R.G = G;
     R.wave_mul = (uint32_t)(((1ull << 32) + waves - 1) / waves);
     R.scale_log2e = s->scale * spd::kLog2e;
-    const int64_t rows = (int64_t)v0->n_users * s->n_kv_heads, cus = std::max(1, ctx->n_cus);
-    R.order = rows * waves > cus * spd::kRowsMaxWaves ? reinterpret_cast<const int32_t *>(e0->dev + e0->off_rows) : nullptr;
+    const bool by_length = whole_rows_by_length((int64_t)v0->n_users * s->n_kv_heads, waves, ctx->n_cus);
+    R.order = by_length ? reinterpret_cast<const int32_t *>(e0->dev + e0->off_rows) : nullptr;
     R.q = static_cast<const char *>(q);
     R.a_in = mg.a_in;
     R.lse_in = mg.lse_in;

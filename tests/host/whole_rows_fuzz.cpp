@@ -111,6 +111,12 @@ int main()
         const int least = std::min(4, (h.head_channels + 255) / 256);
         if (whole_rows_choice(h) != (waves ? std::max(waves, least) : 0))
             FAIL("%d waves for %d result channels", whole_rows_choice(h), h.head_channels);
+        // by length as soon as a row has to wait for another's end: a unit holds three workgroups of four waves, one of eight
+        for (int w : {4, 8, 12}) {
+            const int64_t resident = (int64_t)c.n_cus * (w == 4 ? 3 : 1);
+            if (whole_rows_by_length(resident, w, c.n_cus) || !whole_rows_by_length(resident + 1, w, c.n_cus))
+                FAIL("launch order of %lld rows of %d waves", (long long)resident, w);
+        }
         // the kernel's division by the wave count: x * ceil(2^32 / waves) >> 32, for every product it forms
         for (int w = 1; w <= spd::kRowsMaxWaves; ++w) {
             const uint32_t mul = (uint32_t)(((1ull << 32) + w - 1) / w);
