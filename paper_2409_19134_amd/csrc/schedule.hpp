@@ -352,57 +352,103 @@ inline bool whole_rows_by_length(int64_t rows, int waves, int n_cus)
     return rows > (int64_t)std::max(1, n_cus) * (spd::kRowsMaxWaves / waves);
 }
 
-// Whether a call's rows are taken whole, one workgroup each, and by how many waves.  In units of 16 KB (a wave's step):
-// `longest` is the longest row, `share` what each of the workgroups resident at once gets if the rows spread evenly.  The
-// launch lasts (longest - share) units longer than its bytes take, ~0.27 us each, against the 4-5 us that the split
-// schedule's closing launch costs: whole rows up to a difference of 16.  Measured, us per fused step, 8B shape in bf16,
-// split / whole (difference): 1 user 256 + 64 tokens 8.6 / 6.6 (10), 4 users of <= 384 + 128 8.5 / 7.8 (12), of <= 512 + 256
-// 8.8 / 9.1 (16.1), 16 such users 13.0 / 11.9 (12), 16 users of <= 768 + 256 13.5 / 15.3 (16.7), 32 of them 20.2 / 18.7
-// (10), 64 34.5 / 30.2; 256 users of <= 192 + 64 51.2 / 31.5, <= 384 + 128 73.5 / 56.2, <= 768 + 256 112.1 / 106.1,
-// 250-2000 + 64 215 / 199; 100 users with lognormal prompts of median 128, up to 2048, 38.7 / 49.3 (60).  Rows of more than
-// 64 units (2048 tokens at 256 bytes) gain nothing on balanced launches (256 users of 500-4000 + 1000: 454 / 477) and stay
-// with the split schedule, fp32 rows of 512 bytes from 48 (256 users of 96-768 + 256 tokens, 64 units: 201 / 203).
+// Whether a call's rows are taken whole, one workgroup each, and by how many waves.  In units of 16 KB (a wave's step; with
+// rows of 128 bytes two steps): `longest` is the longest row, `share` what each of the workgroups resident at once gets if the
+// rows spread evenly.  Against the split schedule a whole-rows launch saves the closing launch and the ends of segments inside
+// a piece, and loses what the device idles while its last rows end.  Where the lines lie was measured on 540 random calls over
+// all layouts, element types and head groupings (1 to 256 users, rows of up to 90 units, appends, fused steps and one owner's
+// calls), split against whole; us per call, 256 units:
+//  - a unit for every row (rows <= units): the longest row's excess over the share, 0.3-0.5 us a unit, against 3-5 us.  Fused
+//    steps 13.2 / 8.7 (excess 2), 18.9 / 17.5 (11), 18.0 / 17.4 (14), 17.2 / 19.5 (20); 14.7 / 16.6 (16); 10.5 / 12.2 (14).  One
+//    owner's call saves less: 13.2 / 11.8 (9.6), 13.2 / 13.9 (11), 13.8 / 15.3 (12.4).
+//    With a few rows (up to an eighth of the units), 1 and 4 users: 8.6 / 7.9 and 8.7 / 8.4 (14), 8.3 / 8.6 and 8.7 / 9.3 (16), with
+//    the append in pages 8.7 / 8.2 and 8.7 / 8.6 (13), 8.6 / 9.3 (4 users, 14); rows of 128 bytes 8.5 / 7.5 (11), 8.8 / 9.0 (14),
+//    with the append in pages 8.5 / 8.7 and 8.6 / 10.3; fp32 10.0 / 9.2 (14), 9.2 / 11.0 (7 heads, 15.5).  One owner's call up
+//    to 16, where it is even on the device (8.9 / 8.9) and a caller that the host's launches bound saves 3 us (from Python 11.7 /
+//    8.4), fp32 8.9 / 9.9 (15.4).  Rows of 128 bytes in general 9.8 / 9.7 (one owner, 7), 13.4 / 14.1 (8).
+//  - up to two rows a unit and more than 16 steps: two rounds of one eight-wave workgroup per unit.  With half of the second
+//    round empty the first one's saving is lost: 30.9 / 33.1 (320 rows), 54.0 / 71.5 (304), 25.5 / 28.5 (272), 24.0 / 25.1
+//    (400); 33.1 / 32.2 (432), 50.5 / 48.7 (496), 34.7 / 30.2 (512); and with long rows there is nothing left to save, 84.4 / 88.0
+//    (512 of 63 units), 51.0 / 51.7 (424 of up to 64).  With up to 16 steps four waves a row, all resident: 18.2 / 14.7 (376).
+//  - more, up to three a unit: all resident, four waves a row, which cannot take in more than a wave's step at a time: the
+//    excess counts more.  42.6 / 37.1 (3.1), 86.8 / 82.2 (2.3); 41.4 / 42.4 (6.5), 39.9 / 44.1 (12.7), 32.1 / 37.2 (20).  Rows of
+//    128 bytes 22.1 / 20.3 (5), 51.5 / 56.4 (7.5).  With rows of up to 16 units only the start and the end count: 27.3 / 25.0 (5.6).
+//  - more: the shortest rows come last.  If they are long and the last round is nearly empty, the device idles for them: 856 rows
+//    of 56 units 132.9 / 136.7, 932 of 49 122.1 / 122.7; 1160 of 25 86.5 / 87.1, 840 of 16 43.6 / 39.2, 1044 of 36
+//    112.7 / 108.0; of mixed lengths 936 rows of 15-33 97.4 / 90.7, 1016 of 4-35 67.8 / 59.4, 1872 of 2-18 70.0 / 49.7.
+//  - token-major storage that the head-per-wave mapping would take (it reads a token's heads, whole DRAM pages, together): only
+//    short rows, 35.9 / 28.7 (13 units), 54.2 / 44.5 (8), 33.5 / 38.0 (17), 60.5 / 68.8 (25), 59.7 / 78.6 (61) - and longer ones
+//    where 256-byte rows fill several rounds, 130.4 / 116.1 (two parties, 2048 rows of up to 24; of 128 bytes, 1696 of up to 20,
+//    111.4 / 125.0).
+//  - rows of more than 64 units (2048 tokens at 256 bytes) gain nothing on balanced launches (256 users of 500-4000 + 1000:
+//    454 / 477), fp32 rows of 512 bytes from 48 (56.3 / 57.4 at 58).
 struct WholeRowsLoad {
     int tile = 32, step_bytes = 16384;  // tokens and K/V bytes of a wave's step
     int Hkv = 0, n_cus = 0, n_users = 0;
     int head_channels = 0;  // result channels of a row: query heads per KV head * channels
     const int32_t *lens0 = nullptr, *lens1 = nullptr;  // lens1: the second owner's, or nullptr
-    bool limit_halved = false;
+    bool f32 = false;
     bool always = false;  // whole rows whatever the rule says: the wave count is all that is asked for
 };
-// One owner's call saves less (its combine launch is shorter, ~3 us) and keeps the split schedule from 12 on (three calls,
-// 8 users of <= 1536 + 512 tokens, the public call at 12.2: 22.5 / 24.3; 16 users of <= 768 + 256, the private call at 15:
-// 21.9 / 22.5) - except with few rows, where the host's launches are the bound (one user's private call over 500 tokens,
-// 15.5: 10.6-11.9 / 8.3).
-constexpr int kWholeRowsTail = 16, kWholeRowsTailOneOwner = 12, kWholeRowsLimit = 64, kWholeRowsLimit512 = 48;
-inline int whole_rows_choice(const WholeRowsLoad &c)
+constexpr int kWholeRowsLimit = 64, kWholeRowsLimit512 = 48, kWholeRowsLimitTwoRounds = 40;  // longest row
+constexpr int kWholeRowsLimitTokenMajor = 16, kWholeRowsLimitTokenMajorMany = 32;  // (many: two full rounds)
+constexpr int kWholeRowsTail = 12, kWholeRowsTailOneOwner = 10, kWholeRowsTail128 = 7;  // excess over the share
+constexpr int kWholeRowsTailFew = 14, kWholeRowsTailFew128 = 11;
+constexpr int kWholeRowsTailFewOneOwner = 16, kWholeRowsTailFewOneOwnerF32 = 13;
+constexpr int kWholeRowsTailOneRound = 6, kWholeRowsTailOneRound128 = 5, kWholeRowsTailOneRoundShort = 8;
+constexpr int kWholeRowsShort = 5;    // rows that are taken whole whatever their number
+// head_per_wave(steps): whether the head-per-wave mapping would take a call of that many 32-token steps.
+template <class F>
+inline int whole_rows_choice(const WholeRowsLoad &c, F &&head_per_wave)
 {
-    int64_t longest = 0, total = 0;  // steps
+    int64_t longest = 0, shortest = INT64_MAX, total = 0;  // steps
     for (int u = 0; u < c.n_users; ++u) {
         int64_t steps = ((int64_t)c.lens0[u] + c.tile - 1) / c.tile;
         if (c.lens1)
             steps += ((int64_t)c.lens1[u] + c.tile - 1) / c.tile;
         longest = std::max(longest, steps);
+        shortest = std::min(shortest, steps);
         total += steps;
     }
-    const int64_t rows = (int64_t)c.n_users * c.Hkv, cus = std::max(1, c.n_cus);
+    const int64_t rows = (int64_t)c.n_users * c.Hkv, cus = std::max(1, c.n_cus), unit = 16384;
+    const int row_bytes = c.step_bytes / (2 * c.tile);
     // Waves: twelve fit a compute unit, whatever the workgroups.  Rows that all have a unit of their own take as few waves
     // as make the same number of rounds; up to two rows per unit, eight waves (one workgroup per unit and a second round)
     // from 17 steps on and four below (64 users of <= 768 + 256 tokens 30.1 / 32.0 us, of <= 192 + 64 12.0 / 11.0); more
     // rows, four waves (256 users of <= 512 + 256 tokens: 82 us, 94 with eight or twelve).
+    const bool two_rounds = rows > cus && rows <= 2 * cus && longest > 16;
     int64_t waves = 4, slots = 3 * cus;
     if (rows <= cus) {
         const int64_t rounds = std::max<int64_t>(1, (longest + spd::kRowsMaxWaves - 1) / spd::kRowsMaxWaves);
         waves = std::max<int64_t>(1, (longest + rounds - 1) / rounds);
         slots = cus;
-    } else if (rows <= 2 * cus && longest > 16) {
+    } else if (two_rounds) {
         waves = 8;
         slots = cus;
     }
-    const int64_t limit = (c.step_bytes / c.tile == 1024 ? kWholeRowsLimit512 : kWholeRowsLimit) >> (c.limit_halved ? 1 : 0);
-    const int64_t unit = 16384, tail = c.lens1 || rows * 8 <= cus ? kWholeRowsTail : kWholeRowsTailOneOwner;
-    if (!c.always && (longest * c.step_bytes > limit * unit || longest * c.step_bytes - total * c.Hkv * c.step_bytes / slots > tail * unit))
-        return 0;
+    if (!c.always) {
+        int64_t limit = row_bytes == 512 ? kWholeRowsLimit512 : kWholeRowsLimit;
+        if (head_per_wave(total))
+            limit = rows >= 2 * slots && row_bytes > 128 ? kWholeRowsLimitTokenMajorMany : kWholeRowsLimitTokenMajor;
+        if (two_rounds)
+            limit = std::min<int64_t>(limit, kWholeRowsLimitTwoRounds);
+        int64_t tail = row_bytes == 128 ? kWholeRowsTail128 : c.lens1 ? kWholeRowsTail : kWholeRowsTailOneOwner;
+        if (rows * 8 <= cus)
+            tail = c.lens1 ? (row_bytes == 128 ? kWholeRowsTailFew128 : kWholeRowsTailFew)
+                           : (c.f32 ? kWholeRowsTailFewOneOwnerF32 : kWholeRowsTailFewOneOwner);
+        else if (rows > 2 * cus && rows <= slots)
+            tail = longest * c.step_bytes <= 16 * unit ? kWholeRowsTailOneRoundShort
+                   : row_bytes == 128                  ? kWholeRowsTailOneRound128
+                                                       : kWholeRowsTailOneRound;
+        if (longest * c.step_bytes > limit * unit || longest * c.step_bytes - total * c.Hkv * c.step_bytes / slots > tail * unit)
+            return 0;
+        if (two_rounds && 16 * rows <= 25 * cus && longest * c.step_bytes > kWholeRowsShort * unit)
+            return 0;
+        // the part of the last round that is empty, in slots, times the shortest row
+        const int64_t empty = (slots - rows % slots) % slots;
+        if (rows > 2 * cus && rows > slots && shortest * c.step_bytes * empty > 16 * unit * slots)
+            return 0;
+    }
     // No more waves than the longest row has steps - but up to four for the reduction of many result channels, whatever the
     // steps (a thread takes four channels at a time; 16 query heads of 128 channels, one step: 6.3 us per call, with four waves 4.2,
     // split 4.7; 8 heads 4.9 / 3.7 / 4.3).

@@ -422,13 +422,11 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
     load.head_channels = s->n_q_heads / s->n_kv_heads * s->head_dim;
     load.lens0 = v0->lens;
     load.lens1 = v1 ? v1->lens : nullptr;
+    load.f32 = s->dtype == SPD_F32;
     load.always = always;
-    // token-major storage long enough for the head-per-wave mapping, which reads whole DRAM pages: up to half the limit
-    // (two parties appending, token-major, 256 users of 96-768 + 256 tokens 116.1 us against 130.4, 192-1536 + 512: 214.5
-    // against 208.6)
-    load.limit_halved = head_per_wave_layout(s, v0) && (!v1 || head_per_wave_layout(s, v1)) &&
-                        head_per_wave_choice(ctx, s, total_steps(v0) + (v1 ? total_steps(v1) : 0)) != 0;
-    return std::min(whole_rows_choice(load), spd::rows_waves_that_fit(s->head_dim, s->n_q_heads / s->n_kv_heads));
+    const bool token_major = head_per_wave_layout(s, v0) && (!v1 || head_per_wave_layout(s, v1));
+    const int waves = whole_rows_choice(load, [&](int64_t steps) { return token_major && head_per_wave_choice(ctx, s, steps) != 0; });
+    return std::min(waves, spd::rows_waves_that_fit(s->head_dim, s->n_q_heads / s->n_kv_heads));
 }
 
 // Validation, schedule lookup and scratch growth of one partial-attention call.

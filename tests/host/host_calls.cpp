@@ -231,7 +231,7 @@ int main(int argc, char **argv)
         for (int d = 64; d <= 128; d *= 2)
             for (int dtype : {SPD_F32, SPD_BF16, SPD_F16}) {
                 const int tile = dtype == SPD_F32 && d == 128 ? 16 : 32;
-                for (int steps = 1; steps <= 14; ++steps) {
+                for (int steps = 1; steps <= 12; ++steps) {
                     Step st(dtype, 2 * G, 2, d, 1, steps * tile, 1, false);
                     launches.clear();
                     if (spd_decode_step_(ctx, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf, st.buf, st.buf,

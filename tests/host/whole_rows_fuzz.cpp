@@ -24,8 +24,39 @@ static uint64_t rnd()
         return 1;                 \
     } while (0)
 
+// Equal rows on 256 compute units, 16-bit rows of 128 channels and 8 KV heads: on which side of the rule's lines they are.
+static int measured_shapes()
+{
+    struct Shape {
+        int users, tokens;
+        bool token_major, whole;
+    };
+    const Shape shapes[] = {
+        {1, 500, false, true}, {1, 800, false, false},      // a few rows: the excess of the longest
+        {16, 500, false, true}, {16, 900, false, false},    // a row for every second unit
+        {42, 1000, false, false}, {62, 1136, false, true},  // two rounds of eight waves: the second half empty, or nearly full
+        {70, 900, false, false}, {81, 620, false, true},    // one round of four waves
+        {107, 1755, false, false}, {105, 487, false, true}, {250, 1000, false, true},  // several: a last round of long rows
+        {104, 796, true, false}, {86, 366, true, true}, {250, 800, true, true},        // what the head-per-wave mapping reads better
+        {250, 2100, false, false},
+    };
+    for (const Shape &x : shapes) {
+        std::vector<int32_t> lens((size_t)x.users, x.tokens);
+        WholeRowsLoad c;
+        c.Hkv = 8;
+        c.n_cus = 256;
+        c.n_users = x.users;
+        c.lens0 = lens.data();
+        if ((whole_rows_choice(c, [&](int64_t) { return x.token_major; }) != 0) != x.whole)
+            FAIL("%d users of %d tokens", x.users, x.tokens);
+    }
+    return 0;
+}
+
 int main()
 {
+    if (measured_shapes())
+        return 1;
     for (int iter = 0; iter < 600; ++iter) {
         const int n = (int)(rnd() % 40), Hkv = 1 + (int)(rnd() % 16), es = rnd() % 2 ? 2 : 4, d = rnd() % 2 ? 64 : 128;
         const int top = 1 + (int)(rnd() % 3000);
@@ -98,19 +129,21 @@ int main()
         for (int u = 0; u < n; ++u)
             longest = std::max<int64_t>(longest, (lens[(size_t)u] + c.tile - 1) / c.tile +
                                                      (c.lens1 ? (lens1[(size_t)u] + c.tile - 1) / c.tile : 0));
-        const int waves = whole_rows_choice(c);
+        const bool token_major = rnd() % 2;
+        auto head_per_wave = [token_major](int64_t steps) { return token_major && steps > 500; };
+        const int waves = whole_rows_choice(c, head_per_wave);
         if (waves < 0 || waves > spd::kRowsMaxWaves || (waves > 1 && waves > longest))
             FAIL("%d waves for rows of up to %lld steps", waves, (long long)longest);
         if (waves > 0 && longest * c.step_bytes > kWholeRowsLimit * 16384)
             FAIL("whole rows of %lld steps", (long long)longest);
-        if (longest * c.step_bytes <= (c.lens1 ? kWholeRowsTail : kWholeRowsTailOneOwner) * 16384 && waves == 0)
+        if (longest * c.step_bytes <= kWholeRowsShort * 16384 && waves == 0)
             FAIL("rows of %lld steps are short whatever their number", (long long)longest);
         // result channels ask for up to four waves, whatever the steps
         WholeRowsLoad h = c;
         h.head_channels = 64 * (1 + (int)(rnd() % 32));
         const int least = std::min(4, (h.head_channels + 255) / 256);
-        if (whole_rows_choice(h) != (waves ? std::max(waves, least) : 0))
-            FAIL("%d waves for %d result channels", whole_rows_choice(h), h.head_channels);
+        if (whole_rows_choice(h, head_per_wave) != (waves ? std::max(waves, least) : 0))
+            FAIL("%d waves for %d result channels", whole_rows_choice(h, head_per_wave), h.head_channels);
         // by length as soon as a row has to wait for another's end: a unit holds three workgroups of four waves, one of eight
         for (int w : {4, 8, 12}) {
             const int64_t resident = (int64_t)c.n_cus * (w == 4 ? 3 : 1);
