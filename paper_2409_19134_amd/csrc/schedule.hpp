@@ -401,15 +401,23 @@ constexpr int kWholeRowsShort = 5;    // rows that are taken whole whatever thei
 template <class F>
 inline int whole_rows_choice(const WholeRowsLoad &c, F &&head_per_wave)
 {
-    int64_t longest = 0, shortest = INT64_MAX, total = 0;  // steps
-    for (int u = 0; u < c.n_users; ++u) {
-        int64_t steps = ((int64_t)c.lens0[u] + c.tile - 1) / c.tile;
-        if (c.lens1)
-            steps += ((int64_t)c.lens1[u] + c.tile - 1) / c.tile;
-        longest = std::max(longest, steps);
-        shortest = std::min(shortest, steps);
+    // (one pass over the lengths per call: a step's tokens are a power of two, and the steps of two lengths of at most 2^30 tokens
+    // fit 32 bits)
+    const int shift = __builtin_ctz((unsigned)c.tile), up = c.tile - 1;
+    int32_t longest_row = 0, shortest_row = INT32_MAX;
+    int64_t total = 0;  // steps
+    auto take = [&](int32_t steps) {
+        longest_row = std::max(longest_row, steps);
+        shortest_row = std::min(shortest_row, steps);
         total += steps;
-    }
+    };
+    if (c.lens1)
+        for (int u = 0; u < c.n_users; ++u)
+            take(((c.lens0[u] + up) >> shift) + ((c.lens1[u] + up) >> shift));
+    else
+        for (int u = 0; u < c.n_users; ++u)
+            take((c.lens0[u] + up) >> shift);
+    const int64_t longest = longest_row, shortest = shortest_row;
     const int64_t rows = (int64_t)c.n_users * c.Hkv, cus = std::max(1, c.n_cus), unit = 16384;
     const int row_bytes = c.step_bytes / (2 * c.tile);
     // Waves: twelve fit a compute unit, whatever the workgroups.  Rows that all have a unit of their own take as few waves

@@ -920,12 +920,6 @@ int split_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_
     return head_per_wave_choice(ctx, shape, total_steps(priv) + total_steps(pub));
 }
 
-// The same, or kWholeRows where the step's rows are short.
-int fused_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_view *priv, const spd_kv_view *pub)
-{
-    return whole_rows_waves(ctx, shape, priv, pub) ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
-}
-
 // Both owners of a fused step also share the device: if each would cut its rows into a full resident round of equal
 // pieces, the two rounds together are more than fit at once, the second owner's pieces start when the first's end, and
 // result rows are written all along (see the result ring in partial_mfma.hpp).  Where the pieces cross many rows -
@@ -947,19 +941,19 @@ Tuning fused_step_tuning(const spd_ctx *ctx, const spd_shape *shape, const spd_k
 }
 
 // The launches of a fused step, given both owners' schedules (device resident) and where their chunk partials go.
+// waves: of a whole-rows workgroup, 0 if the rows are split.
 int launch_decode_step(spd_ctx *ctx, const spd_shape *shape, const void *q, const spd_kv_view *priv, const spd_kv_view *pub,
-                       NewToken nt, const CachedSchedule *ep, const CachedSchedule *eo, const ScratchPtrs &sp_in,
+                       NewToken nt, int waves, const CachedSchedule *ep, const CachedSchedule *eo, const ScratchPtrs &sp_in,
                        const ScratchPtrs &sp_out, float *a_in, float *lse_in, float *a_out, float *lse_out, float *y,
                        float *lse, float *w_in, hipStream_t stream)
 {
     int rc;
-    if (ep->hpw == kWholeRows) {
+    if (waves) {
         MergeArgs mg;
         mg.y = y;
         mg.lse = lse;
         mg.w_in = w_in;
-        return launch_whole_rows(ctx, 0, whole_rows_waves(ctx, shape, priv, pub, true), ep, priv, a_in, lse_in, eo, pub, a_out, lse_out, shape,
-                                 q, nt, mg, stream);
+        return launch_whole_rows(ctx, 0, waves, ep, priv, a_in, lse_in, eo, pub, a_out, lse_out, shape, q, nt, mg, stream);
     }
     // one grid for both owners, the private owner's long streams first (measured faster than public first): the
     // public owner's short, latency-bound pieces then run beside them on the workgroup slots that remain
@@ -1371,12 +1365,12 @@ try {
     if (rc != SPD_OK || priv->n_users == 0)
         return rc;
     CachedSchedule *ep = nullptr, *eo = nullptr;
-    const int rule = fused_step_mapping(ctx, shape, priv, pub);
+    const int rule = whole_rows_waves(ctx, shape, priv, pub);
+    int waves = 0;
     rc = kNotRemembered;
     for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {  // see kNotRemembered
-        int hpw = rule;
-        if (t == 1)
-            hpw = rule != kWholeRows && whole_rows_waves(ctx, shape, priv, pub, true) ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
+        waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, shape, priv, pub, true);
+        const int hpw = waves ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
         const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);
         rc = prepare_partial(ctx, 0, shape, q, priv, a_in, lse_in, hpw, &tune, stream, t == kTries - 1, &ep);
         if (rc == SPD_OK)
@@ -1384,7 +1378,7 @@ try {
     }
     if (rc != SPD_OK)
         return rc;
-    return launch_decode_step(ctx, shape, q, priv, pub, nt, ep, eo, scratch_of(ctx->owner[0]), scratch_of(ctx->owner[1]), a_in,
+    return launch_decode_step(ctx, shape, q, priv, pub, nt, waves, ep, eo, scratch_of(ctx->owner[0]), scratch_of(ctx->owner[1]), a_in,
                               lse_in, a_out, lse_out, y, lse, w_in, stream);
 } catch (...) {  // a failed host allocation (std::vector): no C++ exception leaves the library
     return SPD_ERR_NOMEM;
@@ -1409,12 +1403,13 @@ try {
     StaticScratch &st = g_static[(size_t)ctx->device];
     if (!st.ptr)
         return SPD_ERR_WORKSPACE;
-    int hpw = fused_step_mapping(ctx, shape, priv, pub);
-    const int split = hpw == kWholeRows ? split_step_mapping(ctx, shape, priv, pub) : hpw;
+    int waves = whole_rows_waves(ctx, shape, priv, pub);
+    const int split = split_step_mapping(ctx, shape, priv, pub);
     // The tables of rows taken whole can be larger than the split schedule's - token-major storage has an item per group of
     // four or eight heads there, one per head here: what the array has no room for stays split.
-    if (hpw == kWholeRows && whole_rows_bytes(priv->n_users, shape->n_kv_heads) > kStaticSchedBytes)
-        hpw = split;
+    if (whole_rows_bytes(priv->n_users, shape->n_kv_heads) > kStaticSchedBytes)
+        waves = 0;
+    const int hpw = waves ? kWholeRows : split;
     const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, split);
     const int G = shape->n_q_heads / shape->n_kv_heads;
     // both schedules are built and checked against the array's limits before anything is enqueued; the step is refused by
@@ -1429,20 +1424,26 @@ try {
             (size_t)B[w].n_slots * G * shape->head_dim + 4 > kStaticPartOFloats)
             return SPD_ERR_WORKSPACE;
     }
-    for (int w = 0; w < 2 && hpw == kWholeRows; ++w) {
-        B[w] = ScheduleBlob();
-        build_blob(shape, views[w], hpw, ctx->n_cus, tune, B[w]);
-    }
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     SPD_HIP(ctx, hipStreamIsCapturing(stream, &capture));
     if (capture != hipStreamCaptureStatusNone)
         st.replayed = true;
+    // a schedule that the array already holds is not sent again - unless graph replays may have replaced it since
+    bool send[2];
+    for (int w = 0; w < 2; ++w) {
+        send[w] = st.replayed || st.key[w] != key[w];
+        if (waves) {
+            B[w] = ScheduleBlob();
+            B[w].off_rows = whole_rows_order_offset(views[w]->n_users, shape->n_kv_heads);
+            if (send[w])
+                build_blob(shape, views[w], hpw, ctx->n_cus, tune, B[w]);
+        }
+    }
     CachedSchedule e[2];
     ScratchPtrs sp[2];
     for (int w = 0; w < 2; ++w) {
         char *dst = st.ptr + (size_t)w * kStaticSchedBytes;
-        // a schedule that the array already holds is not sent again - unless graph replays may have replaced it since
-        if (st.replayed || st.key[w] != key[w]) {
+        if (send[w]) {
             st.key[w].clear();
             rc = upload_through_args(ctx, B[w].bytes, dst, stream);
             if (rc != SPD_OK)
@@ -1463,7 +1464,7 @@ try {
         sp[w].part_lse = reinterpret_cast<float *>(st.ptr + kStaticOffLse) + (size_t)w * kStaticLseFloats;
         sp[w].part_o = reinterpret_cast<float *>(st.ptr + kStaticOffPartO) + (size_t)w * kStaticPartOFloats;
     }
-    return launch_decode_step(ctx, shape, q, priv, pub, nt, &e[0], &e[1], sp[0], sp[1], a_in, lse_in, a_out, lse_out, y, lse,
+    return launch_decode_step(ctx, shape, q, priv, pub, nt, waves, &e[0], &e[1], sp[0], sp[1], a_in, lse_in, a_out, lse_out, y, lse,
                               w_in, stream);
 } catch (...) {  // a failed host allocation (std::vector): no C++ exception leaves the library
     return SPD_ERR_NOMEM;
