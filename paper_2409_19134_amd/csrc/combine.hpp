@@ -20,6 +20,10 @@
 namespace spd {
 
 constexpr int kCombineStage = 512;  // chunk weights staged in LDS per pass
+// Chunks per row up to which combine_chunks_kernel holds a row in registers.  For one owner's combine it is the faster one that far:
+// two waves per head instead of half a wave, 8 users of 1500 tokens 13.9 us per call against close_kernel's 14.4, of 2000 16.8 / 17.5;
+// with more chunks its way over the LDS is not, 4 users of 3001 tokens (24 chunks) 15.3 / 14.5.
+constexpr int kCombineSmall = 16;
 
 // e^x through the hardware's 2^x (one instruction after the scaling; the library expf is a dozen, and these kernels
 // are a few microseconds of pure latency in which every thread computes the same few weights).  fast_exp(0) is
@@ -178,9 +182,8 @@ __global__ __launch_bounds__(D) void combine_chunks_kernel(const CombineRow *__r
     const int g = blockIdx.y;
     const int64_t row = (int64_t)r.user * Hq + (int64_t)r.kv_head * G + g;
     float a, ls;
-    constexpr int kSmall = 16;
-    if (r.n_chunks <= kSmall)  // every load at once: one memory round trip
-        reduce_row(load_row<D, kSmall>(RowInfo{r.first_slot, r.n_chunks}, G, g, row, part_o, part_lse, out, lse), a, ls);
+    if (r.n_chunks <= kCombineSmall)  // every load at once: one memory round trip
+        reduce_row(load_row<D, kCombineSmall>(RowInfo{r.first_slot, r.n_chunks}, G, g, row, part_o, part_lse, out, lse), a, ls);
     else
         combine_row<D>(part_lse + (int64_t)r.first_slot * G + g,
                        part_o + ((int64_t)r.first_slot * G + g) * D + threadIdx.x, r.n_chunks, G, sm_w, sm_red, a, ls);
@@ -340,39 +343,40 @@ struct CloseRow {
 
     // GUARD: pairs past the end are left out instead of given a weight of 0
     template <bool GUARD, int C = 0>
-    __device__ __forceinline__ void weighted(const float (&w)[NL], f32x4 &o) const
+    __device__ __forceinline__ void weighted(const float (&w)[NL], f32x4 &o, float &den) const
     {
         if constexpr (C < MAXC) {
             const float wc = row_dpp<0x150 + (C & 15)>(w[C / 16]);  // row_newbcast: lane C & 15's value
+            den += wc;
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 o[v] = fmaf(wc, GUARD && C >= n ? 0.f : x[C][v], o[v]);
-            weighted<GUARD, C + 1>(w, o);
+            weighted<GUARD, C + 1>(w, o, den);
         }
     }
 
-    // n-way form of Theorem 1, chunks in order; a single pair passes through unchanged (it may be an empty row: 0, -inf)
+    // n-way form of Theorem 1, chunks and weights in order, as combine_row: the same bits whichever kernel closes a call.  A single
+    // pair passes through unchanged (it may be an empty row: 0, -inf).
     __device__ __forceinline__ void reduce(f32x4 &a_out, float &lse_out) const
     {
         const int lane = threadIdx.x & 15;
-        float m = -INFINITY, w[NL], den = 0.f;
+        float m = -INFINITY, w[NL];
 #pragma unroll
         for (int i = 0; i < NL; ++i)
             m = fmaxf(m, l[i]);
         const float M = row_max(m);
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
+        for (int i = 0; i < NL; ++i)
             w[i] = lane + 16 * i >= n ? 0.f : n == 1 ? 1.f : fast_exp(l[i] - M);
-            den += w[i];
-        }
-        den = row_sum(den);
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        weighted<false>(w, o);
+        float den = 0.f;
+        weighted<false>(w, o, den);
         // an infinite value times a stand-in's weight of 0 is NaN: once more without the stand-ins
         const float nan_if_any = (o[0] + o[1]) + (o[2] + o[3]);
         if (__any(nan_if_any != nan_if_any)) {
             o = f32x4{0.f, 0.f, 0.f, 0.f};
-            weighted<true>(w, o);
+            den = 0.f;
+            weighted<true>(w, o, den);
         }
         a_out = n == 1 ? x[0] : o * fast_rcp(den);
         lse_out = n == 1 ? l[0] : M + fast_log(den);

@@ -744,13 +744,14 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
     return SPD_OK;
 }
 
-// The closing kernel for rows of at most kCloseMaxChunks chunks (max_in: of the first owner, 0 if it is not there); false if
-// a row has more, or the heads do not fit its indices, and the general kernels have to do it.
+// The closing kernel for rows of at most kCloseMaxChunks chunks (max_in: of the first owner, 0 for the combine of one owner's rows,
+// which it only does for rows of more than kCombineSmall); false if the general kernels have to do it: a row has more, or the heads
+// do not fit its indices.
 bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd::CloseArgs &C, hipStream_t stream)
 {
     const int D = s->head_dim;
     const int64_t heads = (int64_t)n_users * s->n_q_heads;
-    if (std::max(max_in, max_out) > spd::kCloseMaxChunks || heads * D >= (1ll << 30))
+    if (std::max(max_in, max_out) > spd::kCloseMaxChunks || (max_in == 0 && max_out <= spd::kCombineSmall) || heads * D >= (1ll << 30))
         return false;
     C.heads = (int32_t)heads;
     C.G = s->n_q_heads / s->n_kv_heads;
@@ -760,9 +761,13 @@ bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd:
     return with_value<64, 128>(D, [&](auto d) {
         return with_value<0, 4, 8, 16, 32>(max_in ? size(max_in) : 0, [&](auto mi) {
             return with_value<4, 8, 16, 32>(size(max_out), [&](auto mo) {
-                hipLaunchKernelGGL((spd::close_kernel<decltype(d)::value, decltype(mi)::value, decltype(mo)::value>), grid, dim3(64), 0,
-                                   stream, C);
-                return true;
+                if constexpr (decltype(mi)::value == 0 && decltype(mo)::value <= spd::kCombineSmall) {
+                    return false;
+                } else {
+                    hipLaunchKernelGGL((spd::close_kernel<decltype(d)::value, decltype(mi)::value, decltype(mo)::value>), grid, dim3(64), 0,
+                                       stream, C);
+                    return true;
+                }
             });
         });
     });
