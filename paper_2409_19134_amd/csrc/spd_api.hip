@@ -1373,7 +1373,9 @@ try {
     const int rule = whole_rows_waves(ctx, shape, priv, pub);
     int waves = 0;
     rc = kNotRemembered;
+    const int64_t hits = ctx->schedule_hits;
     for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {  // see kNotRemembered
+        ctx->schedule_hits = hits;  // one owner's schedule found in a try that the other's absence ended does not count
         waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, shape, priv, pub, true);
         const int hpw = waves ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
         const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);

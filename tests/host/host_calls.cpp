@@ -56,6 +56,7 @@ static void launched(const void *fn, dim3 grid, dim3 block, void **args, size_t 
 
 static int last_error = 0;
 static bool other_capture = false;
+static int this_capture = 0;
 
 extern "C" {
 struct Config {
@@ -89,7 +90,7 @@ int hipStreamIsCapturing(void *stream, int *status)
 {
     if (!stream && other_capture)
         return last_error = 906;
-    return *status = 0, 0;
+    return *status = this_capture, 0;
 }
 void **__hipRegisterFatBinary(const void *)
 {
@@ -171,6 +172,7 @@ int main(int argc, char **argv)
     SYM(spd_decode_step_static);
     SYM(spd_decode_step);
     SYM(spd_partial_attn_private);
+    SYM(spd_get_schedule_stats);
     spd_ctx *ctx = nullptr;
     if (spd_create_(&ctx, 0) != SPD_OK)
         FAIL("spd_create");
@@ -223,6 +225,36 @@ int main(int argc, char **argv)
                 FAIL("%d tokens on the null stream while another stream is captured", tokens);
         }
     other_capture = false;
+
+    // A captured step whose public rows have grown across the border between whole and split rows, while the private rows are
+    // remembered split as well as whole: both owners' schedules count as found, once each, and nothing is built.
+    {
+        Step grown(SPD_BF16, 8, 2, 128, 1, 200, 161, false);
+        auto step = [&](int pub_tokens) {
+            grown.lens[1][0] = pub_tokens;
+            return spd_decode_step_(ctx, &grown.s, grown.buf, &grown.v[0], &grown.v[1], nullptr, nullptr, grown.buf, grown.buf, grown.buf,
+                                    grown.buf, grown.buf, grown.buf, grown.buf, nullptr);
+        };
+        auto whole = [] {
+            bool any = false;
+            for (const Launch &l : launches)
+                any = any || l.kernel.find("whole_rows_kernel") != std::string::npos;
+            launches.clear();
+            return any;
+        };
+        launches.clear();
+        if (step(161) != SPD_OK || !whole() || step(3001) != SPD_OK || whole())
+            FAIL("which rows are taken whole");
+        int64_t builds[2], hits[2];
+        this_capture = 1;
+        spd_get_schedule_stats_(ctx, &builds[0], &hits[0]);
+        if (step(161 + 64) != SPD_OK || !whole())
+            FAIL("a captured step does not keep its remembered schedules");
+        spd_get_schedule_stats_(ctx, &builds[1], &hits[1]);
+        this_capture = 0;
+        if (builds[1] != builds[0] || hits[1] - hits[0] != 2)
+            FAIL("a captured step: %lld schedules built, %lld found", (long long)(builds[1] - builds[0]), (long long)(hits[1] - hits[0]));
+    }
 
     // whole rows: no launch asks for more than 64 KB of LDS, the kernel's static part (argv[2], from the compiler's report) and
     // the slots together

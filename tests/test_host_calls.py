@@ -8,8 +8,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def test_uploads_and_launches_on_a_recorded_runtime(tmp_path, resource_report):
-    """What the calls ask of the runtime: the static step's schedules stay inside their parts of the fixed array, and a
-    whole-rows launch inside 64 KB of LDS."""
+    """What the calls ask of the runtime: the static step's schedules stay inside their parts of the fixed array, a
+    whole-rows launch inside 64 KB of LDS; calls beside a capture of another stream; what a captured step counts as found."""
     static_lds = {int(x) for name, x in re.findall(r"Function Name: (\S+)(?:(?!Function Name).)*?LDS Size \[bytes/block\]: (\d+)",
                                                    resource_report, re.S) if "whole_rows_kernel" in name}
     assert len(static_lds) == 1, static_lds
