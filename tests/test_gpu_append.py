@@ -119,7 +119,7 @@ def test_append_with_larger_pages(ctx, page_tokens, paged, fused):
 
 @pytest.mark.parametrize("dtype,Hq,Hkv,d,lp,lo,layout,paged", CASES)
 @pytest.mark.parametrize("fused", [False, True, "two_parties"])
-@pytest.mark.parametrize("steps", [None, 2])
+@pytest.mark.parametrize("steps", [None, 1, 2])     # 1, 2: the split kernels, also where short rows are taken whole
 def test_append_then_attend(ctx, mapping_of, in_flight, dtype, Hq, Hkv, d, lp, lo, layout, paged, fused, steps):
     layout = mapping_of(layout)
     in_flight(steps)
@@ -150,6 +150,10 @@ def test_append_then_attend(ctx, mapping_of, in_flight, dtype, Hq, Hkv, d, lp, l
     else:
         ctx.spd_partial_attn_public_batched_append(step.shape, wl.q, k_new, v_new, step.public, step.a_out, step.lse_out)
     torch.cuda.synchronize()
+    if steps:
+        assert ctx.spd_last_kernel_name().startswith("partial_mfma_kernel<")
+    elif U > 200 and not paged:
+        assert ctx.spd_last_kernel_name().startswith("whole_rows_kernel<")
 
     got = step.a_out.cpu().double().numpy().reshape(A_out.shape)
     assert np.abs(got - A_out).max() <= tol

@@ -296,14 +296,18 @@ def test_padded_strides(ctx, mapping_of, layout, dtype, d):
     check_against_oracle(ctx, wl)
 
 
-def test_many_users_with_short_rows(ctx):
-    """Thousands of workgroups that each take a whole short row (or only write an empty one)."""
+@pytest.mark.parametrize("steps", [None, 1, 2])
+def test_many_users_with_short_rows(ctx, in_flight, steps):
+    """Thousands of workgroups that each take a whole short row (or only write an empty one); on the split kernels thousands of
+    pieces and of workgroups for empty rows."""
+    in_flight(steps)
     rng = np.random.default_rng(77)
     U = 1500
     lp = rng.integers(0, 300, U).tolist()
     lo = rng.integers(0, 40, U).tolist()
     wl = workloads.random_case(104, torch.bfloat16, U, 16, 8, 128, lp, lo, device=DEV, layout="hnd_exact")
     check_against_oracle(ctx, wl)
+    assert ctx.spd_last_kernel_name().startswith("partial_mfma_kernel<" if steps else "whole_rows_kernel<")
 
 
 @pytest.mark.parametrize("chunk_max", [None, 128])
