@@ -5,8 +5,9 @@
 //                          A separate launch, not a last-workgroup-reduces scheme inside the partial kernel: on this
 //                          multi-die GPU a device-scope release/acquire writes back and invalidates a whole L2, which
 //                          cost more than the extra launch when every workgroup had to issue one.
-//   close_kernel           the closing kernel of both - one owner's combine, or both owners' and their merge - for rows of
-//                          at most 32 chunks, which is nearly all of them; the two kernels around it take the others
+//   close_kernel           both owners' combine and their merge in launches whose rows hold at most 32 chunks, which is nearly
+//                          all of them, and one owner's combine where a row holds 17 to 32; the two kernels around it take
+//                          the others
 //   finalize_step_kernel   last kernel of the fused step: combines whichever rows were split, for both owners, and
 //                          merges the owners, in one launch
 //   lse_merge_kernel       the two-owner merge itself: Y = w0 A_in + w1 A_out with w_x = exp(lse_x - lse).
@@ -233,8 +234,10 @@ __global__ __launch_bounds__(D) void finalize_step_kernel(const RowInfo *__restr
     const int64_t row = (int64_t)user * Hq + kvh * G + g;
     const int tid = threadIdx.x;
     const RowInfo ri = rows_in ? rows_in[user * Hkv + kvh] : RowInfo{0, 1}, ro = rows_out[user * Hkv + kvh];
-    // Measured on this kernel (4 us, pure latency): the 8-wide straight-line form is the fastest for rows of up to 8
-    // chunks; loading both owners' pairs in one go, or 16-wide for everything, made it 1.3-2.3 us slower.
+    // (It runs where some row has more chunks than close_kernel's instances hold; most rows still have few.)  Measured on this
+    // kernel, in which every thread computes every weight: the 8-wide straight-line form is the fastest for rows of up to 8
+    // chunks; loading both owners' pairs in one go, or 16-wide for everything, made it 1.3-2.3 us slower.  close_kernel, whose
+    // weights are a lane's each, loads both.
     constexpr int kSmall = 8, kMedium = 16;
     float x0, l0, x1, l1;
     if (ri.n_chunks > 1 && ri.n_chunks <= kSmall) {
@@ -289,9 +292,9 @@ __global__ __launch_bounds__(D) void finalize_step_kernel(const RowInfo *__restr
 // of them holds the log-sum-exps (and weights) of chunks i and i + 16.  Bound by latency: three dependent round trips
 // (arguments, RowInfo, partials) and ~2 ns per instruction of a wave, so every load of both owners leaves at once, a
 // chunk's weight is computed once per row instead of once per channel, and 64-thread workgroups spread over the device.
-// Measured against the kernels above, which take rows of more chunks (us per call, before / after): the headline batch, 16
-// users of 512-4096 + 1-512 tokens, fused 33.6 / 33.0, 16 users of 96-768 + 256 13.4 / 12.9, 4 of them 8.8 / 8.4, 48 users
-// in token-major pages 164.0 / 162.7, 256 skewed users 453.0 / 450.7.
+// Measured against the kernels above, which take launches with rows of more chunks (us per call, before / after): the headline
+// batch, 16 users of 512-4096 + 1-512 tokens, fused 33.6 / 33.0, 16 users of 96-768 + 256 13.4 / 12.9, 4 of them 8.8 / 8.4.  The
+// instance is picked by the row of most chunks.
 constexpr int kCloseMaxChunks = 32;
 
 // All-reduce over the sixteen lanes of a DPP row (rotations by 8, 4, 2, 1).

@@ -25,13 +25,15 @@
 // loads, the token each of its values belongs to and the layout of the results are the same as above, only the
 // number of MFMAs per step differs (D/4 for S^T, D/2 for O^T at fp32, against D/16 and D/8 at 16 bits); P needs no
 // split.
-// fp32 with D = 128 and at most four query heads per KV head (kF32Quad) takes v_mfma_f32_4x4x1_16b_f32 instead, sixteen independent
+// fp32 with at most four query heads per KV head (kF32Quad; in this kernel with D = 128 only, in the whole-rows kernel at either
+// D) takes v_mfma_f32_4x4x1_16b_f32 instead, sixteen independent
 // 4x4 products per instruction at the same rate: the 16x16 tile spends 32 cycles on sixteen head columns of which G
 // hold a head, 4096 cycles per 32 tokens at D = 128 (1.7 us in which no other wave of the SIMD has the pipe); the 4x4
-// blocks need 1024.  With r = 4 * rq + i, block (grp, rq) of S^T takes tokens tb + grp*8 + a*4 + i and the
+// blocks need 1024.  With r = 4 * rq + i and NE tokens per lane group and step (8, or 4 with 512-byte rows), block (grp, rq) of
+// S^T takes tokens tb + grp*NE + a*4 + i and the
 // 16-byte piece rq of every 64 channel bytes (the four pieces are then summed over rq inside the 16-lane row with DPP
-// adds), so a lane ends up with head i and tokens tb + grp*8 + e, exactly the P that block (grp, rq) of O^T needs for
-// channels (4*rq + i)*(D/16) + cc.  O^T stays split over grp (disjoint tokens) until the segment ends.
+// adds), so a lane ends up with head i and tokens tb + grp*NE + e, exactly the P that block (grp, rq) of O^T needs for
+// channels o_channel(4*rq + i, cc).  O^T stays split over grp (disjoint tokens) until the segment ends.
 // fp32 rows of 512 bytes (D = 128) are HBM-bound once three things are so (8B shape, 16 users of 512-4096 tokens, 338 MB,
 // us per fused step): the 4x4 blocks 73.9 -> 71.7; a lane's V loads cover 256 contiguous bytes per instruction instead
 // of every other 16 (whose lines were asked for twice) -> 64.6; a wave's step is 16 tokens, 16 KB as at 16 bits, so that
@@ -82,7 +84,7 @@ struct Elt<SPD_F32> {
     }
 };
 
-// fp32 with D = 128 and at most four query heads per KV head: the kernels' own dtype code for the 4x4 blocks (see above).
+// fp32 with at most four query heads per KV head: the kernels' own dtype code for the 4x4 blocks (see above).
 constexpr int kF32Quad = 3;
 constexpr int kQuadHeads = 4;
 template <>
@@ -177,7 +179,7 @@ struct TileRegs {
 
 struct LaneConst {
     int r, grp;
-    int kt, kc;  // the lane's K rows: tokens tb + kt*8 + a*4 + (r & 3), 16-byte piece kc (r / 4 and grp; kF32Quad: grp and r / 4)
+    int kt, kc;  // the lane's K rows: tokens tb + kt*NE + a*4 + (r & 3) (NE = 4 * step_tiles), 16-byte piece kc (r / 4 and grp; kF32Quad: grp and r / 4)
     const char *k_base;  // contiguous: user's K + head offset; paged: pool + head offset
     const char *v_base;
     const int32_t *bt_row;
@@ -442,7 +444,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
     __shared__ float *ring_dst_o[kRingMaxRows], *ring_dst_l[kRingMaxRows];  // where the ring's rows go
     extern __shared__ __align__(16) float sm_o[];  // [waves][G * kOStride], sized by the launch: only G heads are staged; then the ring
     constexpr int kOStride = o_stride(D);
-    constexpr int CP = D / 16;  // channel phases of the O^T tile: a lane holds CP consecutive channels per accumulator row
+    constexpr int CP = D / 16;  // channel phases of the O^T tile; which channel a phase of a row holds: o_channel
     constexpr int kRowBytes = D * Elt<DT>::kBytes;
     constexpr int RB = kRowBytes;
     constexpr bool kQuad = DT == kF32Quad;

@@ -63,15 +63,16 @@ inline Tuning tuning_from_env()
     return t;
 }
 
-// The split schedule ("stream-K" over tokens).  All KV heads of a user hold the same tokens, so the schedule is laid
+// The split schedule ("stream-K" over tokens), for calls whose rows are not taken whole (whole_rows_choice).
+// All KV heads of a user hold the same tokens, so the schedule is laid
 // out on token steps (32 tokens) per user and replicated over the KV heads: the steps of all users, laid end to end,
 // are divided into groups of equal length (+-1 step), and every group becomes one piece (one workgroup) per KV head.
 // The pieces of a group are adjacent in launch order, so with token-major storage the heads that share DRAM pages
 // stream them at the same time.  A group that crosses a user boundary gives pieces with several segments.
 // Equal pieces matter because the path is HBM-bound: a launch lasts as long as its longest workgroup.
 //   - if no user is longer than a few hundred tokens the work is latency-bound: every row is cut into chunks of 128
-//     tokens (one step per wave: one memory round trip).  That also holds for a standalone call, although it then
-//     needs the combine launch: whole rows of up to 512 tokens per workgroup measured 2.4 us slower;
+//     tokens (one step per wave: one memory round trip), also for a standalone call, although it then needs the combine
+//     launch (rows that pay for being whole are taken by the whole-rows kernel instead);
 //   - work that fits one resident wave of workgroups (2 per CU) gets exactly that many pieces;
 //   - larger work gets pieces of at most `piece_max` tokens, their number rounded up to a multiple of the resident
 //     wave, and relies on the hardware's dynamic workgroup dispatch.
