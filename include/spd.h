@@ -227,7 +227,8 @@ int spd_lse_merge_n(spd_ctx *ctx, int32_t n_parts, int32_t n_rows, int32_t head_
  * The paper's prototype overlaps the users' private computation with the service's public one; here both owners'
  * work is placed in one launch (the public owner's short pieces run beside the private owner's long streams on the
  * same compute units) and a single closing kernel combines whatever rows either owner had to split and merges the
- * two owners.  (A step over short rows is one launch that does all of this.)  Results are those of the three calls above made in sequence, all of them still delivered:
+ * two owners.  (A step over short rows is one launch that does all of this.)  Results are those of the three calls above
+ * made in sequence, all of them still delivered:
  *   a_in, lse_in   = spd_partial_attn_private(q, priv)            [n_users][Hq][d], [n_users][Hq]
  *   a_out, lse_out = spd_partial_attn_public_batched(q, pub)
  *   y, lse, w_in   = spd_lse_merge(a_in, lse_in, a_out, lse_out)   (all three required here)

@@ -6,7 +6,7 @@
 // (three per SIMD) that share a row's steps out evenly, both owners' in one line: the old split of such calls into
 // one-step workgroups spread better over idle compute units but needed a second launch to close.  Measured, split kernels /
 // this one (us per call): fp32 1 user 128 + 16 tokens 8.5 / 4.9 (fused), bf16 32 users of 64-512 + 1-256 with the append
-// 18.9 / 15.8, 256 such users 90.3 / 82.3 (5.5 TB/s), 256 users of 24-192 + 64 51.2 / 31.5; fp16 with 64 channels, 16 users
+// 18.9 / 15.2, 256 such users 90.3 / 82.3 (5.5 TB/s), 256 users of 24-192 + 64 51.2 / 31.5; fp16 with 64 channels, 16 users
 // as three calls 19.8 / 14.2.  When it pays is whole_rows_choice's rule (schedule.hpp).
 #pragma once
 #include <type_traits>
