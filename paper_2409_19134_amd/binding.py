@@ -187,8 +187,14 @@ class KVView:
                    head_strides=getattr(side, "head_strides", None), device_pointer_tables=device_pointer_tables)
 
 
+# torch's current stream as a pointer, without the Stream object around it (2 us of a call that takes 11) where torch offers that
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device()) or None
         stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
@@ -226,8 +232,9 @@ class Context:
         if lse is None:
             lse = torch.empty((n, Hq), device=q.device, dtype=torch.float32)
         assert q.is_contiguous() and out.is_contiguous() and lse.is_contiguous()
-        assert tuple(q.shape) == (n, Hq, d) and tuple(out.shape) == (n, Hq, d) and tuple(lse.shape) == (n, Hq)
-        assert out.dtype == torch.float32 and lse.dtype == torch.float32
+        rows = (n, Hq, d)
+        assert q.shape == rows and out.shape == rows and lse.shape == (n, Hq)
+        assert out.dtype is torch.float32 and lse.dtype is torch.float32
         rc = fn(self.handle, C.byref(shape), q.data_ptr(), C.byref(view.struct), out.data_ptr(), lse.data_ptr(),
                 _stream_ptr(stream))
         self._check(rc, name)
@@ -288,8 +295,8 @@ class Context:
         if lse is None:
             lse = torch.empty((n, Hq), device=q.device, dtype=torch.float32)
         for t in (k_new, v_new):
-            assert t.is_contiguous() and t.dtype == q.dtype and tuple(t.shape) == (n, shape.n_kv_heads, d)
-        assert q.is_contiguous() and tuple(q.shape) == (n, Hq, d)
+            assert t.is_contiguous() and t.dtype == q.dtype and t.shape == (n, shape.n_kv_heads, d)
+        assert q.is_contiguous() and q.shape == (n, Hq, d)
         rc = lib.spd_partial_attn_public_batched_append(self.handle, C.byref(shape), q.data_ptr(), k_new.data_ptr(),
                                                         v_new.data_ptr(), C.byref(view.struct), out.data_ptr(),
                                                         lse.data_ptr(), _stream_ptr(stream))
@@ -300,12 +307,12 @@ class Context:
                         k_new=None, v_new=None):
         n, Hq, d = private.struct.n_users, shape.n_q_heads, shape.head_dim
         for t in (a_in, a_out, y):
-            assert t.is_contiguous() and t.dtype == torch.float32 and tuple(t.shape) == (n, Hq, d)
+            assert t.is_contiguous() and t.dtype is torch.float32 and t.shape == (n, Hq, d)
         for t in (lse_in, lse_out, lse, w_in):
-            assert t.is_contiguous() and t.dtype == torch.float32 and tuple(t.shape) == (n, Hq)
-        assert q.is_contiguous() and tuple(q.shape) == (n, Hq, d)
+            assert t.is_contiguous() and t.dtype is torch.float32 and t.shape == (n, Hq)
+        assert q.is_contiguous() and q.shape == (n, Hq, d)
         for t in (k_new, v_new):
-            assert t is None or (t.is_contiguous() and t.dtype == q.dtype and tuple(t.shape) == (n, shape.n_kv_heads, d))
+            assert t is None or (t.is_contiguous() and t.dtype == q.dtype and t.shape == (n, shape.n_kv_heads, d))
         rc = lib.spd_decode_step(self.handle, C.byref(shape), q.data_ptr(), C.byref(private.struct),
                                  C.byref(public.struct), None if k_new is None else k_new.data_ptr(),
                                  None if v_new is None else v_new.data_ptr(),
@@ -319,12 +326,12 @@ class Context:
         """spd_decode_step on the library's fixed scratch array (allocates nothing)."""
         n, Hq, d = private.struct.n_users, shape.n_q_heads, shape.head_dim
         for t in (a_in, a_out, y):
-            assert t.is_contiguous() and t.dtype == torch.float32 and tuple(t.shape) == (n, Hq, d)
+            assert t.is_contiguous() and t.dtype is torch.float32 and t.shape == (n, Hq, d)
         for t in (lse_in, lse_out, lse, w_in):
-            assert t.is_contiguous() and t.dtype == torch.float32 and tuple(t.shape) == (n, Hq)
-        assert q.is_contiguous() and tuple(q.shape) == (n, Hq, d)
+            assert t.is_contiguous() and t.dtype is torch.float32 and t.shape == (n, Hq)
+        assert q.is_contiguous() and q.shape == (n, Hq, d)
         for t in (k_new, v_new):
-            assert t is None or (t.is_contiguous() and t.dtype == q.dtype and tuple(t.shape) == (n, shape.n_kv_heads, d))
+            assert t is None or (t.is_contiguous() and t.dtype == q.dtype and t.shape == (n, shape.n_kv_heads, d))
         rc = lib.spd_decode_step_static(self.handle, C.byref(shape), q.data_ptr(), C.byref(private.struct),
                                         C.byref(public.struct), None if k_new is None else k_new.data_ptr(),
                                         None if v_new is None else v_new.data_ptr(),
@@ -336,7 +343,7 @@ class Context:
     def spd_attention_mass_track(self, w_in, threshold, mass_min=None, mass_sum=None, n_below=None, stream=None):
         n = w_in.numel()
         for t in (w_in, mass_min, mass_sum):
-            assert t is None or (t.is_contiguous() and t.dtype == torch.float32 and t.numel() == n)
+            assert t is None or (t.is_contiguous() and t.dtype is torch.float32 and t.numel() == n)
         assert n_below is None or (n_below.is_contiguous() and n_below.dtype == torch.int32 and n_below.numel() == n)
         ptr = lambda t: None if t is None else t.data_ptr()
         rc = lib.spd_attention_mass_track(self.handle, n, w_in.data_ptr(), float(threshold), ptr(mass_min), ptr(mass_sum),
@@ -350,7 +357,7 @@ class Context:
         if y is None:
             y = torch.empty_like(a0)
         for t in (a0, a1, y, lse0, lse1):
-            assert t.is_contiguous() and t.dtype == torch.float32
+            assert t.is_contiguous() and t.dtype is torch.float32
         assert a0.numel() == n_rows * d == a1.numel() == y.numel() and lse1.numel() == n_rows
         rc = lib.spd_lse_merge(self.handle, n_rows, d, a0.data_ptr(), lse0.data_ptr(), a1.data_ptr(), lse1.data_ptr(),
                                y.data_ptr(), None if lse_out is None else lse_out.data_ptr(),
@@ -364,13 +371,13 @@ class Context:
         """The service's half of a step: public partial (+ append) and the merge with delivered private partials."""
         n, Hq, d = public.struct.n_users, shape.n_q_heads, shape.head_dim
         for t in (a_in, a_out, y):
-            assert t.is_contiguous() and t.dtype == torch.float32 and tuple(t.shape) == (n, Hq, d)
+            assert t.is_contiguous() and t.dtype is torch.float32 and t.shape == (n, Hq, d)
         for t in (lse_in, lse_out, lse, w_in):
-            assert t.is_contiguous() and t.dtype == torch.float32 and tuple(t.shape) == (n, Hq)
-        assert q.is_contiguous() and tuple(q.shape) == (n, Hq, d)
+            assert t.is_contiguous() and t.dtype is torch.float32 and t.shape == (n, Hq)
+        assert q.is_contiguous() and q.shape == (n, Hq, d)
         assert (k_new is None) == (v_new is None)
         for t in (k_new, v_new):
-            assert t is None or (t.is_contiguous() and t.dtype == q.dtype and tuple(t.shape) == (n, shape.n_kv_heads, d))
+            assert t is None or (t.is_contiguous() and t.dtype == q.dtype and t.shape == (n, shape.n_kv_heads, d))
         rc = lib.spd_public_attn_merge(self.handle, C.byref(shape), q.data_ptr(), C.byref(public.struct),
                                        None if k_new is None else k_new.data_ptr(),
                                        None if v_new is None else v_new.data_ptr(), a_in.data_ptr(), lse_in.data_ptr(),
@@ -388,9 +395,9 @@ class Context:
         if y is None:
             y = torch.empty_like(a_parts[0])
         for t in (*a_parts, *lse_parts, y):
-            assert t.is_contiguous() and t.dtype == torch.float32
+            assert t.is_contiguous() and t.dtype is torch.float32
         assert all(a.numel() == n_rows * d for a in a_parts) and all(l.numel() == n_rows for l in lse_parts)
-        assert w_out is None or (w_out.is_contiguous() and w_out.dtype == torch.float32 and w_out.numel() == n * n_rows)
+        assert w_out is None or (w_out.is_contiguous() and w_out.dtype is torch.float32 and w_out.numel() == n * n_rows)
         ap = (C.c_void_p * n)(*[a.data_ptr() for a in a_parts])
         lp = (C.c_void_p * n)(*[l.data_ptr() for l in lse_parts])
         rc = lib.spd_lse_merge_n(self.handle, n, n_rows, d, ap, lp, y.data_ptr(),

@@ -429,13 +429,10 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
     return std::min(waves, spd::rows_waves_that_fit(s->head_dim, s->n_q_heads / s->n_kv_heads));
 }
 
-// Validation, schedule lookup and scratch growth of one partial-attention call.
-int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const void *q, const spd_kv_view *v, float *out,
-                    float *lse, int mapping, const Tuning *tune, hipStream_t stream, bool build, CachedSchedule **e)
+// Schedule lookup and scratch growth of one partial-attention call, whose arguments have been validated.
+int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const spd_kv_view *v, int mapping, const Tuning *tune, hipStream_t stream,
+                    bool build, CachedSchedule **e)
 {
-    const int rc = spd_validate_partial(s, q, v, out, lse);
-    if (rc != SPD_OK)
-        return rc;
     *e = nullptr;
     if (v->n_users == 0)
         return SPD_OK;
@@ -455,14 +452,13 @@ int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const void *q, 
 }
 
 // The schedule of a call for one owner alone: whole rows (*waves > 0) or split, see kNotRemembered.
-int prepare_one_owner(spd_ctx *ctx, int which, const spd_shape *s, const void *q, const spd_kv_view *v, float *out, float *lse,
-                      hipStream_t stream, CachedSchedule **e, int *waves)
+int prepare_one_owner(spd_ctx *ctx, int which, const spd_shape *s, const spd_kv_view *v, hipStream_t stream, CachedSchedule **e, int *waves)
 {
     const int rule = whole_rows_waves(ctx, s, v, nullptr);
     int rc = kNotRemembered;
     for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {
         *waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, s, v, nullptr, true);
-        rc = prepare_partial(ctx, which, s, q, v, out, lse, *waves ? kWholeRows : -1, nullptr, stream, t == kTries - 1, e);
+        rc = prepare_partial(ctx, which, s, v, *waves ? kWholeRows : -1, nullptr, stream, t == kTries - 1, e);
     }
     return rc;
 }
@@ -832,7 +828,7 @@ int partial_attention(spd_ctx *ctx, int which, const spd_shape *s, const void *q
     if (rc != SPD_OK)
         return rc;
     int waves = 0;
-    rc = prepare_one_owner(ctx, which, s, q, v, out, lse, stream, &e, &waves);
+    rc = prepare_one_owner(ctx, which, s, v, stream, &e, &waves);
     if (rc != SPD_OK || !e)
         return rc;
     if (waves)
@@ -1379,9 +1375,9 @@ try {
         waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, shape, priv, pub, true);
         const int hpw = waves ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
         const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);
-        rc = prepare_partial(ctx, 0, shape, q, priv, a_in, lse_in, hpw, &tune, stream, t == kTries - 1, &ep);
+        rc = prepare_partial(ctx, 0, shape, priv, hpw, &tune, stream, t == kTries - 1, &ep);
         if (rc == SPD_OK)
-            rc = prepare_partial(ctx, 1, shape, q, pub, a_out, lse_out, hpw, &tune, stream, t == kTries - 1, &eo);  // an upload, if any, stays on `stream`
+            rc = prepare_partial(ctx, 1, shape, pub, hpw, &tune, stream, t == kTries - 1, &eo);  // an upload, if any, stays on `stream`
     }
     if (rc != SPD_OK)
         return rc;
@@ -1501,7 +1497,7 @@ try {
         return SPD_ERR_ALIGN;
     CachedSchedule *eo = nullptr;
     int waves = 0;
-    rc = prepare_one_owner(ctx, 1, shape, q, pub, a_out, lse_out, stream, &eo, &waves);
+    rc = prepare_one_owner(ctx, 1, shape, pub, stream, &eo, &waves);
     if (rc != SPD_OK)
         return rc;
     if (waves) {
