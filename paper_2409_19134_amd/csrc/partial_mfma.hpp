@@ -97,6 +97,26 @@ struct Elt<kF32Quad> {
     }
 };
 
+// The same arithmetic in the streaming kernel's other forms (D = 128), by dtype codes of its own: 16-bit elements in steps of 16
+// tokens ("half steps"), and kF32Quad with its rows read through buffer descriptors, as the half steps read theirs where they can
+// (contiguous rows without an append).
+// What half steps are for: a round of 16 KB per wave takes ~3.6 us while everything streams, a piece of 17 steps is five rounds to one
+// wave and four to the other three, and nothing is in flight while a wave computes: rounds of half the size leave less of both at a
+// piece's end.  Measured, us per fused step, 32-token steps / half steps: the headline batch 33.1 / 32.7, with the append 34.1 / 33.2, in
+// 16-token pages 33.7 / 32.7; 12 such users 27.0 / 26.7, 24 48.8 / 48.1; 8 users of 4000-12000 tokens 52.3 / 51.5, 2 of 20000-40000
+// 48.3 / 47.0; two parties 40.7 / 40.1.  In buffer descriptors a lane's offset and a scalar per row are all the addressing there
+// is (VALU cycles of a 32-token step 1400 -> 800): fp32, headline batch, 60.9 / 60.0.
+constexpr int kBf16Half = 4, kF16Half = 5, kF32QuadRange = 6;
+template <>
+struct Elt<kBf16Half> : Elt<SPD_BF16> {};
+template <>
+struct Elt<kF16Half> : Elt<SPD_F16> {};
+template <>
+struct Elt<kF32QuadRange> : Elt<kF32Quad> {};
+constexpr bool half_steps(int dt) { return dt == kBf16Half || dt == kF16Half; }
+constexpr bool quad_blocks(int dt) { return dt == kF32Quad || dt == kF32QuadRange; }
+constexpr bool by_descriptor(int dt, bool paged, bool append) { return (half_steps(dt) || dt == kF32QuadRange) && !paged && !append; }
+
 // Sum over the four lanes of a 16-lane row that differ in bits 2 and 3 (rq), in all of them: two rotations of the row.
 __device__ __forceinline__ float row_quad_sum(float v)
 {
@@ -136,12 +156,14 @@ template <>
 struct VRow<128> {
     u32x2 w;
     __device__ __forceinline__ void load(const char *p) { w = stream_load<u32x2>(p); }
+    __device__ __forceinline__ void load(row_rsrc b, unsigned lane, unsigned at) { w = stream_load8(b, lane, at); }
     __device__ __forceinline__ unsigned dword(int i) const { return w[i]; }
 };
 template <>
 struct VRow<256> {
     u32x4 w;
     __device__ __forceinline__ void load(const char *p) { w = stream_load16(p); }
+    __device__ __forceinline__ void load(row_rsrc b, unsigned lane, unsigned at) { w = stream_load16(b, lane, at); }
     __device__ __forceinline__ unsigned dword(int i) const { return w[i]; }
 };
 template <>
@@ -151,6 +173,11 @@ struct VRow<512> {
     {
         w0 = stream_load16(p);
         w1 = stream_load16(p + 256);
+    }
+    __device__ __forceinline__ void load(row_rsrc b, unsigned lane, unsigned at)
+    {
+        w0 = stream_load16(b, lane, at);
+        w1 = stream_load16(b, lane + 256, at);
     }
     __device__ __forceinline__ unsigned dword(int i) const { return i < 4 ? w0[i] : w1[i - 4]; }  // i is a constant
 };
@@ -167,14 +194,14 @@ __device__ __forceinline__ constexpr int o_channel(int row, int cc)
 }
 
 // 16-token S tiles per step of a wave: two, or one where rows are 512 bytes (fp32 with D = 128), so that a step is 16 KB
-// at either row size.
-__host__ __device__ constexpr int step_tiles(int RB) { return RB == 512 ? 1 : 2; }
+// at either row size; half that in half steps.
+__host__ __device__ constexpr int step_tiles(int RB, bool half = false) { return RB == 512 || half ? 1 : 2; }
 __host__ __device__ constexpr int step_tokens(int RB) { return 16 * step_tiles(RB); }
 
-template <int RB>
+template <int RB, int NA>
 struct TileRegs {
-    u32x4 k[step_tiles(RB)][RB / 64];  // [S tile a][piece kk]: token row kt of tile a, bytes kk*64 + kc*16 .. +16 (see LaneConst)
-    VRow<RB> v[4 * step_tiles(RB)];    // [e]: token tb + grp*NE + e, RB/16 bytes from r*v_lane_bytes on
+    u32x4 k[NA][RB / 64];  // [S tile a][piece kk]: token row kt of tile a, bytes kk*64 + kc*16 .. +16 (see LaneConst)
+    VRow<RB> v[4 * NA];    // [e]: token tb + grp*NE + e, RB/16 bytes from r*v_lane_bytes on
 };
 
 struct LaneConst {
@@ -206,13 +233,31 @@ __device__ __forceinline__ PagePair load_pages(const LaneConst &L, int tb, int t
     return P;
 }
 
-// Issues the 16 loads of the step at tb.  Paged: P holds that step's page ids on entry and the following step's
+// Issues the loads of the step at tb, NA 16-token tiles.  Paged: P holds that step's page ids on entry and the following step's
 // (tb + step) on return: the lookup is issued behind the data loads, one whole step before it is needed, so that no
 // wave ever waits for a block-table entry before it can ask for data.
-template <int RB, bool PAGED, bool APPEND>
-__device__ __forceinline__ void load_tile(TileRegs<RB> &T, const LaneConst &L, int tb, int t_last, PagePair &P, int step)
+// RANGE: through buffer descriptors whose range ends with the segment (rows past it are zeros and cost no traffic); token strides below
+// kBufferStrideLimit, so that offsets inside a step fit 32 bits.
+template <int RB, int NA, bool PAGED, bool APPEND, bool RANGE = false>
+__device__ __forceinline__ void load_tile(TileRegs<RB, NA> &T, const LaneConst &L, int tb, int t_last, PagePair &P, int step)
 {
-    constexpr int NE = 4 * step_tiles(RB);
+    constexpr int NE = 4 * NA;
+    if constexpr (RANGE) {
+        static_assert(!PAGED && !APPEND);
+        const unsigned stride = (unsigned)L.token_stride;
+        const unsigned k_lane = (L.kt * NE + (L.r & 3)) * stride + L.kc * 16, v_lane = L.grp * NE * stride + L.r * v_lane_bytes(RB);
+        const row_rsrc kb = row_buffer(L.k_base, tb, t_last, L.token_stride, RB), vb = row_buffer(L.v_base, tb, t_last, L.token_stride, RB);
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int kk = 0; kk < RB / 64; ++kk)
+                T.k[a][kk] = stream_load16(kb, k_lane + kk * 64, a * 4 * stride);
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            T.v[e].load(vb, v_lane, e * stride);
+        __builtin_amdgcn_sched_barrier(0);
+        return;
+    }
     const int gk = tb + L.kt * NE;       // first token of the NE-token group this lane's K rows fall in
     const int gv = tb + L.grp * NE;      // first token of the group this lane's V rows fall in
     const char *kp = L.k_base, *vp = L.v_base;
@@ -221,7 +266,7 @@ __device__ __forceinline__ void load_tile(TileRegs<RB> &T, const LaneConst &L, i
         vp += (int64_t)((gv - tb) >= 16 ? P.p1 : P.p0) * L.block_stride;
     }
 #pragma unroll
-    for (int a = 0; a < step_tiles(RB); ++a) {
+    for (int a = 0; a < NA; ++a) {
         const int t = min(gk + a * 4 + (L.r & 3), t_last);  // rows past the chunk re-read its last token (masked later)
         const char *p = kp + (int64_t)(PAGED ? (t & L.page_mask) : t) * L.token_stride + L.kc * 16;
         if (APPEND && L.k_new_row && t == t_last)  // the appended token is read from the caller's buffer, not the cache
@@ -246,13 +291,13 @@ __device__ __forceinline__ void load_tile(TileRegs<RB> &T, const LaneConst &L, i
 }
 
 // qB: Q as the B operand, loaded like a K row (head r instead of token r): bytes kk*64 + kc*16 .. +16 of the row.
-template <int DT, int D>
-__device__ __forceinline__ void compute_tile(const TileRegs<D * Elt<DT>::kBytes> &T,
+template <int DT, int D, int NA>
+__device__ __forceinline__ void compute_tile(const TileRegs<D * Elt<DT>::kBytes, NA> &T,
                                              const u32x4 (&qB)[D * Elt<DT>::kBytes / 64], int tb, int grp, int t_end,
                                              float c, float &m, float &l, f32x4 (&acc)[D / 16])
 {
     constexpr int RB = D * Elt<DT>::kBytes;
-    constexpr int NA = step_tiles(RB), NE = 4 * NA;
+    constexpr int NE = 4 * NA;
     f32x4 s[NA];
 #pragma unroll
     for (int a = 0; a < NA; ++a)
@@ -273,7 +318,7 @@ __device__ __forceinline__ void compute_tile(const TileRegs<D * Elt<DT>::kBytes>
             for (int a = 0; a < NA; ++a)
                 s[a] = Elt<DT>::mfma(__builtin_bit_cast(vec8, T.k[a][kk]), __builtin_bit_cast(vec8, qB[kk]), s[a]);
     }
-    if constexpr (DT == kF32Quad) {  // the four 16-byte pieces of every 64 channel bytes
+    if constexpr (quad_blocks(DT)) {  // the four 16-byte pieces of every 64 channel bytes
 #pragma unroll
         for (int a = 0; a < NA; ++a)
 #pragma unroll
@@ -307,7 +352,7 @@ __device__ __forceinline__ void compute_tile(const TileRegs<D * Elt<DT>::kBytes>
         for (int cc = 0; cc < D / 16; ++cc)
             acc[cc] *= alpha;
     }
-    if constexpr (DT == kF32Quad) {
+    if constexpr (quad_blocks(DT)) {
         // a block per lane-group token and four of the lane's channels; the phases are independent chains
 #pragma unroll
         for (int e = 0; e < NE; ++e)
@@ -322,6 +367,25 @@ __device__ __forceinline__ void compute_tile(const TileRegs<D * Elt<DT>::kBytes>
 #pragma unroll
             for (int e = 0; e < NE; ++e)
                 acc[cc] = Elt<DT>::mfma(__uint_as_float(T.v[e].dword(cc)), p[e], acc[cc]);
+    } else if constexpr (NA == 1) {
+        // four tokens to a lane: the high and the low parts of their probabilities fill one operand, the V values the other twice
+        typedef typename Elt<DT>::vec8 vec8;
+        typedef typename Elt<DT>::type E;
+        vec8 pp;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            pp[e] = (E)p[e];
+            pp[e + 4] = (E)(p[e] - (float)pp[e]);
+        }
+#pragma unroll
+        for (int cc = 0; cc < D / 16; ++cc) {
+            const unsigned sel = (cc & 1) ? 0x07060302u : 0x05040100u;
+            u32x4 vt;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                vt[j] = vt[j + 2] = __builtin_amdgcn_perm(T.v[2 * j + 1].dword(cc >> 1), T.v[2 * j].dword(cc >> 1), sel);
+            acc[cc] = Elt<DT>::mfma(__builtin_bit_cast(vec8, vt), pp, acc[cc]);
+        }
     } else {
         typedef typename Elt<DT>::vec8 vec8;
         typedef typename Elt<DT>::type E;
@@ -447,20 +511,22 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
     constexpr int CP = D / 16;  // channel phases of the O^T tile; which channel a phase of a row holds: o_channel
     constexpr int kRowBytes = D * Elt<DT>::kBytes;
     constexpr int RB = kRowBytes;
-    constexpr bool kQuad = DT == kF32Quad;
+    constexpr bool kQuad = quad_blocks(DT);
+    constexpr bool kHalf = half_steps(DT), kRange = by_descriptor(DT, PAGED, APPEND);
+    constexpr int NA = step_tiles(RB, kHalf);  // 16-token tiles of a wave's step
     const int o_wave_stride = G * kOStride;
     // head-per-wave results go through a wave-private tile if the launch gave the room
     const bool staged = HPW && staging_fits(D, (int)(blockDim.x >> 6), G);
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    constexpr int kTile = step_tokens(RB);  // tokens per step of a wave
+    constexpr int kTile = 16 * NA;  // tokens per step of a wave
     constexpr int kStep = HPW ? kTile : kTile * kWaves;
 
     // Everything a segment needs before its first MFMA: addresses, the KV append copy, Q, and the loads of the wave's
     // first 32-token step.  Issued for the *next* segment before the current one's epilogue, so that the barriers
     // and the result stores of the epilogue overlap the memory round trip instead of preceding it.
-    auto begin_segment = [&](const DevItem &it, LaneConst &L, u32x4 (&qB)[RB / 64], int &tb, TileRegs<RB> &T0, PagePair &P) {
+    auto begin_segment = [&](const DevItem &it, LaneConst &L, u32x4 (&qB)[RB / 64], int &tb, TileRegs<RB, NA> &T0, PagePair &P) {
         L.r = lane & 15;
         L.grp = lane >> 4;
         L.kt = kQuad ? L.grp : L.r >> 2;
@@ -502,12 +568,12 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
             if (head < G)
                 qB[kk] = *reinterpret_cast<const u32x4 *>(qrow + kk * 64);
         }
-        // head-major: the four waves take interleaved 32-token steps; token-major: every wave takes every step
-        tb = HPW ? it.t_begin : it.t_begin + ((uniform(wave) - (it.rot & 3)) & (kWaves - 1)) * kTile;
+        // head-major: the four waves take interleaved steps (rot counts 32-token ones); token-major: every wave takes every step
+        tb = HPW ? it.t_begin : it.t_begin + ((uniform(wave) - (kHalf ? 2 * it.rot : it.rot)) & (kWaves - 1)) * kTile;
         if (PAGED)
             P = load_pages(L, tb, t_last);
         if (PREFETCH && tb < it.t_end)
-            load_tile<RB, PAGED, APPEND>(T0, L, tb, t_last, P, kStep);
+            load_tile<RB, NA, PAGED, APPEND, kRange>(T0, L, tb, t_last, P, kStep);
     };
 
     DevItem it = scalar_load_item(items, second ? (int)blockIdx.x - n0 : (int)blockIdx.x, grow);
@@ -526,7 +592,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
     LaneConst L;
     u32x4 qB[RB / 64];
     int tb;
-    TileRegs<RB> T0;
+    TileRegs<RB, NA> T0;
     PagePair P = {0, 0};
     int n_ring = 0;  // rows held in the result ring (head-major mapping only)
     begin_segment(it, L, qB, tb, T0, P);
@@ -546,13 +612,13 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
 
         if (!PREFETCH) {
             for (; tb < it.t_end; tb += kStep) {
-                TileRegs<RB> T;
-                load_tile<RB, PAGED, APPEND>(T, L, tb, t_last, P, kStep);
+                TileRegs<RB, NA> T;
+                load_tile<RB, NA, PAGED, APPEND, kRange>(T, L, tb, t_last, P, kStep);
                 compute_tile<DT, D>(T, qB, tb, L.grp, it.t_end, scale_log2e, m, l, acc);
             }
         } else if (tb < it.t_end) {  // T0 already holds (the loads of) step tb
             {
-                TileRegs<RB> T1;
+                TileRegs<RB, NA> T1;
                 for (;;) {
                     const int tb1 = tb + kStep;
                     const bool more1 = tb1 < it.t_end;
@@ -561,7 +627,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
                     if (HPW)
                         __builtin_amdgcn_s_barrier();
                     if (more1)
-                        load_tile<RB, PAGED, APPEND>(T1, L, tb1, t_last, P, kStep);
+                        load_tile<RB, NA, PAGED, APPEND>(T1, L, tb1, t_last, P, kStep);
                     compute_tile<DT, D>(T0, qB, tb, L.grp, it.t_end, scale_log2e, m, l, acc);
                     if (!more1)
                         break;
@@ -570,7 +636,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
                     if (HPW)
                         __builtin_amdgcn_s_barrier();
                     if (more2)
-                        load_tile<RB, PAGED, APPEND>(T0, L, tb2, t_last, P, kStep);
+                        load_tile<RB, NA, PAGED, APPEND>(T0, L, tb2, t_last, P, kStep);
                     compute_tile<DT, D>(T1, qB, tb1, L.grp, it.t_end, scale_log2e, m, l, acc);
                     if (!more2)
                         break;
@@ -579,7 +645,12 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
             }
         }
 
-        const int grp = L.grp, r = L.r;
+        // (half steps and 512-byte rows: what only the epilogue needs of the lane and thread index is computed there, not held across
+        // the streaming loop, which opaque copies of them see to)
+        int late_lane = lane;
+        if constexpr (kHalf)
+            asm("" : "+v"(late_lane));
+        const int grp = late_lane >> 4, r = late_lane & 15;
         // the two-per-CU kernel has the registers to let the next segment's loads fly during the epilogue below
         if (PREFETCH && it.next >= 0)
             begin_segment(nx, L, qB, tb, T0, P);
@@ -671,10 +742,8 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
         }
 
         // ---- ... and the four waves (LDS) ----
-        // (512-byte rows have no register to spare: their epilogue addresses are computed here, not held across the
-        // streaming loop, which an opaque copy of the thread index sees to)
         int tid = threadIdx.x;
-        if constexpr (RB == 512)
+        if constexpr (NA == 1)
             asm("" : "+v"(tid));
         const int head = kQuad ? r & (kQuadHeads - 1) : r;  // the query head of the lane's results
         if (grp == 0) {  // (4x4 blocks: entries past head 3 are copies, never read)

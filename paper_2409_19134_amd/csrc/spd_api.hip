@@ -47,6 +47,7 @@ struct CachedSchedule {
     std::vector<uint8_t> key;
     int64_t n_items = 0, n_slots = 0, n_segments = 0;
     int max_chunks = 0;      // chunks of the row that has the most
+    int64_t steps = 0;       // 32-token steps of one KV head
     int hpw = 0;             // 0, the KV heads per workgroup of the head-per-wave kernel the pieces are for, or kWholeRows
     int n_split_rows = 0;    // rows with several chunks: CombineRow[n_split_rows] follows the items (whole rows: the launch order)
     size_t off_rows = 0, off_info = 0;
@@ -170,6 +171,7 @@ struct ScheduleBlob {
     int64_t n_segments = 0;   // segments with tokens
     int n_split_rows = 0;
     int max_chunks = 0;
+    int64_t steps = 0;        // 32-token steps of one KV head
 };
 
 void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, const Tuning &tune, ScheduleBlob &B)
@@ -205,6 +207,7 @@ void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, co
     B.n_slots = S.n_slots;
     B.n_segments = T.n_segments;
     B.n_split_rows = (int)T.split_rows.size();
+    B.steps = total_steps(v);
     for (const RowInfo &r : T.row_info)
         B.max_chunks = std::max(B.max_chunks, (int)r.n_chunks);
 }
@@ -339,6 +342,7 @@ int get_schedule(spd_ctx *ctx, Owner &own, const spd_shape *s, const spd_kv_view
     e.n_segments = B.n_segments;
     e.n_split_rows = B.n_split_rows;
     e.max_chunks = B.max_chunks;
+    e.steps = B.steps;
     e.off_rows = B.off_rows;
     e.off_info = B.off_info;
     *out = &e;
@@ -519,6 +523,14 @@ bool with_bool(bool b, F &&f)
     return b ? f(std::true_type()) : f(std::false_type());
 }
 
+constexpr int64_t kHalfStepsMinSteps = 12;  // 32-token steps of a piece, see launch_partial
+
+// Whether offsets inside a step of this view's rows fit a buffer descriptor's 32 bits.
+bool token_strides_below_limit(const spd_shape *s, const spd_kv_view *v)
+{
+    return v->token_stride < spd::kBufferStrideLimit / elt_size(s->dtype);
+}
+
 struct MfmaLaunch {
     dim3 grid, block;
     uint32_t lds;
@@ -529,18 +541,22 @@ struct MfmaLaunch {
 
 // The kernel instances that exist: the head-per-wave mapping always keeps two steps in flight, fp32 always one (and
 // has no head-per-wave mapping), rows of 128 bytes always two.
-template <int DT, int D, bool PREFETCH, bool HPW>
+template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 constexpr bool mfma_instance_exists()
 {
-    constexpr bool f32 = DT == SPD_F32 || DT == spd::kF32Quad;
-    constexpr int RB = D * (f32 ? 4 : 2);
+    constexpr int RB = D * spd::Elt<DT>::kBytes;
+    constexpr bool f32 = spd::Elt<DT>::kBytes == 4;
+    if (spd::half_steps(DT))
+        return D == 128 && !PREFETCH && !HPW;
+    if (DT == spd::kF32QuadRange)
+        return D == 128 && !PREFETCH && !HPW && !PAGED && !APPEND;
     return !(HPW && !PREFETCH) && !(f32 && (HPW || PREFETCH)) && !(RB == 128 && !PREFETCH) && !(DT == spd::kF32Quad && D != 128);
 }
 
 template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 bool launch_mfma(const MfmaLaunch &L)
 {
-    if constexpr (mfma_instance_exists<DT, D, PREFETCH, HPW>()) {
+    if constexpr (mfma_instance_exists<DT, D, PAGED, PREFETCH, HPW, APPEND>()) {
         hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT, D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
                               L.stream, L.ev0, L.ev1, 0, L.args);
         return true;
@@ -626,8 +642,19 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     // accumulators (32 registers more than the kernel has), and the 16x16 tile is fuller there.  With 64 channels the
     // kernel is HBM-bound either way (16 users of 8192-32768 tokens 204.4 / 203.5 us), and on calls of one or two users,
     // which the host's launches bound, the shorter kernel only drains the queue (7.5 / 8.1 us).
-    const int dt_code = f32 && D == 128 && G <= spd::kQuadHeads ? spd::kF32Quad : s->dtype;
-    const bool ok = with_value<SPD_F32, SPD_BF16, SPD_F16, spd::kF32Quad>(dt_code, [&](auto dt) {
+    int dt_code = f32 && D == 128 && G <= spd::kQuadHeads ? spd::kF32Quad : s->dtype;
+    // The kernel's other forms (see partial_mfma.hpp).  Half steps where one step is in flight and pieces are long enough to have a few
+    // rounds - 12 steps on average; at 8 it is even (8 users of 512-4096 tokens 21.0 / 21.0, 1000-3000 18.7 / 18.8), and chunks of one
+    // step per wave lose (1 user of 500 8.2 / 8.5) - end few rows (two of three pieces one row: 64 users of mixed lengths, two rows a
+    // piece, 103.6 / 106.9; with the result ring 451.6 / 455.5) and read rows that lie end to end (token-major 36.4 / 36.9).
+    const bool range = v0->block_size == 0 && !nt.k && token_strides_below_limit(s, v0) && (!v1 || token_strides_below_limit(s, v1));
+    const bool end_to_end = v0->token_stride == D && (!v1 || v1->token_stride == D);
+    if (dt_code == spd::kF32Quad && range)
+        dt_code = spd::kF32QuadRange;
+    if (!f32 && D == 128 && !hpw && !prefetch && ctx->steps_in_flight < 0 && ring_rows == 0 && end_to_end && n0 > 0 &&
+        e0->steps * s->n_kv_heads >= kHalfStepsMinSteps * n0 && 2 * segments < 3 * (n0 + n1))
+        dt_code = s->dtype == SPD_BF16 ? spd::kBf16Half : spd::kF16Half;
+    const bool ok = with_value<SPD_F32, SPD_BF16, SPD_F16, spd::kF32Quad, spd::kBf16Half, spd::kF16Half, spd::kF32QuadRange>(dt_code, [&](auto dt) {
         return with_value<64, 128>(D, [&](auto d) {
             return with_bool(v0->block_size != 0, [&](auto paged) {
                 return with_bool(prefetch, [&](auto pf) {
@@ -1462,6 +1489,7 @@ try {
         e[w].hpw = hpw;
         e[w].n_split_rows = B[w].n_split_rows;
         e[w].max_chunks = B[w].max_chunks;
+        e[w].steps = B[w].steps;
         e[w].off_rows = B[w].off_rows;
         e[w].off_info = B[w].off_info;
         sp[w].part_lse = reinterpret_cast<float *>(st.ptr + kStaticOffLse) + (size_t)w * kStaticLseFloats;

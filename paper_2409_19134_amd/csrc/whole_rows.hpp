@@ -207,7 +207,7 @@ template <int DT, int D, bool PAGED, bool APPEND>
 __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsArgs A)
 {
     constexpr int RB = D * Elt<DT>::kBytes;
-    constexpr int kTile = step_tokens(RB);
+    constexpr int NA = step_tiles(RB), kTile = step_tokens(RB);
     constexpr bool kTwo = RB == 128;  // two steps in flight where a step is 8 KB
     constexpr bool kQuad = DT == kF32Quad;
     constexpr int CP = D / 16;
@@ -309,40 +309,40 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
                 // the first step in front of the loop or in it: which of the two the compiler schedules better differs (append, 1
                 // user of 400 + 100 tokens 7.4 / 8.0 us contiguous, 8.6 / 8.2 paged; without the append, tiny fp32 5.0 / 4.9)
                 if constexpr (APPEND && !PAGED) {
-                    TileRegs<RB> T;
-                    load_tile<RB, PAGED, APPEND>(T, L, tb, t_last, P, kTile);
+                    TileRegs<RB, NA> T;
+                    load_tile<RB, NA, PAGED, APPEND>(T, L, tb, t_last, P, kTile);
                     store_new_token();
                     for (;;) {
                         compute_tile<DT, D>(T, qB, tb, L.grp, t_end, A.scale_log2e, m, l, acc);
                         tb += kTile;
                         if (tb >= tb_end)
                             break;
-                        load_tile<RB, PAGED, APPEND>(T, L, tb, t_last, P, kTile);
+                        load_tile<RB, NA, PAGED, APPEND>(T, L, tb, t_last, P, kTile);
                     }
                 } else {
                     for (; tb < tb_end; tb += kTile) {
-                        TileRegs<RB> T;
-                        load_tile<RB, PAGED, APPEND>(T, L, tb, t_last, P, kTile);
+                        TileRegs<RB, NA> T;
+                        load_tile<RB, NA, PAGED, APPEND>(T, L, tb, t_last, P, kTile);
                         if (APPEND && tb == b * kTile)
                             store_new_token();
                         compute_tile<DT, D>(T, qB, tb, L.grp, t_end, A.scale_log2e, m, l, acc);
                     }
                 }
             } else {
-                TileRegs<RB> T0, T1;
-                load_tile<RB, PAGED, APPEND>(T0, L, tb, t_last, P, kTile);
+                TileRegs<RB, NA> T0, T1;
+                load_tile<RB, NA, PAGED, APPEND>(T0, L, tb, t_last, P, kTile);
                 store_new_token();
                 for (;;) {
                     const bool more1 = tb + kTile < tb_end;
                     if (more1)
-                        load_tile<RB, PAGED, APPEND>(T1, L, tb + kTile, t_last, P, kTile);
+                        load_tile<RB, NA, PAGED, APPEND>(T1, L, tb + kTile, t_last, P, kTile);
                     compute_tile<DT, D>(T0, qB, tb, L.grp, t_end, A.scale_log2e, m, l, acc);
                     if (!more1)
                         break;
                     tb += 2 * kTile;
                     const bool more2 = tb < tb_end;
                     if (more2)
-                        load_tile<RB, PAGED, APPEND>(T0, L, tb, t_last, P, kTile);
+                        load_tile<RB, NA, PAGED, APPEND>(T0, L, tb, t_last, P, kTile);
                     compute_tile<DT, D>(T1, qB, tb - kTile, L.grp, t_end, A.scale_log2e, m, l, acc);
                     if (!more2)
                         break;
