@@ -106,7 +106,9 @@ struct Elt<kF32Quad> {
 // 16-token pages 33.7 / 32.7; 12 such users 27.0 / 26.7, 24 48.8 / 48.1; 8 users of 4000-12000 tokens 52.3 / 51.5, 2 of 20000-40000
 // 48.3 / 47.0; two parties 40.7 / 40.1.  In buffer descriptors a lane's offset and a scalar per row are all the addressing there
 // is (VALU cycles of a 32-token step 1400 -> 800): fp32, headline batch, 60.9 / 60.0.
-constexpr int kBf16Half = 4, kF16Half = 5, kF32QuadRange = 6;
+constexpr int kFormStep = 3;  // from a dtype's code to its other form's
+constexpr int kBf16Half = SPD_BF16 + kFormStep, kF16Half = SPD_F16 + kFormStep, kF32QuadRange = kF32Quad + kFormStep;
+constexpr int form_of(int dt) { return dt >= kBf16Half ? 1 : 0; }
 template <>
 struct Elt<kBf16Half> : Elt<SPD_BF16> {};
 template <>
@@ -482,8 +484,7 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 //
 // APPEND = true adds the KV append (the address substitution costs ~1 % when nothing is appended, hence a flag).
 template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
-__global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
-    PartialArgs A)
+__device__ __forceinline__ void partial_mfma(const PartialArgs &A)
 {
     const OwnerArgs &a0 = A.a0, &a1 = A.a1;
     const int n0 = A.n0, Hq = A.Hq, G = A.G;
@@ -830,6 +831,21 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT
         it = nx;
         __syncthreads();  // the LDS staging arrays are reused by the next segment
     }
+}
+
+template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
+__global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
+    PartialArgs A)
+{
+    partial_mfma<DT, D, PAGED, PREFETCH, HPW, APPEND>(A);
+}
+
+// The same for a dtype's other form (FORM = 1, see form_of): in a profile the first argument stays the dtype.
+template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND, int FORM>
+__global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
+    PartialArgs A)
+{
+    partial_mfma<DT + FORM * kFormStep, D, PAGED, PREFETCH, HPW, APPEND>(A);
 }
 
 }  // namespace spd

@@ -556,12 +556,16 @@ constexpr bool mfma_instance_exists()
 template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 bool launch_mfma(const MfmaLaunch &L)
 {
-    if constexpr (mfma_instance_exists<DT, D, PAGED, PREFETCH, HPW, APPEND>()) {
-        hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT, D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
+    if constexpr (!mfma_instance_exists<DT, D, PAGED, PREFETCH, HPW, APPEND>()) {
+        return false;
+    } else if constexpr (spd::form_of(DT) != 0) {
+        hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT - spd::kFormStep, D, PAGED, PREFETCH, HPW, APPEND, 1>), L.grid, L.block, L.lds,
                               L.stream, L.ev0, L.ev1, 0, L.args);
         return true;
     } else {
-        return false;
+        hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT, D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
+                              L.stream, L.ev0, L.ev1, 0, L.args);
+        return true;
     }
 }
 

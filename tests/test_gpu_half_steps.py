@@ -1,5 +1,5 @@
 """The streaming kernel's forms for long pieces and for fp32 rows read through buffer descriptors: 16-bit rows in 16-token steps
-(dtype codes 4 and 5), fp32 on 4x4 matrix blocks (6).  Against the fp64 oracle at lengths around their tiles, in the storage
+(form 1 of dtypes 1 and 2), fp32 on 4x4 matrix blocks (of 3).  Against the fp64 oracle at lengths around their tiles, in the storage
 modes and with the append; the tolerances are the parity tests' (sums of the same values in another order)."""
 import copy
 
@@ -25,6 +25,12 @@ def ctx():
     c.close()
 
 
+def _ran(ctx, code):
+    """code: the kernel's dtype, "+" behind it for the dtype's other form."""
+    name = ctx.spd_last_kernel_name()
+    assert name.startswith(f"partial_mfma_kernel<{code[0]}, 128, ") and name.endswith(", 1>") == code.endswith("+"), name
+
+
 def _nan_behind(side):
     """What lies behind a user's last token in its head-major buffer is never part of a result."""
     for u, n in enumerate(side.lens):
@@ -39,8 +45,9 @@ LENS = [([3072], [0]), ([4081], [1]), ([4095], [15]), ([4096], [16]), ([4097], [
 
 @pytest.mark.parametrize("lp,lo", LENS)
 @pytest.mark.parametrize("dtype,code,G,storage", [
-    (torch.bfloat16, 4, 1, "hnd"), (torch.bfloat16, 4, 4, "hnd_exact"), (torch.bfloat16, 4, 16, "paged"), (torch.float16, 5, 3, "hnd"),
-    (torch.float16, 5, 2, "paged"), (torch.float32, 6, 4, "hnd"), (torch.float32, 6, 1, "hnd_exact"), (torch.float32, 3, 2, "paged")])
+    (torch.bfloat16, "1+", 1, "hnd"), (torch.bfloat16, "1+", 4, "hnd_exact"), (torch.bfloat16, "1+", 16, "paged"),
+    (torch.float16, "2+", 3, "hnd"), (torch.float16, "2+", 2, "paged"), (torch.float32, "3+", 4, "hnd"), (torch.float32, "3+", 1, "hnd_exact"),
+    (torch.float32, "3", 2, "paged")])
 def test_forms_at_tile_edges(ctx, lp, lo, dtype, code, G, storage):
     Hkv = 32
     wl = workloads.random_case(311, dtype, len(lp), Hkv * G, Hkv, 128, lp, lo, device=DEV, layout="hnd" if storage == "paged" else storage,
@@ -51,11 +58,11 @@ def test_forms_at_tile_edges(ctx, lp, lo, dtype, code, G, storage):
         _nan_behind(wl.private)
         _nan_behind(wl.public)
     _check_one(ctx, wl, want, None, TOL[dtype], True)
-    assert ctx.spd_last_kernel_name().startswith(f"partial_mfma_kernel<{code}, 128, "), ctx.spd_last_kernel_name()
+    _ran(ctx, code)
 
 
 @pytest.mark.parametrize("lo", [[1, 16], [17, 15], [700, 32]])
-@pytest.mark.parametrize("dtype,code,storage", [(torch.bfloat16, 4, "hnd"), (torch.float16, 5, "paged"), (torch.float32, 3, "hnd")])
+@pytest.mark.parametrize("dtype,code,storage", [(torch.bfloat16, "1+", "hnd"), (torch.float16, "2+", "paged"), (torch.float32, "3", "hnd")])
 def test_append(ctx, lo, dtype, code, storage):
     import paper_2409_19134_amd as spd
     Hkv, U = 32, 2
@@ -69,7 +76,7 @@ def test_append(ctx, lo, dtype, code, storage):
     step = spd.DecodeStep.from_workload(ctx, wl)
     step.run_fused(wl.q, k_new=k_new, v_new=v_new)
     torch.cuda.synchronize()
-    assert ctx.spd_last_kernel_name().startswith(f"partial_mfma_kernel<{code}, 128, "), ctx.spd_last_kernel_name()
+    _ran(ctx, code)
     Y, _ = orc.attention(orc.from_workload(want))
     assert maxerr(step.y, Y) <= TOL[dtype]
     for a, b in zip((wl.public.k_pool, wl.public.v_pool) if storage == "paged" else (*wl.public.k, *wl.public.v),
