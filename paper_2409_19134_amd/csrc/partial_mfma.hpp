@@ -483,9 +483,15 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 // a token range of one (user, KV head) row and its four waves take interleaved steps.
 //
 // APPEND = true adds the KV append (the address substitution costs ~1 % when nothing is appended, hence a flag).
-template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
-__device__ __forceinline__ void partial_mfma(const PartialArgs &A)
+// CHANNELS = -D is the dtype's other form (see form_of): so written, a profile's first argument stays the dtype and the other
+// instances' names what they were.  (A body shared by two kernel templates costs registers: workload 5 +3 %.)
+template <int DTYPE, int CHANNELS, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
+__global__ __launch_bounds__(HPW ? 512 : kThreads,
+                             mfma_waves_per_simd((CHANNELS < 0 ? -CHANNELS : CHANNELS) * Elt<DTYPE>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
+    PartialArgs A)
 {
+    constexpr int D = CHANNELS < 0 ? -CHANNELS : CHANNELS;
+    constexpr int DT = CHANNELS < 0 ? DTYPE + kFormStep : DTYPE;
     const OwnerArgs &a0 = A.a0, &a1 = A.a1;
     const int n0 = A.n0, Hq = A.Hq, G = A.G;
     const char *__restrict__ q = A.q;
@@ -831,21 +837,6 @@ __device__ __forceinline__ void partial_mfma(const PartialArgs &A)
         it = nx;
         __syncthreads();  // the LDS staging arrays are reused by the next segment
     }
-}
-
-template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
-__global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
-    PartialArgs A)
-{
-    partial_mfma<DT, D, PAGED, PREFETCH, HPW, APPEND>(A);
-}
-
-// The same for a dtype's other form (FORM = 1, see form_of): in a profile the first argument stays the dtype.
-template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND, int FORM>
-__global__ __launch_bounds__(HPW ? 512 : kThreads, mfma_waves_per_simd(D *Elt<DT>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
-    PartialArgs A)
-{
-    partial_mfma<DT + FORM * kFormStep, D, PAGED, PREFETCH, HPW, APPEND>(A);
 }
 
 }  // namespace spd

@@ -1,5 +1,5 @@
 """The streaming kernel's forms for long pieces and for fp32 rows read through buffer descriptors: 16-bit rows in 16-token steps
-(form 1 of dtypes 1 and 2), fp32 on 4x4 matrix blocks (of 3).  Against the fp64 oracle at lengths around their tiles, in the storage
+(-128 channels of dtypes 1 and 2 in the kernel's name), fp32 on 4x4 matrix blocks (of 3).  Against the fp64 oracle at lengths around their tiles, in the storage
 modes and with the append; the tolerances are the parity tests' (sums of the same values in another order)."""
 import copy
 
@@ -28,7 +28,7 @@ def ctx():
 def _ran(ctx, code):
     """code: the kernel's dtype, "+" behind it for the dtype's other form."""
     name = ctx.spd_last_kernel_name()
-    assert name.startswith(f"partial_mfma_kernel<{code[0]}, 128, ") and name.endswith(", 1>") == code.endswith("+"), name
+    assert name.startswith(f"partial_mfma_kernel<{code[0]}, {-128 if code.endswith('+') else 128}, "), name
 
 
 def _nan_behind(side):
@@ -82,6 +82,16 @@ def test_append(ctx, lo, dtype, code, storage):
     for a, b in zip((wl.public.k_pool, wl.public.v_pool) if storage == "paged" else (*wl.public.k, *wl.public.v),
                     (want.public.k_pool, want.public.v_pool) if storage == "paged" else (*want.public.k, *want.public.v)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,page,code", [(12288, 16, "1+"), (12544, 16, "1"), (12544, 0, "1+")])
+def test_long_pieces_of_one_owner(ctx, n, page, code):
+    """48 and 49 steps a piece: pages leave the 16-token form there, contiguous rows do not."""
+    wl = workloads.random_case(313, torch.bfloat16, 1, 32, 32, 128, [n], [5], device=DEV, layout="hnd", paged=bool(page))
+    step, _ = _check_one(ctx, wl, _oracle_outputs(orc.from_workload(wl), None), None, TOL[wl.dtype], False)
+    ctx.spd_partial_attn_private(step.shape, wl.q, step.private, step.a_in, step.lse_in)
+    torch.cuda.synchronize()
+    _ran(ctx, code)
 
 
 def test_strides_past_the_descriptors_range():
