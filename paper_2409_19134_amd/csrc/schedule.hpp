@@ -16,7 +16,9 @@ constexpr int kShortPieceSteps = 64;  // 32-token steps per piece up to which Tu
 // (32-token steps * KV heads) per CU from which the head-per-wave mapping is used, and from which its workgroups take
 // eight heads instead of four (see head_per_wave_choice in spd_api.hip)
 constexpr int kHeadPerWaveMinHeadSteps = 65;
+constexpr int kHeadPerWaveMinHeadSteps64 = 40, kHeadPerWaveMinHeadSteps64OneOwner = 32, kHeadPerWaveMinHeadStepsOneOwner = 41;
 constexpr int kHeadPerWaveWideHeadSteps = 900;
+constexpr int kHeadPerWaveWideHeadStepsMany = 340;  // more than eight KV heads
 
 // What shapes a schedule besides the lengths.  A context starts from the defaults below, replaced by SPD_* variables
 // of the environment that spd_create finds set (tuning_from_env), and spd_set_option changes them per context; all

@@ -133,31 +133,65 @@ int64_t total_steps(const spd_kv_view *v)
     return T;
 }
 
+// (32-token steps * KV heads) per CU of a call: what fixes the crossovers between the mappings for 8 to 32 KV heads.  Fewer than
+// eight heads count as eight (us per fused step, 4 heads of 64, head-major / four heads per workgroup: 24 users of workload 2's
+// lengths 19.0 / 20.8, 32 users 24.0 / 23.5).
+int64_t head_steps_per_cu(const spd_ctx *ctx, const spd_shape *s, int64_t steps)
+{
+    return steps * std::max(8, s->n_kv_heads) / std::max(1, ctx->n_cus);
+}
+
+// What a choice of mapping is for: a call over one owner, a fused step, or a fused step whose tables and partials have to fit
+// the library's fixed array.  The last keeps to the lines that its limits have been stated with: a smaller line would refuse
+// steps that fit (an item and its partials per group of heads).
+enum class MappingFor { kOneOwner, kFusedStep, kFixedArray };
+
 // KV heads (waves) per workgroup of the head-per-wave mapping for a launch of `steps` 32-token steps per KV head, or 0
 // for the head-major mapping.  The mapping pays once the launch is bandwidth-bound, i.e. every workgroup gets several
 // steps; below that the four interleaving waves of the head-major mapping finish a short piece sooner.  Workgroups of
 // four heads (two or three per CU, 1 KB of every token) take over from ~280 MB of K/V; workgroups of eight (one per
-// CU, a token's whole 2 KB with eight KV heads) are ahead from a few GB of long rows (workload 3: 1.2 %), and for more
-// than eight KV heads.  Measured (256 CUs, 8 KV heads, token-major, us per fused step; head-major / four / eight):
-// workload 2's lengths with 16 users 35.5 / 40.2 / 48.1, 24 users 46.8 / 50.0 / -, 32 users 63.2 / 59.5 / 66.5,
-// 64 users 115.7 / 102.5 / 110.0; workload 4 - / 445.5 / 452.9; workload 3 - / 783 / 774.  The bounds are on
-// steps * KV heads per CU, which is what fixed the earlier crossovers for 16 and 32 KV heads (~330 MB each).
+// CU, a token's whole 2 KB with eight KV heads) are ahead from a few GB of long rows (workload 3: 1.2 %).
+// Measured (256 CUs, 8 KV heads, token-major, us per fused step; head-major / four / eight):
+// workload 2's lengths with 16 users 36.3 / 39.3 / 48.1, 24 users 51.9 / 51.9 / -, 32 users 63.2 / 59.5 / 66.5,
+// 64 users 115.7 / 102.5 / 110.0; workload 4 - / 445.5 / 452.9; workload 3 - / 783 / 774.
+// The line lies lower, in rows enough that a row's pieces stay few (80 on 256 CUs: each piece costs the closing kernel a partial
+// per head; 8 users of <= 6000 tokens, D = 64, 24.0 head-major against 27.1, 10 users of <= 5000 24.7 / 24.1),
+//   - for heads of 64 values, where a row of one head is only 128 bytes of every token's (fused, workload 2's lengths, us
+//     head-major / four: 12 users 20.4 / 24.0, 16 users 24.6 / 24.1, 20 users 28.8 / 26.9, 24 users 34.0 / 31.0; one owner: 12
+//     users 19.0 / 19.5, 14 users 20.5 / 19.6, 16 users 22.2 / 20.0, 24 users 31.0 / 27.6);
+//   - for one owner with heads of 128 and up to four query heads per KV head (16 users 31.7 / 31.3, 18 users 36.4 / 34.9, 22 users
+//     41.8 / 39.7; 32 KV heads, eight per workgroup: 4 users 34.2 / 35.5, 6 users 49.6 / 46.5; eight query heads, 20 users
+//     39.6 / 40.5).
+// More than eight KV heads, 8-head against 4-head workgroups: a fused step below ~340 head steps per CU is ahead with four, whose
+// pieces are twice as many (32 heads of 128, 8 / 16 / 18 / 24 users of workload 2's lengths 73.1 / 65.6, 115.0 / 114.3, 137.1 /
+// 133.4, 177.6 / 170.1; 16 heads, 16 users 69.6 / 63.5, 32 users 121.5 / 117.0; 12 heads, 6-head workgroups, 26 users 88.5 / 79.5; 32
+// heads of 64, 8 users 42.1 / 37.7); above it (32 heads of 128, 128 users of <= 1280 tokens 254.0 / 256.4, 64 users 409.4 / 414.6)
+// and for one owner (8 users 58.9 / 60.9, 16 users 99.8 / 101.7) the eight are.
 // The option SPD_OPT_HEAD_PER_WAVE overrides the rule: 0 never, 1 whenever the layout allows (group size by the rule),
 // 2..8 that many heads per workgroup (the largest divisor of the KV head count up to it): for tests and measurements.
-int head_per_wave_choice(const spd_ctx *ctx, const spd_shape *s, int64_t steps)
+int head_per_wave_choice(const spd_ctx *ctx, const spd_shape *s, int64_t steps, int n_users, MappingFor what)
 {
     const int opt = ctx->head_per_wave;
     if (opt == 0)
         return 0;
-    const int64_t head_steps = steps * std::max(8, s->n_kv_heads) / std::max(1, ctx->n_cus);
-    if (opt < 0 && head_steps < kHeadPerWaveMinHeadSteps)
+    const int Hkv = s->n_kv_heads;
+    const int64_t head_steps = head_steps_per_cu(ctx, s, steps);
+    int line = kHeadPerWaveMinHeadSteps;
+    if (what != MappingFor::kFixedArray && Hkv >= 8 && 16 * (int64_t)n_users * Hkv >= 5 * (int64_t)ctx->n_cus) {
+        if (s->head_dim == 64)
+            line = what == MappingFor::kOneOwner ? kHeadPerWaveMinHeadSteps64OneOwner : kHeadPerWaveMinHeadSteps64;
+        else if (s->head_dim == 128 && what == MappingFor::kOneOwner && s->n_q_heads <= 4 * Hkv)
+            line = kHeadPerWaveMinHeadStepsOneOwner;
+    }
+    if (opt < 0 && head_steps < line)
         return 0;
     int most = 8;
     if (opt >= 2)
         most = opt;
-    else if (head_steps < kHeadPerWaveWideHeadSteps && s->n_kv_heads <= 8)
+    else if (Hkv <= 8 ? head_steps < kHeadPerWaveWideHeadSteps
+                      : what == MappingFor::kFusedStep && Hkv % 4 == 0 && head_steps < kHeadPerWaveWideHeadStepsMany)
         most = 4;
-    const int w = head_per_wave_waves(s->n_kv_heads, most);
+    const int w = head_per_wave_waves(Hkv, most);
     return w >= 2 ? w : 0;
 }
 
@@ -429,7 +463,8 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
     load.f32 = s->dtype == SPD_F32;
     load.always = always;
     const bool token_major = head_per_wave_layout(s, v0) && (!v1 || head_per_wave_layout(s, v1));
-    const int waves = whole_rows_choice(load, [&](int64_t steps) { return token_major && head_per_wave_choice(ctx, s, steps) != 0; });
+    const int waves = whole_rows_choice(
+        load, [&](int64_t steps) { return token_major && head_steps_per_cu(ctx, s, steps) >= kHeadPerWaveMinHeadSteps; });
     return std::min(waves, spd::rows_waves_that_fit(s->head_dim, s->n_q_heads / s->n_kv_heads));
 }
 
@@ -445,7 +480,7 @@ int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const spd_kv_vi
     // on its own
     int hpw = mapping;
     if (hpw < 0)
-        hpw = head_per_wave_layout(s, v) ? head_per_wave_choice(ctx, s, total_steps(v)) : 0;
+        hpw = head_per_wave_layout(s, v) ? head_per_wave_choice(ctx, s, total_steps(v), v->n_users, MappingFor::kOneOwner) : 0;
     // tune: the fused step's; none for a call that serves one owner alone
     const int rs = get_schedule(ctx, own, s, v, hpw, tune ? *tune : hpw == kWholeRows ? ctx->tuning : standalone_tuning(ctx, s, v, hpw),
                                 stream, build, e);
@@ -950,11 +985,11 @@ int validate_decode_step(spd_ctx *ctx, const spd_shape *shape, const void *q, co
 
 // Both owners of a fused step share one launch, so they share the mapping: head per wave if both layouts allow it and
 // the two together are bandwidth-bound (the value is the KV heads per workgroup, 0 for the head-major mapping).
-int split_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_view *priv, const spd_kv_view *pub)
+int split_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_view *priv, const spd_kv_view *pub, MappingFor what)
 {
     if (!head_per_wave_layout(shape, priv) || !head_per_wave_layout(shape, pub))
         return 0;
-    return head_per_wave_choice(ctx, shape, total_steps(priv) + total_steps(pub));
+    return head_per_wave_choice(ctx, shape, total_steps(priv) + total_steps(pub), priv->n_users, what);
 }
 
 // Both owners of a fused step also share the device: if each would cut its rows into a full resident round of equal
@@ -1409,7 +1444,7 @@ try {
     for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {  // see kNotRemembered
         ctx->schedule_hits = hits;  // one owner's schedule found in a try that the other's absence ended does not count
         waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, shape, priv, pub, true);
-        const int hpw = waves ? kWholeRows : split_step_mapping(ctx, shape, priv, pub);
+        const int hpw = waves ? kWholeRows : split_step_mapping(ctx, shape, priv, pub, MappingFor::kFusedStep);
         const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);
         rc = prepare_partial(ctx, 0, shape, priv, hpw, &tune, stream, t == kTries - 1, &ep);
         if (rc == SPD_OK)
@@ -1443,7 +1478,7 @@ try {
     if (!st.ptr)
         return SPD_ERR_WORKSPACE;
     int waves = whole_rows_waves(ctx, shape, priv, pub);
-    const int split = split_step_mapping(ctx, shape, priv, pub);
+    const int split = split_step_mapping(ctx, shape, priv, pub, MappingFor::kFixedArray);
     // The tables of rows taken whole can be larger than the split schedule's - token-major storage has an item per group of
     // four or eight heads there, one per head here: what the array has no room for stays split.
     if (whole_rows_bytes(priv->n_users, shape->n_kv_heads) > kStaticSchedBytes)
