@@ -68,7 +68,8 @@ __device__ __forceinline__ V stream_load(const char *p)
 __device__ __forceinline__ u32x4 stream_load16(const char *p) { return stream_load<u32x4>(p); }
 
 // The same through a buffer descriptor over a row's tokens from tb to t_last, its last (rows of `bytes` bytes): a lane's offset
-// from token tb, and a uniform one.  What lies past the last token's row is zero; so is everything if tb does.
+// from token tb.  What lies past the last token's row is zero; so is everything if tb does.  All of an offset is in the lane's
+// part (and the instruction's immediate): those are what the range check is specified to cover, the scalar part is not.
 typedef __amdgpu_buffer_rsrc_t row_rsrc;
 constexpr int64_t kBufferStrideLimit = 1 << 27;  // bytes from token to token: 16 of them and a row stay inside 32 bits
 __device__ __forceinline__ row_rsrc row_buffer(const char *row, int tb, int t_last, int64_t token_stride, int bytes)
@@ -78,13 +79,9 @@ __device__ __forceinline__ row_rsrc row_buffer(const char *row, int tb, int t_la
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row + (int64_t)tb * token_stride), 0, (int)n, 0x00020000);  // raw, no swizzle
 }
 constexpr int kBufferNonTemporal = 2;
-__device__ __forceinline__ u32x4 stream_load16(row_rsrc b, unsigned lane, unsigned at)
+__device__ __forceinline__ u32x4 stream_load16(row_rsrc b, unsigned at)
 {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, lane, at, kBufferNonTemporal));
-}
-__device__ __forceinline__ u32x2 stream_load8(row_rsrc b, unsigned lane, unsigned at)
-{
-    return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(b, lane, at, kBufferNonTemporal));
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, kBufferNonTemporal));
 }
 
 // Wave-uniform values (work item fields arrive through vector loads): tell the compiler, so that address arithmetic

@@ -158,14 +158,13 @@ template <>
 struct VRow<128> {
     u32x2 w;
     __device__ __forceinline__ void load(const char *p) { w = stream_load<u32x2>(p); }
-    __device__ __forceinline__ void load(row_rsrc b, unsigned lane, unsigned at) { w = stream_load8(b, lane, at); }
     __device__ __forceinline__ unsigned dword(int i) const { return w[i]; }
 };
 template <>
 struct VRow<256> {
     u32x4 w;
     __device__ __forceinline__ void load(const char *p) { w = stream_load16(p); }
-    __device__ __forceinline__ void load(row_rsrc b, unsigned lane, unsigned at) { w = stream_load16(b, lane, at); }
+    __device__ __forceinline__ void load(row_rsrc b, unsigned at) { w = stream_load16(b, at); }
     __device__ __forceinline__ unsigned dword(int i) const { return w[i]; }
 };
 template <>
@@ -176,10 +175,10 @@ struct VRow<512> {
         w0 = stream_load16(p);
         w1 = stream_load16(p + 256);
     }
-    __device__ __forceinline__ void load(row_rsrc b, unsigned lane, unsigned at)
+    __device__ __forceinline__ void load(row_rsrc b, unsigned at)
     {
-        w0 = stream_load16(b, lane, at);
-        w1 = stream_load16(b, lane + 256, at);
+        w0 = stream_load16(b, at);
+        w1 = stream_load16(b, at + 256);
     }
     __device__ __forceinline__ unsigned dword(int i) const { return i < 4 ? w0[i] : w1[i - 4]; }  // i is a constant
 };
@@ -246,6 +245,7 @@ __device__ __forceinline__ void load_tile(TileRegs<RB, NA> &T, const LaneConst &
     constexpr int NE = 4 * NA;
     if constexpr (RANGE) {
         static_assert(!PAGED && !APPEND);
+        // (the whole offset is the lane's, see row_buffer: 3 registers more than with scalar parts for the tokens, fp32 6, and the same time)
         const unsigned stride = (unsigned)L.token_stride;
         const unsigned k_lane = (L.kt * NE + (L.r & 3)) * stride + L.kc * 16, v_lane = L.grp * NE * stride + L.r * v_lane_bytes(RB);
         const row_rsrc kb = row_buffer(L.k_base, tb, t_last, L.token_stride, RB), vb = row_buffer(L.v_base, tb, t_last, L.token_stride, RB);
@@ -253,10 +253,10 @@ __device__ __forceinline__ void load_tile(TileRegs<RB, NA> &T, const LaneConst &
         for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int kk = 0; kk < RB / 64; ++kk)
-                T.k[a][kk] = stream_load16(kb, k_lane + kk * 64, a * 4 * stride);
+                T.k[a][kk] = stream_load16(kb, k_lane + a * 4 * stride + kk * 64);
 #pragma unroll
         for (int e = 0; e < NE; ++e)
-            T.v[e].load(vb, v_lane, e * stride);
+            T.v[e].load(vb, v_lane + e * stride);
         __builtin_amdgcn_sched_barrier(0);
         return;
     }
