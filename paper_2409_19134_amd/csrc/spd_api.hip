@@ -560,6 +560,7 @@ bool with_bool(bool b, F &&f)
 
 constexpr int64_t kHalfStepsMinSteps = 12;  // 32-token steps of a piece, see launch_partial
 constexpr int64_t kHalfStepsMaxStepsPaged = 96, kHalfStepsMaxStepsPagedOneOwner = 48;
+constexpr int64_t kHalfStepsSecondShare = 4;  // the second owner's pieces, where they wait for others' ends: at most a quarter of the first's
 
 // Whether offsets inside a step of this view's rows fit a buffer descriptor's 32 bits.
 bool token_strides_below_limit(const spd_shape *s, const spd_kv_view *v)
@@ -687,15 +688,21 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     // rounds - 12 steps on average; at 8 it is even (8 users of 512-4096 tokens 21.0 / 21.0, 1000-3000 18.7 / 18.8), and chunks of one
     // step per wave lose (1 user of 500 8.2 / 8.5) - end few rows (two of three pieces one row: 64 users of mixed lengths, two rows a
     // piece, 103.6 / 106.9; with the result ring 451.6 / 455.5) and read rows that lie end to end (token-major 36.4 / 36.9).
+    // The second owner's pieces, dispatched behind the first's, are short where three per CU don't hold all: the last of them run one
+    // or two to a CU, and of half steps too little is in flight then (us per fused step, 32-token / half steps, at mean lengths of the
+    // second owner's pieces in the first's: 24 users of 2000-4000 tokens, 0.25 64.9 / 63.3, 0.40 70.1 / 71.9, 0.60 78.7 / 84.0; 16 such
+    // 0.26 45.1 / 45.4, 0.42 48.9 / 50.2; in pages, 16 users of 4000-12000, 0.20 103.7 / 101.2, 0.39 116.4 / 126.3; 4000-8000 + 16000-32000,
+    // 4.2 318 / 395).
     // Pages, whose ids every step asks for: up to 48 steps a piece where one owner's three pieces per CU run (us of private calls, fp16
-    // in 64-token pages: 26 steps 55.2 / 54.1, 73 148.4 / 149.3, 80 162.3 / 164.1, 450 844.5 / 859.8; contiguous rows 834.0 / 825.2),
-    // up to 96 in a fused step (63 steps 94.9 / 94.2, 94 137.6 / 136.6).
+    // in 64-token pages: 26 steps 55.5 / 54.1, 39 78.8 / 78.5, 47 96.2 / 96.3, 57 115.6 / 115.8, 73 148.4 / 149.3, 450 844.5 / 859.8;
+    // contiguous rows 834.0 / 825.2), up to 96 in a fused step (63 steps 94.9 / 94.2, 94 127.3 / 126.2, 187 243.3 / 242.8, 424 528 / 548).
     const bool range = v0->block_size == 0 && !nt.k && token_strides_below_limit(s, v0) && (!v1 || token_strides_below_limit(s, v1));
     const bool end_to_end = v0->token_stride == D && (!v1 || v1->token_stride == D);
     if (dt_code == spd::kF32Quad && range)
         dt_code = spd::kF32QuadRange;
     if (!f32 && D == 128 && !hpw && !prefetch && ctx->steps_in_flight < 0 && ring_rows == 0 && end_to_end && n0 > 0 &&
         e0->steps * s->n_kv_heads >= kHalfStepsMinSteps * n0 && 2 * segments < 3 * (n0 + n1) &&
+        (!e1 || n0 + n1 <= 3 * cus || kHalfStepsSecondShare * e1->steps * n0 <= e0->steps * n1) &&
         (v0->block_size == 0 || e0->steps * s->n_kv_heads <= (e1 ? kHalfStepsMaxStepsPaged : kHalfStepsMaxStepsPagedOneOwner) * n0))
         dt_code = s->dtype == SPD_BF16 ? spd::kBf16Half : spd::kF16Half;
     const bool ok = with_value<SPD_F32, SPD_BF16, SPD_F16, spd::kF32Quad, spd::kBf16Half, spd::kF16Half, spd::kF32QuadRange>(dt_code, [&](auto dt) {

@@ -256,6 +256,57 @@ int main(int argc, char **argv)
             FAIL("a captured step: %lld schedules built, %lld found", (long long)(builds[1] - builds[0]), (long long)(hits[1] - hits[0]));
     }
 
+    // Half steps, both sides of the rule's lines (256 units: an owner's resident round is 512 pieces, 768 where it is alone): tokens per
+    // user of 16 users with eight KV heads unless said otherwise.  The streaming kernel's form is its second argument's sign.
+    struct Form {
+        int users, lp, lo, page;
+        bool one_owner, half;
+        const char *what;
+    };
+    const Form forms[] = {
+        {16, 1536, 1, 0, false, true, "12 steps a piece"},
+        {16, 1504, 1, 0, false, false, "fewer"},
+        {16, 3008, 736, 0, false, true, "1024 pieces, the second owner's a quarter (5.75 in 23.5 steps)"},
+        {16, 3008, 768, 0, false, false, "1024 pieces, the second owner's longer"},
+        {16, 3008, 3008, 0, false, false, "1024 equal pieces"},
+        {16, 6000, 24000, 16, false, false, "the second owner's four times as long, in pages"},
+        {16, 1536, 256, 0, false, true, "768 pieces, all resident, the second owner's a third"},
+        {16, 1536, 320, 0, false, false, "896 pieces, the second owner's more than a quarter"},
+        {16, 12288, 1, 16, false, true, "pages, 96 steps a piece"},
+        {16, 12289, 1, 16, false, false, "pages, more"},
+        {16, 12289, 1, 0, false, true, "the same rows without pages"},
+        {16, 9216, 1, 16, true, true, "pages, one owner, 48 steps a piece"},
+        {16, 9217, 1, 16, true, false, "pages, one owner, more"},
+        {33, 3000, 1, 0, true, true, "744 segments in 512 pieces"},
+        {35, 3000, 1, 0, true, false, "776 segments"},
+    };
+    for (const Form &f : forms) {
+        Step st(SPD_BF16, 32, 8, 128, f.users, f.lp, f.lo, false);
+        for (spd_kv_view &v : st.v)
+            if (f.page) {
+                v.block_size = f.page;
+                v.k_pool = v.v_pool = v.block_table = reinterpret_cast<int32_t *>(st.buf);
+                v.max_blocks = 1 << 20;
+                v.head_stride = (int64_t)f.page * 128;
+                v.block_stride = 8 * v.head_stride;
+            }
+        spd_ctx *ctx = nullptr;  // (one of its own: a view's schedule also serves the same view grown)
+        if (spd_create_(&ctx, 0) != SPD_OK)
+            FAIL("spd_create");
+        launches.clear();
+        const int rc = f.one_owner ? spd_partial_attn_private_(ctx, &st.s, st.buf, &st.v[0], st.buf, st.buf, nullptr)
+                                   : spd_decode_step_(ctx, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf,
+                                                      st.buf, st.buf, st.buf, st.buf, nullptr);
+        bool half = false, streaming = false;
+        for (const Launch &l : launches) {
+            streaming = streaming || l.kernel.find("partial_mfma_kernelILi1E") != std::string::npos;
+            half = half || l.kernel.find("partial_mfma_kernelILi1ELin128E") != std::string::npos;
+        }
+        spd_destroy_(ctx);
+        if (rc != SPD_OK || !streaming || half != f.half)
+            FAIL("half steps, %d users of %d + %d tokens (%s): %d, %d", f.users, f.lp, f.lo, f.what, rc, half);
+    }
+
     // whole rows: no launch asks for more than 64 KB of LDS, the kernel's static part (argv[2], from the compiler's report) and
     // the slots together
     const size_t static_lds = (size_t)std::atoi(argv[2]);
