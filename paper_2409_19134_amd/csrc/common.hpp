@@ -67,11 +67,11 @@ __device__ __forceinline__ V stream_load(const char *p)
 }
 __device__ __forceinline__ u32x4 stream_load16(const char *p) { return stream_load<u32x4>(p); }
 
-// The same through a buffer descriptor over a row's tokens from tb to t_last, its last (rows of `bytes` bytes): a lane's offset
-// from token tb.  What lies past the last token's row is zero; so is everything if tb does.  All of an offset is in the lane's
-// part (and the instruction's immediate): those are what the range check is specified to cover, the scalar part is not.
+// The same through a buffer descriptor over a row's tokens from tb to t_last, its last (rows of `bytes` bytes that lie end to end:
+// offsets inside a step are small): a lane's offset from token tb.  What lies past the last token's row is zero; so is everything if
+// tb does.  All of an offset is in the lane's part (and the instruction's immediate): those are what the range check is specified to
+// cover, the scalar part is not.
 typedef __amdgpu_buffer_rsrc_t row_rsrc;
-constexpr int64_t kBufferStrideLimit = 1 << 27;  // bytes from token to token: 16 of them and a row stay inside 32 bits
 __device__ __forceinline__ row_rsrc row_buffer(const char *row, int tb, int t_last, int64_t token_stride, int bytes)
 {
     const int64_t left = (int64_t)(t_last - tb) * token_stride + bytes;

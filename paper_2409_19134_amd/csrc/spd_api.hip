@@ -562,12 +562,6 @@ constexpr int64_t kHalfStepsMinSteps = 12;  // 32-token steps of a piece, see la
 constexpr int64_t kHalfStepsMaxStepsPaged = 96, kHalfStepsMaxStepsPagedOneOwner = 48;
 constexpr int64_t kHalfStepsSecondShare = 4;  // the second owner's pieces, where they wait for others' ends: at most a quarter of the first's
 
-// Whether offsets inside a step of this view's rows fit a buffer descriptor's 32 bits.
-bool token_strides_below_limit(const spd_shape *s, const spd_kv_view *v)
-{
-    return v->token_stride < spd::kBufferStrideLimit / elt_size(s->dtype);
-}
-
 struct MfmaLaunch {
     dim3 grid, block;
     uint32_t lds;
@@ -696,9 +690,11 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     // Pages, whose ids every step asks for: up to 48 steps a piece where one owner's three pieces per CU run (us of private calls, fp16
     // in 64-token pages: 26 steps 55.5 / 54.1, 39 78.8 / 78.5, 47 96.2 / 96.3, 57 115.6 / 115.8, 73 148.4 / 149.3, 450 844.5 / 859.8;
     // contiguous rows 834.0 / 825.2), up to 96 in a fused step (63 steps 94.9 / 94.2, 94 127.3 / 126.2, 187 243.3 / 242.8, 424 528 / 548).
-    const bool range = v0->block_size == 0 && !nt.k && token_strides_below_limit(s, v0) && (!v1 || token_strides_below_limit(s, v1));
+    // fp32 through descriptors: contiguous rows that lie end to end, without an append (us per fused step, without / with: 4 users of
+    // 1000-3000 + 1000-3000 tokens 33.2 / 31.4, 16 such 90.0 / 88.4, 48 of 64-512 + 1-256 40.3 / 39.8; token-major, 4 such users
+    // 34.2 / 32.6, but 6 40.1 / 40.6, 16 91.0 / 91.4, 20 of 512-4096 + 1-512 74.2 / 74.9).
     const bool end_to_end = v0->token_stride == D && (!v1 || v1->token_stride == D);
-    if (dt_code == spd::kF32Quad && range)
+    if (dt_code == spd::kF32Quad && v0->block_size == 0 && !nt.k && end_to_end)
         dt_code = spd::kF32QuadRange;
     if (!f32 && D == 128 && !hpw && !prefetch && ctx->steps_in_flight < 0 && ring_rows == 0 && end_to_end && n0 > 0 &&
         e0->steps * s->n_kv_heads >= kHalfStepsMinSteps * n0 && 2 * segments < 3 * (n0 + n1) &&

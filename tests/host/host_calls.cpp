@@ -307,6 +307,33 @@ int main(int argc, char **argv)
             FAIL("half steps, %d users of %d + %d tokens (%s): %d, %d", f.users, f.lp, f.lo, f.what, rc, half);
     }
 
+    // fp32 rows through descriptors (the negative second argument of dtype 3): contiguous, end to end and without an append
+    struct Fp32 {
+        int users, stride;
+        bool token_major, append, range;
+    };
+    for (const Fp32 &f : {Fp32{16, 128, false, false, true}, Fp32{48, 128, false, false, true}, Fp32{16, 128, false, true, false},
+                          Fp32{16, 1024, true, false, false}, Fp32{16, 132, false, false, false}}) {
+        Step st(SPD_F32, 32, 8, 128, f.users, 3000, 3000, f.token_major);
+        for (spd_kv_view &v : st.v)
+            v.token_stride = f.stride;
+        spd_ctx *ctx = nullptr;
+        if (spd_create_(&ctx, 0) != SPD_OK)
+            FAIL("spd_create");
+        launches.clear();
+        const float *token = f.append ? st.buf : nullptr;
+        const int rc = spd_decode_step_(ctx, &st.s, st.buf, &st.v[0], &st.v[1], token, token, st.buf, st.buf, st.buf, st.buf, st.buf,
+                                        st.buf, st.buf, nullptr);
+        bool range = false, plain = false;
+        for (const Launch &l : launches) {
+            range = range || l.kernel.find("partial_mfma_kernelILi3ELin128E") != std::string::npos;
+            plain = plain || l.kernel.find("partial_mfma_kernelILi3ELi128E") != std::string::npos;
+        }
+        spd_destroy_(ctx);
+        if (rc != SPD_OK || range != f.range || plain == range)
+            FAIL("fp32 rows, %d users, stride %d: %d, %d, %d", f.users, f.stride, rc, range, plain);
+    }
+
     // whole rows: no launch asks for more than 64 KB of LDS, the kernel's static part (argv[2], from the compiler's report) and
     // the slots together
     const size_t static_lds = (size_t)std::atoi(argv[2]);
