@@ -243,7 +243,9 @@ int spd_decode_step(spd_ctx *ctx, const spd_shape *shape, const void *q, const s
 
 /*
  * spd_decode_step for callers that cannot allocate device memory: code that is being recorded into a HIP graph,
- * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same results; but the split schedules and the
+ * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same results - bit for bit those of
+ * spd_decode_step's first call on the view (a schedule built for shorter lengths that serves a grown view, and a smaller
+ * one here where that step's own does not fit the array, take the sums in another order).  The split schedules and the
  * chunk partials live in one fixed array of SPD_STATIC_SCRATCH_BYTES of device memory that
  * belongs to the library (one copy per GPU, held until the process ends), the schedules reach it through kernel
  * arguments, and the call makes no hipMalloc, hipFree, hipHostMalloc or copy command - it only launches kernels.

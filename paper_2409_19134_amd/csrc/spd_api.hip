@@ -142,8 +142,8 @@ int64_t head_steps_per_cu(const spd_ctx *ctx, const spd_shape *s, int64_t steps)
 }
 
 // What a choice of mapping is for: a call over one owner, a fused step, or a fused step whose tables and partials have to fit
-// the library's fixed array.  The last keeps to the lines that its limits have been stated with: a smaller line would refuse
-// steps that fit (an item and its partials per group of heads).
+// the library's fixed array and do not with the fused step's own choice.  The last is by the lines that need least (an item and its
+// partials per group of heads).
 enum class MappingFor { kOneOwner, kFusedStep, kFixedArray };
 
 // KV heads (waves) per workgroup of the head-per-wave mapping for a launch of `steps` 32-token steps per KV head, or 0
@@ -1481,26 +1481,39 @@ try {
     if (!st.ptr)
         return SPD_ERR_WORKSPACE;
     int waves = whole_rows_waves(ctx, shape, priv, pub);
-    const int split = split_step_mapping(ctx, shape, priv, pub, MappingFor::kFixedArray);
     // The tables of rows taken whole can be larger than the split schedule's - token-major storage has an item per group of
     // four or eight heads there, one per head here: what the array has no room for stays split.
     if (whole_rows_bytes(priv->n_users, shape->n_kv_heads) > kStaticSchedBytes)
         waves = 0;
-    const int hpw = waves ? kWholeRows : split;
-    const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, split);
     const int G = shape->n_q_heads / shape->n_kv_heads;
     // both schedules are built and checked against the array's limits before anything is enqueued; the step is refused by
-    // the split schedule's needs also if its rows are taken whole, so that the limits do not depend on the mapping
+    // the split schedule's needs also if its rows are taken whole, so that the limits do not depend on the mapping.  The split is
+    // spd_decode_step's own - the same results bit for bit - or, where that one does not fit, the one that needs least.
     ScheduleBlob B[2];
     const spd_kv_view *views[2] = {priv, pub};
-    std::vector<uint8_t> key[2];
-    for (int w = 0; w < 2; ++w) {
-        build_blob(shape, views[w], split, ctx->n_cus, tune, B[w]);
-        make_key(shape, views[w], hpw, &tune.target_wg_per_cu, kTuningInts, key[w]);
-        if (B[w].bytes.size() > kStaticSchedBytes || (size_t)B[w].n_slots * G + 4 > kStaticLseFloats ||
-            (size_t)B[w].n_slots * G * shape->head_dim + 4 > kStaticPartOFloats)
+    int split = split_step_mapping(ctx, shape, priv, pub, MappingFor::kFusedStep);
+    Tuning tune = fused_step_tuning(ctx, shape, priv, pub, split);
+    auto built_and_fits = [&] {
+        for (int w = 0; w < 2; ++w) {
+            B[w] = ScheduleBlob();
+            build_blob(shape, views[w], split, ctx->n_cus, tune, B[w]);
+            if (B[w].bytes.size() > kStaticSchedBytes || (size_t)B[w].n_slots * G + 4 > kStaticLseFloats ||
+                (size_t)B[w].n_slots * G * shape->head_dim + 4 > kStaticPartOFloats)
+                return false;
+        }
+        return true;
+    };
+    if (!built_and_fits()) {
+        const int first = split;
+        split = split_step_mapping(ctx, shape, priv, pub, MappingFor::kFixedArray);
+        tune = fused_step_tuning(ctx, shape, priv, pub, split);
+        if (split == first || !built_and_fits())
             return SPD_ERR_WORKSPACE;
     }
+    const int hpw = waves ? kWholeRows : split;
+    std::vector<uint8_t> key[2];
+    for (int w = 0; w < 2; ++w)
+        make_key(shape, views[w], hpw, &tune.target_wg_per_cu, kTuningInts, key[w]);
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     SPD_HIP(ctx, hipStreamIsCapturing(stream, &capture));
     if (capture != hipStreamCaptureStatusNone)

@@ -214,6 +214,44 @@ int main(int argc, char **argv)
                 FAIL("static step, %d users: the owners' tables overlap at %zu", c.users, at[i].first);
     }
 
+    // the static step launches what spd_decode_step launches, with the same tables, wherever they fit the array: also for
+    // token-major heads of 64 from 40 (32-token steps * KV heads) per unit and for groups of four of more than eight KV heads
+    struct Same {
+        int Hq, Hkv, d, users, lp, lo;
+        bool token_major, same;
+    };
+    for (const Same &c : {Same{32, 8, 64, 12, 3400, 200, true, true}, Same{32, 8, 64, 12, 2900, 200, true, true},
+                          Same{32, 8, 64, 9, 5000, 200, true, true}, Same{12, 12, 128, 9, 5000, 300, true, true},
+                          Same{32, 32, 128, 4, 5000, 300, true, true}, Same{32, 16, 128, 20, 6000, 500, true, true},
+                          Same{16, 16, 128, 40, 20000, 500, true, true}, Same{32, 8, 128, 16, 3000, 300, true, true},
+                          Same{32, 8, 128, 16, 3000, 300, false, true},
+                          Same{128, 8, 64, 12, 3400, 200, true, false}}) {  // its own split has partials for more than the array
+        Step st(SPD_BF16, c.Hq, c.Hkv, c.d, c.users, c.lp, c.lo, c.token_major);
+        std::vector<Launch> ran[2];
+        for (int fixed = 0; fixed < 2; ++fixed) {
+            spd_ctx *own = nullptr;
+            if (spd_create_(&own, 0) != SPD_OK)
+                FAIL("spd_create");
+            launches.clear();
+            uploads.clear();
+            const int rc = (fixed ? spd_decode_step_static_ : spd_decode_step_)(own, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr,
+                                                                               st.buf, st.buf, st.buf, st.buf, st.buf, st.buf, st.buf, nullptr);
+            if (rc != SPD_OK)
+                FAIL("%d users of %d + %d tokens, fixed %d: %d", c.users, c.lp, c.lo, fixed, rc);
+            for (const Launch &l : launches)
+                if (l.kernel.find("upload") == std::string::npos)
+                    ran[fixed].push_back(l);
+            spd_destroy_(own);
+        }
+        bool same = ran[0].size() == ran[1].size();
+        for (size_t i = 0; same && i < ran[0].size(); ++i) {
+            const Launch &a = ran[0][i], &b = ran[1][i];
+            same = a.kernel == b.kernel && a.grid.x == b.grid.x && a.block.x == b.block.x && a.lds == b.lds;
+        }
+        if (same != c.same)
+            FAIL("static step, %d users of %d + %d tokens, %d heads of %d: %s", c.users, c.lp, c.lo, c.Hkv, c.d, same ? "as the other" : "launches differ");
+    }
+
     // calls on the null stream while another stream is being captured: new schedules, split and whole rows, and remembered ones
     other_capture = true;
     for (int again = 0; again < 2; ++again)

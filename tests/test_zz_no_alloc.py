@@ -138,3 +138,31 @@ def test_static_step_whose_whole_rows_tables_exceed_the_array():
     _same({n: getattr(ref, n) for n in OUTPUTS}, {n: getattr(step, n) for n in OUTPUTS})
     split.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("users,Hq,Hkv,d,lp,lo", [(12, 32, 8, 64, 3400, 200), (9, 12, 12, 128, 5000, 300), (6, 16, 16, 128, 9000, 300)])
+def test_static_step_takes_the_fused_steps_mapping(users, Hq, Hkv, d, lp, lo):
+    """Token-major views between the mapping rule's lines: 64-channel heads from 40 head steps per unit, groups of four of more
+    than eight KV heads."""
+    import paper_2409_19134_amd as spd
+    ctx = spd.Context(0)
+    wl = workloads.random_case(85, torch.bfloat16, users, Hq, Hkv, d, [lp - 31 * u for u in range(users)], [lo] * users, device=DEV,
+                               layout="nhd")
+    ref, got = _both(ctx, wl)
+    assert ctx.spd_last_kernel_name().split(", ")[4] == "true"             # head per wave
+    _same(ref, got)
+    ctx.close()
+
+
+def test_static_step_with_a_split_of_its_own_where_the_fused_steps_does_not_fit():
+    """16 query heads per KV head of 64 channels: the partials of a wave per head are more than the array holds."""
+    import paper_2409_19134_amd as spd
+    from oracle import spd_oracle as orc
+    ctx = spd.Context(0)
+    wl = workloads.random_case(86, torch.bfloat16, 12, 128, 8, 64, [3400 - 31 * u for u in range(12)], [200] * 12, device=DEV, layout="nhd")
+    ref, got = _both(ctx, wl)
+    assert ctx.spd_last_kernel_name().split(", ")[4] == "false"            # head-major
+    Y, _ = orc.attention(orc.from_workload(wl))
+    for out in (ref, got):
+        assert np.abs(out["y"].cpu().double().numpy().reshape(Y.shape) - Y).max() <= 2e-3
+    ctx.close()
