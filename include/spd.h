@@ -162,7 +162,9 @@ int spd_get_option(spd_ctx *ctx, int32_t option, int32_t *value);
  * contiguous mode without device pointer arrays, the per-user base pointers - not by q, the outputs, the block table
  * or the pools; so the layers of a model that share lengths (and a block table, or pass k_ptrs_dev / v_ptrs_dev) share
  * one schedule.  A view whose lengths have all grown by the same 1..64 tokens since its schedule was built (a decode
- * loop that appends a token per user and step) is served by that schedule too and counts as a hit.
+ * loop that appends a token per user and step) is served by that schedule too and counts as a hit - unless the growth takes
+ * the view across a line of the rules that pick kernels, where a new schedule is built; while the stream is being captured,
+ * when nothing can be built, it is served there too.
  */
 int spd_get_schedule_stats(const spd_ctx *ctx, int64_t *builds, int64_t *hits);
 

@@ -246,11 +246,11 @@ void build_blob(const spd_shape *s, const spd_kv_view *v, int hpw, int n_cus, co
         B.max_chunks = std::max(B.max_chunks, (int)r.n_chunks);
 }
 
-// A view whose lengths have grown can cross the border between whole and split rows: the schedule that the rule now wants
-// is then a new one, where the old one would still have served the call.  While the stream is being captured nothing is
-// built as long as the other way of taking the rows is remembered: the calls try the rule's, the other, and then build.
+// A view whose lengths have grown can cross a line of the rules - between whole and split rows, between the mappings and their
+// head groups, between the sizes of a resident round: the schedule that the rules now want is then a new one, where the old one would
+// still have served the call.  While the stream is being captured nothing is built as long as a schedule of another way to take the
+// rows is remembered: the calls try the rules' way, the others (WaysToTakeRows), and then build.
 constexpr int kNotRemembered = 1;  // (not an error code: those are negative)
-constexpr int kTries = 3;
 
 // Find or build the device-resident schedule for this view (hpw: pieces for the head-per-wave kernel).  Uploads are
 // enqueued on `stream`.  build: false leaves it at kNotRemembered if the stream is being captured.
@@ -420,11 +420,14 @@ int ensure_scratch(spd_ctx *ctx, Owner &own, size_t o_floats, size_t lse_floats)
 // CU.  Measured as two parties, us per step, 3 against 2 per CU (both on the one-step kernel): workload 2's length law
 // with 8 / 16 / 24 / 32 users 25.4 / 38.7 / 49.6 / 62.2 against 25.2 / 38.1 / 49.2 / 61.8; with 64 users (72 steps per
 // piece) 109.5 against 109.7, workloads 3 and 4 781.6 / 453.2 against 782.8 / 454.8.
+Tuning wide_round(Tuning t)
+{
+    t.target_wg_per_cu += t.target_wg_per_cu / 2;
+    return t;
+}
 Tuning standalone_tuning(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *v, int hpw)
 {
-    const Tuning base = ctx->tuning;
-    Tuning t = base;
-    t.target_wg_per_cu += t.target_wg_per_cu / 2;
+    const Tuning base = ctx->tuning, t = wide_round(base);
     if (hpw || base.target_wg_per_cu < 2)
         return t;
     int64_t rows = 0, steps = 0;
@@ -468,37 +471,101 @@ int whole_rows_waves(const spd_ctx *ctx, const spd_shape *s, const spd_kv_view *
     return std::min(waves, spd::rows_waves_that_fit(s->head_dim, s->n_q_heads / s->n_kv_heads));
 }
 
+// How a call takes its rows: whole (waves > 0, hpw = kWholeRows) or split under a mapping and a tuning.
+struct RowsWay {
+    int waves = 0;
+    int hpw = 0;  // KV heads per workgroup of the head-per-wave mapping, 0 = head-major, kWholeRows
+    Tuning tune;
+};
+
+RowsWay whole_way(const spd_ctx *ctx, int waves)
+{
+    RowsWay w;
+    w.waves = waves;
+    w.hpw = kWholeRows;
+    w.tune = ctx->tuning;
+    return w;
+}
+
+// The ways that a call can take under the context's options, whatever the rules say, one after the other: whole rows if they are
+// possible at all (waves_if_whole > 0), then every mapping under each of the two tunings that the call's rule picks from.
+struct WaysToTakeRows {
+    const spd_ctx *ctx;
+    const spd_shape *s;
+    bool token_major;  // the layout of every view allows the head-per-wave mapping
+    int waves_if_whole;
+    Tuning tunings[2];
+    int at = 0;
+
+    bool next(RowsWay *w)
+    {
+        if (at == 0 && ++at && waves_if_whole > 0) {
+            *w = whole_way(ctx, waves_if_whole);
+            return true;
+        }
+        const int opt = token_major ? ctx->head_per_wave : 0, Hkv = s->n_kv_heads;
+        const int groups[3] = {0, head_per_wave_waves(Hkv, opt >= 2 ? opt : 4), head_per_wave_waves(Hkv, opt >= 2 ? opt : 8)};
+        while (at <= 6) {
+            const int group = groups[(at - 1) / 2];
+            const Tuning &t = tunings[(at - 1) % 2];
+            ++at;
+            if (group == 0 ? opt <= 0 : opt != 0 && group >= 2) {
+                w->waves = 0;
+                w->hpw = group;
+                w->tune = t;
+                return true;
+            }
+        }
+        return false;
+    }
+};
+
+// prepare(way, build) returned kNotRemembered for the rules' way: the others, and if none is remembered either the rules' way, built.
+template <class Prepare>
+int prepare_some_way(RowsWay *way, WaysToTakeRows others, Prepare &&prepare)
+{
+    const RowsWay rule = *way;
+    int rc = kNotRemembered;
+    while (rc == kNotRemembered) {
+        const bool other = others.next(way);
+        if (!other)
+            *way = rule;
+        rc = prepare(*way, !other);
+    }
+    return rc;
+}
+
 // Schedule lookup and scratch growth of one partial-attention call, whose arguments have been validated.
-int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const spd_kv_view *v, int mapping, const Tuning *tune, hipStream_t stream,
-                    bool build, CachedSchedule **e)
+int prepare_partial(spd_ctx *ctx, int which, const spd_shape *s, const spd_kv_view *v, const RowsWay &way, hipStream_t stream, bool build,
+                    CachedSchedule **e)
 {
     *e = nullptr;
     if (v->n_users == 0)
         return SPD_OK;
     Owner &own = ctx->owner[which];
-    // mapping: KV heads per workgroup of the head-per-wave mapping, 0 = head-major, kWholeRows, -1 = whatever suits this view
-    // on its own
-    int hpw = mapping;
-    if (hpw < 0)
-        hpw = head_per_wave_layout(s, v) ? head_per_wave_choice(ctx, s, total_steps(v), v->n_users, MappingFor::kOneOwner) : 0;
-    // tune: the fused step's; none for a call that serves one owner alone
-    const int rs = get_schedule(ctx, own, s, v, hpw, tune ? *tune : hpw == kWholeRows ? ctx->tuning : standalone_tuning(ctx, s, v, hpw),
-                                stream, build, e);
+    const int rs = get_schedule(ctx, own, s, v, way.hpw, way.tune, stream, build, e);
     if (rs != SPD_OK)
         return rs;
     const int G = s->n_q_heads / s->n_kv_heads;
     return ensure_scratch(ctx, own, (size_t)(*e)->n_slots * G * s->head_dim + 4, (size_t)(*e)->n_slots * G + 4);
 }
 
-// The schedule of a call for one owner alone: whole rows (*waves > 0) or split, see kNotRemembered.
+// The schedule of a call for one owner alone: whole rows (*waves > 0) or split.
 int prepare_one_owner(spd_ctx *ctx, int which, const spd_shape *s, const spd_kv_view *v, hipStream_t stream, CachedSchedule **e, int *waves)
 {
-    const int rule = whole_rows_waves(ctx, s, v, nullptr);
-    int rc = kNotRemembered;
-    for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {
-        *waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, s, v, nullptr, true);
-        rc = prepare_partial(ctx, which, s, v, *waves ? kWholeRows : -1, nullptr, stream, t == kTries - 1, e);
+    const bool token_major = head_per_wave_layout(s, v);
+    RowsWay way = whole_way(ctx, whole_rows_waves(ctx, s, v, nullptr));
+    if (!way.waves) {
+        way.hpw = token_major ? head_per_wave_choice(ctx, s, total_steps(v), v->n_users, MappingFor::kOneOwner) : 0;
+        way.tune = standalone_tuning(ctx, s, v, way.hpw);
     }
+    auto prepare = [&](const RowsWay &w, bool build) { return prepare_partial(ctx, which, s, v, w, stream, build, e); };
+    int rc = prepare(way, false);
+    if (rc == kNotRemembered) {
+        const WaysToTakeRows others{ctx, s, token_major, whole_rows_waves(ctx, s, v, nullptr, true), {ctx->tuning, wide_round(ctx->tuning)}};
+        rc = prepare_some_way(&way, others, prepare);
+    }
+    *waves = way.waves;
     return rc;
 }
 
@@ -1002,17 +1069,20 @@ int split_step_mapping(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_
 // and with more rows to hold back each (with the ring; us per fused step, 512 + 512 pieces against 256 + 256:
 // workload 4 444.3 / 434.4, its length law with 128 users 230.7 / 227.0, 256 users of 64-512 tokens 92.7 / 91.3).
 // With few, long rows the shorter pieces stay (workload 2's length law with 64 users: 103.9 / 107.2).
+Tuning half_round(Tuning t)
+{
+    t.target_wg_per_cu = std::max(1, t.target_wg_per_cu / 2);
+    return t;
+}
 Tuning fused_step_tuning(const spd_ctx *ctx, const spd_shape *shape, const spd_kv_view *priv, const spd_kv_view *pub, int hpw)
 {
-    Tuning t = ctx->tuning;
+    const Tuning t = ctx->tuning;
     if (hpw || t.target_wg_per_cu < 2)
         return t;
     int64_t rows_p = 0, rows_o = 0;
     const int64_t np = single_round_pieces(shape->n_kv_heads, priv->n_users, priv->lens, ctx->n_cus, t, &rows_p);
     const int64_t no = single_round_pieces(shape->n_kv_heads, pub->n_users, pub->lens, ctx->n_cus, t, &rows_o);
-    if (np > 0 && no > 0 && rows_p + rows_o >= 2 * (np + no))
-        t.target_wg_per_cu /= 2;
-    return t;
+    return np > 0 && no > 0 && rows_p + rows_o >= 2 * (np + no) ? half_round(t) : t;
 }
 
 // The launches of a fused step, given both owners' schedules (device resident) and where their chunk partials go.
@@ -1440,22 +1510,26 @@ try {
     if (rc != SPD_OK || priv->n_users == 0)
         return rc;
     CachedSchedule *ep = nullptr, *eo = nullptr;
-    const int rule = whole_rows_waves(ctx, shape, priv, pub);
-    int waves = 0;
-    rc = kNotRemembered;
+    RowsWay way = whole_way(ctx, whole_rows_waves(ctx, shape, priv, pub));
+    if (!way.waves) {
+        way.hpw = split_step_mapping(ctx, shape, priv, pub, MappingFor::kFusedStep);
+        way.tune = fused_step_tuning(ctx, shape, priv, pub, way.hpw);
+    }
     const int64_t hits = ctx->schedule_hits;
-    for (int t = 0; t < kTries && rc == kNotRemembered; ++t) {  // see kNotRemembered
+    auto prepare = [&](const RowsWay &w, bool build) {
         ctx->schedule_hits = hits;  // one owner's schedule found in a try that the other's absence ended does not count
-        waves = t != 1 ? rule : rule ? 0 : whole_rows_waves(ctx, shape, priv, pub, true);
-        const int hpw = waves ? kWholeRows : split_step_mapping(ctx, shape, priv, pub, MappingFor::kFusedStep);
-        const Tuning tune = fused_step_tuning(ctx, shape, priv, pub, hpw);
-        rc = prepare_partial(ctx, 0, shape, priv, hpw, &tune, stream, t == kTries - 1, &ep);
-        if (rc == SPD_OK)
-            rc = prepare_partial(ctx, 1, shape, pub, hpw, &tune, stream, t == kTries - 1, &eo);  // an upload, if any, stays on `stream`
+        const int found = prepare_partial(ctx, 0, shape, priv, w, stream, build, &ep);
+        return found != SPD_OK ? found : prepare_partial(ctx, 1, shape, pub, w, stream, build, &eo);  // an upload, if any, stays on `stream`
+    };
+    rc = prepare(way, false);
+    if (rc == kNotRemembered) {
+        const WaysToTakeRows others{ctx, shape, head_per_wave_layout(shape, priv) && head_per_wave_layout(shape, pub),
+                                    whole_rows_waves(ctx, shape, priv, pub, true), {ctx->tuning, half_round(ctx->tuning)}};
+        rc = prepare_some_way(&way, others, prepare);
     }
     if (rc != SPD_OK)
         return rc;
-    return launch_decode_step(ctx, shape, q, priv, pub, nt, waves, ep, eo, scratch_of(ctx->owner[0]), scratch_of(ctx->owner[1]), a_in,
+    return launch_decode_step(ctx, shape, q, priv, pub, nt, way.waves, ep, eo, scratch_of(ctx->owner[0]), scratch_of(ctx->owner[1]), a_in,
                               lse_in, a_out, lse_out, y, lse, w_in, stream);
 } catch (...) {  // a failed host allocation (std::vector): no C++ exception leaves the library
     return SPD_ERR_NOMEM;

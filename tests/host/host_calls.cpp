@@ -294,6 +294,57 @@ int main(int argc, char **argv)
             FAIL("a captured step: %lld schedules built, %lld found", (long long)(builds[1] - builds[0]), (long long)(hits[1] - hits[0]));
     }
 
+    // Captured calls over views that have grown across a line of the other rules: the schedules built on the near side serve them.
+    // entry 0: the fused step, 1: one owner; eager at lp + lo tokens, captured 64 later (the fused step's public rows, the owner's).
+    struct Line {
+        int entry, Hq, Hkv, d, users, lp, lo;
+        bool token_major;
+        const char *what;
+    };
+    const Line lines[] = {
+        {0, 32, 8, 64, 12, 3200, 160, true, "fused, heads of 64: 39 and 40 head steps"},
+        {1, 32, 8, 64, 12, 2720, 0, true, "one owner, heads of 64: 31 and 32"},
+        {1, 32, 8, 128, 12, 3488, 0, true, "one owner, heads of 128: 40 and 41"},
+        {0, 32, 8, 128, 16, 4096, 32, true, "fused, heads of 128: 64 and 66"},
+        {0, 16, 16, 128, 32, 5376, 32, true, "fused, groups of four and eight of sixteen heads: 338 and 342"},
+        {0, 32, 8, 128, 32, 28672, 64, true, "fused, groups of four and eight of eight heads: 898 and 900"},
+        {1, 32, 8, 128, 16, 8192, 0, false, "one owner, two and three pieces per unit: 64 and 65 steps"},
+    };
+    for (const Line &l : lines) {
+        Step st(SPD_BF16, l.Hq, l.Hkv, l.d, l.users, l.lp, l.lo, l.token_major);
+        spd_ctx *ctx = nullptr, *fresh = nullptr;
+        if (spd_create_(&ctx, 0) != SPD_OK || spd_create_(&fresh, 0) != SPD_OK)
+            FAIL("spd_create");
+        auto call = [&](spd_ctx *c, std::string *ran) {
+            launches.clear();
+            const int rc = l.entry == 1 ? spd_partial_attn_private_(c, &st.s, st.buf, &st.v[0], st.buf, st.buf, nullptr)
+                                        : spd_decode_step_(c, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf,
+                                                           st.buf, st.buf, st.buf, st.buf, nullptr);
+            for (const Launch &x : launches)
+                if (x.kernel.find("partial_mfma_kernel") != std::string::npos)
+                    *ran = x.kernel + " " + std::to_string(x.grid.x) + " x " + std::to_string(x.block.x);
+            return rc;
+        };
+        int64_t builds[2], hits;
+        std::string eager, captured, anew;
+        int rc = call(ctx, &eager);
+        for (int32_t &n : st.lens[l.entry == 1 ? 0 : 1])
+            n += 64;
+        if (rc == SPD_OK)
+            rc = call(fresh, &anew);
+        spd_get_schedule_stats_(ctx, &builds[0], &hits);
+        this_capture = 1;
+        if (rc == SPD_OK)
+            rc = call(ctx, &captured);
+        this_capture = 0;
+        spd_get_schedule_stats_(ctx, &builds[1], &hits);
+        spd_destroy_(ctx);
+        spd_destroy_(fresh);
+        if (rc != SPD_OK || eager == anew || captured != eager || builds[1] != builds[0])
+            FAIL("capture, %s: %d, %lld built, eager %s, captured %s, anew %s", l.what, rc, (long long)(builds[1] - builds[0]), eager.c_str(),
+                 captured.c_str(), anew.c_str());
+    }
+
     // Half steps, both sides of the rule's lines (256 units: an owner's resident round is 512 pieces, 768 where it is alone): tokens per
     // user of 16 users with eight KV heads unless said otherwise.  The streaming kernel's form is its second argument's sign.
     struct Form {

@@ -68,3 +68,48 @@ def test_calls_that_stay_head_major(ctx, d, Hkv, G, users, head_steps, fused):
     (64, 16, 5, 1, torch.bfloat16, False)])
 def test_fused_steps_in_groups_of_four(ctx, d, Hkv, G, users, dtype, paged):
     _run(ctx, d, Hkv, G, users, 66, True, True, dtype=dtype, paged=paged)
+
+
+@pytest.mark.parametrize("d,users,lp,lo,fused", [(64, 12, 3200, 160, True), (64, 12, 2720, 0, False), (128, 16, 4096, 32, True)])
+def test_capture_of_a_view_that_has_grown_across_a_line(d, users, lp, lo, fused):
+    """Eight heads on 256 units: run eagerly below the line, captured 64 tokens later above it - on the schedules of before."""
+    import paper_2409_19134_amd as spd
+    own = spd.Context(0)
+    grow = 64
+    wl = workloads.random_case(412, torch.bfloat16, users, 32, 8, d, [lp + (0 if fused else grow)] * users, [lo + grow] * users, device=DEV,
+                               layout="nhd")
+    side_of = "public" if fused else "private"
+    full = getattr(wl, side_of).lens.copy()
+    side = torch.cuda.Stream()
+
+    def call(step):
+        if fused:
+            step.run_fused(wl.q)
+        else:
+            own.spd_partial_attn_private(step.shape, wl.q, step.private, step.a_in, step.lse_in)
+
+    with torch.cuda.stream(side):
+        getattr(wl, side_of).lens = (full - grow).astype(np.int32)
+        call(spd.DecodeStep.from_workload(own, wl))
+        torch.cuda.synchronize()
+        before, builds = own.spd_last_kernel_name(), own.spd_get_schedule_stats()[0]
+        getattr(wl, side_of).lens = full
+        step = spd.DecodeStep.from_workload(own, wl)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            call(step)
+        assert own.spd_last_kernel_name() == before and before.split(", ")[4] == "false"
+        hw = orc.from_workload(wl)
+        A, _, _ = orc.partial(hw, hw.public if fused else hw.private)
+        got = step.a_out if fused else step.a_in
+        for _ in range(3):
+            got.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.abs(got.cpu().double().numpy().reshape(A.shape) - A).max() <= TOL[wl.dtype]
+        assert own.spd_get_schedule_stats()[0] == builds
+        call(step)                                     # outside a capture the rule decides
+        torch.cuda.synchronize()
+        assert own.spd_last_kernel_name().split(", ")[4] == "true"
+    own.close()
