@@ -247,8 +247,7 @@ class Context:
         b = lambda x: "true" if x else "false"
         if a[4] == 2:     # short rows, one workgroup each
             return f"whole_rows_kernel<{a[0]}, {a[1]}, {b(a[2])}, {b(a[5])}>"
-        dtype, channels = (a[0] - 3, -a[1]) if a[0] > 3 else (a[0], a[1])     # 4..6: the other forms of dtypes 1..3
-        return f"partial_mfma_kernel<{dtype}, {channels}, {b(a[2])}, {b(a[3])}, {b(a[4])}, {b(a[5])}>"
+        return f"partial_mfma_kernel<{a[0]}, {a[1]}, {b(a[2])}, {b(a[3])}, {b(a[4])}, {b(a[5])}>"
 
     def spd_set_option(self, option: int, value: int):
         self._check(lib.spd_set_option(self.handle, int(option), int(value)), "spd_set_option")

@@ -784,7 +784,9 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     });
     if (!ok)
         return SPD_ERR_SHAPE;  // no kernel instance for this combination: a bug in the rules above
-    const int32_t inst[6] = {dt_code, D, v0->block_size != 0, prefetch, hpw, nt.k != nullptr};
+    const bool other_form = spd::form_of(dt_code) != 0;
+    const int32_t inst[6] = {other_form ? dt_code - spd::kFormStep : dt_code, other_form ? -D : D, v0->block_size != 0, prefetch, hpw,
+                             nt.k != nullptr};
     std::memcpy(ctx->last_instance, inst, sizeof inst);
     SPD_HIP(ctx, hipGetLastError());
     if (timed)

@@ -139,6 +139,22 @@ static F symbol(void *lib, F, const char *name)
 }
 #define SYM(f) const auto f##_ = symbol(lib, &f, #f)
 
+// The template arguments in a streaming kernel's mangled name (Li<value>E or, negative, Lin<value>E, and Lb<0 or 1>E).
+static void template_arguments(const std::string &kernel, int32_t args[6])
+{
+    size_t at = kernel.find("partial_mfma_kernelI");
+    if (at == std::string::npos)
+        return;
+    at += std::strlen("partial_mfma_kernelI");
+    for (int i = 0; i < 6; ++i) {
+        at += 2;  // "Li" or "Lb"
+        const bool negative = kernel[at] == 'n';
+        const int v = std::atoi(kernel.c_str() + at + negative);
+        args[i] = negative ? -v : v;
+        at = kernel.find('E', at) + 1;
+    }
+}
+
 // Both owners of a step over users of `lp` and `lo` tokens; addresses are passed on, never read.
 struct Step {
     spd_shape s;
@@ -173,6 +189,7 @@ int main(int argc, char **argv)
     SYM(spd_decode_step);
     SYM(spd_partial_attn_private);
     SYM(spd_get_schedule_stats);
+    SYM(spd_get_last_kernel_instance);
     spd_ctx *ctx = nullptr;
     if (spd_create_(&ctx, 0) != SPD_OK)
         FAIL("spd_create");
@@ -391,6 +408,12 @@ int main(int argc, char **argv)
             streaming = streaming || l.kernel.find("partial_mfma_kernelILi1E") != std::string::npos;
             half = half || l.kernel.find("partial_mfma_kernelILi1ELin128E") != std::string::npos;
         }
+        int32_t got[6] = {}, ran[6] = {};
+        spd_get_last_kernel_instance_(ctx, got);
+        for (const Launch &l : launches)
+            template_arguments(l.kernel, ran);
+        if (std::memcmp(got, ran, sizeof got) != 0)
+            FAIL("%s: the last instance is not what ran: <%d, %d, ..>, <%d, %d, ..>", f.what, got[0], got[1], ran[0], ran[1]);
         spd_destroy_(ctx);
         if (rc != SPD_OK || !streaming || half != f.half)
             FAIL("half steps, %d users of %d + %d tokens (%s): %d, %d", f.users, f.lp, f.lo, f.what, rc, half);
@@ -418,6 +441,12 @@ int main(int argc, char **argv)
             range = range || l.kernel.find("partial_mfma_kernelILi3ELin128E") != std::string::npos;
             plain = plain || l.kernel.find("partial_mfma_kernelILi3ELi128E") != std::string::npos;
         }
+        int32_t got[6] = {}, ran[6] = {};
+        spd_get_last_kernel_instance_(ctx, got);
+        for (const Launch &l : launches)
+            template_arguments(l.kernel, ran);
+        if (std::memcmp(got, ran, sizeof got) != 0)
+            FAIL("fp32 rows: the last instance is not what ran: <%d, %d, ..>, <%d, %d, ..>", got[0], got[1], ran[0], ran[1]);
         spd_destroy_(ctx);
         if (rc != SPD_OK || range != f.range || plain == range)
             FAIL("fp32 rows, %d users, stride %d: %d, %d, %d", f.users, f.stride, rc, range, plain);
