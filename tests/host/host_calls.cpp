@@ -311,6 +311,62 @@ int main(int argc, char **argv)
             FAIL("a captured step: %lld schedules built, %lld found", (long long)(builds[1] - builds[0]), (long long)(hits[1] - hits[0]));
     }
 
+    // The mapping of token-major calls on both sides of its lines: the KV heads (waves) of a workgroup, 0 the head-major mapping, at
+    // exactly so many (32-token steps * KV heads) per unit.
+    struct Mapped {
+        bool fused;
+        int Hq, Hkv, d, users, head_steps, below, waves;
+    };
+    const Mapped mapped[] = {
+        // fused steps of more than eight KV heads: groups of four below 340 where four divides them, else the widest up to eight
+        {true, 12, 12, 128, 16, 66, 0, 4}, {true, 12, 12, 128, 16, 340, 1, 4}, {true, 12, 12, 128, 16, 340, 0, 6},
+        {true, 16, 16, 128, 16, 340, 1, 4}, {true, 16, 16, 128, 16, 340, 0, 8}, {true, 40, 20, 64, 16, 340, 1, 4}, {true, 40, 20, 64, 16, 340, 0, 5},
+        {true, 28, 28, 128, 16, 340, 1, 4}, {true, 28, 28, 128, 16, 340, 0, 7}, {true, 32, 32, 128, 3, 66, 0, 4}, {true, 32, 32, 64, 16, 340, 0, 8},
+        {true, 10, 10, 128, 16, 66, 0, 5}, {true, 18, 18, 128, 16, 66, 0, 6}, {true, 80, 16, 64, 1, 66, 0, 4},
+        // one owner: the widest
+        {false, 12, 12, 128, 16, 66, 0, 6}, {false, 16, 16, 128, 16, 66, 0, 8}, {false, 32, 32, 64, 16, 339, 0, 8},
+        // up to eight KV heads: groups of four up to 900
+        {true, 32, 8, 128, 16, 65, 1, 0}, {true, 32, 8, 128, 16, 65, 0, 4}, {true, 32, 8, 128, 16, 900, 1, 4}, {true, 32, 8, 128, 16, 900, 0, 8},
+        {true, 24, 6, 128, 16, 65, 0, 3}, {true, 16, 4, 64, 24, 65, 1, 0}, {true, 16, 4, 64, 24, 65, 0, 4},
+        // heads of 64 from 40, one owner 32; one owner's heads of 128 with up to four query heads 41; from 80 rows on
+        {true, 32, 8, 64, 10, 40, 1, 0}, {true, 32, 8, 64, 10, 40, 0, 4}, {true, 32, 8, 64, 9, 64, 0, 0}, {true, 64, 16, 64, 5, 40, 0, 4},
+        {false, 32, 8, 64, 10, 32, 1, 0}, {false, 32, 8, 64, 10, 32, 0, 4}, {false, 32, 8, 64, 9, 64, 0, 0},
+        {false, 32, 8, 128, 10, 41, 1, 0}, {false, 32, 8, 128, 10, 41, 0, 4}, {false, 40, 8, 128, 10, 64, 0, 0}, {false, 40, 8, 128, 10, 65, 0, 4},
+    };
+    for (const Mapped &m : mapped) {
+        const int steps = (m.head_steps * 256 + std::max(8, m.Hkv) - 1) / std::max(8, m.Hkv) - m.below - (m.fused ? m.users : 0);
+        for (int form = 0; form < (m.fused ? 4 : 3); ++form) {  // bf16; fp16; in pages of 32; with the append
+            Step st(form == 1 ? SPD_F16 : SPD_BF16, m.Hq, m.Hkv, m.d, m.users, steps / m.users * 32, 1, true);
+            st.lens[0][0] += steps % m.users * 32 - 31;  // (the last of its steps is one token)
+            for (spd_kv_view &v : st.v)
+                if (form == 2) {
+                    v.block_size = 32;
+                    v.k_pool = v.v_pool = v.block_table = reinterpret_cast<int32_t *>(st.buf);
+                    v.max_blocks = 1 << 20;
+                    v.block_stride = v.block_size * v.token_stride;
+                }
+            const float *token = form == 3 ? st.buf : nullptr;
+            spd_ctx *ctx = nullptr;
+            if (spd_create_(&ctx, 0) != SPD_OK)
+                FAIL("spd_create");
+            launches.clear();
+            const int rc = m.fused ? spd_decode_step_(ctx, &st.s, st.buf, &st.v[0], &st.v[1], token, token, st.buf, st.buf, st.buf, st.buf,
+                                                      st.buf, st.buf, st.buf, nullptr)
+                                   : spd_partial_attn_private_(ctx, &st.s, st.buf, &st.v[0], st.buf, st.buf, nullptr);
+            int waves = -1;
+            for (const Launch &l : launches)
+                if (l.kernel.find("partial_mfma_kernel") != std::string::npos) {
+                    int32_t args[6];
+                    template_arguments(l.kernel, args);
+                    waves = args[4] ? (int)l.block.x / 64 : 0;
+                }
+            spd_destroy_(ctx);
+            if (rc != SPD_OK || waves != m.waves)
+                FAIL("mapping, fused %d, form %d, %d heads of %d, %d users, %d head steps - %d: %d, %d waves", m.fused, form, m.Hkv, m.d, m.users,
+                     m.head_steps, m.below, rc, waves);
+        }
+    }
+
     // Captured calls over views that have grown across a line of the other rules: the schedules built on the near side serve them.
     // entry 0: the fused step, 1: one owner; eager at lp + lo tokens, captured 64 later (the fused step's public rows, the owner's).
     struct Line {

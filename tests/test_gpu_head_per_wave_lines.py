@@ -1,5 +1,6 @@
-"""Where token-major calls change from the head-major mapping to a wave per KV head, and the head groups that fused steps with more
-than eight KV heads take: on both sides of each line, by the kernel that ran and against the fp64 oracle."""
+"""Where token-major calls change from the head-major mapping to a wave per KV head: on both sides of the lower lines, by the kernel
+that ran and against the fp64 oracle; and calls in the groups of heads that fused steps with more than eight KV heads take (which
+groups those are, on both sides of every line, tests/host/host_calls.cpp reads from the launches)."""
 import numpy as np
 import pytest
 import torch
@@ -54,6 +55,12 @@ def test_lines(ctx, d, Hkv, G, users, line, fused, below):
     _run(ctx, d, Hkv, G, users, line, fused, below == 0, below)
 
 
+@pytest.mark.parametrize("d,Hkv,G,users,line,fused", [(64, 8, 4, 10, 40, True), (64, 16, 2, 7, 32, False), (128, 8, 4, 16, 41, False)])
+@pytest.mark.parametrize("below", [0, 1])
+def test_lines_in_pages_of_fp16(ctx, d, Hkv, G, users, line, fused, below):
+    _run(ctx, d, Hkv, G, users, line, fused, below == 0, below, dtype=torch.float16, paged="token_major")
+
+
 @pytest.mark.parametrize("d,Hkv,G,users,head_steps,fused", [
     (64, 8, 4, 9, 45, True),       # 72 rows: their pieces are too many
     (64, 4, 4, 24, 28, True),      # fewer than eight heads
@@ -67,6 +74,7 @@ def test_calls_that_stay_head_major(ctx, d, Hkv, G, users, head_steps, fused):
     (128, 12, 1, 9, torch.bfloat16, False), (64, 20, 2, 5, torch.float16, "token_major"), (128, 32, 1, 3, torch.float16, False),
     (64, 16, 5, 1, torch.bfloat16, False)])
 def test_fused_steps_in_groups_of_four(ctx, d, Hkv, G, users, dtype, paged):
+    """(The kernel's name shows the mapping, not the group.)"""
     _run(ctx, d, Hkv, G, users, 66, True, True, dtype=dtype, paged=paged)
 
 
