@@ -102,10 +102,14 @@ struct Elt<kF32Quad> {
 // (contiguous rows without an append).
 // What half steps are for: a round of 16 KB per wave takes ~3.6 us while everything streams, a piece of 17 steps is five rounds to one
 // wave and four to the other three, and nothing is in flight while a wave computes: rounds of half the size leave less of both at a
-// piece's end.  Measured, us per fused step, 32-token steps / half steps: the headline batch 33.1 / 32.7, with the append 34.1 / 33.2, in
-// 16-token pages 33.7 / 32.7; 12 such users 27.0 / 26.7, 24 48.8 / 48.1; 8 users of 4000-12000 tokens 52.3 / 51.5, 2 of 20000-40000
-// 48.3 / 47.0; two parties 40.7 / 40.1.  In buffer descriptors a lane's offset and a scalar per row are all the addressing there
-// is (VALU cycles of a 32-token step 1400 -> 800): fp32, headline batch, 60.9 / 60.0.
+// piece's end.  Measured, us per fused step, 32-token steps / half steps: 16 users of 512-4096 + 1-512 tokens 33.2 / 32.6, with the
+// append 34.2 / 33.3, in 16-token pages 33.8 / 32.7, both 34.6 / 32.9, as two parties 40.4 / 40.2; 12 such users 27.1 / 26.3, 24
+// 46.9 / 46.0; 8 users of 4000-12000 49.8 / 48.7, 2 of 20000-40000 48.2 / 46.8; workload 2 itself the same within its noise (31.0 /
+// 31.0, with the append 32.0 / 31.7, as two parties 37.8 / 37.4).  They take 10 % more vector instructions per token (workload 2:
+// 3.50 M against 3.17 M).
+// In buffer descriptors a lane's offset and a scalar per row are all the addressing there is: fp32, 16 such users, 60.9 / 60.0 (workload
+// 2's lengths 55.4 / 55.0; vector instructions 4.25 M / 3.73 M).
+// An append reads its last row elsewhere, and one instance serves a launch: it keeps plain addresses for both owners.
 constexpr int kFormStep = 3;  // from a dtype's code to its other form's
 constexpr int kBf16Half = SPD_BF16 + kFormStep, kF16Half = SPD_F16 + kFormStep, kF32QuadRange = kF32Quad + kFormStep;
 constexpr int form_of(int dt) { return dt >= kBf16Half ? 1 : 0; }
@@ -238,7 +242,7 @@ __device__ __forceinline__ PagePair load_pages(const LaneConst &L, int tb, int t
 // (tb + step) on return: the lookup is issued behind the data loads, one whole step before it is needed, so that no
 // wave ever waits for a block-table entry before it can ask for data.
 // RANGE: through buffer descriptors whose range ends with the segment (rows past it are zeros and cost no traffic), for rows that lie
-// end to end.  (Their stride is read all the same: with constant offsets the headline batch's fp32 takes the same time, but 16 users
+// end to end.  (Their stride is read all the same: with constant offsets 16 users of 512-4096 + 1-512 tokens take the same time, but 16
 // of 1000-3000 + 1000-3000 tokens 92.3 us instead of 88.4, 4 such 32.5 instead of 31.4.)
 template <int RB, int NA, bool PAGED, bool APPEND, bool RANGE = false>
 __device__ __forceinline__ void load_tile(TileRegs<RB, NA> &T, const LaneConst &L, int tb, int t_last, PagePair &P, int step)
@@ -472,7 +476,7 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 // and always run with PREFETCH; fp32 rows of 512 bytes need ~160 with one 16-token step in flight and never run with it.)
 // PREFETCH = true keeps two 32-token steps of loads in flight per wave (~245 VGPRs, two waves per SIMD): for launches
 // that run several rounds of workgroups, and for small ones that fit two per CU anyway (half as many dependent round
-// trips per wave).  PREFETCH = false holds one step (~160 VGPRs, three waves per SIMD): as fast when the private
+// trips per wave).  PREFETCH = false holds one step (~160 VGPRs, three waves per SIMD; half steps 132-137): as fast when the private
 // owner's pieces are one resident round, and it leaves room on every CU for the other owner's pieces.
 //
 // HPW ("head per wave") is the mapping for contiguous token-major storage, where the KV heads of a token are adjacent
@@ -484,8 +488,8 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 // a token range of one (user, KV head) row and its four waves take interleaved steps.
 //
 // APPEND = true adds the KV append (the address substitution costs ~1 % when nothing is appended, hence a flag).
-// CHANNELS = -D is the dtype's other form (see form_of): so written, a profile's first argument stays the dtype and the other
-// instances' names what they were.  (A body shared by two kernel templates costs registers: workload 5 +3 %.)
+// CHANNELS = -D is the dtype's other form (see form_of): so the first argument stays the dtype, and a profile's names of the other
+// instances stay what they are in stored ones.  (A body shared by two kernel templates costs registers: workload 5 +3 %.)
 template <int DTYPE, int CHANNELS, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 __global__ __launch_bounds__(HPW ? 512 : kThreads,
                              mfma_waves_per_simd((CHANNELS < 0 ? -CHANNELS : CHANNELS) * Elt<DTYPE>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(

@@ -152,8 +152,8 @@ enum class MappingFor { kOneOwner, kFusedStep, kFixedArray };
 // four heads (two or three per CU, 1 KB of every token) take over from ~280 MB of K/V; workgroups of eight (one per
 // CU, a token's whole 2 KB with eight KV heads) are ahead from a few GB of long rows (workload 3: 1.2 %).
 // Measured (256 CUs, 8 KV heads, token-major, us per fused step; head-major / four / eight):
-// workload 2's lengths with 16 users 36.3 / 39.3 / 48.1, 24 users 51.9 / 51.9 / -, 32 users 63.2 / 59.5 / 66.5,
-// 64 users 115.7 / 102.5 / 110.0; workload 4 - / 445.5 / 452.9; workload 3 - / 783 / 774.
+// workload 2's lengths with 16 users 36.4 / 38.0 / 46.0, 24 users 48.3 / 48.0 / 55.7, 32 users 62.7 / 58.7 / 65.8,
+// 64 users 114.7 / 102.0 / 108.7; workload 4 488 / 442 / 451; workload 3 907 / 784 / 775.
 // The line lies lower, in rows enough that a row's pieces stay few (80 on 256 CUs: each piece costs the closing kernel a partial
 // per head; 8 users of <= 6000 tokens, D = 64, 24.0 head-major against 27.1, 10 users of <= 5000 24.7 / 24.1),
 //   - for heads of 64 values, where a row of one head is only 128 bytes of every token's (fused, workload 2's lengths, us
@@ -753,10 +753,11 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     // or two to a CU, and of half steps too little is in flight then (us per fused step, 32-token / half steps, at mean lengths of the
     // second owner's pieces in the first's: 24 users of 2000-4000 tokens, 0.25 64.9 / 63.3, 0.40 70.1 / 71.9, 0.60 78.7 / 84.0; 16 such
     // 0.26 45.1 / 45.4, 0.42 48.9 / 50.2; in pages, 16 users of 4000-12000, 0.20 103.7 / 101.2, 0.39 116.4 / 126.3; 4000-8000 + 16000-32000,
-    // 4.2 318 / 395).
+    // 4.2 318 / 395).  The first owner's length decides: short rows in front of long ones stay with whole steps (16 users of 64-512 +
+    // 512-4096 40.8 / 42.2, 8 such 18.7 / 19.0; where all are resident half steps would gain, 2 users of 1-512 + 20000-40000 49.1 / 48.1).
     // Pages, whose ids every step asks for: up to 48 steps a piece where one owner's three pieces per CU run (us of private calls, fp16
     // in 64-token pages: 26 steps 55.5 / 54.1, 39 78.8 / 78.5, 47 96.2 / 96.3, 57 115.6 / 115.8, 73 148.4 / 149.3, 450 844.5 / 859.8;
-    // contiguous rows 834.0 / 825.2), up to 96 in a fused step (63 steps 94.9 / 94.2, 94 127.3 / 126.2, 187 243.3 / 242.8, 424 528 / 548).
+    // contiguous rows 834.0 / 825.2), up to 96 in a fused step (62 steps 87.6 / 86.7, 94 127.3 / 126.2, 187 243.3 / 242.8, 424 528 / 548).
     // fp32 through descriptors: contiguous rows that lie end to end, without an append (us per fused step, without / with: 4 users of
     // 1000-3000 + 1000-3000 tokens 33.2 / 31.4, 16 such 90.0 / 88.4, 48 of 64-512 + 1-256 40.3 / 39.8; token-major, 4 such users
     // 34.2 / 32.6, but 6 40.1 / 40.6, 16 91.0 / 91.4, 20 of 512-4096 + 1-512 74.2 / 74.9).
