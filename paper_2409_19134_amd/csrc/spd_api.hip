@@ -509,7 +509,7 @@ struct WaysToTakeRows {
             const int group = groups[(at - 1) / 2];
             const Tuning &t = tunings[(at - 1) % 2];
             ++at;
-            if (group == 0 ? opt <= 0 : opt != 0 && group >= 2) {
+            if (group == 0 ? opt <= 0 || groups[1] < 2 : opt != 0 && group >= 2) {  // (seven heads have no groups of up to four)
                 w->waves = 0;
                 w->hpw = group;
                 w->tune = t;

@@ -190,6 +190,8 @@ int main(int argc, char **argv)
     SYM(spd_partial_attn_private);
     SYM(spd_get_schedule_stats);
     SYM(spd_get_last_kernel_instance);
+    SYM(spd_set_option);
+    SYM(spd_public_attn_merge);
     spd_ctx *ctx = nullptr;
     if (spd_create_(&ctx, 0) != SPD_OK)
         FAIL("spd_create");
@@ -416,6 +418,62 @@ int main(int argc, char **argv)
         if (rc != SPD_OK || eager == anew || captured != eager || builds[1] != builds[0])
             FAIL("capture, %s: %d, %lld built, eager %s, captured %s, anew %s", l.what, rc, (long long)(builds[1] - builds[0]), eager.c_str(),
                  captured.c_str(), anew.c_str());
+    }
+
+    // ... and over random views, options and growth, of the owners that can grow: nothing is built, each owner's schedule found once
+    {
+        uint32_t seed = 12345;
+        auto below = [&](int n) { return (int)((seed = seed * 1664525u + 1013904223u) >> 8) % n; };
+        auto one_of = [&](std::initializer_list<int> l) { return *(l.begin() + below((int)l.size())); };
+        int across = 0;
+        for (int i = 0; i < 30000; ++i) {
+            const int Hkv = one_of({2, 4, 6, 7, 8, 8, 9, 12, 16, 32}), G = one_of({1, 2, 4, 8, 16}), d = one_of({64, 128}), entry = below(3);
+            const int users = 1 + below(one_of({2, 20, 80})), dtype = one_of({SPD_F32, SPD_BF16, SPD_F16}), top = one_of({100, 700, 3000, 9000, 30000});
+            const bool token_major = below(3) != 0, even = below(4) == 0, both = below(3) == 0;
+            const int grow = 1 + below(64), mapping = below(4) ? -1 : one_of({0, 1, 2, 4, 8}), round = below(6) ? 2 : one_of({1, 3, 4});
+            Step st(dtype, Hkv * G, Hkv, d, users, top, top, token_major);
+            if (!even)
+                for (std::vector<int32_t> &lens : st.lens)
+                    for (int32_t &n : lens)
+                        n = 1 + below(&lens == &st.lens[1] && both ? 300 : top);
+            auto call = [&](spd_ctx *c, std::string *ran) {
+                launches.clear();
+                const int rc = entry == 0   ? spd_decode_step_(c, &st.s, st.buf, &st.v[0], &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf,
+                                                               st.buf, st.buf, st.buf, st.buf, nullptr)
+                               : entry == 1 ? spd_partial_attn_private_(c, &st.s, st.buf, &st.v[0], st.buf, st.buf, nullptr)
+                                            : spd_public_attn_merge_(c, &st.s, st.buf, &st.v[1], nullptr, nullptr, st.buf, st.buf, st.buf, st.buf,
+                                                                     st.buf, st.buf, st.buf, nullptr);
+                for (const Launch &x : launches)
+                    if (x.kernel.find("upload") == std::string::npos)
+                        *ran += x.kernel + " " + std::to_string(x.grid.x) + " x " + std::to_string(x.block.x) + "; ";
+                return rc;
+            };
+            spd_ctx *c[2];
+            std::string ran[3];
+            int rc = 0;
+            for (spd_ctx *&x : c)
+                rc |= spd_create_(&x, 0) | spd_set_option_(x, SPD_OPT_HEAD_PER_WAVE, mapping) | spd_set_option_(x, SPD_OPT_TARGET_WG_PER_CU, round);
+            rc |= call(c[0], &ran[0]);
+            for (int w = 0; w < 2; ++w)
+                if (entry == 0 ? w == 1 || both : w == (entry == 1 ? 0 : 1))
+                    for (int32_t &n : st.lens[w])
+                        n += grow;
+            int64_t builds[2], hits[2];
+            spd_get_schedule_stats_(c[0], &builds[0], &hits[0]);
+            this_capture = 1;
+            rc |= call(c[0], &ran[1]);
+            this_capture = 0;
+            spd_get_schedule_stats_(c[0], &builds[1], &hits[1]);
+            rc |= call(c[1], &ran[2]);
+            across += ran[1] != ran[2];
+            for (spd_ctx *x : c)
+                spd_destroy_(x);
+            if (rc != SPD_OK || builds[1] != builds[0] || hits[1] - hits[0] != (entry == 0 ? 2 : 1))
+                FAIL("capture, random view %d (entry %d, %d x %d heads of %d, %d users, grown by %d, options %d, %d): %d, %lld built, %s / %s", i, entry,
+                     Hkv, G, d, users, grow, mapping, round, rc, (long long)(builds[1] - builds[0]), ran[0].c_str(), ran[1].c_str());
+        }
+        if (across < 3000)
+            FAIL("capture, random views: only %d differ from a view anew", across);
     }
 
     // Half steps, both sides of the rule's lines (256 units: an owner's resident round is 512 pieces, 768 where it is alone): tokens per
