@@ -103,13 +103,14 @@ struct Elt<kF32Quad> {
 // What half steps are for: a round of 16 KB per wave takes ~3.6 us while everything streams, a piece of 17 steps is five rounds to one
 // wave and four to the other three, and nothing is in flight while a wave computes: rounds of half the size leave less of both at a
 // piece's end.  Measured, us per fused step, 32-token steps / half steps: 16 users of 512-4096 + 1-512 tokens 33.2 / 32.6, with the
-// append 34.2 / 33.3, in 16-token pages 33.8 / 32.7, both 34.6 / 32.9, as two parties 40.4 / 40.2; 12 such users 27.1 / 26.3, 24
+// append 34.1 / 33.2, in 16-token pages 33.8 / 32.7, both 34.4 / 32.8, as two parties 40.4 / 40.2; 12 such users 27.1 / 26.3, 24
 // 46.9 / 46.0; 8 users of 4000-12000 49.8 / 48.7, 2 of 20000-40000 48.2 / 46.8; workload 2 itself the same within its noise (31.0 /
 // 31.0, with the append 32.0 / 31.7, as two parties 37.8 / 37.4).  They take 10 % more vector instructions per token (workload 2:
 // 3.50 M against 3.17 M).
 // In buffer descriptors a lane's offset and a scalar per row are all the addressing there is: fp32, 16 such users, 60.9 / 60.0 (workload
 // 2's lengths 55.4 / 55.0; vector instructions 4.25 M / 3.73 M).
-// An append reads its last row elsewhere, and one instance serves a launch: it keeps plain addresses for both owners.
+// An append reads its last row elsewhere, and one instance serves a launch: it keeps plain addresses for both owners.  Contiguous rows
+// then gain by how the rounds divide (14 users 30.8 / 31.1, 16 34.1 / 33.2, 18 37.6 / 37.4, 20 40.4 / 39.3, 24 47.2 / 47.7, 32 60.5 / 60.5).
 constexpr int kFormStep = 3;  // from a dtype's code to its other form's
 constexpr int kBf16Half = SPD_BF16 + kFormStep, kF16Half = SPD_F16 + kFormStep, kF32QuadRange = kF32Quad + kFormStep;
 constexpr int form_of(int dt) { return dt >= kBf16Half ? 1 : 0; }

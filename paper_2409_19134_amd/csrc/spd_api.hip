@@ -752,7 +752,7 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     // The second owner's pieces, dispatched behind the first's, are short where three per CU don't hold all: the last of them run one
     // or two to a CU, and of half steps too little is in flight then (us per fused step, 32-token / half steps, at mean lengths of the
     // second owner's pieces in the first's: 24 users of 2000-4000 tokens, 0.25 64.9 / 63.3, 0.40 70.1 / 71.9, 0.60 78.7 / 84.0; 16 such
-    // 0.26 45.1 / 45.4, 0.42 48.9 / 50.2; in pages, 16 users of 4000-12000, 0.20 103.7 / 101.2, 0.39 116.4 / 126.3; 4000-8000 + 16000-32000,
+    // 0.21 43.6 / 43.7, 0.26 45.1 / 45.4, 0.42 48.9 / 50.2; in pages, 16 users of 4000-12000, 0.20 103.7 / 101.2, 0.39 116.4 / 126.3; 4000-8000 + 16000-32000,
     // 4.2 318 / 395).  The first owner's length decides: short rows in front of long ones stay with whole steps (16 users of 64-512 +
     // 512-4096 40.8 / 42.2, 8 such 18.7 / 19.0; where all are resident half steps would gain, 2 users of 1-512 + 20000-40000 49.1 / 48.1).
     // Pages, whose ids every step asks for: up to 48 steps a piece where one owner's three pieces per CU run (us of private calls, fp16
