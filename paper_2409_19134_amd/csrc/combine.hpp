@@ -310,6 +310,17 @@ __device__ __forceinline__ float row_max(float v)
     v = fmaxf(v, row_dpp<0x122>(v));
     return fmaxf(v, row_dpp<0x121>(v));
 }
+// The same for values that are no NaN: max(a, b) is the median of a, b and infinity (fmaxf first quiets what a lane exchange brings, an
+// instruction more each).
+__device__ __forceinline__ float row_max_ordered(float v)
+{
+    float inf = INFINITY;
+    asm("" : "+v"(inf));  // (a median with a known infinity becomes that maximum again)
+    v = __builtin_amdgcn_fmed3f(v, row_dpp<0x128>(v), inf);
+    v = __builtin_amdgcn_fmed3f(v, row_dpp<0x124>(v), inf);
+    v = __builtin_amdgcn_fmed3f(v, row_dpp<0x122>(v), inf);
+    return __builtin_amdgcn_fmed3f(v, row_dpp<0x121>(v), inf);
+}
 __device__ __forceinline__ float row_sum(float v)
 {
     v += row_dpp<0x128>(v);

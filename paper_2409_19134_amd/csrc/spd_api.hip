@@ -795,26 +795,17 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     return SPD_OK;
 }
 
-spd::RowsOwner rows_owner(const CachedSchedule *e, const spd_shape *s, const spd_kv_view *v, float *out, float *lse, NewToken nt)
+void set_rows_owner(spd::RowsArgs &R, int i, const CachedSchedule *e, const spd_shape *s, const spd_kv_view *v, NewToken nt)
 {
-    const OwnerArgs a = owner_args(ScratchPtrs(), e, s, v, out, lse, nt.k, nt.v);
-    spd::RowsOwner r;
-    r.items = reinterpret_cast<const spd::RowItem *>(e->dev);
-    r.k_pool = a.k_pool;
-    r.v_pool = a.v_pool;
-    r.k_ptrs = a.k_ptrs;
-    r.v_ptrs = a.v_ptrs;
-    r.block_table = a.kv.block_table;
-    r.max_blocks = a.kv.max_blocks;
-    r.page_shift = a.kv.page_shift;
-    r.token_stride = a.kv.token_stride;
-    r.block_stride = a.kv.block_stride;
-    r.k_new = a.k_new;
-    r.v_new = a.v_new;
-    r.out = out;
-    r.lse = lse;
-    r.grow = e->grow;
-    return r;
+    const OwnerArgs a = owner_args(ScratchPtrs(), e, s, v, nullptr, nullptr, nt.k, nt.v);
+    R.items[i] = reinterpret_cast<const spd::RowItem *>(e->dev);
+    R.grow[i] = e->grow;
+    R.token_stride[i] = a.kv.token_stride;
+    R.k_ptrs[i] = a.k_ptrs;
+    R.v_ptrs[i] = a.v_ptrs;
+    R.k_new[i] = a.k_new;
+    R.v_new[i] = a.v_new;
+    R.paging[i] = {a.k_pool, a.v_pool, a.kv.block_table, a.kv.max_blocks, a.kv.page_shift, a.kv.block_stride};
 }
 
 // What a whole-rows launch merges, or nullptrs: with both owners their own partials, with one the delivered a_in / lse_in.
@@ -837,8 +828,8 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
 {
     const int G = s->n_q_heads / s->n_kv_heads, D = s->head_dim;
     spd::RowsArgs R;
-    R.a0 = rows_owner(e0, s, v0, out0, lse0, which == 1 ? nt : NewToken());
-    R.a1 = e1 ? rows_owner(e1, s, v1, out1, lse1, which == 0 ? nt : NewToken()) : R.a0;
+    set_rows_owner(R, 0, e0, s, v0, which == 1 ? nt : NewToken());
+    set_rows_owner(R, 1, e1 ? e1 : e0, s, e1 ? v1 : v0, e1 ? (which == 0 ? nt : NewToken()) : which == 1 ? nt : NewToken());
     R.waves = waves;
     R.both = e1 != nullptr;
     R.Hkv = s->n_kv_heads;
@@ -849,11 +840,7 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
     const bool by_length = whole_rows_by_length((int64_t)v0->n_users * s->n_kv_heads, waves, ctx->n_cus);
     R.order = by_length ? reinterpret_cast<const int32_t *>(e0->dev + e0->off_rows) : nullptr;
     R.q = static_cast<const char *>(q);
-    R.a_in = mg.a_in;
-    R.lse_in = mg.lse_in;
-    R.y = mg.y;
-    R.lse = mg.lse;
-    R.w_in = mg.w_in;
+    R.results = {out0, lse0, e1 ? out1 : nullptr, lse1, e1 ? nullptr : mg.a_in, mg.lse_in, mg.y, mg.lse, mg.w_in};
     Owner &town = ctx->owner[e1 ? 0 : which];
     const bool timed = ctx->timing && town.ev_used < (int)town.ev_start.size();
     MfmaLaunch L;

@@ -1,14 +1,16 @@
 // Short rows whole: one workgroup computes a (user, KV head) row's attention over all of its tokens - one owner's, or both
 // owners' and their merge (Theorem 1) - so that a call is one launch, without chunk partials and without a closing kernel.
 // What bounds it: with few rows latency - two scalar round trips to the row's addresses (0.7 us), the tiles at what one
-// compute unit can take in (~40 bytes a cycle: 16 KB per 0.17 us), and the instructions of the epilogue, ~2 ns each for
-// the wave that executes them, hence a thread per channel there; with many rows HBM.  Workgroups of up to twelve waves
+// compute unit can take in (~40 bytes a cycle: 16 KB per 0.17 us; how fast a wave asks makes no difference, row addresses of one
+// instruction instead of seven gained nothing), and the instructions of the epilogue, ~2 ns each for the wave that executes them; with
+// many rows HBM.  Workgroups of up to twelve waves
 // (three per SIMD) that share a row's steps out evenly, both owners' in one line: the old split of such calls into
 // one-step workgroups spread better over idle compute units but needed a second launch to close.  Measured, split kernels /
-// this one (us per call): fp32 1 user 128 + 16 tokens 8.5 / 4.9 (fused), bf16 32 users of 64-512 + 1-256 with the append
-// 18.9 / 15.2, 256 such users 90.3 / 82.3 (5.5 TB/s), 256 users of 24-192 + 64 51.2 / 31.5; fp16 with 64 channels, 16 users
-// as three calls 19.8 / 14.2.  When it pays is whole_rows_choice's rule (schedule.hpp).
+// this one (us per call): fp32 1 user 128 + 16 tokens 8.5 / 4.8 (fused), bf16 32 users of 64-512 + 1-256 with the append
+// 18.9 / 15.0, 256 such users 90.3 / 81.9 (5.5 TB/s), 256 users of 24-192 + 64 51.2 / 31.5; fp16 with 64 channels, 16 users
+// as three calls 19.8 / 13.8.  When it pays is whole_rows_choice's rule (schedule.hpp).
 #pragma once
+#include <cstddef>
 #include <type_traits>
 
 #include "combine.hpp"
@@ -20,8 +22,6 @@ namespace spd {
 // size is a multiple of 16.
 struct alignas(16) RowsShared {
     float2 ml[kRowsMaxWaves + 1][16];  // running max and sum of every slot
-    int n0;                            // slots [0, n0) are owner 0's
-    int extra;                         // whether the extra slot is used
 };
 static_assert(sizeof(RowsShared) % 16 == 0, "the dynamic part starts where this ends");
 
@@ -33,35 +33,46 @@ __host__ __device__ constexpr int rows_waves_that_fit(int D, int G)
     return n > (size_t)kRowsMaxWaves ? kRowsMaxWaves : (int)n;
 }
 
-// One owner's call as the kernel needs it.
-struct RowsOwner {
-    const RowItem *items;
-    const char *k_pool, *v_pool;  // paged mode
-    const char *const *k_ptrs, *const *v_ptrs;  // contiguous mode with device pointer tables, else nullptr
-    const int32_t *block_table;   // paged mode
-    int32_t max_blocks, page_shift;
-    int64_t token_stride, block_stride;  // bytes
-    const char *k_new, *v_new;    // KV append
-    float *out, *lse;
-    int32_t grow;                 // see OwnerArgs
+// Where the results go (the whole call's arrays).
+struct RowsResults {
+    float *out0, *lse0, *out1, *lse1;  // out1: nullptr unless both owners are the launch's
+    const float *a_in, *lse_in;        // the other owner's finished partials, nullptr unless they were delivered
+    float *y, *lse, *w_in;             // y: nullptr if nothing is merged
 };
 
-struct RowsArgs {
-    RowsOwner a0, a1;    // a1: a copy of a0 unless `both`
-    const int32_t *order;  // [n_users] users in launch order, or nullptr
-    const char *q;       // [U][Hq][D]
-    int32_t waves, both;  // both: both owners' rows, merged into y; else a0's alone - merged too if y is given, with a_in / lse_in
-    int32_t Hkv, Hq, G;
-    uint32_t wave_mul;   // ceil(2^32 / waves): x / waves is the high word of x * wave_mul
-    float scale_log2e;
-    const float *a_in, *lse_in;  // the other owner's finished partials
-    float *y, *lse, *w_in;       // the merge's results, or nullptr
+// What a paged call needs of an owner besides.
+struct RowsPaging {
+    const char *k_pool, *v_pool;
+    const int32_t *block_table;
+    int32_t max_blocks, page_shift;
+    int64_t block_stride;  // bytes
 };
+
+// In the order in which a wave needs it: a scalar load of the arguments misses once for every 64-byte line, and the lines of one batch
+// of loads don't come at once (until the row's length is there: 1400 -> 1040 cycles in the three calls, 1680 -> 1420 in tiny fp32).  Index 0 and 1: the owners; what belongs to owner 1 repeats owner 0's unless `both`.
+struct RowsArgs {
+    const RowItem *items[2];
+    const int32_t *order;  // [n_users] users in launch order, or nullptr
+    const char *q;         // [U][Hq][D]
+    int32_t grow[2];       // see OwnerArgs
+    int32_t waves, both;   // both: both owners' rows, merged into y; else the first's alone - merged too if partials were delivered
+    int32_t Hkv, Hq, G;
+    uint32_t wave_mul;     // ceil(2^32 / waves): x / waves is the high word of x * wave_mul
+    int64_t token_stride[2];  // bytes
+    const char *const *k_ptrs[2], *const *v_ptrs[2];  // contiguous mode with device pointer tables, else nullptr
+    const char *k_new[2], *v_new[2];  // KV append, or nullptr
+    float scale_log2e;
+    RowsResults results;
+    RowsPaging paging[2];
+};
+static_assert(offsetof(RowsArgs, token_stride) == 64, "a row's address and share come from one line");
 
 __device__ __forceinline__ RowItem scalar_load_row(const RowItem *items, int idx, int grow)
 {
-    static_assert(sizeof(RowItem) == 32, "a row is read as five dwords of eight");
-    const const_u32_ptr w = (const_u32_ptr)(uintptr_t)(items + idx);
+    static_assert(sizeof(RowItem) == 32, "a row is read as eight dwords at once");
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+    typedef const u32x8 __attribute__((address_space(4))) *const_u32x8_ptr;
+    const u32x8 w = *(const_u32x8_ptr)(uintptr_t)(items + idx);
     RowItem it;
     it.k_base = reinterpret_cast<const char *>(((uint64_t)w[1] << 32) | w[0]);
     it.v_base = reinterpret_cast<const char *>(((uint64_t)w[3] << 32) | w[2]);
@@ -69,120 +80,158 @@ __device__ __forceinline__ RowItem scalar_load_row(const RowItem *items, int idx
     return it;
 }
 
-// sum[v] += weight of slot S * os[S][v] over the slots; owner 0's sums (slots [0, n0)) move to `first`.
-template <int MAXS, int VEC, int S = 0>
-__device__ __forceinline__ void weighted_slots(const float (&os)[MAXS][VEC], float w, int n0, float (&first)[VEC], float (&sum)[VEC])
+// The same as the kernel reads it: pointers that arrive through memory are told to be global ones (else: flat stores).
+typedef float __attribute__((address_space(1))) *global_f32_ptr;
+struct DevResults {
+    global_f32_ptr out0, lse0, out1, lse1, a_in, lse_in, y, lse, w_in;
+};
+__device__ __forceinline__ DevResults scalar_load_results(uintptr_t at)
 {
-    if constexpr (S < MAXS) {
-        if (S == n0) {  // uniform
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                first[v] = sum[v];
-                sum[v] = 0.f;
-            }
-        }
-        const float ws = row_dpp<0x150 + S>(w);  // row_newbcast: lane S's value
-#pragma unroll
-        for (int v = 0; v < VEC; ++v)
-            sum[v] = fmaf(ws, os[S][v], sum[v]);
-        weighted_slots<MAXS, VEC, S + 1>(os, w, n0, first, sum);
-    }
+    static_assert(sizeof(RowsResults) == 72 && offsetof(RowsArgs, results) % 8 == 0, "read as nine pointers");
+    const const_u64_ptr p = (const_u64_ptr)at;
+    return DevResults{(global_f32_ptr)p[0], (global_f32_ptr)p[1], (global_f32_ptr)p[2], (global_f32_ptr)p[3], (global_f32_ptr)p[4],
+                      (global_f32_ptr)p[5], (global_f32_ptr)p[6], (global_f32_ptr)p[7], (global_f32_ptr)p[8]};
 }
 
 template <int VEC>
+struct FloatVec {
+    typedef float type __attribute__((ext_vector_type(VEC)));
+    typedef type __attribute__((address_space(1))) *global_ptr;
+};
+template <int VEC>
 __device__ __forceinline__ void load_vec(float (&x)[VEC], const float *p)
 {
-    typedef float vec __attribute__((ext_vector_type(VEC)));
-    const vec t = *reinterpret_cast<const vec *>(p);
+    const auto t = *reinterpret_cast<const typename FloatVec<VEC>::type *>(p);
 #pragma unroll
     for (int v = 0; v < VEC; ++v)
         x[v] = t[v];
 }
 template <int VEC>
-__device__ __forceinline__ void store_vec(float *p, const float (&x)[VEC])
+__device__ __forceinline__ void load_vec(float (&x)[VEC], global_f32_ptr p)
 {
-    typedef float vec __attribute__((ext_vector_type(VEC)));
-    vec t;
+    const auto t = *(typename FloatVec<VEC>::global_ptr)p;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v)
+        x[v] = t[v];
+}
+template <int VEC>
+__device__ __forceinline__ void store_vec(global_f32_ptr p, const float (&x)[VEC])
+{
+    typename FloatVec<VEC>::type t;
 #pragma unroll
     for (int v = 0; v < VEC; ++v)
         t[v] = x[v];
-    *reinterpret_cast<vec *>(p) = t;
+    *(typename FloatVec<VEC>::global_ptr)p = t;
 }
 
-// Combines the slots' states and writes the row's results.  A thread takes VEC consecutive channels of one query head (one
-// where the workgroup has a thread for every channel: this is the tail of a launch, and a wave's instructions take 2 ns
-// each); the slots' weights are computed once per 16-lane row, lane i for slot i.  Straight-line over MAXS slots (the last
-// one stands in, with weight 0, for those past n_slots), so that every LDS read leaves at once.  An owner's sums see its
-// own slots only: a NaN in one owner's cache stays out of the other's partial.
-template <int DT, int D, int MAXS, int VEC>
-__device__ __forceinline__ void reduce_slots(const RowsArgs &A, const float2 (*sm_ml)[16], const float *sm_o, int n0, int n_slots,
-                                             bool any0, bool any1, int64_t head0)
-{
-    constexpr int kOStride = o_stride(D);
-    const int G = A.G, slot = threadIdx.x & 15;
-    for (int idx = (int)threadIdx.x * VEC; idx < G * D; idx += (int)blockDim.x * VEC) {  // whole 16-lane rows: D / VEC >= 16
-        const int g = idx / D, ch = idx % D;
-        const int64_t at = head0 * D + idx, at_l = head0 + g;
-        float x0[VEC] = {}, l0 = -INFINITY;
-        if (A.y && !A.both) {  // the other owner's finished partial
-            load_vec<VEC>(x0, A.a_in + at);
-            l0 = A.lse_in[at_l];
-        }
-        const float2 ml = slot < n_slots ? sm_ml[slot][g] : make_float2(-INFINITY, 0.f);
-        float os[MAXS][VEC];
+// One owner's slots [first, first + n) as a lane reduces them: lane i of every 16-lane row holds the running max and sum of slot
+// first + i, each lane VEC channels of all slots.  Every LDS read leaves at once, in groups of four slots (a uniform branch each; a
+// read past the owner's slots repeats its last one, with weight 0), so rows of few slots pay for few.
+template <int D, int VEC>
+struct SlotSums {
+    static constexpr int kMost = kRowsMaxWaves, kGroup = 4;  // an owner has a slot per wave at most
+    static_assert(kMost % kGroup == 0 && kMost <= 16);
+    float2 ml;
+    float x[kMost][VEC];
+    int n;
+
+    __device__ __forceinline__ void load(const float2 (*sm_ml)[16], const float *sm_o, int first, int n_, int G, int g, int ch)
+    {
+        n = n_;
+        const int lane = threadIdx.x & 15, last = max(n - 1, 0);
+        ml = sm_ml[first + min(lane, last)][g];
+        const float *o = sm_o + (first * G + g) * o_stride(D) + ch;
+        const int slot = G * o_stride(D), last_slot = last * slot;
 #pragma unroll
-        for (int s = 0; s < MAXS; ++s)
-            load_vec<VEC>(os[s], sm_o + (min(s, n_slots - 1) * G + g) * kOStride + ch);
-        const bool mine0 = slot < n0;
-        const float M0 = row_max(mine0 ? ml.x : -INFINITY), M1 = row_max(mine0 ? -INFINITY : ml.x);
-        const float w = ml.y == 0.f ? 0.f : fast_exp2(ml.x - (mine0 ? M0 : M1));  // a slot without steps holds l = 0
-        const float wl = w * ml.y;
-        const float L0 = row_sum(mine0 ? wl : 0.f), L1 = row_sum(mine0 ? 0.f : wl);
-        float o0[VEC] = {}, o1[VEC] = {};
-        weighted_slots<MAXS, VEC>(os, w, n0, o0, o1);
+        for (int s0 = 0; s0 < kMost; s0 += kGroup)
+            if (s0 < n) {
+#pragma unroll
+                for (int s = s0; s < s0 + kGroup; ++s)
+                    load_vec<VEC>(x[s], o + min(s * slot, last_slot));
+            }
+    }
+
+    // GUARD: slots past the owner's are left out instead of given a weight of 0
+    template <bool GUARD, int S = 0>
+    __device__ __forceinline__ void weighted(float w, float (&o)[VEC]) const
+    {
+        if constexpr (S < kMost) {
+            if (S % kGroup == 0 && S >= n)
+                return;
+            const float ws = row_dpp<0x150 + S>(w);  // row_newbcast: lane S's value
+#pragma unroll
+            for (int v = 0; v < VEC; ++v)
+                o[v] = fmaf(ws, GUARD && S >= n ? 0.f : x[S][v], o[v]);
+            weighted<GUARD, S + 1>(w, o);
+        }
+    }
+
+    // The owner's A and lse; without tokens (any false) 0 and -inf.
+    __device__ __forceinline__ void reduce(bool any, float p_shift, float (&a)[VEC], float &lse) const
+    {
+        const bool on = (int)(threadIdx.x & 15) < n;
+        const float m = on ? ml.x : -INFINITY, l = on ? ml.y : 0.f;
+        const float M = row_max_ordered(m);
+        const float w = l == 0.f ? 0.f : fast_exp2(m - M);  // a slot without steps holds l = 0
+        const float L = row_sum(w * l);
+        float o[VEC] = {};
+        weighted<false>(w, o);
         // an infinite value times a stand-in's weight of 0 is NaN: once more, over the slots that there are
-        float nan_if_any = 0.f;
+        float nan_if_any = o[0];
+#pragma unroll
+        for (int v = 1; v < VEC; ++v)
+            nan_if_any += o[v];
+        if (__any(nan_if_any != nan_if_any)) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v)
+                o[v] = 0.f;
+            weighted<true>(w, o);
+        }
+        const float inv = fast_rcp(L);
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
-            nan_if_any += o0[v] + o1[v];
-        if (__any(nan_if_any != nan_if_any)) {
-            float sums[2][VEC] = {};
-#pragma unroll 1
-            for (int s = 0; s < n_slots; ++s) {
-                float x[VEC];
-                load_vec<VEC>(x, sm_o + (s * G + g) * kOStride + ch);
-                const float ws = __shfl(w, s, 16);
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    sums[0][v] = s < n0 ? fmaf(ws, x[v], sums[0][v]) : sums[0][v];
-                    sums[1][v] = s < n0 ? sums[1][v] : fmaf(ws, x[v], sums[1][v]);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                o0[v] = sums[0][v];
-                o1[v] = n0 >= MAXS ? sums[0][v] : sums[1][v];
-            }
+            a[v] = any ? o[v] * inv : 0.f;
+        lse = any ? (M + fast_log2(L) - p_shift) * kLn2 : -INFINITY;
+    }
+};
+
+// Combines the slots' states and writes the row's results.  A thread takes VEC consecutive channels of one query head: this is the
+// tail of a launch, in which a wave's instruction takes 2 ns and two waves of a SIMD take turns, so the channels are spread over four
+// waves - one per SIMD - where the workgroup has more than four.  (A channel per thread of eight waves, both owners' sums formed over
+// all slots, with the argument order of then: tiny fp32 4.95 / 4.77 us, three calls of 16 users 14.25 / 13.85, 32 users with the append
+// 15.12 / 14.97.)  An owner's sums see its own slots only: a NaN in one owner's cache stays out
+// of the other's partial.
+template <int DT, int D, int VEC, bool ONE_PASS>
+__device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (*sm_ml)[16], const float *sm_o, int64_t head0, int G,
+                                             int threads, int n0, int n1, bool any0, bool any1)
+{
+    const int64_t from = head0 * D;
+    auto body = [&](int idx) __attribute__((always_inline)) {
+        asm("" : "+s"(n0), "+s"(n1));  // (what follows from them is computed where it is used, not in front of the loop)
+        const unsigned at = idx, g = at / D, ch = at % D;
+        float x0[VEC] = {}, l0 = -INFINITY;
+        if (R.a_in) {  // the other owner's finished partial
+            load_vec<VEC>(x0, R.a_in + from + at);
+            l0 = (R.lse_in + head0)[g];
         }
-        // an owner without tokens: A = 0, lse = -inf
-        const float i0 = fast_rcp(L0), i1 = fast_rcp(L1);
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            o0[v] = any0 ? (n0 >= MAXS ? o1[v] : o0[v]) * i0 : 0.f;
-            o1[v] = any1 ? o1[v] * i1 : 0.f;
-        }
-        const float e0 = any0 ? (M0 + fast_log2(L0) - Elt<DT>::kPShift) * kLn2 : -INFINITY;
-        const float e1 = any1 ? (M1 + fast_log2(L1) - Elt<DT>::kPShift) * kLn2 : -INFINITY;
-        store_vec<VEC>(A.a0.out + at, o0);
+        SlotSums<D, VEC> s0, s1;
+        s0.load(sm_ml, sm_o, 0, n0, G, g, ch);
+        if (R.out1)
+            s1.load(sm_ml, sm_o, n0, n1, G, g, ch);
+        float o0[VEC], e0;
+        s0.reduce(any0, Elt<DT>::kPShift, o0, e0);
+        store_vec<VEC>(R.out0 + from + at, o0);
         if (ch == 0)
-            A.a0.lse[at_l] = e0;
-        if (!A.y)
-            continue;
+            (R.lse0 + head0)[g] = e0;
+        if (!R.y)
+            return;
         float w0, w1, ls_y, y[VEC];
-        if (A.both) {
-            store_vec<VEC>(A.a1.out + at, o1);
+        if (R.out1) {
+            float o1[VEC], e1;
+            s1.reduce(any1, Elt<DT>::kPShift, o1, e1);
+            store_vec<VEC>(R.out1 + from + at, o1);
             if (ch == 0)
-                A.a1.lse[at_l] = e1;
+                (R.lse1 + head0)[g] = e1;
             merge_weights(e0, e1, w0, w1, ls_y);
 #pragma unroll
             for (int v = 0; v < VEC; ++v)
@@ -193,11 +242,19 @@ __device__ __forceinline__ void reduce_slots(const RowsArgs &A, const float2 (*s
             for (int v = 0; v < VEC; ++v)
                 y[v] = (w0 == 0.f ? 0.f : w0 * x0[v]) + (w1 == 0.f ? 0.f : w1 * o0[v]);
         }
-        store_vec<VEC>(A.y + at, y);
+        store_vec<VEC>(R.y + from + at, y);
         if (ch == 0) {
-            A.lse[at_l] = ls_y;
-            A.w_in[at_l] = w0;
+            (R.lse + head0)[g] = ls_y;
+            (R.w_in + head0)[g] = w0;
         }
+    };
+    int idx = (int)threadIdx.x * VEC;  // whole 16-lane rows: D / VEC >= 16
+    if constexpr (ONE_PASS) {
+        if (idx < G * D)
+            body(idx);
+    } else {
+        for (; idx < G * D; idx += threads * VEC)
+            body(idx);
     }
 }
 
@@ -215,10 +272,13 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     __shared__ RowsShared sm;
     extern __shared__ __align__(16) float sm_o[];  // [waves + 1][G][kOStride]
 
+    // (every line of the arguments that a row needs is asked for here: one that is first touched later costs its whole trip there, the
+    // results' 0.3 us)
+    asm volatile("" ::"s"(A.items[0]), "s"(A.token_stride[0]), "s"(A.k_new[0]), "s"(A.results.out0), "s"(A.results.w_in));
     const int kvh = blockIdx.x;
     const int user = A.order ? scalar_load_i32(A.order, blockIdx.y) : (int)blockIdx.y;
     const int row = user * A.Hkv + kvh, G = A.G;
-    const RowItem i0 = scalar_load_row(A.a0.items, row, A.a0.grow), i1 = scalar_load_row(A.a1.items, row, A.a1.grow);
+    const RowItem i0 = scalar_load_row(A.items[0], row, A.grow[0]), i1 = scalar_load_row(A.items[1], row, A.grow[1]);
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6)), W = A.waves;
 
     LaneConst L;
@@ -234,20 +294,20 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     for (int kk = 0; kk < RB / 64; ++kk)
         qB[kk] = *reinterpret_cast<const u32x4 *>(qrow + kk * 64);
 
+    // One wait for the row and for what its tiles need of the arguments: the compiler otherwise asks for the addresses behind the lengths.
+    asm volatile("" ::"s"(i0.k_base), "s"(i0.v_base), "s"(i1.k_base), "s"(i1.v_base), "s"(A.token_stride[0]), "s"(A.token_stride[1]),
+                 "s"(A.k_ptrs[0]), "s"(A.v_ptrs[0]), "s"(A.k_ptrs[1]), "s"(A.v_ptrs[1]));
     const int S0 = (unsigned)(i0.t_end + kTile - 1) / kTile;
     const int S1 = A.both ? (unsigned)(i1.t_end + kTile - 1) / kTile : 0;
     const unsigned total = S0 + S1;
     const int lo = __umulhi(total * wave, A.wave_mul);  // wave 0: 0
     const int hi = wave + 1 == W ? (int)total : (int)__umulhi(total * (wave + 1), A.wave_mul);
 
-    if (lane == 0) {
-        if (lo < S0 && S0 <= hi) {  // the wave that holds owner 0's last step
-            sm.n0 = wave + 1;
-            sm.extra = S0 < hi;
-        } else if (S0 == 0 && wave == 0) {
-            sm.n0 = sm.extra = 0;
-        }
-    }
+    // Slots [0, n0) are owner 0's: up to the first wave whose run reaches its last step (lane i looks at wave i).  If that run goes on
+    // into owner 1's steps, the extra slot is used.
+    const int run_end = lane + 1 < W ? (int)__umulhi(total * (lane + 1), A.wave_mul) : (int)total;
+    const int n0 = S0 ? (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(run_end >= S0)) + 1 : 0;
+    const bool extra = S0 && ((__builtin_amdgcn_ballot_w64(run_end > S0) >> (n0 - 1)) & 1);
 
     // one run per wave, two for the wave that crosses from owner 0 to owner 1; a wave without steps leaves an idle slot
 #pragma unroll 1
@@ -261,22 +321,22 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
             acc[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (b < e) {
             const int t_end = second ? i1.t_end : i0.t_end, t_last = t_end - 1;
-            L.token_stride = second ? A.a1.token_stride : A.a0.token_stride;
+            L.token_stride = second ? A.token_stride[1] : A.token_stride[0];
             L.k_base = second ? i1.k_base : i0.k_base;
             L.v_base = second ? i1.v_base : i0.v_base;
             if constexpr (PAGED) {
-                L.block_stride = second ? A.a1.block_stride : A.a0.block_stride;
-                L.page_shift = second ? A.a1.page_shift : A.a0.page_shift;
+                L.block_stride = second ? A.paging[1].block_stride : A.paging[0].block_stride;
+                L.page_shift = second ? A.paging[1].page_shift : A.paging[0].page_shift;
                 L.page_mask = (1 << L.page_shift) - 1;
-                L.k_base += reinterpret_cast<uintptr_t>(second ? A.a1.k_pool : A.a0.k_pool);
-                L.v_base += reinterpret_cast<uintptr_t>(second ? A.a1.v_pool : A.a0.v_pool);
-                L.bt_row = (second ? A.a1.block_table : A.a0.block_table) + (int64_t)user * (second ? A.a1.max_blocks : A.a0.max_blocks);
+                L.k_base += reinterpret_cast<uintptr_t>(second ? A.paging[1].k_pool : A.paging[0].k_pool);
+                L.v_base += reinterpret_cast<uintptr_t>(second ? A.paging[1].v_pool : A.paging[0].v_pool);
+                L.bt_row = (second ? A.paging[1].block_table : A.paging[0].block_table) + (int64_t)user * (second ? A.paging[1].max_blocks : A.paging[0].max_blocks);
             } else {
-                L.k_base += user_base(second ? A.a1.k_ptrs : A.a0.k_ptrs, user);
-                L.v_base += user_base(second ? A.a1.v_ptrs : A.a0.v_ptrs, user);
+                L.k_base += user_base(second ? A.k_ptrs[1] : A.k_ptrs[0], user);
+                L.v_base += user_base(second ? A.v_ptrs[1] : A.v_ptrs[0], user);
             }
             L.k_new_row = L.v_new_row = nullptr;
-            const char *k_new = second ? A.a1.k_new : A.a0.k_new, *v_new = second ? A.a1.v_new : A.a0.v_new;
+            const char *k_new = second ? A.k_new[1] : A.k_new[0], *v_new = second ? A.v_new[1] : A.v_new[0];
             // KV append: the wave that holds the row's last token reads it from the caller's buffer, and copies it to the cache
             // (16 bytes per lane, K in the first lanes, V in the next).  Its copy is asked for before the first tile and stored
             // when that has been asked for too: nothing waits for it.
@@ -381,19 +441,23 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     }
     __syncthreads();
 
-    const int n0 = uniform(sm.n0), n_slots = W + uniform(sm.extra);
-    const bool thread_per_channel = G * D <= (int)blockDim.x;
-    auto reduce = [&](auto max_slots, auto vec) {
-        reduce_slots<DT, D, decltype(max_slots)::value, decltype(vec)::value>(A, sm.ml, sm_o, n0, n_slots, S0 > 0, S1 > 0, head0);
+    // The results' pointers are read here, next to the slots: scalar registers that hold them across the tiles are spilled, and a spill
+    // is an instruction each way.  (In front of the barrier the slowest wave would wait for them.)
+    uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const DevResults R = scalar_load_results(args + offsetof(RowsArgs, results));
+    const int n1 = W + extra - n0;
+    auto reduce = [&](auto vec, auto one_pass) __attribute__((always_inline)) {
+        reduce_slots<DT, D, decltype(vec)::value, decltype(one_pass)::value>(R, sm.ml, sm_o, head0, G, W * 64, n0, n1, S0 > 0, S1 > 0);
     };
-    constexpr std::integral_constant<int, 5> few;  // four waves
-    constexpr std::integral_constant<int, kRowsMaxWaves + 1> most;
-    constexpr std::integral_constant<int, 1> one;
-    constexpr std::integral_constant<int, 4> four;
-    if (n_slots <= few)
-        thread_per_channel ? reduce(few, one) : reduce(few, four);
+    // (two waves where there are four: such rows run three workgroups to a compute unit or are the shortest)
+    const int threads = min(W, W > 4 ? 4 : 2) * 64;
+    if (G * D <= threads)
+        reduce(std::integral_constant<int, 1>(), std::true_type());
+    else if (G * D <= 2 * threads)
+        reduce(std::integral_constant<int, 2>(), std::true_type());
     else
-        thread_per_channel ? reduce(most, one) : reduce(most, four);
+        reduce(std::integral_constant<int, 4>(), std::false_type());
 }
 
 }  // namespace spd
