@@ -795,11 +795,11 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     return SPD_OK;
 }
 
-void set_rows_owner(spd::RowsArgs &R, int i, const CachedSchedule *e, const spd_shape *s, const spd_kv_view *v, NewToken nt)
+void set_rows_owner(spd::RowsHead &H, spd::RowsArgs &R, int i, const CachedSchedule *e, const spd_shape *s, const spd_kv_view *v, NewToken nt)
 {
     const OwnerArgs a = owner_args(ScratchPtrs(), e, s, v, nullptr, nullptr, nt.k, nt.v);
-    R.items[i] = reinterpret_cast<const spd::RowItem *>(e->dev);
-    R.grow[i] = e->grow;
+    H.items[i] = reinterpret_cast<const spd::RowItem *>(e->dev);
+    H.grow[i] = e->grow;
     R.token_stride[i] = a.kv.token_stride;
     R.k_ptrs[i] = a.k_ptrs;
     R.v_ptrs[i] = a.v_ptrs;
@@ -815,9 +815,10 @@ struct MergeArgs {
 };
 
 template <int DT, int D, bool PAGED, bool APPEND>
-bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsArgs &args)
+bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsHead &H, const spd::RowsArgs &args)
 {
-    hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0, args);
+    hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0,
+                          H.items[0], H.items[1], H.order, H.q, H.Hkv, H.G, H.grow[0], H.grow[1], H.waves, H.both, args);
     return true;
 }
 
@@ -827,19 +828,19 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
                       NewToken nt, const MergeArgs &mg, hipStream_t stream)
 {
     const int G = s->n_q_heads / s->n_kv_heads, D = s->head_dim;
+    spd::RowsHead H;
     spd::RowsArgs R;
-    set_rows_owner(R, 0, e0, s, v0, which == 1 ? nt : NewToken());
-    set_rows_owner(R, 1, e1 ? e1 : e0, s, e1 ? v1 : v0, e1 ? (which == 0 ? nt : NewToken()) : which == 1 ? nt : NewToken());
-    R.waves = waves;
-    R.both = e1 != nullptr;
-    R.Hkv = s->n_kv_heads;
-    R.Hq = s->n_q_heads;
-    R.G = G;
+    set_rows_owner(H, R, 0, e0, s, v0, which == 1 ? nt : NewToken());
+    set_rows_owner(H, R, 1, e1 ? e1 : e0, s, e1 ? v1 : v0, e1 ? (which == 0 ? nt : NewToken()) : which == 1 ? nt : NewToken());
+    H.waves = waves;
+    H.both = e1 != nullptr;
+    H.Hkv = s->n_kv_heads;
+    H.G = G;
     R.wave_mul = (uint32_t)(((1ull << 32) + waves - 1) / waves);
     R.scale_log2e = s->scale * spd::kLog2e;
     const bool by_length = whole_rows_by_length((int64_t)v0->n_users * s->n_kv_heads, waves, ctx->n_cus);
-    R.order = by_length ? reinterpret_cast<const int32_t *>(e0->dev + e0->off_rows) : nullptr;
-    R.q = static_cast<const char *>(q);
+    H.order = by_length ? reinterpret_cast<const int32_t *>(e0->dev + e0->off_rows) : nullptr;
+    H.q = static_cast<const char *>(q);
     R.results = {out0, lse0, e1 ? out1 : nullptr, lse1, e1 ? nullptr : mg.a_in, mg.lse_in, mg.y, mg.lse, mg.w_in};
     Owner &town = ctx->owner[e1 ? 0 : which];
     const bool timed = ctx->timing && town.ev_used < (int)town.ev_start.size();
@@ -856,7 +857,7 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
             return with_bool(v0->block_size != 0, [&](auto paged) {
                 return with_bool(nt.k != nullptr, [&](auto app) {
                     return launch_rows_instance<decltype(dt)::value, decltype(d)::value, decltype(paged)::value,
-                                                decltype(app)::value>(L, R);
+                                                decltype(app)::value>(L, H, R);
                 });
             });
         });

@@ -1,14 +1,14 @@
 // Short rows whole: one workgroup computes a (user, KV head) row's attention over all of its tokens - one owner's, or both
 // owners' and their merge (Theorem 1) - so that a call is one launch, without chunk partials and without a closing kernel.
-// What bounds it: with few rows latency - two scalar round trips to the row's addresses (0.7 us), the tiles at what one
+// What bounds it: with few rows latency - a scalar round trip to the row's address and the arguments, the tiles at what one
 // compute unit can take in (~40 bytes a cycle: 16 KB per 0.17 us; how fast a wave asks makes no difference, row addresses of one
 // instruction instead of seven gained nothing), and the instructions of the epilogue, ~2 ns each for the wave that executes them; with
 // many rows HBM.  Workgroups of up to twelve waves
 // (three per SIMD) that share a row's steps out evenly, both owners' in one line: the old split of such calls into
 // one-step workgroups spread better over idle compute units but needed a second launch to close.  Measured, split kernels /
-// this one (us per call): fp32 1 user 128 + 16 tokens 8.5 / 4.8 (fused), bf16 32 users of 64-512 + 1-256 with the append
-// 18.9 / 15.0, 256 such users 90.3 / 81.9 (5.5 TB/s), 256 users of 24-192 + 64 51.2 / 31.5; fp16 with 64 channels, 16 users
-// as three calls 19.8 / 13.8.  When it pays is whole_rows_choice's rule (schedule.hpp).
+// this one (us per call): fp32 1 user 128 + 16 tokens 8.5 / 4.6 (fused), bf16 32 users of 64-512 + 1-256 with the append
+// 18.9 / 14.8, 256 such users 90.3 / 81.9 (5.5 TB/s), 256 users of 24-192 + 64 51.2 / 31.5; fp16 with 64 channels, 16 users
+// as three calls 19.8 / 13.4.  When it pays is whole_rows_choice's rule (schedule.hpp).
 #pragma once
 #include <cstddef>
 #include <type_traits>
@@ -48,24 +48,34 @@ struct RowsPaging {
     int64_t block_stride;  // bytes
 };
 
-// In the order in which a wave needs it: a scalar load of the arguments misses once for every 64-byte line, and the lines of one batch
-// of loads don't come at once (until the row's length is there: 1400 -> 1040 cycles in the three calls, 1680 -> 1420 in tiny fp32).  Index 0 and 1: the owners; what belongs to owner 1 repeats owner 0's unless `both`.
-struct RowsArgs {
+// What a row's address and its share of the waves need, as the launch hands it over: as parameters of their own, the first of which
+// arrive in scalar registers with the wave (kernel-argument preloading: up to 14 dwords, not out of a struct).  The row is then asked
+// for by a wave's first instructions instead of behind a scalar round trip to the arguments (us per call: tiny fp32 4.77 / 4.58, fp16
+// three calls of 16 users 13.71 / 13.44, 32 users with the append 14.97 / 14.81).  Index 0 and 1: the owners; what belongs to owner 1
+// repeats owner 0's unless `both`.
+struct RowsHead {
     const RowItem *items[2];
     const int32_t *order;  // [n_users] users in launch order, or nullptr
     const char *q;         // [U][Hq][D]
+    int32_t Hkv, G;
     int32_t grow[2];       // see OwnerArgs
     int32_t waves, both;   // both: both owners' rows, merged into y; else the first's alone - merged too if partials were delivered
-    int32_t Hkv, Hq, G;
+};
+static_assert(sizeof(RowsHead) == 14 * 4, "all of it is preloaded");
+
+// The rest, in the order in which a wave needs it: a scalar load of the arguments misses once for every 64-byte line, and the lines of
+// one batch of loads don't come at once.  The kernel's last parameter.
+struct RowsArgs {
     uint32_t wave_mul;     // ceil(2^32 / waves): x / waves is the high word of x * wave_mul
+    float scale_log2e;
     int64_t token_stride[2];  // bytes
     const char *const *k_ptrs[2], *const *v_ptrs[2];  // contiguous mode with device pointer tables, else nullptr
     const char *k_new[2], *v_new[2];  // KV append, or nullptr
-    float scale_log2e;
     RowsResults results;
     RowsPaging paging[2];
 };
-static_assert(offsetof(RowsArgs, token_stride) == 64, "a row's address and share come from one line");
+constexpr int kRowsArgsAt = sizeof(RowsHead);  // in the kernel's arguments: its parameters lie end to end
+static_assert(alignof(RowsArgs) == 8 && kRowsArgsAt % 8 == 0);
 
 __device__ __forceinline__ RowItem scalar_load_row(const RowItem *items, int idx, int grow)
 {
@@ -87,7 +97,7 @@ struct DevResults {
 };
 __device__ __forceinline__ DevResults scalar_load_results(uintptr_t at)
 {
-    static_assert(sizeof(RowsResults) == 72 && offsetof(RowsArgs, results) % 8 == 0, "read as nine pointers");
+    static_assert(sizeof(RowsResults) == 72 && (kRowsArgsAt + offsetof(RowsArgs, results)) % 8 == 0, "read as nine pointers");
     const const_u64_ptr p = (const_u64_ptr)at;
     return DevResults{(global_f32_ptr)p[0], (global_f32_ptr)p[1], (global_f32_ptr)p[2], (global_f32_ptr)p[3], (global_f32_ptr)p[4],
                       (global_f32_ptr)p[5], (global_f32_ptr)p[6], (global_f32_ptr)p[7], (global_f32_ptr)p[8]};
@@ -261,7 +271,9 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
 // The steps of both owners, laid end to end, are shared out to the waves in equal contiguous runs.  At most one wave gets
 // the end of owner 0's steps and the beginning of owner 1's: its second result goes to one extra slot.
 template <int DT, int D, bool PAGED, bool APPEND>
-__global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsArgs A)
+__global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
+    const RowItem *items0, const RowItem *items1, const int32_t *order, const char *q, int32_t Hkv, int32_t G, int32_t grow0,
+    int32_t grow1, int32_t waves, int32_t both, RowsArgs A)  // see RowsHead
 {
     constexpr int RB = D * Elt<DT>::kBytes;
     constexpr int NA = step_tiles(RB), kTile = step_tokens(RB);
@@ -272,14 +284,15 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     __shared__ RowsShared sm;
     extern __shared__ __align__(16) float sm_o[];  // [waves + 1][G][kOStride]
 
-    // (every line of the arguments that a row needs is asked for here: one that is first touched later costs its whole trip there, the
-    // results' 0.3 us)
-    asm volatile("" ::"s"(A.items[0]), "s"(A.token_stride[0]), "s"(A.k_new[0]), "s"(A.results.out0), "s"(A.results.w_in));
     const int kvh = blockIdx.x;
-    const int user = A.order ? scalar_load_i32(A.order, blockIdx.y) : (int)blockIdx.y;
-    const int row = user * A.Hkv + kvh, G = A.G;
-    const RowItem i0 = scalar_load_row(A.items[0], row, A.grow[0]), i1 = scalar_load_row(A.items[1], row, A.grow[1]);
-    const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6)), W = A.waves;
+    int user = blockIdx.y;
+    if (order) {
+        user = scalar_load_i32(order, user);
+        asm volatile("" : "+s"(user));  // (its wait belongs in here: behind the branch it would be every launch's, for all loads so far)
+    }
+    const int row = user * Hkv + kvh, W = waves;
+    const RowItem i0 = scalar_load_row(items0, row, grow0), i1 = scalar_load_row(items1, row, grow1);
+    const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
 
     LaneConst L;
     L.r = lane & 15;
@@ -287,18 +300,21 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     L.kt = kQuad ? L.grp : L.r >> 2;
     L.kc = kQuad ? L.r >> 2 : L.grp;
     const int head = kQuad ? L.r & (kQuadHeads - 1) : L.r;  // the query head of the lane's Q operand and results
-    const int64_t head0 = (int64_t)user * A.Hq + (int64_t)kvh * G;
+    const int64_t head0 = (int64_t)row * G;
     u32x4 qB[RB / 64];  // (lanes past the last head take a copy of it; their results are not stored)
-    const char *qrow = A.q + (head0 + min(head, G - 1)) * RB + L.kc * 16;
+    const char *qrow = q + (head0 + min(head, G - 1)) * RB + L.kc * 16;
 #pragma unroll
     for (int kk = 0; kk < RB / 64; ++kk)
         qB[kk] = *reinterpret_cast<const u32x4 *>(qrow + kk * 64);
 
     // One wait for the row and for what its tiles need of the arguments: the compiler otherwise asks for the addresses behind the lengths.
+    // (Every line of the arguments that a row needs is asked for here: one that is first touched later costs its whole trip there, the
+    // results' 0.3 us.)
     asm volatile("" ::"s"(i0.k_base), "s"(i0.v_base), "s"(i1.k_base), "s"(i1.v_base), "s"(A.token_stride[0]), "s"(A.token_stride[1]),
-                 "s"(A.k_ptrs[0]), "s"(A.v_ptrs[0]), "s"(A.k_ptrs[1]), "s"(A.v_ptrs[1]));
+                 "s"(A.k_ptrs[0]), "s"(A.v_ptrs[0]), "s"(A.k_ptrs[1]), "s"(A.v_ptrs[1]), "s"(A.wave_mul), "s"(A.k_new[0]), "s"(A.results.out0),
+                 "s"(A.results.w_in));
     const int S0 = (unsigned)(i0.t_end + kTile - 1) / kTile;
-    const int S1 = A.both ? (unsigned)(i1.t_end + kTile - 1) / kTile : 0;
+    const int S1 = both ? (unsigned)(i1.t_end + kTile - 1) / kTile : 0;
     const unsigned total = S0 + S1;
     const int lo = __umulhi(total * wave, A.wave_mul);  // wave 0: 0
     const int hi = wave + 1 == W ? (int)total : (int)__umulhi(total * (wave + 1), A.wave_mul);
@@ -445,7 +461,7 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(RowsA
     // is an instruction each way.  (In front of the barrier the slowest wave would wait for them.)
     uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
-    const DevResults R = scalar_load_results(args + offsetof(RowsArgs, results));
+    const DevResults R = scalar_load_results(args + kRowsArgsAt + offsetof(RowsArgs, results));
     const int n1 = W + extra - n0;
     auto reduce = [&](auto vec, auto one_pass) __attribute__((always_inline)) {
         reduce_slots<DT, D, decltype(vec)::value, decltype(one_pass)::value>(R, sm.ml, sm_o, head0, G, W * 64, n0, n1, S0 > 0, S1 > 0);
