@@ -202,28 +202,25 @@ __device__ __forceinline__ void write_empty_row(const DevItem &it, int G, int Hq
         lse[head0 + threadIdx.x] = -INFINITY;
 }
 
-// Everything a partial kernel needs to know about one owner's call.  A launch serves one owner, or - for the fused
-// decode step - both at once: workgroups [0, n0) take owner 0's pieces, the rest owner 1's.
+// Everything a partial kernel needs to know about one owner's call, besides its items and their growth.  A launch serves one owner,
+// or - for the fused decode step - both at once: workgroups [0, n0) take owner 0's pieces, the rest owner 1's.  First what a
+// workgroup needs before its first tile.
 struct OwnerArgs {
-    const DevItem *items;
-    const char *k_pool;  // paged mode: the items' k_base / v_base are byte offsets inside these; else nullptr
-    const char *v_pool;
     // contiguous mode with device pointer tables: the items' k_base / v_base are byte offsets from k_ptrs[user] /
     // v_ptrs[user] (so that the schedule does not depend on the buffers' addresses); else nullptr
     const char *const *k_ptrs;
     const char *const *v_ptrs;
     KvAddr kv;
-    float *part_o;    // [slots][G][D] chunk partials of split rows
-    float *part_lse;  // [slots][G]
-    float *out;       // [U][Hq][D]
-    float *lse;       // [U][Hq]
+    const char *k_pool;  // paged mode: the items' k_base / v_base are byte offsets inside these; else nullptr
+    const char *v_pool;
     // KV append (protocol step 3a), or nullptr: [U][Hkv][D] rows of the new token's K and V.  The row's last token
     // (position lens[u] - 1) is then taken from here, and the segment that ends the row also writes it to the cache.
     const char *k_new;
     const char *v_new;
-    // Tokens every row has gained since the schedule was built (a decode loop appends one token per user and step):
-    // added to t_end of the segments that end their row, so that a schedule serves several consecutive steps.
-    int32_t grow;
+    float *out;       // [U][Hq][D]
+    float *lse;       // [U][Hq]
+    float *part_o;    // [slots][G][D] chunk partials of split rows
+    float *part_lse;  // [slots][G]
 };
 
 // A work item with the row's growth applied.
@@ -244,13 +241,24 @@ struct RowInfo {
     int32_t first_slot, n_chunks;
 };
 
-// The partial kernel's arguments.
-struct PartialArgs {
-    OwnerArgs a0, a1;
-    int32_t n0;             // workgroups [0, n0) serve a0, the rest a1
+// The partial kernel's arguments.  The head's fields are parameters of their own, which arrive in scalar registers with the wave
+// (kernel-argument preloading: up to 14 dwords, not out of a struct), so that a workgroup's first instructions ask for its item; the
+// owners are the last parameter, read at the one that the workgroup serves.
+struct PartialHead {
+    const DevItem *items[2];
     const char *q;          // [U][Hq][D]
+    int32_t n0;             // workgroups [0, n0) serve owner 0, the rest owner 1
+    // Tokens every row has gained since the schedule was built (a decode loop appends one token per user and step):
+    // added to t_end of the segments that end their row, so that a schedule serves several consecutive steps.
+    int32_t grow[2];
     int32_t Hq, G;
     float scale_log2e;
     int32_t ring_rows;      // result rows a workgroup may hold back in LDS (see the result ring in partial_mfma.hpp); 0: none
 };
+static_assert(sizeof(PartialHead) <= 14 * 4, "all of it is preloaded");
+struct PartialArgs {
+    OwnerArgs owner[2];
+};
+constexpr int kPartialArgsAt = sizeof(PartialHead);  // in the kernel's arguments: padded as its parameters are
+static_assert(alignof(PartialArgs) == 8 && kPartialArgsAt == (3 * 8 + 7 * 4 + 7) / 8 * 8);
 }  // namespace spd

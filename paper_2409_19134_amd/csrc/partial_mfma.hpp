@@ -494,28 +494,30 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 template <int DTYPE, int CHANNELS, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 __global__ __launch_bounds__(HPW ? 512 : kThreads,
                              mfma_waves_per_simd((CHANNELS < 0 ? -CHANNELS : CHANNELS) * Elt<DTYPE>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
-    PartialArgs A)
+    const DevItem *items0, const DevItem *items1, const char *__restrict__ q, int32_t n0, int32_t grow0, int32_t grow1, int32_t Hq, int32_t G,
+    float scale_log2e, int32_t ring_rows, PartialArgs)  // see PartialHead
 {
     constexpr int D = CHANNELS < 0 ? -CHANNELS : CHANNELS;
     constexpr int DT = CHANNELS < 0 ? DTYPE + kFormStep : DTYPE;
-    const OwnerArgs &a0 = A.a0, &a1 = A.a1;
-    const int n0 = A.n0, Hq = A.Hq, G = A.G;
-    const char *__restrict__ q = A.q;
-    const float scale_log2e = A.scale_log2e;
     const bool second = (int)blockIdx.x >= n0;  // workgroup-uniform: which owner this workgroup serves
-    const DevItem *__restrict__ items = second ? a1.items : a0.items;
-    const KvAddr kv = second ? a1.kv : a0.kv;
-    const uintptr_t k_pool = reinterpret_cast<uintptr_t>(second ? a1.k_pool : a0.k_pool);  // 0 unless paged
-    const uintptr_t v_pool = reinterpret_cast<uintptr_t>(second ? a1.v_pool : a0.v_pool);
-    const char *const *k_ptrs = second ? a1.k_ptrs : a0.k_ptrs;  // null unless the view brought device pointer tables
-    const char *const *v_ptrs = second ? a1.v_ptrs : a0.v_ptrs;
-    float *__restrict__ part_o = second ? a1.part_o : a0.part_o;
-    float *__restrict__ part_lse = second ? a1.part_lse : a0.part_lse;
-    float *__restrict__ out = second ? a1.out : a0.out;
-    float *__restrict__ lse = second ? a1.lse : a0.lse;
-    const char *k_new = second ? a1.k_new : a0.k_new;
-    const char *v_new = second ? a1.v_new : a0.v_new;
-    const int grow = second ? a1.grow : a0.grow;
+    const DevItem *__restrict__ items = second ? items1 : items0;
+    const int grow = second ? grow1 : grow0;
+    DevItem it = scalar_load_item(items, second ? (int)blockIdx.x - n0 : (int)blockIdx.x, grow);
+    // The owner's arguments come beside the item, at an address of their own (a field chosen from either owner's is two addresses and a
+    // selection each), and there is one wait for all that the first tile needs: as the compiler placed them, up to six round trips
+    // stood in front of it.  With the preloaded head, us per call before / after: 16 users of 512-4096 + 1-512 tokens fused 32.46 / 31.98,
+    // token-major as two parties with the append 43.43 / 42.28, 32 users of 32768-131072 in 16-token pages 1713 / 1707.
+    const auto own = (const OwnerArgs __attribute__((address_space(4))) *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
+                                                                          kPartialArgsAt + (second ? (int)sizeof(OwnerArgs) : 0));
+    const KvAddr kv = {own->kv.block_table, own->kv.max_blocks, own->kv.page_shift, own->kv.block_stride, own->kv.token_stride, own->kv.head_stride};
+    const uintptr_t k_pool = reinterpret_cast<uintptr_t>(own->k_pool), v_pool = reinterpret_cast<uintptr_t>(own->v_pool);  // 0 unless paged
+    const char *const *k_ptrs = own->k_ptrs, *const *v_ptrs = own->v_ptrs;  // null unless the view brought device pointer tables
+    const char *k_new = own->k_new, *v_new = own->v_new;
+    float *__restrict__ out = own->out, *__restrict__ lse = own->lse;
+    float *__restrict__ part_o = own->part_o, *__restrict__ part_lse = own->part_lse;
+    asm volatile("" ::"s"(it.k_base), "s"(it.v_base), "s"(it.user), "s"(it.rot), "s"(k_ptrs), "s"(v_ptrs), "s"(kv.token_stride), "s"(out));
+    if constexpr (PAGED)
+        asm volatile("" ::"s"(k_pool), "s"(v_pool), "s"(kv.block_table), "s"(kv.max_blocks), "s"(kv.page_shift), "s"(kv.block_stride));
     __shared__ float sm_m[kWaves][16];
     __shared__ float sm_l[kWaves][16];
     __shared__ float *ring_dst_o[kRingMaxRows], *ring_dst_l[kRingMaxRows];  // where the ring's rows go
@@ -589,7 +591,6 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
             load_tile<RB, NA, PAGED, APPEND, kRange>(T0, L, tb, t_last, P, kStep);
     };
 
-    DevItem it = scalar_load_item(items, second ? (int)blockIdx.x - n0 : (int)blockIdx.x, grow);
     if (it.n_chunks == 0) {  // a row without tokens (head-per-wave: a user without tokens) is a piece of its own
         if (HPW) {
             const int64_t head0 = (int64_t)it.user * Hq + (int64_t)(it.kv_head + wave) * G;
@@ -683,9 +684,9 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
             float *res_l = direct ? lse + head0 : part_lse + slot * G;
             // the row waits in the wave's ring - unless the piece ends here with an empty ring, or there is no ring
             const bool last = it.next < 0;
-            const bool to_ring = staged && A.ring_rows > 0 && !(last && n_ring == 0);
+            const bool to_ring = staged && ring_rows > 0 && !(last && n_ring == 0);
             const int hrow = hpw_ring_row_floats(D, G);
-            float *const ring_w = sm_o + (int)(blockDim.x >> 6) * o_wave_stride + wave * A.ring_rows * hrow;
+            float *const ring_w = sm_o + (int)(blockDim.x >> 6) * o_wave_stride + wave * ring_rows * hrow;
             if (staged) {
                 // Through a wave-private LDS tile, so that the wave stores whole rows with consecutive lanes (storing
                 // straight from the accumulator layout puts 16 bytes per lane into 16 different cache lines per
@@ -715,7 +716,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
                         const f32x4 w = *reinterpret_cast<const f32x4 *>(stage + (i / D) * kOStride + (i % D));
                         *reinterpret_cast<f32x4 *>(res + i) = w;
                     }
-                } else if (last || n_ring == A.ring_rows) {
+                } else if (last || n_ring == ring_rows) {
                     typedef __attribute__((address_space(1))) float *global_f32;
                     for (int k = 0; k < n_ring; ++k) {
                         const float *row = ring_w + k * hrow;
@@ -786,7 +787,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
         const int64_t head0 = (int64_t)it.user * Hq + (int64_t)it.kv_head * G;
         // the row goes to the ring - unless the piece ends here with an empty ring, or there is no ring
         const bool last = it.next < 0;
-        const bool to_ring = A.ring_rows > 0 && !(last && n_ring == 0);
+        const bool to_ring = ring_rows > 0 && !(last && n_ring == 0);
         const int GD = G * D, ring_stride = ring_row_floats(D, G);
         float *const ring = sm_o + kWaves * o_wave_stride;
         float *const dst_o = direct ? out + head0 * D : part_o + (int64_t)it.slot * GD;
@@ -823,7 +824,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
                 ring_dst_l[n_ring] = dst_l;
             }
             ++n_ring;
-            if (last || n_ring == A.ring_rows) {
+            if (last || n_ring == ring_rows) {
                 __syncthreads();
                 for (int i = 0; i < n_ring; ++i) {
                     const lds_f32 src = (lds_f32)(ring + i * ring_stride);

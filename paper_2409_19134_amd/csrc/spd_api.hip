@@ -582,12 +582,11 @@ ScratchPtrs scratch_of(const Owner &own)
     return sp;
 }
 
-OwnerArgs owner_args(const ScratchPtrs &own, const CachedSchedule *e, const spd_shape *s, const spd_kv_view *v, float *out,
+OwnerArgs owner_args(const ScratchPtrs &own, const spd_shape *s, const spd_kv_view *v, float *out,
                      float *lse, const void *k_new, const void *v_new)
 {
     const int es = elt_size(s->dtype);
     OwnerArgs a;
-    a.items = reinterpret_cast<const DevItem *>(e->dev);
     a.k_pool = v->block_size ? static_cast<const char *>(v->k_pool) : nullptr;
     a.v_pool = v->block_size ? static_cast<const char *>(v->v_pool) : nullptr;
     a.k_ptrs = v->block_size ? nullptr : reinterpret_cast<const char *const *>(v->k_ptrs_dev);
@@ -604,7 +603,6 @@ OwnerArgs owner_args(const ScratchPtrs &own, const CachedSchedule *e, const spd_
     a.lse = lse;
     a.k_new = static_cast<const char *>(k_new);
     a.v_new = static_cast<const char *>(v_new);
-    a.grow = e->grow;
     return a;
 }
 
@@ -634,6 +632,7 @@ struct MfmaLaunch {
     uint32_t lds;
     hipStream_t stream;
     hipEvent_t ev0, ev1;  // both null unless timing is armed: receive the kernel's own start and stop time stamps
+    spd::PartialHead head;
     spd::PartialArgs args;
 };
 
@@ -658,11 +657,13 @@ bool launch_mfma(const MfmaLaunch &L)
         return false;
     } else if constexpr (spd::form_of(DT) != 0) {
         hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT - spd::kFormStep, -D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
-                              L.stream, L.ev0, L.ev1, 0, L.args);
+                              L.stream, L.ev0, L.ev1, 0, L.head.items[0], L.head.items[1], L.head.q, L.head.n0, L.head.grow[0],
+                              L.head.grow[1], L.head.Hq, L.head.G, L.head.scale_log2e, L.head.ring_rows, L.args);
         return true;
     } else {
         hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT, D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
-                              L.stream, L.ev0, L.ev1, 0, L.args);
+                              L.stream, L.ev0, L.ev1, 0, L.head.items[0], L.head.items[1], L.head.q, L.head.n0, L.head.grow[0],
+                              L.head.grow[1], L.head.Hq, L.head.G, L.head.scale_log2e, L.head.ring_rows, L.args);
         return true;
     }
 }
@@ -682,8 +683,8 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     if (n0 + n1 == 0)
         return SPD_OK;
     // the public owner is entry point 1: the new token, if any, belongs to whichever of the two that is
-    const OwnerArgs a0 = owner_args(sp0, e0, s, v0, out0, lse0, which == 1 ? nt.k : nullptr, which == 1 ? nt.v : nullptr);
-    const OwnerArgs a1 = e1 ? owner_args(sp1, e1, s, v1, out1, lse1, which == 0 ? nt.k : nullptr,
+    const OwnerArgs a0 = owner_args(sp0, s, v0, out0, lse0, which == 1 ? nt.k : nullptr, which == 1 ? nt.v : nullptr);
+    const OwnerArgs a1 = e1 ? owner_args(sp1, s, v1, out1, lse1, which == 0 ? nt.k : nullptr,
                                          which == 0 ? nt.v : nullptr)
                             : a0;
     const int G = s->n_q_heads / s->n_kv_heads;
@@ -705,13 +706,18 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     L.stream = stream;
     L.ev0 = ev0;
     L.ev1 = ev1;
-    L.args.a0 = a0;
-    L.args.a1 = a1;
-    L.args.n0 = (int)n0;
-    L.args.q = static_cast<const char *>(q);
-    L.args.Hq = s->n_q_heads;
-    L.args.G = G;
-    L.args.scale_log2e = c;
+    L.args.owner[0] = a0;
+    L.args.owner[1] = a1;
+    const CachedSchedule *const entry[2] = {e0, e1 ? e1 : e0};
+    for (int i = 0; i < 2; ++i) {
+        L.head.items[i] = reinterpret_cast<const DevItem *>(entry[i]->dev);
+        L.head.grow[i] = entry[i]->grow;
+    }
+    L.head.n0 = (int)n0;
+    L.head.q = static_cast<const char *>(q);
+    L.head.Hq = s->n_q_heads;
+    L.head.G = G;
+    L.head.scale_log2e = c;
     // Two steps in flight (PREFETCH) or one.  Clearly more pieces than the one-step kernel holds at once, three per CU
     // (a few left over just start a little later), run on the two-step kernel, two per CU: fewer workgroup starts and
     // half as many dependent memory round trips per wave.  Everything that is resident at once runs on the one-step
@@ -738,7 +744,7 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     if (2 * segments >= min_x2 * (n0 + n1) && L.lds > 0)  // (head per wave without its staging tiles has no ring either)
         ring_rows = std::min(ctx->result_rows, hpw ? spd::hpw_ring_rows_that_fit(D, G, waves) : spd::ring_rows_that_fit(D, G, two_per_cu));
     L.lds += (uint32_t)(ring_rows * sizeof(float) * (hpw ? (size_t)spd::hpw_ring_row_floats(D, G) * waves : (size_t)spd::ring_row_floats(D, G)));
-    L.args.ring_rows = ring_rows;
+    L.head.ring_rows = ring_rows;
     // fp32 rows of 512 bytes with up to four query heads per KV head run on the 4x4 matrix blocks, a quarter of the 16x16
     // tile's time per step (measured in partial_mfma.hpp).  Five heads would need a second set of blocks and of
     // accumulators (32 registers more than the kernel has), and the 16x16 tile is fuller there.  With 64 channels the
@@ -797,7 +803,7 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
 
 void set_rows_owner(spd::RowsHead &H, spd::RowsArgs &R, int i, const CachedSchedule *e, const spd_shape *s, const spd_kv_view *v, NewToken nt)
 {
-    const OwnerArgs a = owner_args(ScratchPtrs(), e, s, v, nullptr, nullptr, nt.k, nt.v);
+    const OwnerArgs a = owner_args(ScratchPtrs(), s, v, nullptr, nullptr, nt.k, nt.v);
     H.items[i] = reinterpret_cast<const spd::RowItem *>(e->dev);
     H.grow[i] = e->grow;
     R.token_stride[i] = a.kv.token_stride;
