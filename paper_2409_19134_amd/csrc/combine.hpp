@@ -289,8 +289,9 @@ __global__ __launch_bounds__(D) void finalize_step_kernel(const RowInfo *__restr
 
 // ---- the closing kernel of steps and calls whose rows hold at most kCloseMaxChunks chunks ----------------------------
 // A thread takes four consecutive channels of one (user, query head); the sixteen lanes of a DPP row share a head, and lane i
-// of them holds the log-sum-exps (and weights) of chunks i and i + 16.  Bound by latency: three dependent round trips
-// (arguments, RowInfo, partials) and ~2 ns per instruction of a wave, so every load of both owners leaves at once, a
+// of them holds the log-sum-exps (and weights) of chunks i and i + 16.  Bound by latency: two dependent round trips
+// (RowInfo with the arguments, partials; with the arguments in front of the RowInfo the headline batch took 31.94 us instead of 31.66,
+// token-major as two parties with the append 42.30 instead of 42.08) and ~2 ns per instruction of a wave, so every load of both owners leaves at once, a
 // chunk's weight is computed once per row instead of once per channel, and 64-thread workgroups spread over the device.
 // Measured against the kernels above, which take launches with rows of more chunks (us per call, before / after): the headline
 // batch, 16 users of 512-4096 + 1-512 tokens, fused 33.6 / 33.0, 16 users of 96-768 + 256 13.4 / 12.9, 4 of them 8.8 / 8.4.  The
@@ -397,34 +398,40 @@ struct CloseRow {
     }
 };
 
-struct CloseArgs {
+// The head's fields are parameters of their own, preloaded into scalar registers: the RowInfos are asked for by the first instructions,
+// the rest of the arguments comes beside them.
+struct CloseHead {
     const RowInfo *rows_in, *rows_out;  // rows_in: nullptr if the first owner's partials are the caller's, finished
+    int32_t heads, G;  // heads: users * Hq
+    uint32_t g_mul;    // ceil(2^32 / G): x / G is the high word of x * g_mul
+};
+struct CloseArgs {
     const float *part_o_in, *part_lse_in, *part_o_out, *part_lse_out;
     const float *a_in_r, *lse_in_r;
     float *a_in, *lse_in, *a_out, *lse_out;
     float *y, *lse, *w_in;
-    int32_t heads, G;  // heads: users * Hq
-    uint32_t g_mul;    // ceil(2^32 / G): x / G is the high word of x * g_mul
 };
 
 // MAXI, MAXO: at least the chunks of any row of the first and the second owner; both owners' rows and their merge (as
 // finalize_step_kernel), or with MAXI = 0 the second owner's rows alone (as combine_chunks_kernel).
 template <int D, int MAXI, int MAXO>
-__global__ __launch_bounds__(64) void close_kernel(CloseArgs A)
+__global__ __launch_bounds__(64) void close_kernel(const RowInfo *rows_in, const RowInfo *rows_out, int32_t heads, int32_t G, uint32_t g_mul,
+                                                   CloseArgs A)
 {
     const int idx = (blockIdx.x * 64 + threadIdx.x) * 4, ch = idx % D;
     const int64_t head = idx / D;
-    if (head >= A.heads)
+    if (head >= heads)
         return;  // whole 16-lane rows
-    const int row = A.G == 1 ? (int)head : (int)__umulhi((unsigned)head, A.g_mul), g = (int)head - row * A.G;
-    const RowInfo ro = A.rows_out[row], ri = MAXI && A.rows_in ? A.rows_in[row] : RowInfo{0, 1};
+    const int row = G == 1 ? (int)head : (int)__umulhi((unsigned)head, g_mul), g = (int)head - row * G;
+    const RowInfo ro = rows_out[row], ri = MAXI && rows_in ? rows_in[row] : RowInfo{0, 1};
+    asm volatile("" ::"s"(A.part_o_out), "s"(A.y), "s"(A.w_in));  // (every line of them is asked for here)
     CloseRow<D, MAXO> out;
     f32x4 x1;
     float l1;
     if constexpr (MAXI == 0) {
         if (ro.n_chunks <= 1)
             return;  // written by the partial kernel
-        out.load(ro, A.G, g, head, ch, A.part_o_out, A.part_lse_out, A.a_out, A.lse_out);
+        out.load(ro, G, g, head, ch, A.part_o_out, A.part_lse_out, A.a_out, A.lse_out);
         __builtin_amdgcn_sched_barrier(0);  // no load sinks to its use: they all leave now
         out.reduce(x1, l1);
         *reinterpret_cast<f32x4 *>(A.a_out + head * D + ch) = x1;
@@ -432,8 +439,8 @@ __global__ __launch_bounds__(64) void close_kernel(CloseArgs A)
             A.lse_out[head] = l1;
     } else {
         CloseRow<D, MAXI> in;
-        in.load(ri, A.G, g, head, ch, A.part_o_in, A.part_lse_in, A.a_in_r, A.lse_in_r);
-        out.load(ro, A.G, g, head, ch, A.part_o_out, A.part_lse_out, A.a_out, A.lse_out);
+        in.load(ri, G, g, head, ch, A.part_o_in, A.part_lse_in, A.a_in_r, A.lse_in_r);
+        out.load(ro, G, g, head, ch, A.part_o_out, A.part_lse_out, A.a_out, A.lse_out);
         __builtin_amdgcn_sched_barrier(0);
         f32x4 x0;
         float l0;

@@ -881,15 +881,15 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
 // The closing kernel for rows of at most kCloseMaxChunks chunks (max_in: of the first owner, 0 for the combine of one owner's rows,
 // which it only does for rows of more than kCombineSmall); false if the general kernels have to do it: a row has more, or the heads
 // do not fit its indices.
-bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd::CloseArgs &C, hipStream_t stream)
+bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd::CloseHead H, const spd::CloseArgs &C, hipStream_t stream)
 {
     const int D = s->head_dim;
     const int64_t heads = (int64_t)n_users * s->n_q_heads;
     if (std::max(max_in, max_out) > spd::kCloseMaxChunks || (max_in == 0 && max_out <= spd::kCombineSmall) || heads * D >= (1ll << 30))
         return false;
-    C.heads = (int32_t)heads;
-    C.G = s->n_q_heads / s->n_kv_heads;
-    C.g_mul = (uint32_t)(((1ull << 32) + C.G - 1) / C.G);
+    H.heads = (int32_t)heads;
+    H.G = s->n_q_heads / s->n_kv_heads;
+    H.g_mul = (uint32_t)(((1ull << 32) + H.G - 1) / H.G);
     const dim3 grid((unsigned)((heads * D / 4 + 63) / 64));
     auto size = [](int n) { return n <= 4 ? 4 : n <= 8 ? 8 : n <= 16 ? 16 : 32; };
     return with_value<64, 128>(D, [&](auto d) {
@@ -899,7 +899,7 @@ bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd:
                     return false;
                 } else {
                     hipLaunchKernelGGL((spd::close_kernel<decltype(d)::value, decltype(mi)::value, decltype(mo)::value>), grid, dim3(64), 0,
-                                       stream, C);
+                                       stream, H.rows_in, H.rows_out, H.heads, H.G, H.g_mul, C);
                     return true;
                 }
             });
@@ -916,12 +916,13 @@ int launch_combine(spd_ctx *ctx, int which, const CachedSchedule *e, const spd_s
     Owner &own = ctx->owner[which];
     const int G = s->n_q_heads / s->n_kv_heads;
     spd::CloseArgs C = {};
-    C.rows_out = reinterpret_cast<const RowInfo *>(e->dev + e->off_info);
+    spd::CloseHead H = {};
+    H.rows_out = reinterpret_cast<const RowInfo *>(e->dev + e->off_info);
     C.part_o_out = own.part_o;
     C.part_lse_out = own.part_lse;
     C.a_out = out;
     C.lse_out = lse;
-    if (launch_close(s, n_users, 0, e->max_chunks, C, stream)) {
+    if (launch_close(s, n_users, 0, e->max_chunks, H, C, stream)) {
         SPD_HIP(ctx, hipGetLastError());
         return SPD_OK;
     }
@@ -990,8 +991,9 @@ int launch_finalize(spd_ctx *ctx, const spd_shape *shape, int n_users, const Cac
     const RowInfo *ri = ep ? reinterpret_cast<const RowInfo *>(ep->dev + ep->off_info) : nullptr;
     const RowInfo *ro = reinterpret_cast<const RowInfo *>(eo->dev + eo->off_info);
     spd::CloseArgs C = {};
-    C.rows_in = ri;
-    C.rows_out = ro;
+    spd::CloseHead H = {};
+    H.rows_in = ri;
+    H.rows_out = ro;
     C.part_o_in = sp_in.part_o;
     C.part_lse_in = sp_in.part_lse;
     C.part_o_out = sp_out.part_o;
@@ -1005,7 +1007,7 @@ int launch_finalize(spd_ctx *ctx, const spd_shape *shape, int n_users, const Cac
     C.y = y;
     C.lse = lse;
     C.w_in = w_in;
-    if (launch_close(shape, n_users, ep ? std::max(1, ep->max_chunks) : 1, eo->max_chunks, C, stream)) {
+    if (launch_close(shape, n_users, ep ? std::max(1, ep->max_chunks) : 1, eo->max_chunks, H, C, stream)) {
         SPD_HIP(ctx, hipGetLastError());
         return SPD_OK;
     }
