@@ -172,11 +172,12 @@ __device__ __forceinline__ void reduce_row(const RowLoads<MAXC> &r, float &a_out
 
 // One workgroup of D threads per (split row, query head); grid (split rows, G).
 template <int D>
-__global__ __launch_bounds__(D) void combine_chunks_kernel(const CombineRow *__restrict__ rows, int Hq, int G,
-                                                           const float *__restrict__ part_o,
-                                                           const float *__restrict__ part_lse,
-                                                           float *__restrict__ out, float *__restrict__ lse)
+__global__ __launch_bounds__(D) void combine_chunks_kernel(Address rows_, int Hq, int G, Address part_o_, Address part_lse_, Address out_,
+                                                           Address lse_)
 {
+    const CombineRow *__restrict__ rows = global_pointer<const CombineRow>(rows_);
+    const float *__restrict__ part_o = global_pointer<const float>(part_o_), *__restrict__ part_lse = global_pointer<const float>(part_lse_);
+    float *__restrict__ out = global_pointer<float>(out_), *__restrict__ lse = global_pointer<float>(lse_);
     __shared__ float sm_w[kCombineStage];
     __shared__ float sm_red[D];
     const CombineRow r = rows[blockIdx.x];  // grid: (split rows, G) - no integer division on a latency-bound path
@@ -415,7 +416,7 @@ struct CloseArgs {
 // MAXI, MAXO: at least the chunks of any row of the first and the second owner; both owners' rows and their merge (as
 // finalize_step_kernel), or with MAXI = 0 the second owner's rows alone (as combine_chunks_kernel).
 template <int D, int MAXI, int MAXO>
-__global__ __launch_bounds__(64) void close_kernel(const RowInfo *rows_in, const RowInfo *rows_out, int32_t heads, int32_t G, uint32_t g_mul,
+__global__ __launch_bounds__(64) void close_kernel(Address rows_in, Address rows_out, int32_t heads, int32_t G, uint32_t g_mul,
                                                    CloseArgs A)
 {
     const int idx = (blockIdx.x * 64 + threadIdx.x) * 4, ch = idx % D;
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(64) void close_kernel(const RowInfo *rows_in, const
     if (head >= heads)
         return;  // whole 16-lane rows
     const int row = G == 1 ? (int)head : (int)__umulhi((unsigned)head, g_mul), g = (int)head - row * G;
-    const RowInfo ro = rows_out[row], ri = MAXI && rows_in ? rows_in[row] : RowInfo{0, 1};
+    const RowInfo ro = global_pointer<const RowInfo>(rows_out)[row], ri = MAXI && rows_in ? global_pointer<const RowInfo>(rows_in)[row] : RowInfo{0, 1};
     asm volatile("" ::"s"(A.part_o_out), "s"(A.y), "s"(A.w_in));  // (every line of them is asked for here)
     CloseRow<D, MAXO> out;
     f32x4 x1;
@@ -471,24 +472,25 @@ __global__ __launch_bounds__(64) void close_kernel(const RowInfo *rows_in, const
 }
 
 // one thread per 4 channels of one row; block (vec_per_row, rows per block)
-__global__ __launch_bounds__(256) void lse_merge_kernel(int n_rows, int vec_per_row, const float *a0,
-                                                         const float *__restrict__ lse0, const float *a1,
-                                                         const float *__restrict__ lse1, float *y,
-                                                         float *__restrict__ lse_out, float *__restrict__ w0_out)
+__global__ __launch_bounds__(256) void lse_merge_kernel(int n_rows, int vec_per_row, Address a0_, Address lse0_, Address a1_, Address lse1_,
+                                                         Address y_, Address lse_out_, Address w0_out_)
 {
+    const float *lse0 = global_pointer<const float>(lse0_), *lse1 = global_pointer<const float>(lse1_);
+    const f32x4 *a0 = global_pointer<const f32x4>(a0_), *a1 = global_pointer<const f32x4>(a1_);
+    f32x4 *y = global_pointer<f32x4>(y_);
+    float *lse_out = global_pointer<float>(lse_out_), *w0_out = global_pointer<float>(w0_out_);
     const int64_t row = (int64_t)blockIdx.x * blockDim.y + threadIdx.y;
     if (row >= n_rows)
         return;
     const int64_t i = row * vec_per_row + threadIdx.x;
     float w0, w1, ls;
     merge_weights(lse0[row], lse1[row], w0, w1, ls);
-    const f32x4 x0 = reinterpret_cast<const f32x4 *>(a0)[i];
-    const f32x4 x1 = reinterpret_cast<const f32x4 *>(a1)[i];
+    const f32x4 x0 = a0[i], x1 = a1[i];
     f32x4 r;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         r[e] = (w0 == 0.f ? 0.f : w0 * x0[e]) + (w1 == 0.f ? 0.f : w1 * x1[e]);  // a zero weight ignores its side entirely
-    reinterpret_cast<f32x4 *>(y)[i] = r;
+    y[i] = r;
     if (threadIdx.x == 0) {
         if (lse_out)
             lse_out[row] = ls;

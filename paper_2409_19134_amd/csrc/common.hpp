@@ -224,9 +224,8 @@ struct OwnerArgs {
 };
 
 // A work item with the row's growth applied.
-__device__ __forceinline__ DevItem scalar_load_item(const DevItem *items, int idx, int grow)
+__device__ __forceinline__ DevItem grown(DevItem it, int grow)
 {
-    DevItem it = scalar_load_item(items, idx);
     it.t_end += (it.rot & kEndsRow) ? grow : 0;
     return it;
 }

@@ -25,6 +25,7 @@
 
 namespace {
 
+using spd::Address;
 using spd::CombineRow;
 using spd::DevItem;
 using spd::KvAddr;
@@ -657,12 +658,12 @@ bool launch_mfma(const MfmaLaunch &L)
         return false;
     } else if constexpr (spd::form_of(DT) != 0) {
         hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT - spd::kFormStep, -D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
-                              L.stream, L.ev0, L.ev1, 0, L.head.items[0], L.head.items[1], L.head.q, L.head.n0, L.head.grow[0],
+                              L.stream, L.ev0, L.ev1, 0, (Address)L.head.items[0], (Address)L.head.items[1], (Address)L.head.q, L.head.n0, L.head.grow[0],
                               L.head.grow[1], L.head.Hq, L.head.G, L.head.scale_log2e, L.head.ring_rows, L.args);
         return true;
     } else {
         hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT, D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
-                              L.stream, L.ev0, L.ev1, 0, L.head.items[0], L.head.items[1], L.head.q, L.head.n0, L.head.grow[0],
+                              L.stream, L.ev0, L.ev1, 0, (Address)L.head.items[0], (Address)L.head.items[1], (Address)L.head.q, L.head.n0, L.head.grow[0],
                               L.head.grow[1], L.head.Hq, L.head.G, L.head.scale_log2e, L.head.ring_rows, L.args);
         return true;
     }
@@ -824,7 +825,7 @@ template <int DT, int D, bool PAGED, bool APPEND>
 bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsHead &H, const spd::RowsArgs &args)
 {
     hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0,
-                          H.items[0], H.items[1], H.order, H.q, H.Hkv, H.G, H.grow[0], H.grow[1], H.waves, H.both, args);
+                          (Address)H.items[0], (Address)H.items[1], (Address)H.order, (Address)H.q, H.Hkv, H.G, H.grow[0], H.grow[1], H.waves, H.both, args);
     return true;
 }
 
@@ -899,7 +900,7 @@ bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd:
                     return false;
                 } else {
                     hipLaunchKernelGGL((spd::close_kernel<decltype(d)::value, decltype(mi)::value, decltype(mo)::value>), grid, dim3(64), 0,
-                                       stream, H.rows_in, H.rows_out, H.heads, H.G, H.g_mul, C);
+                                       stream, (Address)H.rows_in, (Address)H.rows_out, H.heads, H.G, H.g_mul, C);
                     return true;
                 }
             });
@@ -929,11 +930,11 @@ int launch_combine(spd_ctx *ctx, int which, const CachedSchedule *e, const spd_s
     const CombineRow *rows = reinterpret_cast<const CombineRow *>(e->dev + e->off_rows);
     const dim3 grid((unsigned)e->n_split_rows, (unsigned)G);
     if (s->head_dim == 64)
-        hipLaunchKernelGGL((spd::combine_chunks_kernel<64>), grid, dim3(64), 0, stream, rows, s->n_q_heads, G,
-                           own.part_o, own.part_lse, out, lse);
+        hipLaunchKernelGGL((spd::combine_chunks_kernel<64>), grid, dim3(64), 0, stream, (Address)rows, s->n_q_heads, G,
+                           (Address)own.part_o, (Address)own.part_lse, (Address)out, (Address)lse);
     else
-        hipLaunchKernelGGL((spd::combine_chunks_kernel<128>), grid, dim3(128), 0, stream, rows, s->n_q_heads, G,
-                           own.part_o, own.part_lse, out, lse);
+        hipLaunchKernelGGL((spd::combine_chunks_kernel<128>), grid, dim3(128), 0, stream, (Address)rows, s->n_q_heads, G,
+                           (Address)own.part_o, (Address)own.part_lse, (Address)out, (Address)lse);
     SPD_HIP(ctx, hipGetLastError());
     return SPD_OK;
 }
@@ -1719,7 +1720,8 @@ int spd_lse_merge(spd_ctx *ctx, int32_t n_rows, int32_t head_dim, const float *a
     const int rows_per_block = std::max(1, 256 / vpr);
     const unsigned blocks = (unsigned)(((int64_t)n_rows + rows_per_block - 1) / rows_per_block);
     hipLaunchKernelGGL(spd::lse_merge_kernel, dim3(blocks), dim3((unsigned)vpr, (unsigned)rows_per_block), 0,
-                       static_cast<hipStream_t>(hip_stream), n_rows, vpr, a0, lse0, a1, lse1, y, lse_out, w0_out);
+                       static_cast<hipStream_t>(hip_stream), n_rows, vpr, (Address)a0, (Address)lse0, (Address)a1, (Address)lse1, (Address)y,
+                       (Address)lse_out, (Address)w0_out);
     SPD_HIP(ctx, hipGetLastError());
     return SPD_OK;
 }

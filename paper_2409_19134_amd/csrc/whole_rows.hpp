@@ -77,12 +77,12 @@ struct RowsArgs {
 constexpr int kRowsArgsAt = sizeof(RowsHead);  // in the kernel's arguments: its parameters lie end to end
 static_assert(alignof(RowsArgs) == 8 && kRowsArgsAt % 8 == 0);
 
-__device__ __forceinline__ RowItem scalar_load_row(const RowItem *items, int idx, int grow)
+__device__ __forceinline__ RowItem scalar_load_row(Address items, int idx, int grow)
 {
     static_assert(sizeof(RowItem) == 32, "a row is read as eight dwords at once");
     typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
     typedef const u32x8 __attribute__((address_space(4))) *const_u32x8_ptr;
-    const u32x8 w = *(const_u32x8_ptr)(uintptr_t)(items + idx);
+    const u32x8 w = *(const_u32x8_ptr)(items + (int64_t)idx * sizeof(RowItem));
     RowItem it;
     it.k_base = reinterpret_cast<const char *>(((uint64_t)w[1] << 32) | w[0]);
     it.v_base = reinterpret_cast<const char *>(((uint64_t)w[3] << 32) | w[2]);
@@ -272,7 +272,7 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
 // the end of owner 0's steps and the beginning of owner 1's: its second result goes to one extra slot.
 template <int DT, int D, bool PAGED, bool APPEND>
 __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
-    const RowItem *items0, const RowItem *items1, const int32_t *order, const char *q, int32_t Hkv, int32_t G, int32_t grow0,
+    Address items0, Address items1, Address order, Address q, int32_t Hkv, int32_t G, int32_t grow0,
     int32_t grow1, int32_t waves, int32_t both, RowsArgs A)  // see RowsHead
 {
     constexpr int RB = D * Elt<DT>::kBytes;
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
     const int kvh = blockIdx.x;
     int user = blockIdx.y;
     if (order) {
-        user = scalar_load_i32(order, user);
+        user = scalar_load_i32(reinterpret_cast<const int32_t *>(order), user);
         asm volatile("" : "+s"(user));  // (its wait belongs in here: behind the branch it would be every launch's, for all loads so far)
     }
     const int row = user * Hkv + kvh, W = waves;
@@ -302,10 +302,10 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
     const int head = kQuad ? L.r & (kQuadHeads - 1) : L.r;  // the query head of the lane's Q operand and results
     const int64_t head0 = (int64_t)row * G;
     u32x4 qB[RB / 64];  // (lanes past the last head take a copy of it; their results are not stored)
-    const char *qrow = q + (head0 + min(head, G - 1)) * RB + L.kc * 16;
+    const Address qrow = q + (head0 + min(head, G - 1)) * RB + L.kc * 16;
 #pragma unroll
     for (int kk = 0; kk < RB / 64; ++kk)
-        qB[kk] = *reinterpret_cast<const u32x4 *>(qrow + kk * 64);
+        qB[kk] = *(const u32x4 __attribute__((address_space(1))) *)(qrow + kk * 64);
 
     // One wait for the row and for what its tiles need of the arguments: the compiler otherwise asks for the addresses behind the lengths.
     // (Every line of the arguments that a row needs is asked for here: one that is first touched later costs its whole trip there, the
