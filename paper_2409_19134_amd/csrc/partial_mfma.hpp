@@ -494,13 +494,13 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 template <int DTYPE, int CHANNELS, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 __global__ __launch_bounds__(HPW ? 512 : kThreads,
                              mfma_waves_per_simd((CHANNELS < 0 ? -CHANNELS : CHANNELS) * Elt<DTYPE>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
-    const DevItem *items0, const DevItem *items1, const char *__restrict__ q, int32_t n0, int32_t grow0, int32_t grow1, int32_t Hq, int32_t G,
+    Address items0, Address items1, Address q, int32_t n0, int32_t grow0, int32_t grow1, int32_t Hq, int32_t G,
     float scale_log2e, int32_t ring_rows, PartialArgs)  // see PartialHead
 {
     constexpr int D = CHANNELS < 0 ? -CHANNELS : CHANNELS;
     constexpr int DT = CHANNELS < 0 ? DTYPE + kFormStep : DTYPE;
     const bool second = (int)blockIdx.x >= n0;  // workgroup-uniform: which owner this workgroup serves
-    const DevItem *__restrict__ items = second ? items1 : items0;
+    const DevItem *__restrict__ items = reinterpret_cast<const DevItem *>(second ? items1 : items0);
     const int grow = second ? grow1 : grow0;
     DevItem it = grown(scalar_load_item(items, second ? (int)blockIdx.x - n0 : (int)blockIdx.x), grow);
     // The owner's arguments come beside the item, at an address of their own (a field chosen from either owner's is two addresses and a
@@ -576,12 +576,12 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
         }
         // Q as the B operand: head r (4x4 blocks: r & 3; zero beyond G), read like a K row: bytes kk*64 + kc*16 .. +16
         const int head = kQuad ? L.r & (kQuadHeads - 1) : L.r;
-        const char *qrow = q + ((int64_t)it.user * Hq + (int64_t)kv_head * G + head) * kRowBytes + L.kc * 16;
+        const Address qrow = q + ((int64_t)it.user * Hq + (int64_t)kv_head * G + head) * kRowBytes + L.kc * 16;
 #pragma unroll
         for (int kk = 0; kk < RB / 64; ++kk) {
             qB[kk] = u32x4{0u, 0u, 0u, 0u};
             if (head < G)
-                qB[kk] = *reinterpret_cast<const u32x4 *>(qrow + kk * 64);
+                qB[kk] = *(const u32x4 __attribute__((address_space(1))) *)(qrow + kk * 64);
         }
         // head-major: the four waves take interleaved steps (rot counts 32-token ones); token-major: every wave takes every step
         tb = HPW ? it.t_begin : it.t_begin + ((uniform(wave) - (kHalf ? 2 * it.rot : it.rot)) & (kWaves - 1)) * kTile;
