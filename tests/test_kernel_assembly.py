@@ -33,3 +33,16 @@ def test_all_of_a_buffer_loads_offset_is_range_checked(assembly):
     assert len(loads) >= 30, len(loads)
     scalar = [l for l in loads if not re.match(r"buffer_load_\w+ v\[\d+:\d+\], v\d+, s\[\d+:\d+\], 0 offen( |$)", l)]
     assert not scalar, (len(scalar), scalar[:4])
+
+
+def test_what_a_workgroup_needs_first_is_preloaded(assembly):
+    """The streaming, whole-rows and closing kernels ask for their item or row with their first instructions: the parameters that this
+    takes (RowsHead's 14 dwords, PartialHead's 13, CloseHead's 7) arrive in scalar registers."""
+    least = {"partial_mfma_kernel": 13, "whole_rows_kernel": 14, "close_kernel": 7}
+    seen = dict.fromkeys(least, 0)
+    for name, n in re.findall(r"\.amdhsa_kernel (\S+)(?:(?!\.end_amdhsa_kernel).)*?preload_length (\d+)", assembly, re.S):
+        for kernel, dwords in least.items():
+            if kernel in name:
+                assert int(n) >= dwords, (name, n)
+                seen[kernel] += 1
+    assert all(seen.values()), seen
