@@ -143,12 +143,13 @@ struct SlotSums {
     static_assert(kMost % kGroup == 0 && kMost <= 16);
     float2 ml;
     float x[kMost][VEC];
-    int n;
+    int n, lane;
 
-    __device__ __forceinline__ void load(const float2 (*sm_ml)[16], const float *sm_o, int first, int n_, int G, int g, int ch)
+    __device__ __forceinline__ void load(const float2 (*sm_ml)[16], const float *sm_o, int first, int n_, int G, int g, int ch, int tid)
     {
         n = n_;
-        const int lane = threadIdx.x & 15, last = max(n - 1, 0);
+        lane = tid & 15;
+        const int last = max(n - 1, 0);
         ml = sm_ml[first + min(lane, last)][g];
         const float *o = sm_o + (first * G + g) * o_stride(D) + ch;
         const int slot = G * o_stride(D), last_slot = last * slot;
@@ -179,7 +180,7 @@ struct SlotSums {
     // The owner's A and lse; without tokens (any false) 0 and -inf.
     __device__ __forceinline__ void reduce(bool any, float p_shift, float (&a)[VEC], float &lse) const
     {
-        const bool on = (int)(threadIdx.x & 15) < n;
+        const bool on = lane < n;
         const float m = on ? ml.x : -INFINITY, l = on ? ml.y : 0.f;
         const float M = row_max_ordered(m);
         const float w = l == 0.f ? 0.f : fast_exp2(m - M);  // a slot without steps holds l = 0
@@ -216,6 +217,11 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
                                              int threads, int n0, int n1, bool any0, bool any1)
 {
     const int64_t from = head0 * D;
+    // (an opaque copy: what follows from the thread's index is computed here.  Held across the tiles it cost the 64-channel instances up to
+    // 13 registers and with them a wave per SIMD: 256 users of 24-192 + 1-64 tokens in pages 19.9 us, with the copy 18.4, and contiguous
+    // with the append 20.7 / 18.4.)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     auto body = [&](int idx) __attribute__((always_inline)) {
         asm("" : "+s"(n0), "+s"(n1));  // (what follows from them is computed where it is used, not in front of the loop)
         const unsigned at = idx, g = at / D, ch = at % D;
@@ -225,9 +231,9 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
             l0 = (R.lse_in + head0)[g];
         }
         SlotSums<D, VEC> s0, s1;
-        s0.load(sm_ml, sm_o, 0, n0, G, g, ch);
+        s0.load(sm_ml, sm_o, 0, n0, G, g, ch, tid);
         if (R.out1)
-            s1.load(sm_ml, sm_o, n0, n1, G, g, ch);
+            s1.load(sm_ml, sm_o, n0, n1, G, g, ch, tid);
         float o0[VEC], e0;
         s0.reduce(any0, Elt<DT>::kPShift, o0, e0);
         store_vec<VEC>(R.out0 + from + at, o0);
@@ -258,7 +264,7 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
             (R.w_in + head0)[g] = w0;
         }
     };
-    int idx = (int)threadIdx.x * VEC;  // whole 16-lane rows: D / VEC >= 16
+    int idx = tid * VEC;  // whole 16-lane rows: D / VEC >= 16
     if constexpr (ONE_PASS) {
         if (idx < G * D)
             body(idx);

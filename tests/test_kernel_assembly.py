@@ -46,3 +46,20 @@ def test_what_a_workgroup_needs_first_is_preloaded(assembly):
                 assert int(n) >= dwords, (name, n)
                 seen[kernel] += 1
     assert all(seen.values()), seen
+
+
+def _metadata(assembly, kernel):
+    """(demangled template arguments, metadata block) of every instance of a kernel."""
+    for block in re.findall(r"^  - \.agpr_count:.*?(?=^  - \.agpr_count:|^amdhsa\.target)", assembly, re.S | re.M):
+        name = re.search(r"\.name:\s+(\S+)", block).group(1)
+        if kernel in name:
+            yield tuple(int(v) for v in re.findall(r"L[ib](\d+)E", name)), block
+
+
+def test_short_rows_of_64_channels_keep_four_waves_per_simd(assembly):
+    """Many short rows are bound by the workgroups that a compute unit holds: with at most 128 vector registers a fourth wave fits a SIMD.
+    These instances are at most that large: fp32 (16x16 blocks) without the append, 16-bit rows in pages without it, contiguous with it."""
+    at_most_128 = {(0, 64, 0, 0), (0, 64, 1, 0), (1, 64, 1, 0), (2, 64, 1, 0), (1, 64, 0, 1), (2, 64, 0, 1)}
+    seen = {args: int(re.search(r"\.vgpr_count:\s+(\d+)", block).group(1)) for args, block in _metadata(assembly, "whole_rows_kernel")}
+    assert len(seen) == 32 and at_most_128 <= set(seen), sorted(seen)
+    assert all(seen[args] <= 128 for args in at_most_128), {args: seen[args] for args in at_most_128}
