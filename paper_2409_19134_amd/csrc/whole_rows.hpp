@@ -25,6 +25,8 @@ struct alignas(16) RowsShared {
 };
 static_assert(sizeof(RowsShared) % 16 == 0, "the dynamic part starts where this ends");
 
+constexpr int kFewSlots = 5;  // of up to four waves and the crossing one's second
+
 // Waves per workgroup whose slots (one more than waves), with the static part, fit the 64 KB a launch may ask for: all twelve
 // but with many query heads per KV head (6 for 16 heads of 128 channels).
 __host__ __device__ constexpr int rows_waves_that_fit(int D, int G)
@@ -206,17 +208,140 @@ struct SlotSums {
     }
 };
 
-// Combines the slots' states and writes the row's results.  A thread takes VEC consecutive channels of one query head: this is the
+// Where a thread's channels of a row are: the row's first head, its first channel of the result arrays, the thread's channels behind that.
+struct RowAt {
+    int64_t head0, from;
+    unsigned at, g;
+    bool first;  // of its head's channels
+};
+
+template <int VEC>
+__device__ __forceinline__ void store_partial(global_f32_ptr out, global_f32_ptr lse, const RowAt &p, const float (&o)[VEC], float e)
+{
+    store_vec<VEC>(out + p.from + p.at, o);
+    if (p.first)
+        (lse + p.head0)[p.g] = e;
+}
+
+// The merge of a (private) and b (public).
+template <int VEC>
+__device__ __forceinline__ void store_merged(const DevResults &R, const RowAt &p, const float (&a)[VEC], float la, const float (&b)[VEC], float lb)
+{
+    float wa, wb, ls, y[VEC];
+    merge_weights(la, lb, wa, wb, ls);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v)
+        y[v] = (wa == 0.f ? 0.f : wa * a[v]) + (wb == 0.f ? 0.f : wb * b[v]);
+    store_vec<VEC>(R.y + p.from + p.at, y);
+    if (p.first) {
+        (R.lse + p.head0)[p.g] = ls;
+        (R.w_in + p.head0)[p.g] = wa;
+    }
+}
+
+// sum[v] += weight of slot S * x[S][v] over the slots; owner 0's sums (slots [0, n0)) move to `first`.
+template <int N, int VEC, int S = 0>
+__device__ __forceinline__ void weighted_slots(const float (&x)[N][VEC], float w, int n0, float (&first)[VEC], float (&sum)[VEC])
+{
+    if constexpr (S < N) {
+        if (S == n0) {  // uniform
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                first[v] = sum[v];
+                sum[v] = 0.f;
+            }
+        }
+        const float ws = row_dpp<0x150 + S>(w);  // row_newbcast: lane S's value
+#pragma unroll
+        for (int v = 0; v < VEC; ++v)
+            sum[v] = fmaf(ws, x[S][v], sum[v]);
+        weighted_slots<N, VEC, S + 1>(x, w, n0, first, sum);
+    }
+}
+
+// Combines the slots' states of a workgroup of up to four waves and writes the row's results: five slots at most, both owners' at once,
+// straight-line (the last slot stands in, with weight 0, for those past the row's).  Such workgroups are the shortest rows' or share a
+// compute unit with others, so instructions count whichever wave executes them; owner by owner in groups of four, as below, is up to
+// eight slot reads, two exponentials and two passes over them (us per call, below / this: 256 users of 24-192 + 1-64 tokens, 64 channels
+// 20.0 / 18.9, in 16-token pages 18.4 / 17.5, 128 channels 31.9 / 31.1, fp32 32.9 / 32.5; the below form with groups of one 20.4).
+// VEC: channels of a thread, one where the workgroup has a thread for each.
+template <int DT, int D, int VEC>
+__device__ __forceinline__ void reduce_few_slots(const DevResults &R, const float2 (*sm_ml)[16], const float *sm_o, int64_t head0, int G,
+                                                 int threads, int n0, int n, bool any0, bool any1)
+{
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (see reduce_slots)
+    const int slot = tid & 15;
+    for (int idx = tid * VEC; idx < G * D; idx += threads * VEC) {  // whole 16-lane rows: D / VEC >= 16
+        const unsigned g = (unsigned)idx / D, ch = (unsigned)idx % D;
+        const RowAt p = {head0, head0 * D, (unsigned)idx, g, ch == 0};
+        float x0[VEC] = {}, l0 = -INFINITY;
+        if (R.a_in) {  // the other owner's finished partial
+            load_vec<VEC>(x0, R.a_in + p.from + p.at);
+            l0 = (R.lse_in + head0)[g];
+        }
+        const float2 ml = slot < n ? sm_ml[slot][g] : make_float2(-INFINITY, 0.f);
+        float x[kFewSlots][VEC];
+#pragma unroll
+        for (int s = 0; s < kFewSlots; ++s)
+            load_vec<VEC>(x[s], sm_o + (min(s, n - 1) * G + g) * o_stride(D) + ch);
+        const bool mine0 = slot < n0;
+        const float M0 = row_max_ordered(mine0 ? ml.x : -INFINITY), M1 = row_max_ordered(mine0 ? -INFINITY : ml.x);
+        const float w = ml.y == 0.f ? 0.f : fast_exp2(ml.x - (mine0 ? M0 : M1));  // a slot without steps holds l = 0
+        const float wl = w * ml.y, L0 = row_sum(mine0 ? wl : 0.f), L1 = row_sum(mine0 ? 0.f : wl);
+        float o0[VEC] = {}, o1[VEC] = {};
+        weighted_slots<kFewSlots, VEC>(x, w, n0, o0, o1);  // (n0 < kFewSlots: owner 0's always move)
+        // an infinite value times a stand-in's weight of 0 is NaN: once more, over the slots that there are
+        float nan_if_any = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v)
+            nan_if_any += o0[v] + o1[v];
+        if (__any(nan_if_any != nan_if_any)) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v)
+                o0[v] = o1[v] = 0.f;
+#pragma unroll 1
+            for (int s = 0; s < n; ++s) {
+                float xs[VEC];
+                load_vec<VEC>(xs, sm_o + (s * G + g) * o_stride(D) + ch);
+                const float ws = __shfl(w, s, 16);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    o0[v] = s < n0 ? fmaf(ws, xs[v], o0[v]) : o0[v];
+                    o1[v] = s < n0 ? o1[v] : fmaf(ws, xs[v], o1[v]);
+                }
+            }
+        }
+        // an owner without tokens: A = 0, lse = -inf
+        const float i0 = fast_rcp(L0), i1 = fast_rcp(L1);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            o0[v] = any0 ? o0[v] * i0 : 0.f;
+            o1[v] = any1 ? o1[v] * i1 : 0.f;
+        }
+        const float e0 = any0 ? (M0 + fast_log2(L0) - Elt<DT>::kPShift) * kLn2 : -INFINITY;
+        const float e1 = any1 ? (M1 + fast_log2(L1) - Elt<DT>::kPShift) * kLn2 : -INFINITY;
+        store_partial<VEC>(R.out0, R.lse0, p, o0, e0);
+        if (!R.y)
+            continue;
+        if (R.out1) {
+            store_partial<VEC>(R.out1, R.lse1, p, o1, e1);
+            store_merged<VEC>(R, p, o0, e0, o1, e1);
+        } else {  // owner 0 is the public owner, merged with the delivered private partials
+            store_merged<VEC>(R, p, x0, l0, o0, e0);
+        }
+    }
+}
+
+// The same for more waves, owner by owner.  A thread takes VEC consecutive channels of one query head: this is the
 // tail of a launch, in which a wave's instruction takes 2 ns and two waves of a SIMD take turns, so the channels are spread over four
 // waves - one per SIMD - where the workgroup has more than four.  (A channel per thread of eight waves, both owners' sums formed over
 // all slots, with the argument order of then: tiny fp32 4.95 / 4.77 us, three calls of 16 users 14.25 / 13.85, 32 users with the append
-// 15.12 / 14.97.)  An owner's sums see its own slots only: a NaN in one owner's cache stays out
-// of the other's partial.
+// 15.12 / 14.97.)  In both forms an owner's sums see its own slots only: a NaN in one owner's cache stays out of the other's partial.
 template <int DT, int D, int VEC, bool ONE_PASS>
 __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (*sm_ml)[16], const float *sm_o, int64_t head0, int G,
                                              int threads, int n0, int n1, bool any0, bool any1)
 {
-    const int64_t from = head0 * D;
     // (an opaque copy: what follows from the thread's index is computed here.  Held across the tiles it cost the 64-channel instances up to
     // 13 registers and with them a wave per SIMD: 256 users of 24-192 + 1-64 tokens in pages 19.9 us, with the copy 18.4, and contiguous
     // with the append 20.7 / 18.4.)
@@ -224,10 +349,11 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
     asm volatile("" : "+v"(tid));
     auto body = [&](int idx) __attribute__((always_inline)) {
         asm("" : "+s"(n0), "+s"(n1));  // (what follows from them is computed where it is used, not in front of the loop)
-        const unsigned at = idx, g = at / D, ch = at % D;
+        const unsigned g = (unsigned)idx / D, ch = (unsigned)idx % D;
+        const RowAt p = {head0, head0 * D, (unsigned)idx, g, ch == 0};
         float x0[VEC] = {}, l0 = -INFINITY;
         if (R.a_in) {  // the other owner's finished partial
-            load_vec<VEC>(x0, R.a_in + from + at);
+            load_vec<VEC>(x0, R.a_in + p.from + p.at);
             l0 = (R.lse_in + head0)[g];
         }
         SlotSums<D, VEC> s0, s1;
@@ -236,32 +362,16 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
             s1.load(sm_ml, sm_o, n0, n1, G, g, ch, tid);
         float o0[VEC], e0;
         s0.reduce(any0, Elt<DT>::kPShift, o0, e0);
-        store_vec<VEC>(R.out0 + from + at, o0);
-        if (ch == 0)
-            (R.lse0 + head0)[g] = e0;
+        store_partial<VEC>(R.out0, R.lse0, p, o0, e0);
         if (!R.y)
             return;
-        float w0, w1, ls_y, y[VEC];
         if (R.out1) {
             float o1[VEC], e1;
             s1.reduce(any1, Elt<DT>::kPShift, o1, e1);
-            store_vec<VEC>(R.out1 + from + at, o1);
-            if (ch == 0)
-                (R.lse1 + head0)[g] = e1;
-            merge_weights(e0, e1, w0, w1, ls_y);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v)
-                y[v] = (w0 == 0.f ? 0.f : w0 * o0[v]) + (w1 == 0.f ? 0.f : w1 * o1[v]);
+            store_partial<VEC>(R.out1, R.lse1, p, o1, e1);
+            store_merged<VEC>(R, p, o0, e0, o1, e1);
         } else {  // owner 0 is the public owner, merged with the delivered private partials
-            merge_weights(l0, e0, w0, w1, ls_y);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v)
-                y[v] = (w0 == 0.f ? 0.f : w0 * x0[v]) + (w1 == 0.f ? 0.f : w1 * o0[v]);
-        }
-        store_vec<VEC>(R.y + from + at, y);
-        if (ch == 0) {
-            (R.lse + head0)[g] = ls_y;
-            (R.w_in + head0)[g] = w0;
+            store_merged<VEC>(R, p, x0, l0, o0, e0);
         }
     };
     int idx = tid * VEC;  // whole 16-lane rows: D / VEC >= 16
@@ -469,17 +579,23 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
     asm volatile("" : "+s"(args));
     const DevResults R = scalar_load_results(args + kRowsArgsAt + offsetof(RowsArgs, results));
     const int n1 = W + extra - n0;
+    auto few = [&](auto vec) __attribute__((always_inline)) {
+        reduce_few_slots<DT, D, decltype(vec)::value>(R, sm.ml, sm_o, head0, G, W * 64, n0, n0 + n1, S0 > 0, S1 > 0);
+    };
     auto reduce = [&](auto vec, auto one_pass) __attribute__((always_inline)) {
         reduce_slots<DT, D, decltype(vec)::value, decltype(one_pass)::value>(R, sm.ml, sm_o, head0, G, W * 64, n0, n1, S0 > 0, S1 > 0);
     };
-    // (two waves where there are four: such rows run three workgroups to a compute unit or are the shortest)
-    const int threads = min(W, W > 4 ? 4 : 2) * 64;
-    if (G * D <= threads)
-        reduce(std::integral_constant<int, 1>(), std::true_type());
-    else if (G * D <= 2 * threads)
-        reduce(std::integral_constant<int, 2>(), std::true_type());
+    constexpr std::integral_constant<int, 1> one;
+    constexpr std::integral_constant<int, 2> two;
+    constexpr std::integral_constant<int, 4> four;
+    if (W < kFewSlots)
+        G * D <= W * 64 ? few(one) : few(four);
+    else if (G * D <= 256)
+        reduce(one, std::true_type());
+    else if (G * D <= 512)
+        reduce(two, std::true_type());
     else
-        reduce(std::integral_constant<int, 4>(), std::false_type());
+        reduce(four, std::false_type());
 }
 
 }  // namespace spd

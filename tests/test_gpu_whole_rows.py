@@ -121,6 +121,34 @@ def test_an_infinite_value_stays_infinite(ctx, split_ctx, split, Hq, Hkv, d):
             assert torch.isfinite(other[u]).all()
 
 
+@pytest.mark.parametrize("steps", [1, 2, 3, 4])
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [(torch.bfloat16, 4, 1, 64), (torch.float16, 2, 2, 128), (torch.bfloat16, 24, 3, 128),
+                                            (torch.float32, 5, 1, 64), (torch.float32, 3, 1, 128)])
+def test_up_to_four_waves(ctx, split_ctx, dtype, Hq, Hkv, d, steps):
+    """Workgroups of up to four waves combine both owners' slots at once: every border of the owners among up to four steps, a step
+    shared by no wave, one owner empty, a thread per channel and four channels a thread; and an infinite V value, which the last slot
+    holds, stays the only one (it stands in, with weight 0, for absent slots)."""
+    step = 16 if dtype == torch.float32 and d == 128 else 32
+    pairs = [(i, j) for i in range(steps + 1) for j in range(steps + 1 - i)]
+    lp, lo = [i * step - (7 if i else 0) for i, _ in pairs], [j * step for _, j in pairs]
+    wl = workloads.random_case(508, dtype, len(pairs), Hq, Hkv, d, lp, lo, device=DEV, layout="hnd")
+    _both_ways(ctx, split_ctx, wl)
+    if dtype != torch.float32:  # (16-bit probabilities are pairs, whose low part may be 0)
+        return
+    for u, (a, b) in enumerate(zip(lp, lo)):
+        if a + b:  # the last step's first token (the last one stands in, with weight 0, for a ragged step's absent tokens)
+            (wl.public.v[u][0, b - step] if b else wl.private.v[u][0, (a - 1) // step * step])[u] = float("inf")
+    out = run_step(ctx, wl, True)
+    assert ctx.spd_last_kernel_name().startswith("whole_rows")
+    for u, (a, b) in enumerate(zip(lp, lo)):
+        inf = torch.zeros((Hq, d), dtype=torch.bool, device=DEV)
+        inf[:Hq // Hkv, u] = a + b > 0
+        mine, other = (out.a_out, out.a_in) if b else (out.a_in, out.a_out)
+        for t in (mine[u], out.y[u]):
+            assert torch.equal(t == float("inf"), inf) and torch.isfinite(t[~inf]).all(), u
+        assert torch.isfinite(other[u]).all(), u
+
+
 @pytest.mark.parametrize("paged", [False, True])
 def test_decode_loop_appends_on_whole_rows(ctx, paged):
     """Twenty steps of a growing public cache: the appended rows reach the cache, the schedule is found again, results
