@@ -425,10 +425,12 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
 
     // One wait for the row and for what its tiles need of the arguments: the compiler otherwise asks for the addresses behind the lengths.
     // (Every line of the arguments that a row needs is asked for here: one that is first touched later costs its whole trip there, the
-    // results' 0.3 us.)
+    // results' 0.3 us.  Owner 0's paging lies in the line of w_in, owner 1's in the next.)
     asm volatile("" ::"s"(i0.k_base), "s"(i0.v_base), "s"(i1.k_base), "s"(i1.v_base), "s"(A.token_stride[0]), "s"(A.token_stride[1]),
                  "s"(A.k_ptrs[0]), "s"(A.v_ptrs[0]), "s"(A.k_ptrs[1]), "s"(A.v_ptrs[1]), "s"(A.wave_mul), "s"(A.k_new[0]), "s"(A.results.out0),
                  "s"(A.results.w_in));
+    if constexpr (PAGED)
+        asm volatile("" ::"s"(A.paging[1].block_stride));
     const int S0 = (unsigned)(i0.t_end + kTile - 1) / kTile;
     const int S1 = both ? (unsigned)(i1.t_end + kTile - 1) / kTile : 0;
     const unsigned total = S0 + S1;
@@ -440,6 +442,12 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
     const int run_end = lane + 1 < W ? (int)__umulhi(total * (lane + 1), A.wave_mul) : (int)total;
     const int n0 = S0 ? (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(run_end >= S0)) + 1 : 0;
     const bool extra = S0 && ((__builtin_amdgcn_ballot_w64(run_end > S0) >> (n0 - 1)) & 1);
+
+    auto args = [&]() __attribute__((always_inline)) {  // (opaque: what is read through it is read there)
+        uintptr_t at = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(at));
+        return at + kRowsArgsAt;
+    };
 
     // one run per wave, two for the wave that crosses from owner 0 to owner 1; a wave without steps leaves an idle slot
 #pragma unroll 1
@@ -457,16 +465,26 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
             L.k_base = second ? i1.k_base : i0.k_base;
             L.v_base = second ? i1.v_base : i0.v_base;
             if constexpr (PAGED) {
-                L.block_stride = second ? A.paging[1].block_stride : A.paging[0].block_stride;
-                L.page_shift = second ? A.paging[1].page_shift : A.paging[0].page_shift;
+                // The run's owner's entry, at an address of its own.  Chosen field by field from either owner's, both owners' were held, and
+                // some of them spilled, across the tiles, and their trips stood one behind the other in front of the page ids (with the
+                // order of the loads below, us per call: 16 users of 64-512 + 1-256 tokens with the append 13.7 / 12.5, 10 of 64-384 +
+                // 1-128 9.8 / 8.9, 256 of 64 channels 46.6 / 42.4).
+                const auto pg = (const RowsPaging __attribute__((address_space(4))) *)(args() + offsetof(RowsArgs, paging) + (second ? sizeof(RowsPaging) : 0));
+                L.block_stride = pg->block_stride;
+                L.page_shift = pg->page_shift;
                 L.page_mask = (1 << L.page_shift) - 1;
-                L.k_base += reinterpret_cast<uintptr_t>(second ? A.paging[1].k_pool : A.paging[0].k_pool);
-                L.v_base += reinterpret_cast<uintptr_t>(second ? A.paging[1].v_pool : A.paging[0].v_pool);
-                L.bt_row = (second ? A.paging[1].block_table : A.paging[0].block_table) + (int64_t)user * (second ? A.paging[1].max_blocks : A.paging[0].max_blocks);
+                L.k_base += reinterpret_cast<uintptr_t>(pg->k_pool);
+                L.v_base += reinterpret_cast<uintptr_t>(pg->v_pool);
+                L.bt_row = pg->block_table + (int64_t)user * pg->max_blocks;
             } else {
                 L.k_base += user_base(second ? A.k_ptrs[1] : A.k_ptrs[0], user);
                 L.v_base += user_base(second ? A.v_ptrs[1] : A.v_ptrs[0], user);
             }
+            int tb = b * kTile;
+            const int tb_end = min(e * kTile, t_end);
+            PagePair P = {0, 0};
+            if (PAGED)  // (before the append asks for its page, which is not waited for)
+                P = load_pages(L, tb, t_last);
             L.k_new_row = L.v_new_row = nullptr;
             const char *k_new = second ? A.k_new[1] : A.k_new[0], *v_new = second ? A.v_new[1] : A.v_new[0];
             // KV append: the wave that holds the row's last token reads it from the caller's buffer, and copies it to the cache
@@ -492,11 +510,6 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
                     *reinterpret_cast<u32x4 *>(const_cast<char *>(lane < kRowLanes ? L.k_base : L.v_base) + off) = new_piece;
                 }
             };
-            int tb = b * kTile;
-            const int tb_end = min(e * kTile, t_end);
-            PagePair P = {0, 0};
-            if (PAGED)
-                P = load_pages(L, tb, t_last);
             if constexpr (!kTwo) {
                 // the first step in front of the loop or in it: which of the two the compiler schedules better differs (append, 1
                 // user of 400 + 100 tokens 7.4 / 8.0 us contiguous, 8.6 / 8.2 paged; without the append, tiny fp32 5.0 / 4.9)
@@ -575,9 +588,7 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
 
     // The results' pointers are read here, next to the slots: scalar registers that hold them across the tiles are spilled, and a spill
     // is an instruction each way.  (In front of the barrier the slowest wave would wait for them.)
-    uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args));
-    const DevResults R = scalar_load_results(args + kRowsArgsAt + offsetof(RowsArgs, results));
+    const DevResults R = scalar_load_results(args() + offsetof(RowsArgs, results));
     const int n1 = W + extra - n0;
     auto few = [&](auto vec) __attribute__((always_inline)) {
         reduce_few_slots<DT, D, decltype(vec)::value>(R, sm.ml, sm_o, head0, G, W * 64, n0, n0 + n1, S0 > 0, S1 > 0);

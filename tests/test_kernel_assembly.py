@@ -63,3 +63,11 @@ def test_short_rows_of_64_channels_keep_four_waves_per_simd(assembly):
     seen = {args: int(re.search(r"\.vgpr_count:\s+(\d+)", block).group(1)) for args, block in _metadata(assembly, "whole_rows_kernel")}
     assert len(seen) == 32 and at_most_128 <= set(seen), sorted(seen)
     assert all(seen[args] <= 128 for args in at_most_128), {args: seen[args] for args in at_most_128}
+
+
+def test_short_rows_in_pages_spill_no_scalar_register(assembly):
+    """A row's launch is latency: what a paged run needs of its owner is read where the run begins, not held (and spilled, an instruction
+    each way and a wait in front of the row) beside the other owner's."""
+    spills = {args: int(re.search(r"\.sgpr_spill_count:\s+(\d+)", block).group(1)) for args, block in _metadata(assembly, "whole_rows_kernel")}
+    paged = {args: n for args, n in spills.items() if args[2]}
+    assert len(paged) == 16 and not any(paged.values()), paged
