@@ -3,6 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <tuple>
+#include <type_traits>
+
 #include "../../include/spd.h"
 
 namespace spd {
@@ -27,6 +30,21 @@ __device__ __forceinline__ T *global_pointer(Address a)
 {
     return (T *)(T __attribute__((address_space(1))) *)a;
 }
+
+// A kernel's last parameter: its type, and where it lies among the kernel's arguments (each at the next multiple of its alignment).
+template <class F>
+struct LastParameter;
+template <class... P>
+struct LastParameter<void (*)(P...)> {
+    static constexpr size_t place()
+    {
+        size_t end = 0, at = 0;
+        ((at = (end + alignof(P) - 1) / alignof(P) * alignof(P), end = at + sizeof(P)), ...);
+        return at;
+    }
+    static constexpr size_t at = place();
+    typedef std::tuple_element_t<sizeof...(P) - 1, std::tuple<P...>> type;
+};
 
 // Addressing of one owner's cache; all strides in BYTES.  Base pointers travel in the work items.
 struct KvAddr {
@@ -267,6 +285,5 @@ static_assert(sizeof(PartialHead) <= 14 * 4, "all of it is preloaded");
 struct PartialArgs {
     OwnerArgs owner[2];
 };
-constexpr int kPartialArgsAt = sizeof(PartialHead);  // in the kernel's arguments: padded as its parameters are
-static_assert(alignof(PartialArgs) == 8 && kPartialArgsAt == (3 * 8 + 7 * 4 + 7) / 8 * 8);
+constexpr int kPartialArgsAt = sizeof(PartialHead);  // in the kernel's arguments (the launch checks it against the kernel's own parameters)
 }  // namespace spd

@@ -651,9 +651,18 @@ constexpr bool mfma_instance_exists()
     return !(HPW && !PREFETCH) && !(f32 && (HPW || PREFETCH)) && !(RB == 128 && !PREFETCH) && !(DT == spd::kF32Quad && D != 128);
 }
 
+// A kernel that reads its last parameter by the address of its arguments: of that type and there it is.
+template <class Kernel, class Args>
+constexpr bool ends_with(int at)
+{
+    typedef spd::LastParameter<Kernel> Last;
+    return std::is_same<typename Last::type, Args>::value && Last::at == (size_t)at;
+}
+
 template <int DT, int D, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 bool launch_mfma(const MfmaLaunch &L)
 {
+    static_assert(ends_with<decltype(&spd::partial_mfma_kernel<DT, D, PAGED, PREFETCH, HPW, APPEND>), spd::PartialArgs>(spd::kPartialArgsAt));
     if constexpr (!mfma_instance_exists<DT, D, PAGED, PREFETCH, HPW, APPEND>()) {
         return false;
     } else if constexpr (spd::form_of(DT) != 0) {
@@ -824,6 +833,7 @@ struct MergeArgs {
 template <int DT, int D, bool PAGED, bool APPEND>
 bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsHead &H, const spd::RowsArgs &args)
 {
+    static_assert(ends_with<decltype(&spd::whole_rows_kernel<DT, D, PAGED, APPEND>), spd::RowsArgs>(spd::kRowsArgsAt));
     hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0,
                           (Address)H.items[0], (Address)H.items[1], (Address)H.order, (Address)H.q, H.Hkv, H.G, H.grow[0], H.grow[1], H.waves, H.both, args);
     return true;

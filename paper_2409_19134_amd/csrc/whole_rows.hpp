@@ -76,8 +76,7 @@ struct RowsArgs {
     RowsResults results;
     RowsPaging paging[2];
 };
-constexpr int kRowsArgsAt = sizeof(RowsHead);  // in the kernel's arguments: its parameters lie end to end
-static_assert(alignof(RowsArgs) == 8 && kRowsArgsAt % 8 == 0);
+constexpr int kRowsArgsAt = sizeof(RowsHead);  // in the kernel's arguments (the launch checks it against the kernel's own parameters)
 
 __device__ __forceinline__ RowItem scalar_load_row(Address items, int idx, int grow)
 {

@@ -56,6 +56,20 @@ def _metadata(assembly, kernel):
             yield tuple(int(v) for v in re.findall(r"L[ib](\d+)E", name)), block
 
 
+@pytest.mark.parametrize("kernel", ["partial_mfma_kernel", "whole_rows_kernel"])
+def test_the_arguments_lie_where_the_kernel_reads_them(assembly, kernel):
+    """Both kernels read their last parameter, the owners' arguments, at an offset from the argument segment that the launch side's copy of
+    the parameters in front gives: 56 bytes.  There it is, 240 bytes (two owners' 120, or whole rows' 8 + 5 pairs of 16, 72 of results and two
+    owners' 40 of pages), and nothing but the runtime's hidden arguments behind it."""
+    count = 0
+    for args, block in _metadata(assembly, kernel):
+        explicit = [(int(at), int(size)) for at, size, kind in
+                    re.findall(r"- \.offset:\s+(\d+)\s+\.size:\s+(\d+)\s+\.value_kind:\s+(\w+)", block) if not kind.startswith("hidden")]
+        assert len(explicit) == 11 and explicit[-1] == (56, 240), (args, explicit)
+        count += 1
+    assert count >= 32
+
+
 def test_short_rows_of_64_channels_keep_four_waves_per_simd(assembly):
     """Many short rows are bound by the workgroups that a compute unit holds: with at most 128 vector registers a fourth wave fits a SIMD.
     These instances are at most that large: fp32 (16x16 blocks) without the append, 16-bit rows in pages without it, contiguous with it."""
