@@ -36,8 +36,8 @@ def test_all_of_a_buffer_loads_offset_is_range_checked(assembly):
 
 
 def test_what_a_workgroup_needs_first_is_preloaded(assembly):
-    """The streaming, whole-rows and closing kernels ask for their item or row with their first instructions: the parameters that this
-    takes (RowsHead's 14 dwords, PartialHead's 13, CloseHead's 7) arrive in scalar registers."""
+    """The parameters from which the streaming, whole-rows and closing kernels find their item or row (RowsHead's 14 dwords, PartialHead's
+    13, CloseHead's 7) arrive in scalar registers."""
     least = {"partial_mfma_kernel": 13, "whole_rows_kernel": 14, "close_kernel": 7}
     seen = dict.fromkeys(least, 0)
     for name, n in re.findall(r"\.amdhsa_kernel (\S+)(?:(?!\.end_amdhsa_kernel).)*?preload_length (\d+)", assembly, re.S):
@@ -46,6 +46,39 @@ def test_what_a_workgroup_needs_first_is_preloaded(assembly):
                 assert int(n) >= dwords, (name, n)
                 seen[kernel] += 1
     assert all(seen.values()), seen
+
+
+def _until_asked(body, load):
+    """A kernel's instructions from its entry to the load that the pattern names.  Of the whole-rows kernel the path without a launch
+    order (its first branch taken, on a comparison of the order with null); the code in front of the entry, for firmware that does not
+    preload, is left out."""
+    lines = body.split(".p2align\t8", 1)[1].splitlines()[2:]  # (behind the alignment: the entry's label)
+    skip_to, seen = None, []
+    for line, following in zip(lines, lines[1:]):
+        op = line.split(";")[0].strip()
+        if skip_to:
+            skip_to = None if op == skip_to + ":" else skip_to
+            continue
+        seen.append(op)
+        if re.match(load, op):
+            return seen
+        branch = re.match(r"\s+s_cbranch_scc1 (\S+)", following)
+        if branch and re.match(r"s_cmp_eq_u64 \S+, 0$", op):
+            skip_to = branch.group(1)
+    raise AssertionError(f"no {load}")
+
+
+@pytest.mark.parametrize("kernel,load", [("partial_mfma_kernel", r"s_load_dwordx8 \S+ \S+ 0x10$"),  # dwords 4 to 11 of the item
+                                         ("whole_rows_kernel", r"s_load_dwordx8 \S+ \S+ 0x0$"),     # the row
+                                         ("close_kernel", r"global_load_dwordx2 ")])                 # the row's chunks
+def test_a_workgroup_asks_for_its_item_before_it_waits(assembly, kernel, load):
+    """Nothing is waited for in front of the load of a workgroup's item or row (whole rows: without a launch order): a trip to the
+    arguments there is what preloading is for."""
+    bodies = re.findall(rf"^(_Z\S*{kernel}\S*):.*?\n(.*?)^\.Lfunc_end", assembly, re.S | re.M)
+    assert len(bodies) >= 32, len(bodies)
+    for name, body in bodies:
+        asked = _until_asked(body, load)
+        assert not [op for op in asked if op.startswith("s_waitcnt")], (name, asked)
 
 
 def _metadata(assembly, kernel):
