@@ -399,12 +399,13 @@ struct CloseRow {
     }
 };
 
-// The head's fields are parameters of their own, preloaded into scalar registers: the RowInfos are asked for by the first instructions,
-// the rest of the arguments comes beside them.
+// The head is a parameter of its own, preloaded into scalar registers (as a vector, see HeadWords): the RowInfos are asked for by the first
+// instructions, the rest of the arguments comes beside them.
 struct CloseHead {
     const RowInfo *rows_in, *rows_out;  // rows_in: nullptr if the first owner's partials are the caller's, finished
     int32_t heads, G;  // heads: users * Hq
     uint32_t g_mul;    // ceil(2^32 / G): x / G is the high word of x * g_mul
+    uint32_t unused;
 };
 struct CloseArgs {
     const float *part_o_in, *part_lse_in, *part_o_out, *part_lse_out;
@@ -416,15 +417,18 @@ struct CloseArgs {
 // MAXI, MAXO: at least the chunks of any row of the first and the second owner; both owners' rows and their merge (as
 // finalize_step_kernel), or with MAXI = 0 the second owner's rows alone (as combine_chunks_kernel).
 template <int D, int MAXI, int MAXO>
-__global__ __launch_bounds__(64) void close_kernel(Address rows_in, Address rows_out, int32_t heads, int32_t G, uint32_t g_mul,
-                                                   CloseArgs A)
+__global__ __launch_bounds__(64) void close_kernel(u32x8 head_words, CloseArgs A)
 {
+    CloseHead H;
+    __builtin_memcpy(&H, &head_words, sizeof H);
+    const int G = H.G;
     const int idx = (blockIdx.x * 64 + threadIdx.x) * 4, ch = idx % D;
     const int64_t head = idx / D;
-    if (head >= heads)
+    if (head >= H.heads)
         return;  // whole 16-lane rows
-    const int row = G == 1 ? (int)head : (int)__umulhi((unsigned)head, g_mul), g = (int)head - row * G;
-    const RowInfo ro = global_pointer<const RowInfo>(rows_out)[row], ri = MAXI && rows_in ? global_pointer<const RowInfo>(rows_in)[row] : RowInfo{0, 1};
+    const int row = G == 1 ? (int)head : (int)__umulhi((unsigned)head, H.g_mul), g = (int)head - row * G;
+    const RowInfo ro = global_pointer<const RowInfo>((Address)H.rows_out)[row],
+                  ri = MAXI && H.rows_in ? global_pointer<const RowInfo>((Address)H.rows_in)[row] : RowInfo{0, 1};
     asm volatile("" ::"s"(A.part_o_out), "s"(A.y), "s"(A.w_in));  // (every line of them is asked for here)
     CloseRow<D, MAXO> out;
     f32x4 x1;

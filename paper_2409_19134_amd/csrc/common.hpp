@@ -14,6 +14,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kWaves = 4;            // waves per workgroup in the partial-attention kernels
 constexpr int kThreads = kWaves * 64;
@@ -23,7 +24,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 // A global address as a kernel's own parameter (not in a struct): the runtime looks up the allocation of every parameter that is declared a
-// pointer, on each launch (host time of three whole-rows and merge calls 9.95 us with pointers, 9.75 with these; one private call 5.1 / 5.05).
+// pointer, on each launch (host time of three whole-rows and merge calls 9.95 us with pointers, 9.75 with these).  So the kernels that a step
+// or call launches on its usual paths take addresses; finalize_step_kernel (rows of more than 32 chunks), the merge of more than two parts,
+// the mass tracker and the uploads of a new schedule keep pointers.
 typedef uintptr_t Address;
 template <class T>
 __device__ __forceinline__ T *global_pointer(Address a)
@@ -45,6 +48,34 @@ struct LastParameter<void (*)(P...)> {
     static constexpr size_t at = place();
     typedef std::tuple_element_t<sizeof...(P) - 1, std::tuple<P...>> type;
 };
+
+// A kernel's head, 14 dwords that are preloaded, as the parameters that it travels in: vectors, each one parameter for the runtime to go
+// through on a launch.  (One user's calls through two launches, which the host bounds, us with a parameter for every field / with three
+// vectors / with one struct and nothing preloaded: 9.0 / 8.8 / 8.9, 8.8 / 8.7 / 8.7, fused 7.8 / 7.7 / 7.7.)
+struct HeadWords {
+    u32x8 a;
+    u32x4 b;
+    u32x2 c;
+};
+template <class Head>
+__host__ __device__ __forceinline__ HeadWords head_words(const Head &h)
+{
+    static_assert(sizeof(Head) == 14 * 4, "the head is what the parameters hold");
+    HeadWords w;
+    __builtin_memcpy(&w.a, reinterpret_cast<const char *>(&h), sizeof w.a);
+    __builtin_memcpy(&w.b, reinterpret_cast<const char *>(&h) + sizeof w.a, sizeof w.b);
+    __builtin_memcpy(&w.c, reinterpret_cast<const char *>(&h) + sizeof w.a + sizeof w.b, sizeof w.c);
+    return w;
+}
+template <class Head>
+__device__ __forceinline__ Head head_of(u32x8 a, u32x4 b, u32x2 c)
+{
+    Head h;
+    __builtin_memcpy(reinterpret_cast<char *>(&h), &a, sizeof a);
+    __builtin_memcpy(reinterpret_cast<char *>(&h) + sizeof a, &b, sizeof b);
+    __builtin_memcpy(reinterpret_cast<char *>(&h) + sizeof a + sizeof b, &c, sizeof c);
+    return h;
+}
 
 // Addressing of one owner's cache; all strides in BYTES.  Base pointers travel in the work items.
 struct KvAddr {
@@ -267,9 +298,9 @@ struct RowInfo {
     int32_t first_slot, n_chunks;
 };
 
-// The partial kernel's arguments.  The head's fields are parameters of their own, which arrive in scalar registers with the wave
-// (kernel-argument preloading: up to 14 dwords, not out of a struct), so that a workgroup's first instructions ask for its item; the
-// owners are the last parameter, read at the one that the workgroup serves.
+// The partial kernel's arguments.  The head arrives in scalar registers with the wave (kernel-argument preloading: up to 14 dwords, not
+// out of a struct), so that a workgroup's first instructions ask for its item; the owners are the last parameter, read at the one that the
+// workgroup serves.
 struct PartialHead {
     const DevItem *items[2];
     const char *q;          // [U][Hq][D]
@@ -281,7 +312,6 @@ struct PartialHead {
     float scale_log2e;
     int32_t ring_rows;      // result rows a workgroup may hold back in LDS (see the result ring in partial_mfma.hpp); 0: none
 };
-static_assert(sizeof(PartialHead) <= 14 * 4, "all of it is preloaded");
 struct PartialArgs {
     OwnerArgs owner[2];
 };

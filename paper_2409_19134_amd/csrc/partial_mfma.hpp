@@ -494,14 +494,17 @@ __host__ __device__ constexpr int mfma_waves_per_simd(int RB, bool prefetch, boo
 template <int DTYPE, int CHANNELS, bool PAGED, bool PREFETCH, bool HPW, bool APPEND>
 __global__ __launch_bounds__(HPW ? 512 : kThreads,
                              mfma_waves_per_simd((CHANNELS < 0 ? -CHANNELS : CHANNELS) * Elt<DTYPE>::kBytes, PREFETCH, HPW)) void partial_mfma_kernel(
-    Address items0, Address items1, Address q, int32_t n0, int32_t grow0, int32_t grow1, int32_t Hq, int32_t G,
-    float scale_log2e, int32_t ring_rows, PartialArgs)  // see PartialHead
+    u32x8 head_a, u32x4 head_b, u32x2 head_c, PartialArgs)  // see PartialHead
 {
+    const PartialHead H = head_of<PartialHead>(head_a, head_b, head_c);
+    const int n0 = H.n0, Hq = H.Hq, G = H.G, ring_rows = H.ring_rows;
+    const float scale_log2e = H.scale_log2e;
+    const Address q = (Address)H.q;
     constexpr int D = CHANNELS < 0 ? -CHANNELS : CHANNELS;
     constexpr int DT = CHANNELS < 0 ? DTYPE + kFormStep : DTYPE;
     const bool second = (int)blockIdx.x >= n0;  // workgroup-uniform: which owner this workgroup serves
-    const DevItem *__restrict__ items = reinterpret_cast<const DevItem *>(second ? items1 : items0);
-    const int grow = second ? grow1 : grow0;
+    const DevItem *__restrict__ items = second ? H.items[1] : H.items[0];
+    const int grow = second ? H.grow[1] : H.grow[0];
     DevItem it = grown(scalar_load_item(items, second ? (int)blockIdx.x - n0 : (int)blockIdx.x), grow);
     // The owner's arguments come beside the item, at an address of their own (a field chosen from either owner's is two addresses and a
     // selection each), and there is one wait for all that the first tile needs: as the compiler placed them, up to six round trips

@@ -633,7 +633,7 @@ struct MfmaLaunch {
     uint32_t lds;
     hipStream_t stream;
     hipEvent_t ev0, ev1;  // both null unless timing is armed: receive the kernel's own start and stop time stamps
-    spd::PartialHead head;
+    spd::HeadWords head;  // of a PartialHead or RowsHead
     spd::PartialArgs args;
 };
 
@@ -667,13 +667,11 @@ bool launch_mfma(const MfmaLaunch &L)
         return false;
     } else if constexpr (spd::form_of(DT) != 0) {
         hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT - spd::kFormStep, -D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
-                              L.stream, L.ev0, L.ev1, 0, (Address)L.head.items[0], (Address)L.head.items[1], (Address)L.head.q, L.head.n0, L.head.grow[0],
-                              L.head.grow[1], L.head.Hq, L.head.G, L.head.scale_log2e, L.head.ring_rows, L.args);
+                              L.stream, L.ev0, L.ev1, 0, L.head.a, L.head.b, L.head.c, L.args);
         return true;
     } else {
         hipExtLaunchKernelGGL((spd::partial_mfma_kernel<DT, D, PAGED, PREFETCH, HPW, APPEND>), L.grid, L.block, L.lds,
-                              L.stream, L.ev0, L.ev1, 0, (Address)L.head.items[0], (Address)L.head.items[1], (Address)L.head.q, L.head.n0, L.head.grow[0],
-                              L.head.grow[1], L.head.Hq, L.head.G, L.head.scale_log2e, L.head.ring_rows, L.args);
+                              L.stream, L.ev0, L.ev1, 0, L.head.a, L.head.b, L.head.c, L.args);
         return true;
     }
 }
@@ -708,6 +706,7 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     const int waves = hpw ? e0->hpw : spd::kWaves;
     const int D = s->head_dim;
     MfmaLaunch L;
+    spd::PartialHead H = {};
     L.grid = dim3((unsigned)(n0 + n1));
     L.block = dim3(64u * (unsigned)waves);
     // cross-wave staging; head-per-wave stages its per-wave results too if that fits (the kernel applies the same rule)
@@ -720,14 +719,14 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     L.args.owner[1] = a1;
     const CachedSchedule *const entry[2] = {e0, e1 ? e1 : e0};
     for (int i = 0; i < 2; ++i) {
-        L.head.items[i] = reinterpret_cast<const DevItem *>(entry[i]->dev);
-        L.head.grow[i] = entry[i]->grow;
+        H.items[i] = reinterpret_cast<const DevItem *>(entry[i]->dev);
+        H.grow[i] = entry[i]->grow;
     }
-    L.head.n0 = (int)n0;
-    L.head.q = static_cast<const char *>(q);
-    L.head.Hq = s->n_q_heads;
-    L.head.G = G;
-    L.head.scale_log2e = c;
+    H.n0 = (int)n0;
+    H.q = static_cast<const char *>(q);
+    H.Hq = s->n_q_heads;
+    H.G = G;
+    H.scale_log2e = c;
     // Two steps in flight (PREFETCH) or one.  Clearly more pieces than the one-step kernel holds at once, three per CU
     // (a few left over just start a little later), run on the two-step kernel, two per CU: fewer workgroup starts and
     // half as many dependent memory round trips per wave.  Everything that is resident at once runs on the one-step
@@ -754,7 +753,8 @@ int launch_partial(spd_ctx *ctx, int which, const CachedSchedule *e0, const spd_
     if (2 * segments >= min_x2 * (n0 + n1) && L.lds > 0)  // (head per wave without its staging tiles has no ring either)
         ring_rows = std::min(ctx->result_rows, hpw ? spd::hpw_ring_rows_that_fit(D, G, waves) : spd::ring_rows_that_fit(D, G, two_per_cu));
     L.lds += (uint32_t)(ring_rows * sizeof(float) * (hpw ? (size_t)spd::hpw_ring_row_floats(D, G) * waves : (size_t)spd::ring_row_floats(D, G)));
-    L.head.ring_rows = ring_rows;
+    H.ring_rows = ring_rows;
+    L.head = spd::head_words(H);
     // fp32 rows of 512 bytes with up to four query heads per KV head run on the 4x4 matrix blocks, a quarter of the 16x16
     // tile's time per step (measured in partial_mfma.hpp).  Five heads would need a second set of blocks and of
     // accumulators (32 registers more than the kernel has), and the 16x16 tile is fuller there.  With 64 channels the
@@ -831,11 +831,11 @@ struct MergeArgs {
 };
 
 template <int DT, int D, bool PAGED, bool APPEND>
-bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsHead &H, const spd::RowsArgs &args)
+bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsArgs &args)
 {
     static_assert(ends_with<decltype(&spd::whole_rows_kernel<DT, D, PAGED, APPEND>), spd::RowsArgs>(spd::kRowsArgsAt));
     hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0,
-                          (Address)H.items[0], (Address)H.items[1], (Address)H.order, (Address)H.q, H.Hkv, H.G, H.grow[0], H.grow[1], H.waves, H.both, args);
+                          L.head.a, L.head.b, L.head.c, args);
     return true;
 }
 
@@ -862,6 +862,7 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
     Owner &town = ctx->owner[e1 ? 0 : which];
     const bool timed = ctx->timing && town.ev_used < (int)town.ev_start.size();
     MfmaLaunch L;
+    L.head = spd::head_words(H);
     L.grid = dim3((unsigned)s->n_kv_heads, (unsigned)v0->n_users);
     L.block = dim3(64u * (unsigned)waves);
     L.lds = (uint32_t)spd::staging_bytes(D, waves + 1, G);
@@ -874,7 +875,7 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
             return with_bool(v0->block_size != 0, [&](auto paged) {
                 return with_bool(nt.k != nullptr, [&](auto app) {
                     return launch_rows_instance<decltype(dt)::value, decltype(d)::value, decltype(paged)::value,
-                                                decltype(app)::value>(L, H, R);
+                                                decltype(app)::value>(L, R);
                 });
             });
         });
@@ -901,6 +902,9 @@ bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd:
     H.heads = (int32_t)heads;
     H.G = s->n_q_heads / s->n_kv_heads;
     H.g_mul = (uint32_t)(((1ull << 32) + H.G - 1) / H.G);
+    spd::u32x8 head;
+    static_assert(sizeof H == sizeof head);
+    std::memcpy(&head, &H, sizeof head);
     const dim3 grid((unsigned)((heads * D / 4 + 63) / 64));
     auto size = [](int n) { return n <= 4 ? 4 : n <= 8 ? 8 : n <= 16 ? 16 : 32; };
     return with_value<64, 128>(D, [&](auto d) {
@@ -910,7 +914,7 @@ bool launch_close(const spd_shape *s, int n_users, int max_in, int max_out, spd:
                     return false;
                 } else {
                     hipLaunchKernelGGL((spd::close_kernel<decltype(d)::value, decltype(mi)::value, decltype(mo)::value>), grid, dim3(64), 0,
-                                       stream, (Address)H.rows_in, (Address)H.rows_out, H.heads, H.G, H.g_mul, C);
+                                       stream, head, C);
                     return true;
                 }
             });

@@ -50,7 +50,7 @@ struct RowsPaging {
     int64_t block_stride;  // bytes
 };
 
-// What a row's address and its share of the waves need, as the launch hands it over: as parameters of their own, the first of which
+// What a row's address and its share of the waves need, as the launch hands it over: in parameters of their own (HeadWords), which
 // arrive in scalar registers with the wave (kernel-argument preloading: up to 14 dwords, not out of a struct).  The row is then asked
 // for by a wave's first instructions instead of behind a scalar round trip to the arguments (us per call: tiny fp32 4.77 / 4.58, fp16
 // three calls of 16 users 13.71 / 13.44, 32 users with the append 14.97 / 14.81).  Index 0 and 1: the owners; what belongs to owner 1
@@ -63,7 +63,6 @@ struct RowsHead {
     int32_t grow[2];       // see OwnerArgs
     int32_t waves, both;   // both: both owners' rows, merged into y; else the first's alone - merged too if partials were delivered
 };
-static_assert(sizeof(RowsHead) == 14 * 4, "all of it is preloaded");
 
 // The rest, in the order in which a wave needs it: a scalar load of the arguments misses once for every 64-byte line, and the lines of
 // one batch of loads don't come at once.  The kernel's last parameter.
@@ -387,9 +386,12 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
 // the end of owner 0's steps and the beginning of owner 1's: its second result goes to one extra slot.
 template <int DT, int D, bool PAGED, bool APPEND>
 __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
-    Address items0, Address items1, Address order, Address q, int32_t Hkv, int32_t G, int32_t grow0,
-    int32_t grow1, int32_t waves, int32_t both, RowsArgs A)  // see RowsHead
+    u32x8 head_a, u32x4 head_b, u32x2 head_c, RowsArgs A)  // see RowsHead
 {
+    const RowsHead H = head_of<RowsHead>(head_a, head_b, head_c);
+    const int Hkv = H.Hkv, G = H.G, waves = H.waves;
+    const bool both = H.both;
+    const Address items0 = (Address)H.items[0], items1 = (Address)H.items[1], q = (Address)H.q;
     constexpr int RB = D * Elt<DT>::kBytes;
     constexpr int NA = step_tiles(RB), kTile = step_tokens(RB);
     constexpr bool kTwo = RB == 128;  // two steps in flight where a step is 8 KB
@@ -401,12 +403,12 @@ __global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
 
     const int kvh = blockIdx.x;
     int user = blockIdx.y;
-    if (order) {
-        user = scalar_load_i32(reinterpret_cast<const int32_t *>(order), user);
+    if (H.order) {
+        user = scalar_load_i32(H.order, user);
         asm volatile("" : "+s"(user));  // (its wait belongs in here: behind the branch it would be every launch's, for all loads so far)
     }
     const int row = user * Hkv + kvh, W = waves;
-    const RowItem i0 = scalar_load_row(items0, row, grow0), i1 = scalar_load_row(items1, row, grow1);
+    const RowItem i0 = scalar_load_row(items0, row, H.grow[0]), i1 = scalar_load_row(items1, row, H.grow[1]);
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
 
     LaneConst L;

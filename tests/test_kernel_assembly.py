@@ -36,9 +36,9 @@ def test_all_of_a_buffer_loads_offset_is_range_checked(assembly):
 
 
 def test_what_a_workgroup_needs_first_is_preloaded(assembly):
-    """The parameters from which the streaming, whole-rows and closing kernels find their item or row (RowsHead's 14 dwords, PartialHead's
-    13, CloseHead's 7) arrive in scalar registers."""
-    least = {"partial_mfma_kernel": 13, "whole_rows_kernel": 14, "close_kernel": 7}
+    """The parameters from which the streaming, whole-rows and closing kernels find their item or row (PartialHead's and RowsHead's 14
+    dwords, CloseHead's 8) arrive in scalar registers."""
+    least = {"partial_mfma_kernel": 14, "whole_rows_kernel": 14, "close_kernel": 8}
     seen = dict.fromkeys(least, 0)
     for name, n in re.findall(r"\.amdhsa_kernel (\S+)(?:(?!\.end_amdhsa_kernel).)*?preload_length (\d+)", assembly, re.S):
         for kernel, dwords in least.items():
@@ -91,14 +91,14 @@ def _metadata(assembly, kernel):
 
 @pytest.mark.parametrize("kernel", ["partial_mfma_kernel", "whole_rows_kernel"])
 def test_the_arguments_lie_where_the_kernel_reads_them(assembly, kernel):
-    """Both kernels read their last parameter, the owners' arguments, at an offset from the argument segment that the launch side's copy of
-    the parameters in front gives: 56 bytes.  There it is, 240 bytes (two owners' 120, or whole rows' 8 + 5 pairs of 16, 72 of results and two
+    """Both kernels read their last parameter, the owners' arguments, at an offset from the argument segment that the size of the head in
+    front gives: 56 bytes.  There it is, 240 bytes (two owners' 120, or whole rows' 8 + 5 pairs of 16, 72 of results and two
     owners' 40 of pages), and nothing but the runtime's hidden arguments behind it."""
     count = 0
     for args, block in _metadata(assembly, kernel):
         explicit = [(int(at), int(size)) for at, size, kind in
                     re.findall(r"- \.offset:\s+(\d+)\s+\.size:\s+(\d+)\s+\.value_kind:\s+(\w+)", block) if not kind.startswith("hidden")]
-        assert len(explicit) == 11 and explicit[-1] == (56, 240), (args, explicit)
+        assert explicit == [(0, 32), (32, 16), (48, 8), (56, 240)], (args, explicit)
         count += 1
     assert count >= 32
 
