@@ -482,6 +482,24 @@ def test_fp32_matrix_blocks_at_tile_edges(ctx, G, d, paged):
     check_against_oracle(ctx, wl)
 
 
+@pytest.mark.parametrize("G", [1, 3, 4])
+@pytest.mark.parametrize("d,lp,lo", [(64, [150, 400], [60, 7]), (128, [150, 250], [60, 7]), (128, [5000, 3001], [700, 33])])
+@pytest.mark.parametrize("paged", [False, True])
+def test_fp32_matrix_blocks_keep_one_maximum(ctx, G, d, lp, lo, paged):
+    """4x4 matrix blocks: lanes that hold different channels of a head hold the same scores and maxima to the last bit, so values that
+    are the same in all of a token's channels give results that are the same in all channels: every channel's sum is formed in the same
+    order.  Scores are large, where a last bit is worth most."""
+    wl = workloads.random_case(76 + G, torch.float32, 2, 2 * G, 2, d, lp, lo, device=DEV, layout="hnd", paged=paged, scale=40 / d ** 0.5)
+    for side in (wl.private, wl.public):
+        for v in ([side.v_pool] if paged else side.v):
+            v.copy_(v[..., :1].expand_as(v).clone())
+    for fused in (False, True):
+        step = run_step(ctx, wl, fused)
+        for out in (step.a_in, step.a_out, step.y):
+            rows = out.view(-1, d)
+            assert torch.equal(rows, rows[:, :1].expand_as(rows)), fused
+
+
 def test_fp32_large_launch(ctx):
     """64 users x 8 KV heads x 3000 tokens in fp32 (1.6 GB): several resident rounds of pieces; sampled rows."""
     wl = workloads.random_case(115, torch.float32, 64, 16, 8, 128, [3000] * 64, [100] * 64, device=DEV, layout="hnd")
