@@ -831,9 +831,16 @@ struct MergeArgs {
 };
 
 template <int DT, int D, bool PAGED, bool APPEND>
-bool launch_rows_instance(const MfmaLaunch &L, const spd::RowsArgs &args)
+bool launch_rows_instance(const MfmaLaunch &L, bool three_waves, const spd::RowsArgs &args)
 {
     static_assert(ends_with<decltype(&spd::whole_rows_kernel<DT, D, PAGED, APPEND>), spd::RowsArgs>(spd::kRowsArgsAt));
+    if constexpr (spd::rows_three_waves_form(DT, D, PAGED, APPEND)) {
+        if (three_waves) {
+            hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, -D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0,
+                                  L.head.a, L.head.b, L.head.c, args);
+            return true;
+        }
+    }
     hipExtLaunchKernelGGL((spd::whole_rows_kernel<DT, D, PAGED, APPEND>), L.grid, L.block, L.lds, L.stream, L.ev0, L.ev1, 0,
                           L.head.a, L.head.b, L.head.c, args);
     return true;
@@ -855,7 +862,8 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
     H.G = G;
     R.wave_mul = (uint32_t)(((1ull << 32) + waves - 1) / waves);
     R.scale_log2e = s->scale * spd::kLog2e;
-    const bool by_length = whole_rows_by_length((int64_t)v0->n_users * s->n_kv_heads, waves, ctx->n_cus);
+    const int64_t rows = (int64_t)v0->n_users * s->n_kv_heads;
+    const bool by_length = whole_rows_by_length(rows, waves, ctx->n_cus);
     H.order = by_length ? reinterpret_cast<const int32_t *>(e0->dev + e0->off_rows) : nullptr;
     H.q = static_cast<const char *>(q);
     R.results = {out0, lse0, e1 ? out1 : nullptr, lse1, e1 ? nullptr : mg.a_in, mg.lse_in, mg.y, mg.lse, mg.w_in};
@@ -870,19 +878,21 @@ int launch_whole_rows(spd_ctx *ctx, int which, int waves, const CachedSchedule *
     L.ev0 = timed ? town.ev_start[town.ev_used] : nullptr;
     L.ev1 = timed ? town.ev_stop[town.ev_used] : nullptr;
     const int dt_code = s->dtype == SPD_F32 && G <= spd::kQuadHeads ? spd::kF32Quad : s->dtype;
+    const bool three_waves = by_length && (waves > 4 || (s->dtype == SPD_F32 && (e1 || rows < 4 * (int64_t)ctx->n_cus)));  // (see the form)
     const bool ok = with_value<SPD_F32, SPD_BF16, SPD_F16, spd::kF32Quad>(dt_code, [&](auto dt) {
         return with_value<64, 128>(D, [&](auto d) {
             return with_bool(v0->block_size != 0, [&](auto paged) {
                 return with_bool(nt.k != nullptr, [&](auto app) {
                     return launch_rows_instance<decltype(dt)::value, decltype(d)::value, decltype(paged)::value,
-                                                decltype(app)::value>(L, R);
+                                                decltype(app)::value>(L, three_waves, R);
                 });
             });
         });
     });
     if (!ok)
         return SPD_ERR_SHAPE;
-    const int32_t inst[6] = {dt_code, D, v0->block_size != 0, D * elt_size(s->dtype) == 128, 2, nt.k != nullptr};
+    const int channels = three_waves && spd::rows_three_waves_form(dt_code, D, v0->block_size != 0, nt.k != nullptr) ? -D : D;
+    const int32_t inst[6] = {dt_code, channels, v0->block_size != 0, D * elt_size(s->dtype) == 128, 2, nt.k != nullptr};
     std::memcpy(ctx->last_instance, inst, sizeof inst);
     SPD_HIP(ctx, hipGetLastError());
     if (timed)

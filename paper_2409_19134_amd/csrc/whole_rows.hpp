@@ -35,6 +35,19 @@ __host__ __device__ constexpr int rows_waves_that_fit(int D, int G)
     return n > (size_t)kRowsMaxWaves ? kRowsMaxWaves : (int)n;
 }
 
+// The instances of at most 128 registers, of which a SIMD holds four waves, have a form held to three (but for the append in pages).  Where
+// a unit gets its rows one after the other, the longest first, fewer at a time balance better; where all are resident, or many more, the
+// fourth wave's loads count.  It takes the launches of up to two rows a unit (one workgroup of eight waves at a time instead of two: which
+// rows share a unit is not settled at the start) and, of fp32, those of up to four (three at a time) and all with both owners.  us per call,
+// four / three: 52 users of 352-1411 + 1-171 tokens, 8 heads, bf16 with the append 24.8 / 22.7, 116 of 60-608 + 1-233, 4 KV heads, fp32
+// 29.2 / 25.5, 57 of 58-589 + 1-182 23.0 / 21.4; the append in pages 18.9 / 22.8 (57 of 426-853).  Four waves a row: fp32 49 of 80-322 +
+// 1-192, 16 KV heads 32.5 / 30.2, 256 of 41-411 + 1-67, 4 KV heads 30.6 / 28.4; but one owner's 256 of 95-119 25.7 / 27.8, 16 bits with the
+// append, 118 of 16-85 + 1-191, 13.6 / 14.7, in pages 139 of 26-269 12.3 / 13.1.
+constexpr bool rows_three_waves_form(int DT, int D, bool PAGED, bool APPEND)
+{
+    return D == 64 && (DT == SPD_F32 || DT == kF32Quad ? !APPEND : PAGED != APPEND);
+}
+
 // Where the results go (the whole call's arrays).
 struct RowsResults {
     float *out0, *lse0, *out1, *lse1;  // out1: nullptr unless both owners are the launch's
@@ -384,10 +397,12 @@ __device__ __forceinline__ void reduce_slots(const DevResults &R, const float2 (
 
 // The steps of both owners, laid end to end, are shared out to the waves in equal contiguous runs.  At most one wave gets
 // the end of owner 0's steps and the beginning of owner 1's: its second result goes to one extra slot.
-template <int DT, int D, bool PAGED, bool APPEND>
-__global__ __launch_bounds__(kRowsMaxWaves * 64, 3) void whole_rows_kernel(
+// CHANNELS: the head's, negative: three waves per SIMD at most (see rows_three_waves_form).
+template <int DT, int CHANNELS, bool PAGED, bool APPEND>
+__global__ __launch_bounds__(kRowsMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(3, CHANNELS < 0 ? 3 : 8))) void whole_rows_kernel(
     u32x8 head_a, u32x4 head_b, u32x2 head_c, RowsArgs A)  // see RowsHead
 {
+    constexpr int D = CHANNELS < 0 ? -CHANNELS : CHANNELS;
     const RowsHead H = head_of<RowsHead>(head_a, head_b, head_c);
     const int Hkv = H.Hkv, G = H.G, waves = H.waves;
     const bool both = H.both;

@@ -149,6 +149,43 @@ def test_up_to_four_waves(ctx, split_ctx, dtype, Hq, Hkv, d, steps):
         assert torch.isfinite(other[u]).all(), u
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,U,top,paged,append,three", [
+    (torch.float32, 8, 2, 210, 700, False, False, True),      # up to two rows a unit: eight waves each, one at a time
+    (torch.float32, 10, 2, 210, 700, True, False, True),
+    (torch.float16, 4, 2, 210, 1200, True, False, True),
+    (torch.bfloat16, 4, 2, 210, 1200, False, True, True),
+    (torch.bfloat16, 4, 2, 210, 1200, True, True, False),     # the append in pages keeps two at a time
+    (torch.bfloat16, 4, 2, 210, 1200, False, False, False),   # (an instance of which a unit holds one anyway)
+    (torch.float32, 3, 3, 300, 120, False, False, True),      # four waves each, 900 rows
+    (torch.float32, 10, 2, 600, 90, False, False, True),      # 1200 rows
+    (torch.float16, 4, 2, 600, 90, True, False, False)])
+def test_forms_for_rows_that_wait_for_others(ctx, split_ctx, dtype, Hq, Hkv, U, top, paged, append, three):
+    """64-channel rows, more than are resident at once: the form held to three waves per SIMD takes the calls that its rule says, with
+    the results of the split kernels; the other calls keep the plain instance."""
+    import paper_2409_19134_amd as spd
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    rng = np.random.default_rng(U + top)
+    wl = workloads.random_case(509, dtype, U, Hq, Hkv, 64, rng.integers(top // 3, top, U).tolist(), rng.integers(1, 60, U).tolist(),
+                               device=DEV, layout="hnd", paged=paged)
+    gen = torch.Generator(device=DEV).manual_seed(510)
+    new = [torch.randn((U, Hkv, 64), generator=gen, device=DEV).to(dtype) for _ in range(2)] if append else [None, None]
+    out = []
+    for c in (ctx, split_ctx):
+        step = spd.DecodeStep.from_workload(c, wl)
+        for name in OUTPUTS:
+            getattr(step, name).fill_(float("nan"))
+        step.run_fused(wl.q, None, *new)        # (the second call writes the same rows to the cache again)
+        torch.cuda.synchronize()
+        out.append(step)
+    name = ctx.spd_last_kernel_name()
+    assert name.startswith("whole_rows_kernel<") and (name.split(", ")[1] == "-64") == three, name
+    for key in OUTPUTS:
+        a, b = getattr(out[0], key), getattr(out[1], key)
+        assert torch.isfinite(a).all() and (a - b).abs().max().item() <= 2 * TOL[dtype], key   # both are within TOL of the same value
+    if not append:
+        _check_one(ctx, wl, _oracle_outputs(orc.from_workload(wl), None), None, None, True)
+
+
 @pytest.mark.parametrize("paged", [False, True])
 def test_decode_loop_appends_on_whole_rows(ctx, paged):
     """Twenty steps of a growing public cache: the appended rows reach the cache, the schedule is found again, results
