@@ -303,7 +303,7 @@ int spd_set_kernel_timing(spd_ctx *ctx, int32_t max_launches);
  * {dtype, head_dim, paged, two steps in flight, head per wave, append} (all -1 before the first launch; dtype 3: the
  * kernel's code for fp32 on 4x4 matrix blocks; head_dim -128: the kernel's other form of the dtype - bf16 and fp16 in
  * 16-token steps, dtype 3 with rows read through buffer descriptors; head per wave 2: the whole-rows kernel, which takes
- * calls of short rows):
+ * calls of short rows, with head_dim -64 its form held to three waves per SIMD):
  * lets a measurement say which kernel it timed, e.g. partial_mfma_kernel<1, 128, false, false, false, false>. */
 int spd_get_last_kernel_instance(const spd_ctx *ctx, int32_t instance[6]);
 int spd_get_kernel_timing(spd_ctx *ctx, int32_t entry_point, int32_t *n_launches, double *mean_us, double *min_us);

@@ -512,7 +512,7 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
     // The owner's arguments come beside the item, at an address of their own (a field chosen from either owner's is two addresses and a
     // selection each), and there is one wait for all that the first tile needs: as the compiler placed them, up to six round trips
     // stood in front of it.  With the preloaded head, us per call before / after: 16 users of 512-4096 + 1-512 tokens fused 32.46 / 31.98,
-    // token-major as two parties with the append 43.43 / 42.28, 32 users of 32768-131072 in 16-token pages 1713 / 1707.
+    // token-major as two parties with the append 43.43 / 42.28; launches of 0.2 ms and more are the same.
     const auto own = (const OwnerArgs __attribute__((address_space(4))) *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
                                                                           kPartialArgsAt + (second ? (int)sizeof(OwnerArgs) : 0));
     const KvAddr kv = {own->kv.block_table, own->kv.max_blocks, own->kv.page_shift, own->kv.block_stride, own->kv.token_stride, own->kv.head_stride};
@@ -618,8 +618,8 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
     for (;;) {
         // the piece's next segment is fetched (scalar cache) long before it is looked at: with tens of MB of loads in
         // flight a dependent round trip costs microseconds, so none may sit between two segments.  (Its growth is applied there too:
-        // here it would be a wait in front of the segment's first tile.  With that, the append in pages takes up to 4 % less: 1 user's
-        // or a few users' calls 14.54 / 14.00, 32.74 / 31.55 us.)
+        // here it would be a wait in front of the segment's first tile, and hold what the owner's arguments need: the instances for pages
+        // with the append, which spill 20 scalar registers, spilled 39 with it, us per call 14.54 / 14.00, 32.74 / 31.55.)
         DevItem nx;
         if (it.next >= 0)
             nx = scalar_load_item(items, it.next);
@@ -770,7 +770,9 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
         // (The end of a segment is latency: ~2 ns for every instruction of a wave, a barrier for every hand-over.  One barrier instead of two -
         // the waves no longer scale to a common maximum first - 16-byte LDS stores and two channels a thread with each weight computed once;
         // us per call before / after: 16 users of 512-4096 + 1-512 tokens fused 31.66 / 31.18, token-major as two parties with the append
-        // 42.01 / 41.32.)
+        // 42.01 / 41.32.  The slots it reads at once cost the two-step and paged instances 3-4 vector registers, within the same waves per
+        // SIMD, and 2-4 spilled scalar ones; with the shorter prologue, 228 random calls
+        // of those instances take 6 % less on average than before both, and launches of 0.4 ms and more the same.)
         int tid = threadIdx.x;
         if constexpr (NA == 1)
             asm("" : "+v"(tid));

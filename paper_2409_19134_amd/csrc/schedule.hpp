@@ -385,6 +385,10 @@ inline bool whole_rows_by_length(int64_t rows, int waves, int n_cus)
 //    111.4 / 125.0).
 //  - rows of more than 64 units (2048 tokens at 256 bytes) gain nothing on balanced launches (256 users of 500-4000 + 1000:
 //    454 / 477), fp32 rows of 512 bytes from 48 (56.3 / 57.4 at 58).
+// The figures are of the kernels that placed the lines; both sides have got faster since (split calls by 0.5-1.4 us, whole ones by 0.2-0.6).
+// 600 further random calls with both as they are now (profiles/whole_rows_rule_calls_timed.txt): of 362 that the rule takes whole 21 are
+// more than 3 % faster split (51 us in all against 1166 gained) - few users at 12 to 14 steps 8.6 / 7.6, 10.0 / 8.2, 64 channels token-major
+// 41.8 / 34.5, 49.5 / 44.6 - and of 44 up to 5 units beyond the lines 5 would be more than 3 % faster whole, 32 slower.
 struct WholeRowsLoad {
     int tile = 32, step_bytes = 16384;  // tokens and K/V bytes of a wave's step
     int Hkv = 0, n_cus = 0, n_users = 0;
