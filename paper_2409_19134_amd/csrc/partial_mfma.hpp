@@ -771,8 +771,8 @@ __global__ __launch_bounds__(HPW ? 512 : kThreads,
         // the waves no longer scale to a common maximum first - 16-byte LDS stores and two channels a thread with each weight computed once;
         // us per call before / after: 16 users of 512-4096 + 1-512 tokens fused 31.66 / 31.18, token-major as two parties with the append
         // 42.01 / 41.32.  The slots it reads at once cost the two-step and paged instances 3-4 vector registers, within the same waves per
-        // SIMD, and 2-4 spilled scalar ones; with the shorter prologue, 228 random calls
-        // of those instances take 6 % less on average than before both, and launches of 0.4 ms and more the same.)
+        // SIMD, and 2-5 spilled scalar ones: without them - an opaque copy of the thread's index here, as where NA is 1 - 400 random calls
+        // take what they do with them.)
         int tid = threadIdx.x;
         if constexpr (NA == 1)
             asm("" : "+v"(tid));
